@@ -135,7 +135,6 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
     plan->units.clear();
     plan->merges.clear();
     plan->workspace_floats = 0;
-    plan->max_merge_rows = 0;
     plan->has_tree = false;
 
     // --- size of the K/V split (see XY_SPLIT_AUTO) ---------------------------
@@ -256,7 +255,6 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         place.resize(fam.size());
         xy_work_unit* u = fam.data() + at;
         int64_t* where = place.data() + at;
-        if (k > 1) plan->max_merge_rows = std::max<int32_t>(plan->max_merge_rows, (int32_t)rows);
         for (int32_t hb = 0, hg = 0; hb < c.num_q_heads; hb += hc, ++hg) {
           int64_t base = -1;
           if (k > 1) {

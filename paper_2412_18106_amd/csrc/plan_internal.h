@@ -18,6 +18,14 @@ struct XyDevSeq {
   int64_t mask_off;
 };
 
+// Up to kMergeRows rows of one K/V-split family, merged by one workgroup of the merge pass.
+struct XyDevMergeRows {
+  int64_t ws_offset;                        // the family's first partial
+  int32_t rows, row_begin;                  // rows of the family; the first of this workgroup
+  int32_t num_splits, token_begin;          // pieces; packed token index of the family's first token
+  int32_t head_begin, head_count;
+};
+
 // Working arrays of the planner, kept between rebuilds so that planning a step allocates nothing once the
 // object has seen a batch of that size.
 struct XyPlanScratch {
@@ -40,7 +48,7 @@ struct xy_attn_plan {
   std::vector<int32_t> worker_offsets;      // W + 1
   std::vector<xy_merge_item> merges;
   int64_t workspace_floats = 0;
-  int32_t max_merge_rows = 0;
+  int64_t merge_groups = 0;                 // workgroups of the merge pass (of the tables last copied to the GPU)
   bool has_tree = false;
   XyPlanScratch scratch;
   // Device copy of the tables (owned): one arena on one device and a pinned staging buffer of the same size,

@@ -1,0 +1,54 @@
+"""Small cases at the edges of single kernels and of the branches that choose between their variants, against the fp64
+oracle.  Tolerance as for the parity tests: bf16 outputs of order one (half an ulp is 2^-9 relative), probabilities
+rounded to bf16 (2^-9 relative, averaging down over the keys), fp32 sums: max-abs <= 2e-2, mean-abs <= 2e-3."""
+import numpy as np
+import pytest
+
+from oracle import attention as A
+from paper_2412_18106_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+MAX_ABS, MEAN_ABS = 2e-2, 2e-3
+P, D_, V = W.PREFILL, W.DECODE, W.VERIFY
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("these tests need a GPU (run with -m gpu on an MI355X box)")
+    from paper_2412_18106_amd import runner
+    return runner
+
+
+def run_and_check(gpu, b, what, plan_check=None, **cfg):
+    db = gpu.DeviceBatch(b, **cfg)
+    try:
+        if plan_check is not None:
+            from paper_2412_18106_amd import binding as X
+            plan_check(*X.xy_attn_plan_get(db.plan))
+        got = db.run_numpy()
+    finally:
+        db.close()
+    ref = A.attention_oracle(b.seqs, b.q, b.k_cache, b.v_cache, b.block_table, b.tree_masks,
+                             num_q_heads=b.num_q_heads, num_kv_heads=b.num_kv_heads, block_size=b.block_size, scale=b.scale)
+    assert not np.isnan(got).any(), f"{what}: NaN in output (row never written?)"
+    err = np.abs(got.astype(np.float64) - ref)
+    assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, f"{what}: max {err.max():.3e} mean {err.mean():.3e}"
+
+
+@pytest.mark.parametrize("pieces", [2, 3, 4, 5, 8, 9, 12, 13, 17])
+def test_merge_pass_over_the_number_of_pieces_and_rows(gpu, pieces):
+    """The merge pass takes pieces in batches of eight, four or two and rows in groups of eight per workgroup: every
+    remainder of either, one-row families and families of one row more than a group."""
+    ctx = 128 * pieces - 5
+    for hq, hkv, specs in ((1, 1, [W.SeqSpec(1, ctx, D_)]),
+                           (6, 2, [W.SeqSpec(3, ctx - 3, V), W.SeqSpec(1, ctx, D_), W.SeqSpec(5, ctx - 7, V)]),
+                           (4, 2, [W.SeqSpec(17, ctx - 20, V), W.SeqSpec(128, 128 * pieces - 128, V)])):
+        b = W.make_custom(specs, hq, hkv, 900 + pieces)
+
+        def plan_check(units, _offs, merges):
+            assert pieces in set(merges["num_splits"].tolist())
+        run_and_check(gpu, b, f"{pieces} pieces, {hq}/{hkv} heads", plan_check, split_kv_blocks=1,
+                      verify_tile_tokens=128 if hq == 4 else 5)

@@ -66,7 +66,6 @@ constexpr float kRowSumLimit = 18446744073709551616.f;      // 2^64: a wide unit
 struct RunParams {
   const XyDevUnit* units;
   const int32_t* worker_offsets;
-  const XyDevSeq* seqs;
   const uint16_t* q;
   const uint16_t* k;
   const uint16_t* v;
@@ -76,13 +75,14 @@ struct RunParams {
   float* ws;
   int64_t q_ts, q_hs, kv_bs, kv_hs, kv_ts, o_ts, o_hs;
   int32_t max_blocks, group, num_workers;
+  int32_t free_workers;              // workers without units of their own (plan with a shared list)
   int32_t num_units;                 // all units, the shared list of XY_ASSIGN_DYNAMIC included
   int32_t* counters;                 // plan with a shared list: its cursor and the finished-workgroup counts (kCounterStride apart); else null
   int32_t page_shift, page_mask;     // log2 of the tokens per block-table entry (page), and that size - 1
   float c;      // softmax_scale * log2(e)
 };
 
-// Read-only tables (units, sequences, block table, the kernel arguments themselves) are read through
+// Read-only tables (units, block table, the kernel arguments themselves) are read through
 // the constant address space: with a uniform address such a load is a scalar load, which neither
 // occupies a vector register nor shares the in-order counter of the LDS-direct K/V stream.
 #define XY_CONST __attribute__((address_space(4)))
@@ -101,6 +101,8 @@ __device__ __forceinline__ T load_const(const T* ptr) {
   for (unsigned i = 0; i < sizeof(T) / 4; ++i) dst[i] = src[i];
   return out;
 }
+
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 __device__ __forceinline__ int swap23(int i) {   // exchange bits 2 and 3
   return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1);
@@ -275,23 +277,22 @@ struct UnitCtx {
   bool tree;
 };
 
-__device__ __forceinline__ UnitCtx make_ctx(const RunParams& p, const XyDevUnit& u, const XyDevSeq& sq) {
+__device__ __forceinline__ UnitCtx make_ctx(const RunParams& p, const XyDevUnit& u) {
   UnitCtx c;
   c.hc = u.head_count;
   c.rows = u.q_count * u.head_count;
   c.kvh = u.head_begin / p.group;
-  c.ctx = sq.ctx_len;
-  c.wpr = (sq.q_len + 31) >> 5;
+  c.ctx = u.ctx_len;
+  c.wpr = (u.q_len + 31) >> 5;
   c.tree = (u.flags >> 2) & 1;
-  c.key_end = c.tree ? sq.ctx_len + sq.q_len : sq.ctx_len + u.q_begin + u.q_count;   // exclusive
+  c.key_end = c.tree ? u.ctx_len + u.q_len : u.ctx_len + u.q_begin + u.q_count;   // exclusive
   return c;
 }
 
 // Row bookkeeping and Q fragments (B operand of S^T = K Q^T: lane (col, half) holds
 // d = 16*ks + 8*half .. +7 of its row).  Padding lanes read a real row; their results are dropped.
 template <int NT>
-__device__ __forceinline__ void setup_rows(const RunParams& p, const XyDevUnit& u, const XyDevSeq& sq,
-                                           const UnitCtx& c, int row_base, int col, int half, Rows<NT>& r,
+__device__ __forceinline__ void setup_rows(const RunParams& p, const XyDevUnit& u, const UnitCtx& c, int row_base, int col, int half, Rows<NT>& r,
                                            bf16x8 (&qf)[NT][8]) {
 #pragma unroll
   for (int rt = 0; rt < NT; ++rt) {
@@ -302,13 +303,13 @@ __device__ __forceinline__ void setup_rows(const RunParams& p, const XyDevUnit& 
     r.tok[rt] = u.q_begin + tl;
     r.lim[rt] = r.valid[rt] ? c.ctx + r.tok[rt] + 1 : 0;
     const uint16_t* qrow =
-        p.q + (int64_t)(sq.token_start + r.tok[rt]) * p.q_ts + (int64_t)(u.head_begin + hl) * p.q_hs;
+        p.q + (int64_t)(u.token_start + r.tok[rt]) * p.q_ts + (int64_t)(u.head_begin + hl) * p.q_hs;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks)
       qf[rt][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qrow + 16 * ks + 8 * half));
     r.mw0[rt] = r.mw1[rt] = 0;
     if (c.tree && r.valid[rt]) {
-      const uint32_t* mrow = p.masks + sq.mask_off + (int64_t)r.tok[rt] * c.wpr;
+      const uint32_t* mrow = p.masks + u.mask_off + (int64_t)r.tok[rt] * c.wpr;
       r.mw0[rt] = mrow[0];
       if (c.wpr > 1) r.mw1[rt] = mrow[1];
     }
@@ -345,7 +346,7 @@ __device__ __forceinline__ void qk_step(unsigned kaddr, const LaneOffsets& lo, c
 
 // ---- visibility: causal bound (section 4.2.2) or tree corner (section 4.1.2) ----------
 template <int NT>
-__device__ __forceinline__ void mask_step(const RunParams& p, const XyDevSeq& sq, const UnitCtx& c,
+__device__ __forceinline__ void mask_step(const RunParams& p, const UnitCtx& c,
                                           const Rows<NT>& r, int jbase /* key of register 0 */, f32x16 (&s)[NT]) {
 #pragma unroll
   for (int rt = 0; rt < NT; ++rt) {
@@ -513,7 +514,7 @@ struct UnitState {
 };
 
 // Normalise and store the rows of a finished unit, or hand its un-normalised state to the merge pass.
-__device__ __forceinline__ void finish_unit(const RunParams& p, const XyDevUnit& u, const XyDevSeq& sq,
+__device__ __forceinline__ void finish_unit(const RunParams& p, const XyDevUnit& u,
                                             const UnitCtx& c, const Rows<1>& r, UnitState& st, int row_base,
                                             int col, int half) {
   mfma_results_ready(st.oacc[0][0], st.oacc[0][1], st.oacc[0][2], st.oacc[0][3]);
@@ -538,7 +539,7 @@ __device__ __forceinline__ void finish_unit(const RunParams& p, const XyDevUnit&
     }
   } else {
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    uint16_t* o = p.out + (int64_t)(sq.token_start + u.q_begin + tl) * p.o_ts + (int64_t)(u.head_begin + hl) * p.o_hs;
+    uint16_t* o = p.out + (int64_t)(u.token_start + u.q_begin + tl) * p.o_ts + (int64_t)(u.head_begin + hl) * p.o_hs;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
@@ -633,25 +634,25 @@ __device__ __forceinline__ void scale_acc(f32x16& acc, const float alpha) {
 template <bool PRESCALE, bool ROWS_CONTIGUOUS>
 // force: the second pass over a unit whose optimistic pass overflowed (exact prefix in every iteration).  Returns
 // whether the unit has to be run again that way (only when force is false; nothing has been written then).
-__device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit& u, const XyDevSeq& sq,
+__device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit& u,
                                              unsigned char* smem, int* overflow_flags, const bool force,
                                              const LaneOffsets& lo, const DmaOffsets& dof) {
   constexpr int NT = 2;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const UnitCtx c = make_ctx(p, u, sq);
+  const UnitCtx c = make_ctx(p, u);
   const int row_base = 64 * wave;
   const bool active = row_base < c.rows;
   Rows<NT> r;
   bf16x8 qf[NT][8];
-  setup_rows<NT>(p, u, sq, c, row_base, col, half, r, qf);
+  setup_rows<NT>(p, u, c, row_base, col, half, r, qf);
   const int mask_from = c.tree ? c.ctx : c.ctx + u.q_begin + row_base / c.hc + 1;
   f32x16 oacc[NT][4];
   float m_ref[NT], l_part[NT][4];      // four running partial row sums per tile, added to in place (plain additions:
                                         // the bf16 dot-product instruction would hold the matrix pipe for 16 cycles)
 
   const XY_CONST int32_t* table = as_const(p.block_table) + (int64_t)u.seq * p.max_blocks;
-  const int last_page = (sq.ctx_len + sq.q_len - 1) >> p.page_shift;
+  const int last_page = (u.ctx_len + u.q_len - 1) >> p.page_shift;
   const int64_t head_off = (int64_t)c.kvh * p.kv_hs;
   const int jfirst = u.kv_begin * kB;
   const int nsteps = (min(u.kv_end * kB, c.key_end) - jfirst + 31) >> 5;
@@ -887,7 +888,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
                      bf16x8 (&p_out)[NT][2]) -> bool {
     {
       const int j = jfirst + 32 * t;
-      if (j + 32 > mask_from) mask_step<NT>(p, sq, c, r, j + 8 * half, s_in);
+      if (j + 32 > mask_from) mask_step<NT>(p, c, r, j + 8 * half, s_in);
     }
     if (exact) {
       exact_prefix(s_in, p_in);
@@ -1074,7 +1075,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
     // the epilogue expects the reference as a raw score and multiplies by c itself
     st1.m_ref[0] = m_ref[rt] == -INFINITY ? -INFINITY : (PRESCALE ? m_ref[rt] / cs : m_ref[rt]);
     st1.l_part[0] = (l_part[rt][0] + l_part[rt][1]) + (l_part[rt][2] + l_part[rt][3]);
-    finish_unit(p, u, sq, c, r1, st1, row_base + 32 * rt, col, half);
+    finish_unit(p, u, c, r1, st1, row_base + 32 * rt, col, half);
   }
   return false;
 }
@@ -1084,21 +1085,21 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
 // each refilled as soon as it has been consumed; a second slice in flight per wavefront was measured
 // and gains nothing).  No barrier, no cross-wavefront merge: four such
 // units are in flight per CU and hide each other's latencies.
-__device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit& u, const XyDevSeq& sq,
+__device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit& u,
                                              unsigned char* smem, const LaneOffsets& lo, const DmaOffsets& dof) {
   constexpr int NT = 1;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const UnitCtx c = make_ctx(p, u, sq);
+  const UnitCtx c = make_ctx(p, u);
   Rows<NT> r;
   bf16x8 qf[NT][8];
-  setup_rows<NT>(p, u, sq, c, 0, col, half, r, qf);
+  setup_rows<NT>(p, u, c, 0, col, half, r, qf);
   const int mask_from = c.tree ? c.ctx : c.ctx + u.q_begin + 1;
   UnitState st;
   zero_state<NT>(st.oacc, st.m_ref, st.l_part);
 
   const XY_CONST int32_t* table = as_const(p.block_table) + (int64_t)u.seq * p.max_blocks;
-  const int last_page = (sq.ctx_len + sq.q_len - 1) >> p.page_shift;
+  const int last_page = (u.ctx_len + u.q_len - 1) >> p.page_shift;
   const int64_t head_off = (int64_t)c.kvh * p.kv_hs;
   const int jfirst = u.kv_begin * kB;
   const int nsteps = (min(u.kv_end * kB, c.key_end) - jfirst + 31) >> 5;
@@ -1131,12 +1132,12 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
     }
     v_fetch<0>(vaddr, lo, vf);                // the first V fragments arrive while the softmax runs
     const int j = jfirst + 32 * t;
-    if (j + 32 > mask_from) mask_step<NT>(p, sq, c, r, j + 8 * half, s);
+    if (j + 32 > mask_from) mask_step<NT>(p, c, r, j + 8 * half, s);
     softmax_step<NT>(p.c, s, st.m_ref, st.l_part, st.oacc);
     pv_step<NT>(vaddr, lo, vf, s, st.oacc);   // all V reads have completed when this returns
     if (tn < nsteps) load_slice(jfirst + 32 * tn, false, true);
   }
-  finish_unit(p, u, sq, c, r, st, 0, col, half);
+  finish_unit(p, u, c, r, st, 0, col, half);
 }
 
 // Every workgroup is one worker of the Task-Table (paper section 3.3).  It first works through the
@@ -1145,7 +1146,7 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
 // on its own.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void xy_attn_units_kernel(RunParams p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kTileBytes];
-  __shared__ int cursor;
+  __shared__ int cursor, first_draw;
   __shared__ int overflow_flags[kThreads / 64];
   // consecutive workgroup ids land on different XCDs; give each XCD a contiguous range of workers
   int worker = blockIdx.x;
@@ -1162,16 +1163,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
       ++i;
       continue;
     }
-    const XyDevSeq sq = load_const(p.seqs + u.seq);
     // Folding c into Q rounds q * c to bf16 once more; with the usual 1/sqrt(d) scale that is far inside the
     // tolerance, with a scale so large that scores reach tens of log2 units it is not, and c stays in fp32.
     bool again;
     if (p.kv_ts == kD) {
-      if (p.c <= kPrescaleMaxC) again = process_wide<true, true>(p, u, sq, smem, overflow_flags, force, lo, dof);
-      else again = process_wide<false, true>(p, u, sq, smem, overflow_flags, force, lo, dof);
+      if (p.c <= kPrescaleMaxC) again = process_wide<true, true>(p, u, smem, overflow_flags, force, lo, dof);
+      else again = process_wide<false, true>(p, u, smem, overflow_flags, force, lo, dof);
     } else {
-      if (p.c <= kPrescaleMaxC) again = process_wide<true, false>(p, u, sq, smem, overflow_flags, force, lo, dof);
-      else again = process_wide<false, false>(p, u, sq, smem, overflow_flags, force, lo, dof);
+      if (p.c <= kPrescaleMaxC) again = process_wide<true, false>(p, u, smem, overflow_flags, force, lo, dof);
+      else again = process_wide<false, false>(p, u, smem, overflow_flags, force, lo, dof);
     }
     force = again;              // wavefront- and workgroup-uniform
     if (!again) ++i;
@@ -1191,32 +1191,38 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     if (i >= end) break;
     const XyDevUnit u = load_const(pn.units + i);
     if (u.q_count * u.head_count > 32) continue;
-    const XyDevSeq sq = load_const(pn.seqs + u.seq);
-    process_solo(pn, u, sq, smem, lo, dof);
+    process_solo(pn, u, smem, lo, dof);
   }
   if (pn.counters) {
     // The shared list of narrow units (dynamic assignment): every wavefront of every workgroup draws the
     // next unit of the list, largest first, until it is empty.  The last workgroup to leave puts the
     // counters back to zero for the next launch (a plan runs one launch at a time, as its workspace does).
-    // A wavefront's first unit is the one with its own slot number (wavefront x workers + worker), without
-    // an atomic: a thousand wavefronts asking one counter at the same moment cost 15 us.
+    // First draw: a thousand wavefronts asking one counter at the same moment cost 15 us, so a worker without units
+    // of its own has four entries reserved for it (numbered wavefront-major over such workers: a short list still
+    // reaches every one of them).  A worker that comes here from wide units has none - an entry reserved for it
+    // would wait for those to end while other CUs are idle (4 wide units and a dozen small ones: 25.8 -> 16.4 us, a chunk of 200 tokens beside 24 short decodes
+    // 46.7 -> 36.3 us, a chunk of 512 beside 64 decodes 161 -> 153 us) -
+    // and draws four at once, one atomic for the workgroup.
     const int shared_begin = as_const(pn.worker_offsets)[pn.num_workers];
-    const int slots = pn.num_workers * (kThreads / 64);
-    bool first = true;
+    const int rank = as_const(pn.worker_offsets)[pn.num_workers + 1 + worker];       // among the workers without units, or -1
+    const int slots = pn.free_workers * (kThreads / 64);
+    const bool any_left = shared_begin + slots < pn.num_units;                        // behind the reserved entries
+    int next = wave_id() * pn.free_workers + rank;
+    if (rank < 0) {
+      if (any_left && threadIdx.x == 0) first_draw = slots + atomicAdd(pn.counters, kThreads / 64);
+      __syncthreads();
+      next = any_left ? __builtin_amdgcn_readfirstlane(first_draw) + wave_id() : pn.num_units;
+    }
 #pragma unroll 1
     while (true) {
-      int got = (threadIdx.x >> 6) * pn.num_workers + worker;   // wavefront-major: a short list still reaches every CU
-      if (!first) {
-        if (shared_begin + slots >= pn.num_units) break;       // one unit per wavefront was all there is
-        got = 0;
-        if ((threadIdx.x & 63) == 0) got = slots + atomicAdd(pn.counters, 1);
-      }
-      first = false;
-      const int i = shared_begin + __builtin_amdgcn_readfirstlane(got);
+      const int i = shared_begin + next;
       if (i >= pn.num_units) break;
       const XyDevUnit u = load_const(pn.units + i);
-      const XyDevSeq sq = load_const(pn.seqs + u.seq);
-      process_solo(pn, u, sq, smem, lo, dof);
+      process_solo(pn, u, smem, lo, dof);
+      if (!any_left) break;
+      int got = 0;
+      if ((threadIdx.x & 63) == 0) got = slots + atomicAdd(pn.counters, 1);
+      next = __builtin_amdgcn_readfirstlane(got);
     }
     __syncthreads();            // all four wavefronts are done with the cursor
     // No fence: every cursor draw above has returned its value, so it was performed at the
@@ -1345,7 +1351,7 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
   const bool shared_list = plan->worker_offsets.back() < (int64_t)plan->units.size();
   const size_t off_units = 0;
   const size_t off_offsets = off_units + round_up(plan->units.size() * sizeof(XyDevUnit));
-  const size_t off_seqs = off_offsets + round_up(plan->worker_offsets.size() * sizeof(int32_t));
+  const size_t off_seqs = off_offsets + round_up(2 * plan->worker_offsets.size() * sizeof(int32_t));
   const size_t off_merges = off_seqs + round_up((size_t)plan->num_seqs * sizeof(XyDevSeq));
   int64_t merge_groups = 0;       // workgroups of the merge pass
   for (const xy_merge_item& m : plan->merges) merge_groups += (m.q_count * m.head_count + kMergeRows - 1) / kMergeRows;
@@ -1376,14 +1382,21 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
   XyDevUnit* du = reinterpret_cast<XyDevUnit*>(h + off_units);
   for (size_t i = 0; i < plan->units.size(); ++i) {
     const xy_work_unit& u = plan->units[i];
+    const xy_seq_desc& sd = plan->descs[u.seq];
     du[i] = XyDevUnit{u.seq, u.head_begin, u.head_count, u.q_begin, u.q_count,
-                      u.kv_block_begin, u.kv_block_end, u.kind_flags, u.ws_offset};
+                      u.kv_block_begin, u.kv_block_end, u.kind_flags, u.ws_offset, sd.mask_word_offset,
+                      sd.query_len, sd.context_len, plan->token_start[u.seq], 0};
   }
   memcpy(h + off_offsets, plan->worker_offsets.data(), plan->worker_offsets.size() * sizeof(int32_t));
+  // behind the offsets: a worker's number among the workers that have no units of their own, -1 where it has some
+  int32_t* rank = reinterpret_cast<int32_t*>(h + off_offsets) + plan->worker_offsets.size();
+  plan->free_workers = 0;
+  for (size_t w = 0; w + 1 < plan->worker_offsets.size(); ++w)
+    rank[w] = plan->worker_offsets[w + 1] == plan->worker_offsets[w] ? plan->free_workers++ : -1;
   XyDevSeq* ds = reinterpret_cast<XyDevSeq*>(h + off_seqs);
   for (int32_t i = 0; i < plan->num_seqs; ++i) {
     const xy_seq_desc& s = plan->descs[i];
-    ds[i] = XyDevSeq{s.query_len, s.context_len, plan->token_start[i], s.mask_kind, s.mask_word_offset};
+    ds[i] = XyDevSeq{s.context_len, plan->token_start[i]};
   }
   XyDevMergeRows* dm = reinterpret_cast<XyDevMergeRows*>(h + off_merges);
   for (const xy_merge_item& m : plan->merges) {
@@ -1465,7 +1478,6 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
   RunParams p;
   p.units = static_cast<const XyDevUnit*>(plan->d_units);
   p.worker_offsets = static_cast<const int32_t*>(plan->d_offsets);
-  p.seqs = static_cast<const XyDevSeq*>(plan->d_seqs);
   p.q = static_cast<const uint16_t*>(q);
   p.k = static_cast<const uint16_t*>(k_cache);
   p.v = static_cast<const uint16_t*>(v_cache);
@@ -1479,6 +1491,7 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
   p.page_shift = plan->cfg.block_size == 16 ? 4 : plan->cfg.block_size == 32 ? 5 : plan->cfg.block_size == 64 ? 6 : 7;
   p.group = plan->cfg.num_q_heads / plan->cfg.num_kv_heads;
   p.num_workers = plan->cfg.num_workers;
+  p.free_workers = plan->free_workers;
   p.num_units = (int32_t)plan->units.size();
   p.counters = static_cast<int32_t*>(plan->d_counters);
   p.c = softmax_scale * 1.4426950408889634f;

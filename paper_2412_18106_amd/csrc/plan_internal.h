@@ -6,16 +6,18 @@
 
 #include "xy_attn.h"
 
-// Compact per-unit record read by the persistent kernel.
+// Per-unit record read by the persistent kernel: the unit and what it has to know of its sequence, so that a
+// wavefront goes from the unit's number to addresses with one 64-byte scalar load.
 struct XyDevUnit {
   int32_t seq, head_begin, head_count, q_begin, q_count, kv_begin, kv_end, flags;
-  int64_t ws_offset;
+  int64_t ws_offset, mask_off;
+  int32_t q_len, ctx_len, token_start, reserved;
 };
+static_assert(sizeof(XyDevUnit) == 64, "one aligned scalar load");
 
-// Per-sequence record read by the kernels.
+// Per-sequence record read by the append kernel.
 struct XyDevSeq {
-  int32_t q_len, ctx_len, token_start, mask_kind;
-  int64_t mask_off;
+  int32_t ctx_len, token_start;
 };
 
 // Up to kMergeRows rows of one K/V-split family, merged by one workgroup of the merge pass.
@@ -49,6 +51,7 @@ struct xy_attn_plan {
   std::vector<xy_merge_item> merges;
   int64_t workspace_floats = 0;
   int64_t merge_groups = 0;                 // workgroups of the merge pass (of the tables last copied to the GPU)
+  int32_t free_workers = 0;                 // workers without units of their own (of the tables last copied to the GPU)
   bool has_tree = false;
   XyPlanScratch scratch;
   // Device copy of the tables (owned): one arena on one device and a pinned staging buffer of the same size,

@@ -52,3 +52,29 @@ def test_merge_pass_over_the_number_of_pieces_and_rows(gpu, pieces):
             assert pieces in set(merges["num_splits"].tolist())
         run_and_check(gpu, b, f"{pieces} pieces, {hq}/{hkv} heads", plan_check, split_kv_blocks=1,
                       verify_tile_tokens=128 if hq == 4 else 5)
+
+
+@pytest.mark.parametrize("workers,wide,narrow", [(4, 4, 3), (4, 4, 40), (4, 5, 4), (4, 1, 3), (4, 1, 12), (4, 1, 13),
+                                                 (4, 3, 50), (16, 3, 1), (16, 15, 70), (1, 1, 9)])
+def test_first_draws_from_the_shared_list(gpu, workers, wide, narrow):
+    """Entries of the shared list are reserved for workers without wide units; the others draw four at once.  No free
+    worker, one, most; fewer entries than reserved, exactly as many, one more; three launches (the last workgroup
+    puts the counters back)."""
+    import torch
+    from paper_2412_18106_amd import binding as X
+    specs = [W.SeqSpec(64, 40 + 30 * i, P) for i in range(wide)] + [W.SeqSpec(1, 100 + 37 * i, D_) for i in range(narrow)]
+    b = W.make_custom(specs, 4, 1, 77)
+    ref = A.attention_oracle(b.seqs, b.q, b.k_cache, b.v_cache, b.block_table, b.tree_masks, num_q_heads=4,
+                             num_kv_heads=1, block_size=b.block_size, scale=b.scale)
+    db = gpu.DeviceBatch(b, num_workers=workers, split_kv_blocks=0)
+    try:
+        units, offs, _ = X.plan_arrays(db.plan, workers)
+        assert len(units) == wide + narrow and offs[workers] == wide
+        first = db.run_numpy()
+        err = np.abs(first.astype(np.float64) - ref)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
+        for _ in range(2):
+            assert np.array_equal(db.run_numpy(), first)
+        torch.cuda.synchronize()
+    finally:
+        db.close()

@@ -289,6 +289,28 @@ __device__ __forceinline__ UnitCtx make_ctx(const RunParams& p, const XyDevUnit&
   return c;
 }
 
+// Token and head of row rho of a unit (rho = token * hc + head, fewer than 256 of them).  An integer division is some
+// forty instructions; the reciprocal is exact enough here: (rho + 1/2) / hc is at least 1 / (2 hc) >= 2^-9 away from an
+// integer and is computed to within 2^-14.
+struct RowIndex {
+  int tl, hl;
+};
+__device__ __forceinline__ RowIndex row_index(int rho, int hc, float inv_hc) {
+  RowIndex r;
+  r.tl = (int)(((float)rho + 0.5f) * inv_hc);
+  r.hl = rho - r.tl * hc;
+  return r;
+}
+
+// Byte offset of row (tl, hl) of a Q or O tensor from the unit's first row.  SMALL: strides below kSmallStride
+// elements, so that a row of a unit lies within 2^31 bytes of it (24-bit multiplies, 32-bit offsets).
+constexpr int64_t kSmallStride = 1 << 21;
+template <bool SMALL>
+__device__ __forceinline__ int64_t row_bytes(const RowIndex& r, int64_t ts, int64_t hs) {
+  if (SMALL) return (int64_t)(uint32_t)(__umul24(r.tl, 2 * (unsigned)ts) + __umul24(r.hl, 2 * (unsigned)hs));
+  return 2 * (r.tl * ts + r.hl * hs);
+}
+
 // Row bookkeeping and Q fragments (B operand of S^T = K Q^T: lane (col, half) holds
 // d = 16*ks + 8*half .. +7 of its row).  Padding lanes read a real row; their results are dropped.
 template <int NT>
@@ -513,43 +535,51 @@ struct UnitState {
   float m_ref[1], l_part[1];
 };
 
-// Normalise and store the rows of a finished unit, or hand its un-normalised state to the merge pass.
-__device__ __forceinline__ void finish_unit(const RunParams& p, const XyDevUnit& u,
-                                            const UnitCtx& c, const Rows<1>& r, UnitState& st, int row_base,
-                                            int col, int half) {
+// The un-normalised state of 32 rows of a K/V-split unit, handed to the merge pass: [32 groups of four d][rows][4]
+// floats, then the rows' references (log2 units), then their sums.  The order is the one the accumulators have: a
+// store instruction writes the same four d of 32 consecutive rows, 512 contiguous bytes per half wavefront.
+__device__ __forceinline__ void store_partial(const RunParams& p, const XyDevUnit& u, int rows, int rho, bool valid, int half,
+                                              const f32x16 (&oacc)[4], float m2, float l_tot) {
+  if (!valid) return;
+  char* w = reinterpret_cast<char*>(p.ws + u.ws_offset);
+  const unsigned lane_off = (unsigned)(half * rows + rho) * 16u;
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const f32x4 x = {oacc[dt][4 * a], oacc[dt][4 * a + 1], oacc[dt][4 * a + 2], oacc[dt][4 * a + 3]};
+      *reinterpret_cast<f32x4*>(w + (size_t)((8 * dt + 2 * a) * rows * 16) + lane_off) = x;
+    }
+  if (half == 0) {
+    float* ml = reinterpret_cast<float*>(w) + (int64_t)rows * kD + rho;
+    ml[0] = m2;
+    ml[rows] = l_tot;
+  }
+}
+
+// Normalise and store the rows of a finished narrow unit, or hand its un-normalised state to the merge pass.
+__device__ __forceinline__ void finish_unit(const RunParams& p, const XyDevUnit& u, const UnitCtx& c, const Rows<1>& r,
+                                            UnitState& st, int col, int half) {
   mfma_results_ready(st.oacc[0][0], st.oacc[0][1], st.oacc[0][2], st.oacc[0][3]);
   const float l_tot = st.l_part[0] + other_half(st.l_part[0]);
-  const float m2 = (st.m_ref[0] == -INFINITY) ? -INFINITY : st.m_ref[0] * p.c;     // running max, log2 units
-  if (!r.valid[0]) return;
-  const int rho = row_base + col;
-  const int tl = rho / c.hc, hl = rho - tl * c.hc;
   if (u.ws_offset >= 0) {   // K/V-split unit
-    float* w = p.ws + u.ws_offset;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        f32x4 x = {st.oacc[0][dt][4 * a], st.oacc[0][dt][4 * a + 1], st.oacc[0][dt][4 * a + 2],
-                   st.oacc[0][dt][4 * a + 3]};
-        *reinterpret_cast<f32x4*>(w + (int64_t)rho * kD + 32 * dt + 8 * a + 4 * half) = x;
-      }
-    if (half == 0) {
-      w[(int64_t)c.rows * kD + rho] = m2;
-      w[(int64_t)c.rows * kD + c.rows + rho] = l_tot;
-    }
-  } else {
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    uint16_t* o = p.out + (int64_t)(u.token_start + u.q_begin + tl) * p.o_ts + (int64_t)(u.head_begin + hl) * p.o_hs;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        uint2 w2;
-        w2.x = pack_bf16(st.oacc[0][dt][4 * a] * inv, st.oacc[0][dt][4 * a + 1] * inv);
-        w2.y = pack_bf16(st.oacc[0][dt][4 * a + 2] * inv, st.oacc[0][dt][4 * a + 3] * inv);
-        *reinterpret_cast<uint2*>(o + 32 * dt + 8 * a + 4 * half) = w2;
-      }
+    const float m2 = (st.m_ref[0] == -INFINITY) ? -INFINITY : st.m_ref[0] * p.c;     // running max, log2 units
+    store_partial(p, u, c.rows, col, r.valid[0], half, st.oacc[0], m2, l_tot);
+    return;
   }
+  if (!r.valid[0]) return;
+  const int tl = r.tok[0] - u.q_begin, hl = col - tl * c.hc;
+  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  uint16_t* o = p.out + (int64_t)(u.token_start + u.q_begin + tl) * p.o_ts + (int64_t)(u.head_begin + hl) * p.o_hs;
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      uint2 w2;
+      w2.x = pack_bf16(st.oacc[0][dt][4 * a] * inv, st.oacc[0][dt][4 * a + 1] * inv);
+      w2.y = pack_bf16(st.oacc[0][dt][4 * a + 2] * inv, st.oacc[0][dt][4 * a + 3] * inv);
+      *reinterpret_cast<uint2*>(o + 32 * dt + 8 * a + 4 * half) = w2;
+    }
 }
 
 // ---- wide units (more than 32 rows, MFMA-bound) -------------------------------------------------------
@@ -631,26 +661,20 @@ __device__ __forceinline__ void scale_acc(f32x16& acc, const float alpha) {
 // and the PV MFMAs of step t - 1, as sixteen chunks of two MFMAs (one per row tile, sharing the chunk's
 // K or V fragment) with a few vector instructions and one LDS request behind each MFMA.
 // PRESCALE: Q carries the factor c = scale x log2(e), see the softmax notes inside.
-template <bool PRESCALE, bool ROWS_CONTIGUOUS>
+template <int NT, bool PRESCALE, bool ROWS_CONTIGUOUS>
 // force: the second pass over a unit whose optimistic pass overflowed (exact prefix in every iteration).  Returns
 // whether the unit has to be run again that way (only when force is false; nothing has been written then).
 __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit& u,
                                              unsigned char* smem, int* overflow_flags, const bool force,
                                              const LaneOffsets& lo, const DmaOffsets& dof) {
-  constexpr int NT = 2;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const UnitCtx c = make_ctx(p, u);
-  const int row_base = 64 * wave;
+  const int row_base = 32 * NT * wave;
   const bool active = row_base < c.rows;
-  Rows<NT> r;
+  const float inv_hc = __builtin_amdgcn_rcpf((float)c.hc);
   bf16x8 qf[NT][8];
-  setup_rows<NT>(p, u, c, row_base, col, half, r, qf);
   const int mask_from = c.tree ? c.ctx : c.ctx + u.q_begin + row_base / c.hc + 1;
-  f32x16 oacc[NT][4];
-  float m_ref[NT], l_part[NT][4];      // four running partial row sums per tile, added to in place (plain additions:
-                                        // the bf16 dot-product instruction would hold the matrix pipe for 16 cycles)
-
   const XY_CONST int32_t* table = as_const(p.block_table) + (int64_t)u.seq * p.max_blocks;
   const int last_page = (u.ctx_len + u.q_len - 1) >> p.page_shift;
   const int64_t head_off = (int64_t)c.kvh * p.kv_hs;
@@ -675,58 +699,15 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   // S^T is kept in "score units": log2 units when Q carries the factor c, raw q.k otherwise.
   const float u2l = PRESCALE ? 1.f : cs;                                   // score units -> log2 units
   const float lazy = PRESCALE ? kLazyRescale : kLazyRescale / cs;         // the lazy-rescale margin in score units
-#pragma unroll
-  for (int rt = 0; rt < NT; ++rt)
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      if (!PRESCALE) break;
-      uint4 w = __builtin_bit_cast(uint4, qf[rt][ks]);
-      unsigned* wp = reinterpret_cast<unsigned*>(&w);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        wp[i] = pack_bf16(__uint_as_float(wp[i] << 16) * cs, __uint_as_float(wp[i] & 0xffff0000u) * cs);
-      qf[rt][ks] = __builtin_bit_cast(bf16x8, w);
-      asm volatile("; scaled Q fragment lives in the AGPR file from here on" : "+a"(qf[rt][ks]));
-    }
-
-#pragma unroll
-  for (int rt = 0; rt < NT; ++rt) {
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) oacc[rt][dt][v] = 0.f;
-    m_ref[rt] = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) l_part[rt][i] = 0.f;
-  }
   // ---- the K/V stream (paged cache of section 4.1.1) ---------------------------------------------------
   // Half block h lives in ring slot h & 3; wavefronts 0-1 fetch 32 rows of K each, wavefronts 2-3 32 rows
-  // of V.  A wavefront has nobody to hide behind on its SIMD, so the page-table entries of a request are
-  // read (scalar loads) a whole trip before the request is set up, and K and V take the same
-  // straight-line path (base pointer and swizzle offsets selected once per unit).
+  // of V.  K and V take the same straight-line path (base pointer and swizzle offsets selected once per unit).
   const uint16_t* kv_base = (wave < 2 ? p.k : p.v) + head_off;
   unsigned dsel[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) dsel[e] = wave < 2 ? dof.k[e] : dof.v;
   const int row_sel = 32 * (wave & 1);
-  auto page_entry = [&](const int h, const int g) -> int {      // h counts K half blocks for wavefronts 0-1, V for 2-3
-    const int j = jfirst + 64 * h + row_sel + 16 * g;
-    return table[min(j >> p.page_shift, last_page)];            // rows past the last page are redirected to it
-  };
-  auto request_half_block = [&](const int h, const int entry0, const int entry1) {
-    unsigned char* dst = smem + (h & 3) * 32768 + (wave >> 1) * 16384 + (wave & 1) * 8192;
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {      // sixteen rows share a page
-      const int j = jfirst + 64 * h + row_sel + 16 * g;
-      const uint16_t* src = kv_base + (int64_t)(g ? entry1 : entry0) * p.kv_bs + (int64_t)(j & p.page_mask) * p.kv_ts;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void*)(reinterpret_cast<const char*>(src + (int64_t)(4 * e) * p.kv_ts) + (size_t)dsel[e]),
-            (__attribute__((address_space(3))) void*)(dst + 4096 * g + 1024 * e), 16, 0, 0);
-    }
-  };
-  // After the first four half blocks, the eight loads of a request are issued one by one during the trip
+  // After the first half blocks, the eight loads of a request are issued one by one during the trip
   // that follows its set-up, so that their data reaches LDS a kilobyte at a time, between the fragment
   // reads, instead of as one burst.
   // Where the two sixteen-row runs of a request come from (page-table entry, page stride, row in the page) is 64-bit
@@ -737,16 +718,18 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   const uint16_t* rsrc1 = kv_base;
   unsigned char* rdst = smem;
   unsigned src_lo[2] = {0u, 0u}, src_hi[2] = {0u, 0u};
-  int window = -1;
-  auto fill_table = [&](const int w) {
+  int window = 0;
+  // (64-bit: lanes far behind the unit's last half block look past any sequence length; they are clamped to
+  // the last page like every row behind the sequence's end)
+  auto table_row = [&](const int w, const int g) { return (int64_t)jfirst + 64 * (64 * (int64_t)w + lane) + row_sel + 16 * g; };
+  auto table_entry = [&](const int w, const int g) {
+    const int page = (int)min(table_row(w, g) >> p.page_shift, (int64_t)last_page);
+    return p.block_table[(int64_t)u.seq * p.max_blocks + page];
+  };
+  auto fill_table = [&](const int w, const int entry0, const int entry1) {
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
-      // (64-bit: lanes far behind the unit's last half block look past any sequence length; they are clamped to
-      // the last page like every row behind the sequence's end)
-      const int64_t jl = (int64_t)jfirst + 64 * (64 * (int64_t)w + lane) + row_sel + 16 * g;
-      const int page = (int)min(jl >> p.page_shift, (int64_t)last_page);
-      const int entry = p.block_table[(int64_t)u.seq * p.max_blocks + page];
-      const uint64_t a = (uint64_t)(kv_base + (int64_t)entry * p.kv_bs + (jl & p.page_mask) * p.kv_ts);
+      const uint64_t a = (uint64_t)(kv_base + (int64_t)(g ? entry1 : entry0) * p.kv_bs + (table_row(w, g) & p.page_mask) * p.kv_ts);
       src_lo[g] = (unsigned)a;
       src_hi[g] = (unsigned)(a >> 32);
     }
@@ -755,7 +738,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
     rdst = smem + (h & 3) * 32768 + (wave >> 1) * 16384 + (wave & 1) * 8192;
     if ((h >> 6) != window) {         // once per 64 trips
       window = h >> 6;
-      fill_table(window);
+      fill_table(window, table_entry(window, 0), table_entry(window, 1));
     }
     const int l = h & 63;
     // (the lane read returns a signed int: widened through unsigned, or a low word with its top bit set would
@@ -789,12 +772,104 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   };
   auto k_slice = [&](const int t) { return lds_addr(smem) + ((t >> 1) & 3) * 32768 + (t & 1) * 8192; };
 
-  __syncthreads();
+  // ---- start of a unit -----------------------------------------------------------------------------------
+  // What stands around the loop is paid once per unit and by nobody else's time (a short prompt's units spend more
+  // here than in the loop), so it is laid out for latency: the page-table entries, then Q and the first two half
+  // blocks of K and V are in flight together, and Q goes through LDS.  Read straight into fragments, a Q load touches
+  // 32 rows for 32 bytes each, and the address path of the CU takes about a line per cycle; through LDS an
+  // instruction moves four whole rows.  The rows (256 bytes, 16-byte chunks swizzled by the low four bits of the
+  // row) wait in ring slots 2 and 3, which are requested when every wavefront has its Q.
+  // With the way the results leave (below), the first reference taken without rescaling what is still zero and the
+  // last V fragments requested together, a unit spends 7.6 us around its loop instead of 10.5 (256 rows, alone).
+  __syncthreads();                                          // the ring is free
+  const int entry0 = table_entry(0, 0), entry1 = table_entry(0, 1);
+  unsigned char* const wave_buf = smem + 65536 + wave * (8192 * NT);        // 32 NT rows of 256 bytes
+  const int sub = lane >> 4, pos = lane & 15;               // a load or store of four rows: row, 16-byte chunk
+  auto rows_in_order = [&](const int e) { return row_index(min(row_base + 4 * e + sub, c.rows - 1), c.hc, inv_hc); };
+  auto chunk_of = [&](const int e) { return (pos ^ ((4 * e + sub) & 15)) << 4; };
+  if (active) {
+    const char* q0 = reinterpret_cast<const char*>(p.q + (int64_t)(u.token_start + u.q_begin) * p.q_ts + (int64_t)u.head_begin * p.q_hs);
+    auto q_load = [&](const char* from, const int e) {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)from,
+                                       (__attribute__((address_space(3))) void*)(wave_buf + 1024 * e), 16, 0, 0);
+    };
+    if (p.q_ts < kSmallStride && p.q_hs < kSmallStride) {
 #pragma unroll
-  for (int h = 0; h < 4; ++h)
-    if (h < 3 || wave < 2) request_half_block(h, page_entry(h, 0), page_entry(h, 1));      // K(0..3), V(0..2)
-  wait_vmcnt<0>();
-  __syncthreads();
+      for (int e = 0; e < 8 * NT; ++e) q_load(q0 + row_bytes<true>(rows_in_order(e), p.q_ts, p.q_hs) + chunk_of(e), e);
+    } else {
+#pragma unroll 1
+      for (int e = 0; e < 8 * NT; ++e) q_load(q0 + row_bytes<false>(rows_in_order(e), p.q_ts, p.q_hs) + chunk_of(e), e);
+    }
+  }
+  fill_table(0, entry0, entry1);
+  auto request_now = [&](const int h) {
+    setup_request(h);
+#pragma unroll
+    for (int idx = 0; idx < 8; ++idx) issue(idx);
+  };
+  request_now(0);
+  request_now(1);
+  // the rows a lane owns, while the loads are in flight
+  Rows<NT> r;
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt) {
+    const int rho = row_base + 32 * rt + col;
+    r.valid[rt] = rho < c.rows;
+    r.tok[rt] = u.q_begin + row_index(min(rho, c.rows - 1), c.hc, inv_hc).tl;
+    r.lim[rt] = r.valid[rt] ? c.ctx + r.tok[rt] + 1 : 0;
+    r.mw0[rt] = r.mw1[rt] = 0;
+    if (c.tree && r.valid[rt]) {
+      const uint32_t* mrow = p.masks + u.mask_off + (int64_t)r.tok[rt] * c.wpr;
+      r.mw0[rt] = mrow[0];
+      if (c.wpr > 1) r.mw1[rt] = mrow[1];
+    }
+  }
+  f32x16 oacc[NT][4];
+  float m_ref[NT], l_part[NT][4];      // four running partial row sums per tile, added to in place (plain additions:
+                                        // the bf16 dot-product instruction would hold the matrix pipe for 16 cycles)
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt) {
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) oacc[rt][dt][v] = 0.f;
+    m_ref[rt] = -INFINITY;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) asm volatile("" : "+a"(oacc[rt][dt]));      // zeros written here, not next to the first MFMA
+#pragma unroll
+    for (int i = 0; i < 4; ++i) l_part[rt][i] = 0.f;
+  }
+  wait_vmcnt<16>();                                         // Q has landed; the two half blocks may be in flight
+  if (active) {
+    const unsigned qaddr = lds_addr(wave_buf) + col * 256;
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) {
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks)
+        qf[rt][ks] = lds_read_b128<0>(qaddr + rt * 8192 + (((2 * ks + half) ^ (col & 15)) << 4));
+      lds_wait<4>(qf[rt][0], qf[rt][1], qf[rt][2], qf[rt][3]);
+      lds_wait<0>(qf[rt][4], qf[rt][5], qf[rt][6], qf[rt][7]);
+    }
+  }
+  __builtin_amdgcn_s_barrier();                             // slots 2 and 3 are free
+  request_now(2);                                           // K(0..3), V(0..2)
+  if (wave < 2) request_now(3);
+  if (active) {
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) {
+        if (PRESCALE) {
+          uint4 w = __builtin_bit_cast(uint4, qf[rt][ks]);
+          unsigned* wp = reinterpret_cast<unsigned*>(&w);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            wp[i] = pack_bf16(__uint_as_float(wp[i] << 16) * cs, __uint_as_float(wp[i] & 0xffff0000u) * cs);
+          qf[rt][ks] = __builtin_bit_cast(bf16x8, w);
+        }
+        asm volatile("; Q fragment lives in the AGPR file from here on" : "+a"(qf[rt][ks]));
+      }
+  }
 
   f32x16 sa[NT], sb[NT];
   bf16x8 pa[NT][2], pb[NT][2];
@@ -806,6 +881,9 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
     for (int v = 0; v < 16; ++v) negm[rt][v] = 0.f;
 #pragma unroll
   for (int rt = 0; rt < NT; ++rt) asm volatile("" : "+v"(negm[rt]));
+  if (wave < 2) wait_vmcnt<16>();                           // half blocks 0 and 1 have landed
+  else wait_vmcnt<8>();
+  __builtin_amdgcn_s_barrier();
 
   auto request_k = [&](const unsigned kaddr, const int i) { kf[i] = lds_read_b128<0>(kaddr + lo.k[i]); };
   auto request_v = [&](const unsigned vaddr, const int i) {
@@ -835,13 +913,16 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   // that the pipelined iteration runs unchanged afterwards.  A row that has a reference moves it by a
   // whole number of log2 units, which makes the factor a power of two: the packed probabilities are
   // rescaled without rounding.
-  auto exact_prefix = [&](f32x16 (&s_in)[NT], bf16x8 (&p_in)[NT][2]) {
-    ready_a(oacc[0][0], oacc[0][1], oacc[0][2], oacc[0][3]);
-    ready_a(oacc[1][0], oacc[1][1], oacc[1][2], oacc[1][3]);
+  // first: iteration 0, in which nothing has been built against a reference yet.
+  auto exact_prefix = [&](const bool first, f32x16 (&s_in)[NT], bf16x8 (&p_in)[NT][2]) {
+    if (!first) {
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) ready_a(oacc[rt][0], oacc[rt][1], oacc[rt][2], oacc[rt][3]);
+    }
 #pragma unroll
     for (int rt = 0; rt < NT; ++rt) {
       const float mx = max_both_halves(lane_max(s_in[rt]));       // relative to the reference
-      const bool set = m_ref[rt] != -INFINITY;
+      const bool set = !first && m_ref[rt] != -INFINITY;
       float delta, alpha;
       if (set) {
         const float d2 = mx >= lazy ? ceilf(mx * u2l) : 0.f;      // whole number of log2 units
@@ -856,11 +937,14 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
 #pragma unroll
       for (int v = 0; v < 16; ++v) s_in[rt][v] -= delta;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) l_part[rt][i] *= alpha;
+      for (int i = 0; i < 4; ++i)
+        if (!first) l_part[rt][i] *= alpha;
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt) scale_acc(oacc[rt][dt], alpha);
+      for (int dt = 0; dt < 4; ++dt)
+        if (!first) scale_acc(oacc[rt][dt], alpha);
 #pragma unroll
       for (int h2 = 0; h2 < 2; ++h2) {
+        if (first) break;
         uint4 w = __builtin_bit_cast(uint4, p_in[rt][h2]);
         unsigned* wp = reinterpret_cast<unsigned*>(&w);
 #pragma unroll
@@ -873,14 +957,17 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
       for (int v = 0; v < 16; ++v) negm[rt][v] = nm;
       asm volatile("" : "+v"(negm[rt]));      // sixteen real registers from here on, nothing rebuilt next to the MFMA
     }
-    pending = __builtin_amdgcn_ballot_w64((r.valid[0] && m_ref[0] == -INFINITY) || (r.valid[1] && m_ref[1] == -INFINITY)) != 0;
+    bool waiting = false;
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) waiting = waiting || (r.valid[rt] && m_ref[rt] == -INFINITY);
+    pending = __builtin_amdgcn_ballot_w64(waiting) != 0;
   };
 
   // Iteration t: QK^T of step t + 1 (chunks 0-7), exp2 / pack / row sum of step t (one pair of scores per
   // chunk), PV of step t - 1 (chunks 8-15).  The LDS request issued in a chunk is the fragment needed four
   // chunks later; par >= 0 numbers the iteration inside its trip for the K/V loads it issues.  Returns
-  // whether the next iteration starts with the exact prefix; par == -2 marks the iteration after which no
-  // other follows (its look-ahead scores are never read).
+  // whether the next iteration starts with the exact prefix; par == -1 marks iteration 0, par == -2 the iteration
+  // after which no other follows (its look-ahead scores are never read).
   // kaddr, vaddr, knext: LDS addresses of K of step t + 1, V of step t - 1 and K of step t + 2 (worked out
   // once per trip by the caller).
   auto iterate = [&](const bool exact, const int par, const int t, const unsigned kaddr, const unsigned vaddr,
@@ -891,12 +978,12 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
       if (j + 32 > mask_from) mask_step<NT>(p, c, r, j + 8 * half, s_in);
     }
     if (exact) {
-      exact_prefix(s_in, p_in);
+      exact_prefix(par == -1, s_in, p_in);
       valu_to_mfma_gap();       // the prefix rewrote the reference registers the first MFMA reads
     }
     lds_wait<0>(kf[0], kf[1], kf[2], kf[3]);
-    unsigned packed[16];
-    float e[32];
+    unsigned packed[8 * NT];
+    float e[16 * NT];
     // A lone wavefront issues in order: an MFMA that finds the matrix pipe busy holds up everything behind
     // it, and a gap with more than about 26 cycles of other instructions leaves the pipe idle.  So the
     // vector work of the iteration is dealt out over the 32 gaps behind its MFMAs (two per chunk) by a table
@@ -942,17 +1029,18 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
         if (ch < 8) mfma_qk(ch, s_out[rt], rt);
         else mfma_pv(oacc[rt][(ch - 8) & 3], vf[ch - 8], p_in[rt][(ch - 8) >> 2]);
       };
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_of(0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (ch < 4) request_k(kaddr, 4 + ch);           // the LDS request of the chunk: the fragment needed four chunks on
-      else if (ch < 12) request_v(vaddr, ch - 4);
-      else request_k(knext, ch - 12);
-      gap_work(2 * ch);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_of(1);
-      __builtin_amdgcn_sched_barrier(0);
-      gap_work(2 * ch + 1);
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) {
+        __builtin_amdgcn_sched_barrier(0);
+        mfma_of(rt);
+        __builtin_amdgcn_sched_barrier(0);
+        if (rt == 0) {                                  // the LDS request of the chunk: the fragment needed four chunks on
+          if (ch < 4) request_k(kaddr, 4 + ch);
+          else if (ch < 12) request_v(vaddr, ch - 4);
+          else request_k(knext, ch - 12);
+        }
+        gap_work(NT * ch + rt);
+      }
       if (par >= 0 && (ch & 3) == 1) issue(4 * par + (ch >> 2));      // this trip's share of the K/V stream
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -965,7 +1053,8 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
     // (Only then: where the next iteration reads it, the same statement makes the allocator copy all 32
     // registers behind every iteration.)
     if (par == -2) {
-      asm volatile("" : "+v"(s_out[0]), "+v"(s_out[1]));
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) asm volatile("" : "+v"(s_out[rt]));
       return false;
     }
     return force || pending;      // wavefront-uniform
@@ -977,12 +1066,13 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
     for (int i = 0; i < 8; ++i) request_k(k_slice(0), i);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      lds_wait1<0>(kf[i]);
-      mfma_qk(i, sa[0], 0);
-      mfma_qk(i, sa[1], 1);
+      if (i == 0) lds_wait<4>(kf[0], kf[1], kf[2], kf[3]);
+      if (i == 4) lds_wait<0>(kf[4], kf[5], kf[6], kf[7]);
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) mfma_qk(i, sa[rt], rt);
     }
-    mfma_settle(sa[0]);
-    mfma_settle(sa[1]);
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) mfma_settle(sa[rt]);
 #pragma unroll
     for (int i = 0; i < 4; ++i) request_k(k_slice(1), i);
 #pragma unroll
@@ -1023,8 +1113,8 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   if (2 * j + 1 < nsteps) {     // one more step: no refill (the last PV below still reads V of half block j)
     if (active) {
       iterate(exact, -2, 2 * j + 1, k_slice(2 * j + 2), k_slice(2 * j) + 16384, k_slice(2 * j + 3), sb, sa, pa, pb);
-      settle_a(oacc[0][0], oacc[0][1], oacc[0][2], oacc[0][3]);
-      settle_a(oacc[1][0], oacc[1][1], oacc[1][2], oacc[1][3]);
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) settle_a(oacc[rt][0], oacc[rt][1], oacc[rt][2], oacc[rt][3]);
     }
   }
   if (active) {                 // PV of the last step
@@ -1040,14 +1130,16 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
       asm volatile("" : "+v"(p_last[rt][0]), "+v"(p_last[rt][1]));     // selected here, not next to the MFMAs
     }
 #pragma unroll
+    for (int i = 0; i < 8; ++i) request_v(vaddr, i);
+#pragma unroll
     for (int i = 0; i < 8; ++i) {
-      request_v(vaddr, i);
-      lds_wait1<0>(vf[i]);
-      mfma_pv(oacc[0][i & 3], vf[i], p_last[0][i >> 2]);
-      mfma_pv(oacc[1][i & 3], vf[i], p_last[1][i >> 2]);
+      if (i == 0) lds_wait<8>(vf[0], vf[1], vf[2], vf[3]);          // two requests a fragment
+      if (i == 4) lds_wait<0>(vf[4], vf[5], vf[6], vf[7]);
+#pragma unroll
+      for (int rt = 0; rt < NT; ++rt) mfma_pv(oacc[rt][i & 3], vf[i], p_last[rt][i >> 2]);
     }
-    ready_a(oacc[0][0], oacc[0][1], oacc[0][2], oacc[0][3]);
-    ready_a(oacc[1][0], oacc[1][1], oacc[1][2], oacc[1][3]);
+#pragma unroll
+    for (int rt = 0; rt < NT; ++rt) ready_a(oacc[rt][0], oacc[rt][1], oacc[rt][2], oacc[rt][3]);
   }
   // The check of the optimistic pass.  All four wavefronts stream K/V together, so they repeat the unit together.
   bool bad = false;
@@ -1060,22 +1152,53 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   }
   const bool wave_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
   if (lane == 0) overflow_flags[wave] = wave_bad ? 1 : 0;
+  wait_vmcnt<0>();            // no load of the stream lands in the ring after the barrier
   __syncthreads();
   const int any_bad = overflow_flags[0] | overflow_flags[1] | overflow_flags[2] | overflow_flags[3];
   // The second pass is the caller's next turn of its loop over the units, not a loop in here: what a loop around
   // this function would keep alive across the main loop costs more registers than the wide units have to spare.
   if (__builtin_amdgcn_readfirstlane(any_bad) != 0 && !force) return true;
+  if (!active) return false;
+  float l_tot[NT];
 #pragma unroll
-  for (int rt = 0; rt < NT; ++rt) {       // hand each 32-row tile to the single-tile epilogue
-    Rows<1> r1;
-    r1.lim[0] = r.lim[rt]; r1.tok[0] = r.tok[rt]; r1.valid[0] = r.valid[rt]; r1.mw0[0] = r.mw0[rt]; r1.mw1[0] = r.mw1[rt];
-    UnitState st1;
+  for (int rt = 0; rt < NT; ++rt) {
+    const float l_lane = (l_part[rt][0] + l_part[rt][1]) + (l_part[rt][2] + l_part[rt][3]);
+    l_tot[rt] = l_lane + other_half(l_lane);
+  }
+  if (u.ws_offset >= 0) {
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt) st1.oacc[0][dt] = oacc[rt][dt];
-    // the epilogue expects the reference as a raw score and multiplies by c itself
-    st1.m_ref[0] = m_ref[rt] == -INFINITY ? -INFINITY : (PRESCALE ? m_ref[rt] / cs : m_ref[rt]);
-    st1.l_part[0] = (l_part[rt][0] + l_part[rt][1]) + (l_part[rt][2] + l_part[rt][3]);
-    finish_unit(p, u, c, r1, st1, row_base + 32 * rt, col, half);
+    for (int rt = 0; rt < NT; ++rt)
+      store_partial(p, u, c.rows, row_base + 32 * rt + col, r.valid[rt], half, oacc[rt],
+                    m_ref[rt] == -INFINITY ? -INFINITY : m_ref[rt] * u2l, l_tot[rt]);
+    return false;
+  }
+  // A lane holds four consecutive d of a row at a time; stored as they are, an instruction writes sixteen bytes of each
+  // of 32 rows.  Through the wavefront's part of the ring (nobody reads it any more: the barrier of the check above
+  // stands behind the last use and behind the last load) it writes four whole rows.
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt) {
+    const float inv = l_tot[rt] > 0.f ? 1.f / l_tot[rt] : 0.f;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        uint2 w2;
+        w2.x = pack_bf16(oacc[rt][dt][4 * a] * inv, oacc[rt][dt][4 * a + 1] * inv);
+        w2.y = pack_bf16(oacc[rt][dt][4 * a + 2] * inv, oacc[rt][dt][4 * a + 3] * inv);
+        *reinterpret_cast<uint2*>(wave_buf + (32 * rt + col) * 256 + (((4 * dt + a) ^ (col & 15)) << 4) + 8 * half) = w2;
+      }
+  }
+  char* o0 = reinterpret_cast<char*>(p.out + (int64_t)(u.token_start + u.q_begin) * p.o_ts + (int64_t)u.head_begin * p.o_hs);
+  auto o_store = [&](const int e, const int64_t off) {
+    const uint4 w = *reinterpret_cast<const uint4*>(wave_buf + 1024 * e + 16 * lane);
+    if (row_base + 4 * e + sub < c.rows) *reinterpret_cast<uint4*>(o0 + off + chunk_of(e)) = w;
+  };
+  if (p.o_ts < kSmallStride && p.o_hs < kSmallStride) {
+#pragma unroll
+    for (int e = 0; e < 8 * NT; ++e) o_store(e, row_bytes<true>(rows_in_order(e), p.o_ts, p.o_hs));
+  } else {
+#pragma unroll 1
+    for (int e = 0; e < 8 * NT; ++e) o_store(e, row_bytes<false>(rows_in_order(e), p.o_ts, p.o_hs));
   }
   return false;
 }
@@ -1137,7 +1260,7 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
     pv_step<NT>(vaddr, lo, vf, s, st.oacc);   // all V reads have completed when this returns
     if (tn < nsteps) load_slice(jfirst + 32 * tn, false, true);
   }
-  finish_unit(p, u, c, r, st, 0, col, half);
+  finish_unit(p, u, c, r, st, col, half);
 }
 
 // Every workgroup is one worker of the Task-Table (paper section 3.3).  It first works through the
@@ -1167,11 +1290,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     // tolerance, with a scale so large that scores reach tens of log2 units it is not, and c stays in fp32.
     bool again;
     if (p.kv_ts == kD) {
-      if (p.c <= kPrescaleMaxC) again = process_wide<true, true>(p, u, smem, overflow_flags, force, lo, dof);
-      else again = process_wide<false, true>(p, u, smem, overflow_flags, force, lo, dof);
+      if (p.c <= kPrescaleMaxC) again = process_wide<2, true, true>(p, u, smem, overflow_flags, force, lo, dof);
+      else again = process_wide<2, false, true>(p, u, smem, overflow_flags, force, lo, dof);
     } else {
-      if (p.c <= kPrescaleMaxC) again = process_wide<true, false>(p, u, smem, overflow_flags, force, lo, dof);
-      else again = process_wide<false, false>(p, u, smem, overflow_flags, force, lo, dof);
+      if (p.c <= kPrescaleMaxC) again = process_wide<2, true, false>(p, u, smem, overflow_flags, force, lo, dof);
+      else again = process_wide<2, false, false>(p, u, smem, overflow_flags, force, lo, dof);
     }
     force = again;              // wavefront- and workgroup-uniform
     if (!again) ++i;
@@ -1251,8 +1374,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
 // Merge the partial states of a K/V-split family: O = sum_p 2^(m_p - m*) acc_p / sum_p 2^(m_p - m*) l_p.
 // Bound by memory latency on short steps, by the bytes of the partial results on a cut prefill chunk.  One record
 // of XyDevMergeRows per workgroup holds all a workgroup has to know (one scalar load, no chain of item, sequence
-// and row), half a wavefront merges one row (32 lanes x 16 bytes = one row of one partial per load), and the
-// loads of up to eight pieces are issued together before any of them is used: a row of eight pieces or fewer
+// and row), eight rows side by side read the partials in the order they are stored in (128 contiguous bytes per
+// group of four d), and the loads of up to eight pieces are issued together before any of them is used: a row of eight pieces or fewer
 // costs two round trips to memory, the record and the data.  Against one workgroup of 128 threads per row that
 // walked item, sequence and pieces one after another: 5.6 -> 2.9 us for one decode on 1300 tokens (8 families of
 // 4 rows), 9.5 -> 4.6 us for 24 short decodes, 20 -> 9.2 us for a cut chunk of 1024 tokens x 32 heads.
@@ -1289,11 +1412,11 @@ __device__ __forceinline__ void merge_pieces(const float* acc_row, const float* 
 __global__ __launch_bounds__(kMergeThreads) void xy_attn_merge_kernel(const XyDevMergeRows* items, const float* ws,
                                                                       uint16_t* out, int64_t o_ts, int64_t o_hs) {
   const XyDevMergeRows it = load_const(items + blockIdx.x);
-  const int r = it.row_begin + (threadIdx.x >> 5), d = 4 * (threadIdx.x & 31);
+  const int r = it.row_begin + (threadIdx.x & (kMergeRows - 1)), d4 = threadIdx.x / kMergeRows;      // row, group of four d
   if (r >= it.rows) return;
   const int64_t slab = ((int64_t)it.rows * (kD + 2) + 3) & ~(int64_t)3;
   const float* base = ws + it.ws_offset;
-  const float* acc_row = base + (int64_t)r * kD + d;
+  const float* acc_row = base + ((int64_t)d4 * it.rows + r) * 4;
   const float* m_row = base + (int64_t)it.rows * kD + r;
   const float* l_row = m_row + it.rows;
   float m_run = -INFINITY, den = 0.f;
@@ -1307,7 +1430,7 @@ __global__ __launch_bounds__(kMergeThreads) void xy_attn_merge_kernel(const XyDe
   uint2 w;
   w.x = pack_bf16(num[0] * inv, num[1] * inv);
   w.y = pack_bf16(num[2] * inv, num[3] * inv);
-  *reinterpret_cast<uint2*>(out + (int64_t)(it.token_begin + tl) * o_ts + (int64_t)(it.head_begin + hl) * o_hs + d) = w;
+  *reinterpret_cast<uint2*>(out + (int64_t)(it.token_begin + tl) * o_ts + (int64_t)(it.head_begin + hl) * o_hs + 4 * d4) = w;
 }
 
 }  // namespace

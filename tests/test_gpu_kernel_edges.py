@@ -78,3 +78,37 @@ def test_first_draws_from_the_shared_list(gpu, workers, wide, narrow):
         torch.cuda.synchronize()
     finally:
         db.close()
+
+
+@pytest.mark.parametrize("hq,hkv", [(1, 1), (3, 1), (5, 1), (14, 2), (24, 1)])
+def test_wide_units_row_mapping_through_lds(gpu, hq, hkv):
+    """Q enters and O leaves a wide unit in groups of four rows (row = token x heads + head): group sizes that are no
+    power of two, row counts that end inside a group of four, inside a 32-row tile and at a wavefront's first row;
+    split (partial results) and whole."""
+    g = hq // hkv
+    tokens = [max(33, 33 // g), -(-65 // g), 256 // g, 256 // g + 3]
+    b = W.make_custom([W.SeqSpec(t, 30 + 70 * i, P) for i, t in enumerate(tokens)], hq, hkv, 31 + hq)
+    run_and_check(gpu, b, f"{hq}/{hkv} heads, whole", split_kv_blocks=0)
+    b = W.make_custom([W.SeqSpec(t, 300 + 70 * i, V) for i, t in enumerate(tokens)], hq, hkv, 41 + hq)
+    run_and_check(gpu, b, f"{hq}/{hkv} heads, split", split_kv_blocks=1, verify_tile_tokens=256 // g)
+
+
+@pytest.mark.parametrize("dim", ["token", "head"])
+def test_wide_units_far_strides_of_q_and_out(gpu, dim):
+    """Row offsets of Q and O are 32-bit while the strides stay below 2^21 elements, 64-bit from there on."""
+    import torch
+    from paper_2412_18106_amd import binding as X
+    b = W.make_custom([W.SeqSpec(37, 150, P), W.SeqSpec(1, 90, D_)], 2, 1, 5)
+    db = gpu.DeviceBatch(b)
+    try:
+        want = db.run_numpy()
+        t = b.total_q
+        for stride in ((1 << 21) - 8, 1 << 21):
+            ts, hs = (stride, 128) if dim == "token" else (128, stride)
+            size = (t - 1) * ts + hs + 128
+            q, out = (torch.zeros(size, dtype=torch.bfloat16, device="cuda").as_strided((t, 2, 128), (ts, hs, 1)) for _ in range(2))
+            q.copy_(db.q)
+            X.xy_attn_run(db.plan, q, db.k_cache, db.v_cache, db.block_table, db.tree_masks, out, db.workspace, b.scale)
+            assert np.array_equal(out.float().cpu().numpy(), want), stride
+    finally:
+        db.close()

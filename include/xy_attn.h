@@ -109,8 +109,9 @@ typedef struct {
  * than 32 rows than workers, U < num_workers, and little else to do (a prefill chunk with no or few decodes
  * beside it: 2 N < M (num_workers - U), N the summed load max(rows, cost_row_floor) x nb of the families of at
  * most 32 rows, M the largest load of a wide family) has each wide family cut at
- * max(8, ceil(nb / floor(num_workers / U))) tiles, PREFILL families included (elsewhere a PREFILL family is
- * never cut). */
+ * max(m, ceil(nb / floor(num_workers / U))) tiles, PREFILL families included (elsewhere a PREFILL family is
+ * never cut); m = min(8, max(2, ceil(nb / 4))), and a family of nb <= 4 tiles is not cut (a piece costs about three
+ * tiles' time around its loop, the merge pass one to two more). */
 #define XY_SPLIT_AUTO (-1)
 /* verify_tile_tokens = XY_TILE_AUTO: a DECODE / VERIFY sequence is tiled in 32 / G tokens (G = Hq / Hkv: units of 32
  * rows, one wavefront each), except a sequence with more query tokens than that which visits at least 32 K/V tiles

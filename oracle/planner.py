@@ -39,7 +39,9 @@ Rules
    ``U < W``, and little else to do - ``2 N < M (W - U)`` with ``N`` the summed
    load ``max(rows, cost_row_floor) * nb`` of the families of at most 32 rows
    and ``M`` the largest such load of a wide family - each wide family, PREFILL
-   too, is cut at ``S = max(8, ceil(nb / floor(W / U)))`` instead.
+   too, is cut at ``S = max(m, ceil(nb / floor(W / U)))`` instead, with
+   ``m = min(8, max(2, ceil(nb / 4)))``, and ``m = nb`` (not cut) where
+   ``nb <= 4``.
 3. ``rows = q_count * head_count``; ``cost = max(rows, cost_row_floor) * blocks``
    (``cost_row_floor = 1`` is the paper's tileSize x kvLen in block units).
 4. Stable sort by cost descending, ties by (seq, head_begin, q_begin,
@@ -177,7 +179,7 @@ def plan_oracle(cfg, seqs):
                 s = split_narrow if rows <= NARROW_ROWS else split_wide
                 may_split = kind != PREFILL
                 if rows > NARROW_ROWS and wide_pieces > 1:
-                    s = max(8, _ceil_div(nb, wide_pieces))
+                    s = max(nb if nb <= 4 else min(8, max(2, _ceil_div(nb, 4))), _ceil_div(nb, wide_pieces))
                     may_split = True
                 k = _ceil_div(nb, s) if (may_split and s > 0 and nb > s) else 1
                 slab = _ceil_div(rows * (d + 2), 4) * 4

@@ -33,7 +33,14 @@ constexpr int64_t kAutoSplitMin = 2, kAutoSplitPieceOverhead = 1;
 // its own, and with some three pieces per wavefront the shared list still evens out), never more than 64
 constexpr int64_t kAutoSplitMaxSmall = 16, kAutoSplitMaxLarge = 64;
 constexpr int32_t kAutoSplitWide = 16;
-constexpr int64_t kAutoSplitWideMin = 8;      // tiles: a wide unit costs about four tiles' time around its loop
+// A wide unit costs about three tiles' time around its loop and its family a merge pass of another one to two, so a
+// cut family gets at most four pieces while those are shorter than eight tiles, none of less than two, and a family of
+// at most four tiles stays whole.
+constexpr int64_t kAutoSplitWidePieces = 4, kAutoSplitWideMin = 2, kAutoSplitWideMax = 8, kAutoSplitWideWhole = 4;
+inline int64_t wide_piece_min(int64_t nb) {
+  if (nb <= kAutoSplitWideWhole) return nb;
+  return std::min(kAutoSplitWideMax, std::max(kAutoSplitWideMin, ceil_div(nb, kAutoSplitWidePieces)));
+}
 // XY_ASSIGN_DYNAMIC without a unit of more than 32 rows: a shared list only if some unit visits more tiles than this
 constexpr int32_t kSharedListMinTiles = 2;
 // L2 domains (XCDs) of the GPU the unit kernel is written for
@@ -242,7 +249,7 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         int32_t split = rows <= kNarrowRows ? split_narrow : split_wide;
         bool may_split = !prefill;
         if (rows > kNarrowRows && wide_pieces > 1) {     // PREFILL too: nothing else would use the idle workers
-          split = (int32_t)std::max<int64_t>(kAutoSplitWideMin, ceil_div(nb, wide_pieces));
+          split = (int32_t)std::max<int64_t>(wide_piece_min(nb), ceil_div(nb, wide_pieces));
           may_split = true;
         }
         if (may_split && split > 0 && nb > split) k = (nb + split - 1) / split;

@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes as C
 import itertools
 import os
+import struct
 
 import numpy as np
 import torch  # noqa: F401  (first: the library must bind to the HIP runtime torch has already loaded)
@@ -92,7 +93,7 @@ _lib.xy_attn_run_static.argtypes = list(_lib.xy_attn_run.argtypes[:14]) + [C.c_f
 _lib.xy_attn_append_kv.argtypes = [_plan_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p,
                                    C.c_int64, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p]
 _lib.xy_attn_run_fused_qkv.argtypes = list(_lib.xy_attn_run.argtypes)
-_lib.xy_attn_copy_block_rows.argtypes = [C.POINTER(xy_kv_copy), C.c_int32, C.c_int32, C.c_void_p, C.c_void_p,
+_lib.xy_attn_copy_block_rows.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p,
                                          C.c_int64, C.c_int64, C.c_int64, C.c_void_p]
 _lib.xy_serve_schedule_chunk.argtypes = [C.c_int32, C.c_int32, C.POINTER(xy_queue_entry), C.c_int32,
                                          C.POINTER(xy_chunk_entry), C.POINTER(C.c_int32)]
@@ -167,7 +168,7 @@ def make_descs(seqs):
     n = len(seqs)
     arr = np.zeros(max(1, n), dtype=_DESC_DTYPE)
     if n:
-        if any(len(s) != 5 for s in seqs):
+        if set(map(len, seqs)) != {5}:
             raise ValueError("a sequence descriptor has five fields")
         flat = np.fromiter(itertools.chain.from_iterable(seqs), dtype=np.int64, count=5 * n).reshape(n, 5)
         arr.view(np.int32).reshape(-1, 6)[:n, :4] = flat[:, :4]
@@ -223,10 +224,15 @@ def xy_attn_plan_upload(plan):
     _check(_lib.xy_attn_plan_upload(plan))
 
 
+def _stream(stream):
+    """The hipStream_t of a torch.cuda.Stream, of the current one for None.  (torch.cuda.current_stream() builds a
+    Stream object first: 2.8 us a call, as long as a kernel launch.)"""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+
+
 def xy_attn_plan_upload_async(plan, stream=None):
     """One asynchronous copy of the plan's tables on the stream (default: the current one)."""
-    s = torch.cuda.current_stream() if stream is None else stream
-    _check(_lib.xy_attn_plan_upload_async(plan, C.c_void_p(s.cuda_stream)))
+    _check(_lib.xy_attn_plan_upload_async(plan, _stream(stream)))
 
 
 def xy_attn_plan_destroy(plan):
@@ -234,18 +240,16 @@ def xy_attn_plan_destroy(plan):
 
 
 def _ptr(t):
-    return C.c_void_p(0 if t is None else t.data_ptr())
+    return 0 if t is None else t.data_ptr()
 
 
 def _run_args(plan, q, k_cache, v_cache, block_table, tree_masks, out, workspace, softmax_scale, stream):
-    assert q.stride(-1) == 1 and out.stride(-1) == 1 and k_cache.stride(-1) == 1 and v_cache.stride(-1) == 1
-    assert k_cache.stride() == v_cache.stride() and block_table.is_contiguous()
-    s = torch.cuda.current_stream() if stream is None else stream
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    return (plan, _ptr(q), q.stride(0), q.stride(1), _ptr(k_cache), _ptr(v_cache),
-            k_cache.stride(0), k_cache.stride(1), k_cache.stride(2), _ptr(block_table),
-            _ptr(tree_masks), _ptr(out), out.stride(0), out.stride(1), _ptr(workspace),
-            ws_bytes, float(softmax_scale), C.c_void_p(s.cuda_stream))
+    qs, os_, ks = q.stride(), out.stride(), k_cache.stride()
+    assert qs[-1] == 1 and os_[-1] == 1 and ks[-1] == 1
+    assert ks == v_cache.stride() and block_table.is_contiguous()
+    return (plan, q.data_ptr(), qs[0], qs[1], k_cache.data_ptr(), v_cache.data_ptr(), ks[0], ks[1], ks[2],
+            block_table.data_ptr(), _ptr(tree_masks), out.data_ptr(), os_[0], os_[1], _ptr(workspace),
+            0 if workspace is None else workspace.nbytes, float(softmax_scale), _stream(stream))
 
 
 def xy_attn_run(plan, q, k_cache, v_cache, block_table, tree_masks, out, workspace, softmax_scale,
@@ -280,10 +284,9 @@ def xy_attn_append_kv(plan, k_new, v_new, k_cache, v_cache, block_table, stream=
     are fine); the caches and the block table as for xy_attn_run.  Asynchronous."""
     assert k_new.stride(-1) == 1 and k_new.stride() == v_new.stride()
     assert k_cache.stride(-1) == 1 and k_cache.stride() == v_cache.stride() and block_table.is_contiguous()
-    s = torch.cuda.current_stream() if stream is None else stream
     _check(_lib.xy_attn_append_kv(plan, _ptr(k_new), _ptr(v_new), k_new.stride(0), k_new.stride(1),
                                   _ptr(k_cache), _ptr(v_cache), k_cache.stride(0), k_cache.stride(1),
-                                  k_cache.stride(2), _ptr(block_table), C.c_void_p(s.cuda_stream)))
+                                  k_cache.stride(2), _ptr(block_table), _stream(stream)))
 
 
 def xy_attn_run_fused_qkv(plan, qkv, k_cache, v_cache, block_table, tree_masks, out, workspace, softmax_scale,
@@ -296,20 +299,17 @@ def xy_attn_run_fused_qkv(plan, qkv, k_cache, v_cache, block_table, tree_masks, 
 
 def xy_probe_stream_read(src, sink, stream=None):
     """Read every byte of the tensor src once (see xy_attn.h); sink: any device tensor of >= 4 bytes."""
-    s = torch.cuda.current_stream() if stream is None else stream
-    _check(_lib.xy_probe_stream_read(_ptr(src), src.numel() * src.element_size(), _ptr(sink), C.c_void_p(s.cuda_stream)))
+    _check(_lib.xy_probe_stream_read(_ptr(src), src.numel() * src.element_size(), _ptr(sink), _stream(stream)))
 
 
 def xy_probe_stream_read_once(src, sink, stream=None):
     """The same read with the non-temporal hint on every load."""
-    s = torch.cuda.current_stream() if stream is None else stream
-    _check(_lib.xy_probe_stream_read_once(_ptr(src), src.numel() * src.element_size(), _ptr(sink), C.c_void_p(s.cuda_stream)))
+    _check(_lib.xy_probe_stream_read_once(_ptr(src), src.numel() * src.element_size(), _ptr(sink), _stream(stream)))
 
 
 def xy_probe_mfma(iters, sink, stream=None):
     """2048 wavefronts x iters x 16 bf16 MFMAs of 32768 FLOPs (see xy_attn.h)."""
-    s = torch.cuda.current_stream() if stream is None else stream
-    _check(_lib.xy_probe_mfma(int(iters), _ptr(sink), C.c_void_p(s.cuda_stream)))
+    _check(_lib.xy_probe_mfma(int(iters), _ptr(sink), _stream(stream)))
 
 
 XY_MIX = {"none": 0, "even_4": 1, "uneven_8_0": 2, "dot2": 3, "scalar_2": 4, "attention": 5}
@@ -318,20 +318,21 @@ XY_MIX = {"none": 0, "even_4": 1, "uneven_8_0": 2, "dot2": 3, "scalar_2": 4, "at
 def xy_probe_issue_mix(mix, iters, cycles, sink, stream=None):
     """One wavefront per SIMD: iters x 32 MFMAs with the instructions of mix between them (see xy_attn.h);
     cycles: device int64 tensor of 1024 elements."""
-    s = torch.cuda.current_stream() if stream is None else stream
     assert cycles.numel() >= 1024 and cycles.element_size() == 8
-    _check(_lib.xy_probe_issue_mix(int(mix), int(iters), _ptr(cycles), _ptr(sink), C.c_void_p(s.cuda_stream)))
+    _check(_lib.xy_probe_issue_mix(int(mix), int(iters), _ptr(cycles), _ptr(sink), _stream(stream)))
 
 
 def xy_attn_copy_block_rows(copies, num_kv_heads, k_cache, v_cache, stream=None):
     """copies: list of (src_block, dst_block, rows): the copy-on-write copies of a step (see xy_attn.h)."""
     if not copies:
         return
-    arr = (xy_kv_copy * len(copies))(*[xy_kv_copy(*map(int, c)) for c in copies])
-    s = torch.cuda.current_stream() if stream is None else stream
+    flat = [int(x) for c in copies for x in c]
+    if len(flat) != 3 * len(copies):
+        raise ValueError("a copy has three fields")
+    arr = struct.pack(f"{len(flat)}i", *flat)       # xy_kv_copy records
     _check(_lib.xy_attn_copy_block_rows(arr, len(copies), int(num_kv_heads), _ptr(k_cache), _ptr(v_cache),
                                         k_cache.stride(0), k_cache.stride(1), k_cache.stride(2),
-                                        C.c_void_p(s.cuda_stream)))
+                                        _stream(stream)))
 
 
 def xy_serve_schedule_chunk(token_budget, reserved_decode_slots, queue):

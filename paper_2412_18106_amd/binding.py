@@ -326,10 +326,11 @@ def xy_attn_copy_block_rows(copies, num_kv_heads, k_cache, v_cache, stream=None)
     """copies: list of (src_block, dst_block, rows): the copy-on-write copies of a step (see xy_attn.h)."""
     if not copies:
         return
-    flat = [int(x) for c in copies for x in c]
-    if len(flat) != 3 * len(copies):
-        raise ValueError("a copy has three fields")
-    arr = struct.pack(f"{len(flat)}i", *flat)       # xy_kv_copy records
+    try:
+        flat = [int(x) for src, dst, rows in copies for x in (src, dst, rows)]
+        arr = struct.pack(f"{len(flat)}i", *flat)       # xy_kv_copy records
+    except (ValueError, struct.error):      # fields left out, too many of them or beyond 32 bits: the record's own rules
+        arr = (xy_kv_copy * len(copies))(*[xy_kv_copy(*map(int, c)) for c in copies])
     _check(_lib.xy_attn_copy_block_rows(arr, len(copies), int(num_kv_heads), _ptr(k_cache), _ptr(v_cache),
                                         k_cache.stride(0), k_cache.stride(1), k_cache.stride(2),
                                         _stream(stream)))

@@ -95,8 +95,9 @@ typedef struct {
 
 /* split_kv_blocks = XY_SPLIT_AUTO: the K/V split (this design's extension of the Update stage of section
  * 4.2.1 across workers) is sized to the batch.  Units of at most 32 rows are processed one per wavefront,
- * L = 4 * num_workers wavefronts in all.  Let F be the number of DECODE / VERIFY families of at most 32
- * rows (token tiles x KV heads) and nb the number of 128-key tiles a family visits.
+ * L = 4 * num_workers wavefronts in all.  Let F be the number of families of at most 32 rows (token tiles x head
+ * groups; PREFILL ones, the last tokens of a prompt, count and are cut only if they visit more tiles than
+ * floor((2 t + 5 U) / (4 num_workers)), t the tiles of all families, U those of more than 32 rows) and nb the number of 128-key tiles a family visits.
  *  - All such families visit the same nb: each is cut into k pieces, k minimising
  *    ceil(F k / L) * (ceil(nb / k) + 1) (rounds of wavefront slots x tiles per piece, a piece costing about
  *    one tile on top of its own for set-up, partial result and merge) over k = 1 .. nb, the smallest such
@@ -105,13 +106,21 @@ typedef struct {
  *    split size is min(max(s, 2), max(16, min(64, floor(2 s / 5)))): the share itself for small batches, 16
  *    tiles up to a share of 40, then two fifths of the share (about three pieces per wavefront, which the shared
  *    list still evens out, each piece costing about a tile and a half beyond its own), at most 64.
- * DECODE / VERIFY families of more than 32 rows are split at 16 tiles.  A batch with fewer families of more
- * than 32 rows than workers, U < num_workers, and little else to do (a prefill chunk with no or few decodes
- * beside it: 2 N < M (num_workers - U), N the summed load max(rows, cost_row_floor) x nb of the families of at
- * most 32 rows, M the largest load of a wide family) has each wide family cut at
- * max(m, ceil(nb / floor(num_workers / U))) tiles, PREFILL families included (elsewhere a PREFILL family is
- * never cut); m = min(8, max(2, ceil(nb / 4))), and a family of nb <= 4 tiles is not cut (a piece costs about three
- * tiles' time around its loop, the merge pass one to two more). */
+ * Wide families (more than 32 rows): DECODE / VERIFY ones are split at 16 tiles, PREFILL ones are whole, unless that
+ * leaves workers idle; then all of them, PREFILL too, are cut at T tiles (U = their number, nb their tiles):
+ *  - 2 U <= num_workers and little else to do (a prefill chunk with no or few decodes beside it:
+ *    2 N < M (num_workers - U), N the summed load max(rows, cost_row_floor) x nb of the families of at most 32 rows,
+ *    M the largest load of a wide family, R its largest max(rows, cost_row_floor)): T is the smallest size from
+ *    ceil(B / (num_workers R)), B = R sum nb + floor(N / 2), on at which they make at most
+ *    ceil((num_workers + ceil(num_workers R sum nb / B)) / 2) pieces (others have the narrow work), a family being cut at max(T, m), m = min(8, max(2, ceil(nb / 4))), and whole where nb <= 4 (a piece costs about two and a half
+ *    tiles' time around its loop, the merge pass two more); T is then raised to the longest family that stays
+ *    whole.
+ *  - 2 U > num_workers and the longest costs more than a quarter of a worker's mean load: of the sizes that make at most
+ *    r num_workers pieces, r = ceil(U / num_workers) and the next two, the one with the shortest estimated time
+ *    (pieces, 2 nb + 5 half tiles each, longest first to the worker that is free first; 4 for the merge pass; never
+ *    less than the mean load, a tile of a narrow family counted as 2), if that is a fifth less than without a cut.
+ *  A size whose partial results, with those of the narrow families, exceed XY_STATIC_WORKSPACE_BYTES is doubled until
+ *  they fit (first kind) or not considered (second). */
 #define XY_SPLIT_AUTO (-1)
 /* verify_tile_tokens = XY_TILE_AUTO: a DECODE / VERIFY sequence is tiled in 32 / G tokens (G = Hq / Hkv: units of 32
  * rows, one wavefront each), except a sequence with more query tokens than that which visits at least 32 K/V tiles

@@ -27,21 +27,37 @@ Rules
    ``nb > S`` is cut into ``k = ceil(nb / S)`` units, unit ``p`` covering blocks
    ``[floor(p nb / k), floor((p + 1) nb / k))``.
    ``split_kv_blocks = -1`` (automatic) sizes S to the batch.  Narrow
-   families are the non-PREFILL families of at most 32 rows; ``F`` their
-   number (token tiles times Hkv), ``L = 4 W`` the wavefront slots.  If all of
+   families are those of at most 32 rows; PREFILL ones (the last tokens of a
+   prompt) count, and are cut like the others, if they visit more tiles than
+   ``floor(t / (2 W))``, ``t`` the tiles of all families of the batch; ``F`` their
+   number (token tiles times head groups), ``L = 4 W`` the wavefront slots.  If all of
    them have the same ``nb``: ``S = ceil(nb / k)`` for the ``k`` that minimises
    ``ceil(F k / L) * (ceil(nb / k) + 1)`` over ``k = 1 .. nb``, smallest ``k``
    on ties (the ``+ 1`` is what a piece costs beyond its tiles).  Otherwise
    ``S = min(max(s, 2), max(16, min(64, floor(2 s / 5))))`` with
    ``s = ceil(B / L)`` and ``B`` the sum of their ``nb``.
-   Non-PREFILL families of more than 32 rows use ``S = 16``.  When the batch
-   has fewer families of more than 32 rows (PREFILL included) than workers,
-   ``U < W``, and little else to do - ``2 N < M (W - U)`` with ``N`` the summed
-   load ``max(rows, cost_row_floor) * nb`` of the families of at most 32 rows
-   and ``M`` the largest such load of a wide family - each wide family, PREFILL
-   too, is cut at ``S = max(m, ceil(nb / floor(W / U)))`` instead, with
-   ``m = min(8, max(2, ceil(nb / 4)))``, and ``m = nb`` (not cut) where
-   ``nb <= 4``.
+   Wide families (more than 32 rows) of a DECODE / VERIFY sequence use ``S =
+   16``, PREFILL ones are whole, unless a cut size ``T`` for all wide families,
+   PREFILL too, is found.  ``U`` is the number of wide families:
+   - ``2 U <= W`` and little else to do - ``2 N < M (W - U)`` with ``N`` the
+     summed load ``max(rows, cost_row_floor) * nb`` of the families of at most
+     32 rows and ``M`` the largest such load of a wide family: ``T`` is the
+     smallest size from ``ceil(B / (W R))`` on (``R`` the largest ``max(rows,
+     cost_row_floor)`` of a wide family, ``B = R sum nb + floor(N / 2)``) at
+     which all together make at most ``ceil((W + ceil(W R sum nb / B)) / 2)``
+     pieces, a family being cut at ``max(T, m)``,
+     ``m = min(8, max(2, ceil(nb / 4)))`` or ``nb`` where ``nb <= 4``; then
+     ``T`` is raised to the longest family that stays whole.
+   - ``2 U > W`` and the longest family costs more than a quarter of the mean
+     load of a worker (in half tiles: a piece ``2 nb + 5``, a narrow tile 2):
+     candidates are, for ``r = ceil(U / W)`` and the next two, the smallest
+     ``T >= max(2, ceil(sum nb / (r W)))`` with at most ``r W`` pieces; the one
+     with the smallest estimated time (longest piece first to the least loaded
+     worker, + 4 for the merge pass, at least the mean load) if that is at most
+     ``floor(4 / 5)`` of the estimate without ``T``.
+   Sizes that would need more workspace than XY_STATIC_WORKSPACE_BYTES, narrow
+   partials included, are doubled until they do not (first kind) or left out
+   (second kind).
 3. ``rows = q_count * head_count``; ``cost = max(rows, cost_row_floor) * blocks``
    (``cost_row_floor = 1`` is the paper's tileSize x kvLen in block units).
 4. Stable sort by cost descending, ties by (seq, head_begin, q_begin,
@@ -58,7 +74,9 @@ Rules
    go to the chiplet whose load so far is smallest (lowest index among
    equals); a unit then goes to the least-loaded worker among the W / 8 of its
    group's chiplet.  If the heaviest chiplet exceeds 1.03 times the mean
-   (``max * 8 * 100 > total * 103``), no grouping is used.
+   (``max * 8 * 100 > total * 103``), no grouping is used; nor, with at most
+   ``2 W`` units of more than 32 rows, if the largest load of a worker with it
+   exceeds 1.03 times the largest without.
    ``assign_policy`` 2 (dynamic): units of more than 32 rows are assigned as
    with policy 1, counting only their own costs; units of at most 32 rows are
    emitted behind all workers' lists, in sorted order, as one shared list that
@@ -73,12 +91,15 @@ Rules
 """
 from __future__ import annotations
 
+import heapq
+
 import numpy as np
 
 PREFILL, DECODE, VERIFY = 0, 1, 2
 MASK_CAUSAL, MASK_TREE = 0, 1
 KV_TILE = 128
 SPLIT_AUTO = -1          # split_kv_blocks value that sizes the K/V split to the batch
+STATIC_WORKSPACE_FLOATS = 64 * 1024 * 1024 // 4      # what the library's own workspace holds
 TILE_AUTO = -1           # verify_tile_tokens value that picks the token tile per sequence
 NARROW_ROWS = 32         # units of at most this many rows are processed one per wavefront
 CHIPLETS = 8             # L2 domains of the GPU: workers [x W / 8, (x + 1) W / 8) run on domain x when 8 divides W
@@ -113,6 +134,77 @@ def _ceil_div(a, b):
     return -(-a // b)
 
 
+def _narrow_tile_pieces(nb, size):
+    return _ceil_div(nb, size) if nb > size else 1
+
+
+def _wide_pieces(nb, prefill, size, floor):
+    """Pieces of a wide family of nb tiles; size 0: PREFILL whole, others cut at 16 tiles."""
+    if size == 0:
+        return 1 if prefill else _ceil_div(nb, 16)
+    if floor:
+        size = max(size, nb if nb <= 4 else min(8, max(2, _ceil_div(nb, 4))))
+    return _ceil_div(nb, size)
+
+
+def _wide_estimate(wide, size, w, narrow_tiles):
+    """Half tiles until the last worker is done: pieces (2 per tile + 5) longest first to the worker with the least
+    load, 4 for a merge pass, and never less than all the work over all workers."""
+    costs = []
+    cut = False
+    for nb, _rows, prefill in wide:
+        k = _wide_pieces(nb, prefill, size, False)
+        cut = cut or k > 1
+        costs += [2 * (((p + 1) * nb) // k - (p * nb) // k) + 5 for p in range(k)]
+    load = [0] * w
+    for x in sorted(costs, reverse=True):
+        heapq.heapreplace(load, load[0] + x)
+    return max(max(load) + (4 if cut else 0), _ceil_div(sum(costs) + 2 * narrow_tiles, w))
+
+
+def _wide_cut(wide, narrow_tiles, narrow_load, narrow_ws, w, d, cost_floor):
+    """Rule 2, wide part: (size, floor) of the cut.  wide: one (tiles, rows, is prefill) per family."""
+    if not wide:
+        return 0, False
+    total, longest = sum(x[0] for x in wide), max(x[0] for x in wide)
+
+    def pieces(size, floor):
+        return sum(_wide_pieces(nb, pre, size, floor) for nb, _r, pre in wide)
+
+    def fits(size, floor):
+        ws = sum(_wide_pieces(nb, pre, size, floor) * (_ceil_div(rows * (d + 2), 4) * 4)
+                 for nb, rows, pre in wide if _wide_pieces(nb, pre, size, floor) > 1)
+        return ws <= STATIC_WORKSPACE_FLOATS - narrow_ws
+
+    if 2 * len(wide) <= w:
+        if not narrow_load * 2 < max(max(r, cost_floor) * nb for nb, r, _p in wide) * (w - len(wide)):
+            return 0, False
+        tile_load = max(max(r, cost_floor) for _nb, r, _p in wide)
+        both = total * tile_load + narrow_load // 2
+        size = _ceil_div(both, w * tile_load)
+        room = _ceil_div(w + _ceil_div(w * total * tile_load, both), 2)
+        while size < longest and pieces(size, True) > room:
+            size += 1
+        size = max([size] + [nb for nb, _r, pre in wide if _wide_pieces(nb, pre, size, True) == 1])
+        while size < longest and not fits(size, True):
+            size *= 2
+        return size, True
+    if 4 * (2 * longest + 5) <= _ceil_div(2 * total + 5 * len(wide) + 2 * narrow_tiles, w):
+        return 0, False
+    best, chosen = _wide_estimate(wide, 0, w, narrow_tiles) * 4 // 5 + 1, 0
+    first = _ceil_div(len(wide), w)
+    for rounds in range(first, first + 3):
+        size = max(2, _ceil_div(total, rounds * w))
+        while size < longest and pieces(size, False) > rounds * w:
+            size += 1
+        if size >= longest or not fits(size, False):
+            continue
+        t = _wide_estimate(wide, size, w, narrow_tiles)
+        if t < best:
+            best, chosen = t, size
+    return chosen, False
+
+
 def plan_oracle(cfg, seqs):
     """cfg: dict with the plan parameters; seqs: list of
     (query_len, context_len, kind, mask_kind, mask_word_offset).
@@ -128,43 +220,40 @@ def plan_oracle(cfg, seqs):
     merges = []
     ws_floats = 0
     split_narrow = split_wide = cfg["split_kv_blocks"]
-    wide_pieces = 1
+    wide_size, wide_floor = 0, False
     if cfg["split_kv_blocks"] == SPLIT_AUTO:
-        wide_families = wide_max = narrow_total = 0
+        wide = []               # (tiles, rows, is prefill) of every family of more than 32 rows
+        narrow_load = narrow_tiles = 0
+        narrow = []             # (tiles, rows) of every family of at most 32 rows
         for ql, c, kind, mk, _off in seqs:
             t = cfg["prefill_tile_tokens"] if kind == PREFILL else _verify_tile(cfg, ql, c, group)
             hc = cfg["prefill_heads_per_unit"] if kind == PREFILL else group
             for q_begin in range(0, ql, t):
                 q_count = min(t, ql - q_begin)
                 last = c + ql if mk == MASK_TREE else c + q_begin + q_count
-                load = max(q_count * hc, cfg["cost_row_floor"]) * _ceil_div(last, KV_TILE)
-                if q_count * hc > NARROW_ROWS:
-                    wide_families += hq // hc
-                    wide_max = max(wide_max, load)
-                else:
-                    narrow_total += load * (hq // hc)
-        if 0 < wide_families < w and narrow_total * 2 < wide_max * (w - wide_families):
-            wide_pieces = w // wide_families
-        lengths = []            # nb of every narrow non-PREFILL token tile
-        for ql, c, kind, mk, _off in seqs:
-            if kind == PREFILL:
-                continue
-            tile = _verify_tile(cfg, ql, c, group)
-            for q_begin in range(0, ql, tile):
-                q_count = min(tile, ql - q_begin)
-                if q_count * group > NARROW_ROWS:
+                nb, rows = _ceil_div(last, KV_TILE), q_count * hc
+                if rows > NARROW_ROWS:
+                    wide += [(nb, rows, kind == PREFILL)] * (hq // hc)
                     continue
-                last = c + ql if mk == MASK_TREE else c + q_begin + q_count
-                lengths.append(_ceil_div(last, KV_TILE))
+                narrow_load += max(rows, cfg["cost_row_floor"]) * nb * (hq // hc)
+                narrow_tiles += nb * (hq // hc)
+                narrow += [(nb, rows, kind == PREFILL)] * (hq // hc)
+        prefill_whole = (2 * sum(x[0] for x in wide) + 5 * len(wide) + 2 * narrow_tiles) // (4 * w)
+        narrow = [x for x in narrow if not x[2] or x[0] > prefill_whole]
         slots = 4 * w
-        if lengths and len(set(lengths)) == 1:
-            nb, families = lengths[0], len(lengths) * hkv
+        if len({x[0] for x in narrow}) == 1:
+            nb, families = narrow[0][0], len(narrow)
             best_k = min(range(1, nb + 1), key=lambda k: (_ceil_div(families * k, slots) * (_ceil_div(nb, k) + 1), k))
             split_narrow = _ceil_div(nb, best_k)
         else:
-            share = _ceil_div(sum(lengths) * hkv, slots)
+            share = _ceil_div(sum(x[0] for x in narrow), slots)
             split_narrow = min(max(share, 2), max(16, min(64, 2 * share // 5)))
         split_wide = 16
+        narrow_ws = 0
+        for nb, rows, _pre in narrow:
+            k = _narrow_tile_pieces(nb, split_narrow)
+            narrow_ws += k * (_ceil_div(rows * (d + 2), 4) * 4) if k > 1 else 0
+        wide_size, wide_floor = _wide_cut(wide, narrow_tiles, narrow_load, narrow_ws, w, d, cfg["cost_row_floor"])
     for i, (ql, c, kind, mk, _off) in enumerate(seqs):
         if kind == PREFILL:
             tile, hc = cfg["prefill_tile_tokens"], cfg["prefill_heads_per_unit"]
@@ -177,11 +266,12 @@ def plan_oracle(cfg, seqs):
             for head_begin in range(0, hq, hc):
                 rows = q_count * hc
                 s = split_narrow if rows <= NARROW_ROWS else split_wide
-                may_split = kind != PREFILL
-                if rows > NARROW_ROWS and wide_pieces > 1:
-                    s = max(nb if nb <= 4 else min(8, max(2, _ceil_div(nb, 4))), _ceil_div(nb, wide_pieces))
-                    may_split = True
-                k = _ceil_div(nb, s) if (may_split and s > 0 and nb > s) else 1
+                if rows > NARROW_ROWS and wide_size:
+                    k = _wide_pieces(nb, kind == PREFILL, wide_size, wide_floor)
+                else:
+                    may_split = kind != PREFILL or (cfg["split_kv_blocks"] == SPLIT_AUTO and rows <= NARROW_ROWS
+                                                    and nb > prefill_whole)
+                    k = _ceil_div(nb, s) if (may_split and s > 0 and nb > s) else 1
                 slab = _ceil_div(rows * (d + 2), 4) * 4
                 base = -1
                 if k > 1:
@@ -226,19 +316,29 @@ def plan_oracle(cfg, seqs):
                 chip_load[x] += group_cost[key]
             if max(chip_load) * CHIPLETS * 100 > sum(chip_load) * 103:
                 chip_of_group = None
-        for x in order:
-            u = fam_units[x]
-            narrow = u[2] * u[4] <= NARROW_ROWS
-            if share and narrow:
-                shared.append(u)
-                continue
-            if not narrow and chip_of_group is not None:
-                lo = chip_of_group[u[0] * hkv + u[1] // group] * per_chip
-                k = lo + int(np.argmin(load[lo:lo + per_chip]))
-            else:
-                k = int(np.argmin(load))          # first index of the minimum
-            per_worker[k].append(u)
-            load[k] += u[10]
+        def assign(chips):
+            lists, load, shared_list, wide_units = [[] for _ in range(w)], np.zeros(w, dtype=np.int64), [], 0
+            for x in order:
+                u = fam_units[x]
+                narrow = u[2] * u[4] <= NARROW_ROWS
+                if share and narrow:
+                    shared_list.append(u)
+                    continue
+                wide_units += not narrow
+                if not narrow and chips is not None:
+                    lo = chips[u[0] * hkv + u[1] // group] * per_chip
+                    k = lo + int(np.argmin(load[lo:lo + per_chip]))
+                else:
+                    k = int(np.argmin(load))          # first index of the minimum
+                lists[k].append(u)
+                load[k] += u[10]
+            return lists, shared_list, int(load.max()), wide_units
+
+        per_worker, shared, largest, wide_units = assign(chip_of_group)
+        if chip_of_group is not None and 0 < wide_units <= 2 * w:
+            plain = assign(None)
+            if largest * 100 > plain[2] * 103:
+                per_worker, shared = plain[:2]
     flat = [u for lst in per_worker for u in lst] + shared
     offsets = np.zeros(w + 1, dtype=np.int32)
     offsets[1:] = np.cumsum([len(lst) for lst in per_worker])

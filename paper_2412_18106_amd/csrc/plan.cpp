@@ -33,14 +33,94 @@ constexpr int64_t kAutoSplitMin = 2, kAutoSplitPieceOverhead = 1;
 // its own, and with some three pieces per wavefront the shared list still evens out), never more than 64
 constexpr int64_t kAutoSplitMaxSmall = 16, kAutoSplitMaxLarge = 64;
 constexpr int32_t kAutoSplitWide = 16;
-// A wide unit costs about three tiles' time around its loop and its family a merge pass of another one to two, so a
-// cut family gets at most four pieces while those are shorter than eight tiles, none of less than two, and a family of
-// at most four tiles stays whole.
+// Families of more than kNarrowRows rows (wide: a workgroup works on one unit at a time, whatever its rows, in time
+// proportional to its tiles).  A unit costs about two and a half tiles' time around its loop and a plan with cut
+// families a merge pass of another two; kWideUnitHalves and kWideMergeHalves are these in half tiles.
+constexpr int64_t kWideUnitHalves = 5, kWideMergeHalves = 4;
+// Few wide families (at most half as many as workers): pieces no shorter than eight tiles, or a quarter of the family
+// where that is less, at least two; a family of at most four tiles stays whole.
 constexpr int64_t kAutoSplitWidePieces = 4, kAutoSplitWideMin = 2, kAutoSplitWideMax = 8, kAutoSplitWideWhole = 4;
 inline int64_t wide_piece_min(int64_t nb) {
   if (nb <= kAutoSplitWideWhole) return nb;
   return std::min(kAutoSplitWideMax, std::max(kAutoSplitWideMin, ceil_div(nb, kAutoSplitWidePieces)));
 }
+
+// A token tile: count families (one per head group) of nb tiles
+using XyTileClass = XyPlanScratch::TileClass;
+
+inline int64_t slab_floats(int64_t rows, int64_t d) { return ((rows * (d + 2) + 3) / 4) * 4; }
+
+// How XY_SPLIT_AUTO cuts the wide families: pieces of at most `size` tiles (0: as the stage says, PREFILL whole and
+// VERIFY at kAutoSplitWide), none shorter than wide_piece_min where `floor` is set.
+struct WideCut {
+  int64_t size = 0;
+  bool floor = false;
+  int64_t pieces(const XyTileClass& w) const {
+    int64_t s = size;
+    if (s == 0) s = w.prefill ? w.nb : kAutoSplitWide;
+    else if (floor) s = std::max(s, wide_piece_min(w.nb));
+    return ceil_div(w.nb, s);
+  }
+};
+
+int64_t wide_piece_count(const std::vector<XyTileClass>& wide, const WideCut& cut) {
+  int64_t n = 0;
+  for (const XyTileClass& w : wide) n += w.count * cut.pieces(w);
+  return n;
+}
+
+int64_t wide_workspace(const std::vector<XyTileClass>& wide, const WideCut& cut, int64_t d) {
+  int64_t ws = 0;
+  for (const XyTileClass& w : wide) {
+    const int64_t k = cut.pieces(w);
+    if (k > 1) ws += w.count * k * slab_floats(w.rows, d);
+  }
+  return ws;
+}
+
+// the smallest size from `lo` on at which the families make at most `slots` pieces
+int64_t wide_size_for(const std::vector<XyTileClass>& wide, int64_t lo, int64_t longest, int64_t slots, bool floor) {
+  int64_t hi = std::max(lo, longest);
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    if (wide_piece_count(wide, WideCut{mid, floor}) <= slots) hi = mid; else lo = mid + 1;
+  }
+  return lo;
+}
+
+// Time of the launch in half tiles if the pieces go, longest first, to the worker that is free first and the narrow
+// work (a narrow tile counted as a wide one) fills what is left.  Equal pieces and equally loaded workers are
+// handled together.
+int64_t wide_estimate(const std::vector<XyTileClass>& wide, const WideCut& cut, int64_t workers, int64_t narrow_tiles,
+                      XyPlanScratch& scratch) {
+  auto& sizes = scratch.sizes;          // (cost, pieces)
+  auto& loads = scratch.loads;          // (load, workers), load ascending
+  sizes.clear();
+  bool any_cut = false;
+  int64_t total = 0;
+  for (const XyTileClass& w : wide) {
+    const int64_t k = cut.pieces(w), longer = w.nb % k;
+    any_cut |= k > 1;
+    total += w.count * (2 * w.nb + kWideUnitHalves * k);
+    if (longer) sizes.emplace_back(2 * (w.nb / k + 1) + kWideUnitHalves, w.count * longer);
+    sizes.emplace_back(2 * (w.nb / k) + kWideUnitHalves, w.count * (k - longer));
+  }
+  std::sort(sizes.begin(), sizes.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+  loads.assign(1, {0, workers});
+  for (const auto& [cost, pieces] : sizes) {
+    for (int64_t left = pieces; left > 0;) {
+      const int64_t load = loads.front().first + cost, n = std::min(left, loads.front().second);
+      left -= n;
+      if (n == loads.front().second) loads.erase(loads.begin());
+      else loads.front().second -= n;
+      auto at = std::lower_bound(loads.begin(), loads.end(), load, [](const auto& x, int64_t l) { return x.first < l; });
+      if (at != loads.end() && at->first == load) at->second += n;
+      else loads.insert(at, {load, n});
+    }
+  }
+  return std::max(loads.back().first + (any_cut ? kWideMergeHalves : 0), ceil_div(total + 2 * narrow_tiles, workers));
+}
+
 // XY_ASSIGN_DYNAMIC without a unit of more than 32 rows: a shared list only if some unit visits more tiles than this
 constexpr int32_t kSharedListMinTiles = 2;
 // L2 domains (XCDs) of the GPU the unit kernel is written for
@@ -146,56 +226,57 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
 
     // --- size of the K/V split (see XY_SPLIT_AUTO) ---------------------------
     int32_t split_narrow = c.split_kv_blocks, split_wide = c.split_kv_blocks;
-    int64_t wide_pieces = 1;      // XY_SPLIT_AUTO: pieces a family of more than kNarrowRows rows may be cut into
+    int64_t prefill_whole_tiles = INT64_MAX;      // a PREFILL family of at most 32 rows is whole up to so many tiles
+    WideCut cut;
     if (c.split_kv_blocks == XY_SPLIT_AUTO) {
-      // Fewer wide families than workers, and so little narrow work that the other workers would be done with
-      // it before a wide family is (a prefill chunk with no or few decodes beside it): the wide families are
-      // cut to fill the workers.  Loads as in the cost model, max(rows, floor) x tiles.
-      int64_t wide_families = 0, wide_max = 0, narrow_total = 0;
+      std::vector<XyTileClass>&wide = plan->scratch.wide, &narrow = plan->scratch.narrow;
+      wide.clear();
+      narrow.clear();
+      int64_t wide_families = 0, wide_tiles = 0, wide_longest = 0, wide_max = 0, tile_load = 1, narrow_total = 0, narrow_tiles = 0;
       for (int32_t i = 0; i < num_seqs; ++i) {
         const xy_seq_desc& s = descs[i];
         const bool pre = s.kind == XY_PREFILL, tree = s.mask_kind == XY_MASK_TREE;
         const int32_t tile = pre ? c.prefill_tile_tokens : verify_tile_of(c, s, group);
         const int32_t hc = pre ? c.prefill_heads_per_unit : group;
+        const int64_t count = c.num_q_heads / hc;
         for (int32_t qb = 0; qb < s.query_len; qb += tile) {
           const int32_t qc = std::min(tile, s.query_len - qb);
           const int64_t rows = (int64_t)qc * hc;
           const int64_t last_excl = tree ? (int64_t)s.context_len + s.query_len : (int64_t)s.context_len + qb + qc;
-          const int64_t load = std::max<int64_t>(rows, c.cost_row_floor) * ceil_div(last_excl, kKvTile);
+          const int64_t nb = ceil_div(last_excl, kKvTile), load = std::max<int64_t>(rows, c.cost_row_floor) * nb;
           if (rows > kNarrowRows) {
-            wide_families += c.num_q_heads / hc;
+            wide.push_back(XyTileClass{nb, count, rows, pre});
+            wide_families += count;
+            wide_tiles += nb * count;
+            wide_longest = std::max(wide_longest, nb);
             wide_max = std::max(wide_max, load);
+            tile_load = std::max(tile_load, load / nb);
           } else {
-            narrow_total += load * (c.num_q_heads / hc);
+            narrow_total += load * count;
+            narrow_tiles += nb * count;
+            narrow.push_back(XyTileClass{nb, count, rows, pre});
           }
         }
       }
-      if (wide_families > 0 && wide_families < c.num_workers &&
-          narrow_total * 2 < wide_max * (c.num_workers - wide_families))
-        wide_pieces = c.num_workers / wide_families;
-      int64_t tiles_total = 0;
-      int64_t first_nb = -1;
+      // The last tokens of a prompt may be a narrow PREFILL family.  One that visits more tiles than half a worker's
+      // mean load is cut like the others: a wavefront on its own takes about a microsecond per 32 keys and comes to it
+      // behind the wide units (8 families of 94 tiles beside 23 tiles of wide work a worker 394 -> 103 us, 2 of 19
+      // beside 24 142 -> 105 us); a shorter one fills a gap (8 of 7 beside 15: 65 us whole, 74 cut).
+      prefill_whole_tiles = (2 * wide_tiles + kWideUnitHalves * wide_families + 2 * narrow_tiles) / (4 * (int64_t)c.num_workers);
+      narrow.erase(std::remove_if(narrow.begin(), narrow.end(), [&](const XyTileClass& w) {
+        return w.prefill && w.nb <= prefill_whole_tiles;
+      }), narrow.end());
+      int64_t split_tiles = 0;
       bool uniform = true;
-      for (int32_t i = 0; i < num_seqs; ++i) {
-        const xy_seq_desc& s = descs[i];
-        if (s.kind == XY_PREFILL) continue;
-        const bool tree = s.mask_kind == XY_MASK_TREE;
-        const int32_t vtile = verify_tile_of(c, s, group);
-        for (int32_t qb = 0; qb < s.query_len; qb += vtile) {
-          const int32_t qc = std::min(vtile, s.query_len - qb);
-          if ((int64_t)qc * group > kNarrowRows) continue;
-          const int64_t last_excl = tree ? (int64_t)s.context_len + s.query_len : (int64_t)s.context_len + qb + qc;
-          const int64_t nb = ceil_div(last_excl, kKvTile);
-          tiles_total += nb * c.num_kv_heads;
-          if (first_nb < 0) first_nb = nb;
-          uniform = uniform && nb == first_nb;
-        }
+      for (const XyTileClass& w : narrow) {
+        split_tiles += w.nb * w.count;
+        uniform = uniform && w.nb == narrow[0].nb;
       }
       const int64_t slots = (int64_t)kNarrowSlotsPerWorker * c.num_workers;
-      if (uniform && first_nb > 0) {
+      if (uniform && !narrow.empty()) {
         // equal families: pieces per family that minimise (rounds of slots) x (tiles per piece + what a
         // piece costs on top of its tiles: set-up, partial result and its share of the merge, about one tile)
-        const int64_t families = tiles_total / first_nb;
+        const int64_t first_nb = narrow[0].nb, families = split_tiles / first_nb;
         int64_t best_k = 1, best = ceil_div(families, slots) * (first_nb + kAutoSplitPieceOverhead);
         for (int64_t k = 2; k <= first_nb; ++k) {
           const int64_t piece = ceil_div(first_nb, k);
@@ -207,11 +288,59 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         }
         split_narrow = (int32_t)ceil_div(first_nb, best_k);
       } else {
-        const int64_t share = ceil_div(tiles_total, slots);
+        const int64_t share = ceil_div(split_tiles, slots);
         const int64_t most = std::max<int64_t>(kAutoSplitMaxSmall, std::min<int64_t>(kAutoSplitMaxLarge, 2 * share / 5));
         split_narrow = (int32_t)std::min<int64_t>(std::max<int64_t>(share, kAutoSplitMin), most);
       }
       split_wide = kAutoSplitWide;
+
+      // The wide families are cut along K/V, PREFILL included, where whole ones would leave workers idle.
+      if (wide_families > 0) {
+        // Partial results beyond what xy_attn_run_static holds are not made for the sake of balance.
+        int64_t narrow_ws = 0;
+        for (const XyTileClass& w : narrow) {
+          const int64_t k = ceil_div(w.nb, split_narrow);
+          if (k > 1) narrow_ws += w.count * k * slab_floats(w.rows, D);
+        }
+        const int64_t most = XY_STATIC_WORKSPACE_BYTES / (int64_t)sizeof(float) - narrow_ws;
+        const int64_t W = c.num_workers;
+        if (2 * wide_families <= W) {
+          // Few of them, and so little narrow work that the other workers would be done with it before a wide
+          // family is (a prefill chunk with no or few decodes beside it): at most one piece per worker, all of about
+          // the same length whatever the lengths of the families, no shorter than a worker's share of the wide and half
+          // of the narrow work, on few enough workers to leave half of what the narrow work would take to it, and no
+          // shorter than the longest of the units that stay whole.  Loads as in the cost model, max(rows, floor) x tiles.
+          if (narrow_total * 2 < wide_max * (W - wide_families)) {
+            const int64_t wide_load = wide_tiles * tile_load, both = wide_load + narrow_total / 2;
+            cut = WideCut{wide_size_for(wide, ceil_div(both, W * tile_load), wide_longest, ceil_div(W + ceil_div(W * wide_load, both), 2), true), true};
+            int64_t whole = 0;
+            for (const XyTileClass& w : wide)
+              if (cut.pieces(w) == 1) whole = std::max(whole, w.nb);
+            cut.size = std::max(cut.size, whole);
+            while (cut.size < wide_longest && wide_workspace(wide, cut, D) > most) cut.size *= 2;
+          }
+        } else {
+          // More: the cut of the shortest estimated time among those that fill the workers once, twice, ... with
+          // whole units as the other choice; taken if a fifth shorter (the estimate knows nothing of the caches).
+          // Whole units are within a quarter of the mean anyway where none is longer than a quarter of it.
+          const int64_t mean = ceil_div(2 * wide_tiles + kWideUnitHalves * wide_families + 2 * narrow_tiles, W);
+          if (4 * (2 * wide_longest + kWideUnitHalves) > mean) {
+            const int64_t whole = wide_estimate(wide, WideCut{}, W, narrow_tiles, plan->scratch);
+            int64_t best = whole * 4 / 5 + 1;
+            const int64_t first = ceil_div(wide_families, W);
+            for (int64_t rounds = first; rounds < first + 3; ++rounds) {
+              const int64_t share = std::max(kAutoSplitWideMin, ceil_div(wide_tiles, rounds * W));
+              const WideCut other{wide_size_for(wide, share, wide_longest, rounds * W, false), false};
+              if (other.size >= wide_longest || wide_workspace(wide, other, D) > most) continue;
+              const int64_t t = wide_estimate(wide, other, W, narrow_tiles, plan->scratch);
+              if (t < best) {
+                best = t;
+                cut = other;
+              }
+            }
+          }
+        }
+      }
     }
 
     // --- decomposition (section 3.2.1) + K/V split -------------------------
@@ -246,14 +375,10 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         // pieces of a family and their size: the same for every head group of the token tile
         const int64_t rows = (int64_t)qc * hc;
         int32_t k = 1;
-        int32_t split = rows <= kNarrowRows ? split_narrow : split_wide;
-        bool may_split = !prefill;
-        if (rows > kNarrowRows && wide_pieces > 1) {     // PREFILL too: nothing else would use the idle workers
-          split = (int32_t)std::max<int64_t>(wide_piece_min(nb), ceil_div(nb, wide_pieces));
-          may_split = true;
-        }
-        if (may_split && split > 0 && nb > split) k = (nb + split - 1) / split;
-        const int64_t slab = ((rows * (D + 2) + 3) / 4) * 4;   // keeps every partial 16-byte aligned
+        const int32_t split = rows <= kNarrowRows ? split_narrow : split_wide;
+        if (rows > kNarrowRows && cut.size > 0) k = (int32_t)cut.pieces(XyTileClass{nb, head_groups, rows, prefill});
+        else if ((!prefill || (rows <= kNarrowRows && nb > prefill_whole_tiles)) && split > 0 && nb > split) k = (nb + split - 1) / split;
+        const int64_t slab = slab_floats(rows, D);   // keeps every partial 16-byte aligned
         // piece p covers tiles [floor(p nb / k), floor((p + 1) nb / k)): walked with a running remainder
         const int32_t whole = nb / k, rest = nb % k;
         const int64_t unit_rows = std::max<int64_t>(rows, c.cost_row_floor);
@@ -406,8 +531,6 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
       // overall is the best top.  Workers in index order with no load yet are a heap already.
       const int64_t nheaps = per_chip > 0 ? kChiplets : 1, per_heap = per_chip > 0 ? per_chip : W;
       std::vector<Entry>& heap = plan->scratch.heap;
-      heap.resize(W);
-      for (int32_t w = 0; w < W; ++w) heap[w] = Entry(0, w);
       auto top = [&](int64_t h) -> Entry& { return heap[h * per_heap]; };
       auto add_to_top = [&](int64_t h, int64_t cost) {        // the top worker takes a unit and sinks to its new place
         Entry* first = heap.data() + h * per_heap;
@@ -424,22 +547,40 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         }
         first[hole] = e;
       };
-      for (int64_t pos = 0; pos < (int64_t)order.size(); ++pos) {
-        const xy_work_unit& u = fam[order[pos]];
-        const bool narrow = (int64_t)u.q_count * u.head_count <= kNarrowRows;
-        if (share && narrow) {
-          worker_of[pos] = kShared;
-          continue;
+      int64_t wide_units = 0;
+      auto assign = [&](std::vector<int32_t>& to, const bool by_chip) {       // returns the largest load of a worker
+        heap.resize(W);
+        for (int32_t w = 0; w < W; ++w) heap[w] = Entry(0, w);
+        wide_units = 0;
+        int64_t largest = 0;
+        for (int64_t pos = 0; pos < (int64_t)order.size(); ++pos) {
+          const xy_work_unit& u = fam[order[pos]];
+          const bool narrow = (int64_t)u.q_count * u.head_count <= kNarrowRows;
+          if (share && narrow) {
+            to[pos] = kShared;
+            continue;
+          }
+          wide_units += !narrow;
+          int64_t h = 0;
+          if (!narrow && by_chip) {
+            h = chip_of_group[group_key(u)];
+          } else {
+            for (int64_t x = 1; x < nheaps; ++x)
+              if (top(x) < top(h)) h = x;
+          }
+          to[pos] = top(h).second;
+          largest = std::max(largest, top(h).first + u.cost);
+          add_to_top(h, u.cost);
         }
-        int64_t h = 0;
-        if (!narrow && !chip_of_group.empty()) {
-          h = chip_of_group[group_key(u)];
-        } else {
-          for (int64_t x = 1; x < nheaps; ++x)
-            if (top(x) < top(h)) h = x;
-        }
-        worker_of[pos] = top(h).second;
-        add_to_top(h, u.cost);
+        return largest;
+      };
+      const int64_t largest = assign(worker_of, !chip_of_group.empty());
+      // A short list (two units a worker or fewer): chiplets that are level in load need not be level in units, and a
+      // worker with one unit more than the others is then most of the launch.
+      if (!chip_of_group.empty() && wide_units > 0 && wide_units <= 2 * W) {
+        std::vector<int32_t>& plain = plan->scratch.other_worker_of;
+        plain.resize(fam.size());
+        if (largest * 100 > assign(plain, false) * 103) worker_of.swap(plain);
       }
     }
     for (int64_t pos = 0; pos < (int64_t)order.size(); ++pos)

@@ -35,9 +35,15 @@ struct XyPlanScratch {
   std::vector<int64_t> place;               // a unit's place in the order that breaks ties of the sort
   std::vector<uint64_t> key;                // a unit's cost, complemented
   std::vector<int32_t> order_tmp;
-  std::vector<int32_t> order, worker_of, count, cursor, chip_of_group;
+  std::vector<int32_t> order, worker_of, other_worker_of, count, cursor, chip_of_group;
   std::vector<int64_t> group_cost, by_cost;
   std::vector<std::pair<int64_t, int32_t>> heap;
+  struct TileClass {
+    int64_t nb, count, rows;                // K/V tiles; families (head groups); rows of a family
+    bool prefill;
+  };
+  std::vector<TileClass> wide, narrow;      // token tiles of more than 32 rows, of at most 32
+  std::vector<std::pair<int64_t, int64_t>> sizes, loads;
 };
 
 struct xy_attn_plan {

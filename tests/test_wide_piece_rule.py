@@ -1,5 +1,8 @@
 """Pieces of a family of more than 32 rows that is cut to fill idle workers, over the tiles it visits (worked out by
 hand), and the C++ planner against the oracle planner on the same batches."""
+import math
+import random
+
 import pytest
 
 from oracle import planner as PL
@@ -16,4 +19,50 @@ def test_pieces_of_a_lone_wide_family(tiles, pieces):
     seqs = [(64, 128 * tiles - 64, X.XY_PREFILL, 0, 0)]
     units = PL.plan_oracle(cfg.as_dict(), seqs)[0]
     assert len(units) == pieces and set(units["num_splits"].tolist()) == {pieces}
+    compare(cfg, seqs)
+
+
+def test_pieces_follow_the_lengths_of_few_families():
+    # four verify families of 32 heads in 8: 40, 60, 80, 120 tiles for 24 workers, sum 300 -> T from 13 on: 13 gives
+    # 4 + 5 + 7 + 10 = 26, 14: 3 + 5 + 6 + 9 = 23 <= 24
+    cfg = X.xy_attn_default_config(4, 1, 256, num_workers=24)
+    seqs = [(31, 128 * t - 31, X.XY_VERIFY, 0, 0) for t in (40, 60, 80, 120)]
+    units = PL.plan_oracle(cfg.as_dict(), seqs)[0]
+    assert [int((units["seq"] == i).sum()) for i in range(4)] == [3, 5, 6, 9]
+    compare(cfg, seqs)
+
+
+@pytest.mark.parametrize("count,pieces", [(6, 1), (8, 1), (9, 3), (10, 3), (16, 1), (32, 1)])
+def test_many_equal_families_are_cut_where_a_round_is_nearly_empty(count, pieces):
+    # eight workers, families of 40 tiles: 85 half tiles a round.
+    # 6: one round; two pieces each (45) take two rounds, 94, four (25) three, 79: not 68 or less.
+    # 9, 10: two rounds, 170, of which the second is nearly empty; two pieces each: 3 x 45 + 4 = 139, three (33, 31, 31):
+    # 27 or 30 pieces are four rounds of at most 33 + 4: 136 or less.  8, 16, 32: full rounds.
+    cfg = X.xy_attn_default_config(4, 1, 256, num_workers=8)
+    units = compare(cfg, [(64, 128 * 40 - 64, X.XY_PREFILL, 0, 0)] * count)
+    assert set(units["num_splits"].tolist()) == {pieces}
+
+
+def test_partial_results_stay_within_the_library_workspace():
+    # 64 prefill families of 24 tiles beside 680 narrow ones of 6 tiles in 3 pieces each (34 MB of partials): four pieces
+    # each would take the sum beyond 64 MiB, which xy_attn_run_static refuses
+    cfg = X.xy_attn_default_config(32, 8, 256)
+    seqs = [(64, 24 * 128 - 64, X.XY_PREFILL, 0, 0)] * 8 + [(8, 6 * 128 - 8, X.XY_VERIFY, 0, 0)] * 85
+    units, _, _, ws = PL.plan_oracle(cfg.as_dict(), seqs)
+    assert 4 * ws <= X.XY_STATIC_WORKSPACE_BYTES
+    compare(cfg, seqs)
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_both_planners_agree_on_drawn_batches_with_wide_families(seed):
+    rng = random.Random(seed)
+    cfg = X.xy_attn_default_config(*rng.choice([(4, 1), (8, 2), (32, 8), (64, 8), (8, 8)]), 4096, num_workers=rng.choice([6, 8, 16, 40, 256]))
+    seqs = []
+    for _ in range(rng.randrange(1, 10)):
+        q, c = int(math.exp(rng.uniform(2, 7))), int(math.exp(rng.uniform(3, 9.5)))
+        if rng.random() < 0.6:
+            seqs.append((q, c if rng.random() < 0.7 else 0, X.XY_PREFILL, 0, 0))
+        else:
+            seqs.append((min(q, 31), c, X.XY_VERIFY, 0, 0))
+    seqs += [(1, int(math.exp(rng.uniform(3, 9))), X.XY_DECODE, 0, 0) for _ in range(rng.choice([0, 0, 1, 5, 30]))]
     compare(cfg, seqs)

@@ -29,7 +29,8 @@ Rules
    ``split_kv_blocks = -1`` (automatic) sizes S to the batch.  Narrow
    families are those of at most 32 rows; PREFILL ones (the last tokens of a
    prompt) count, and are cut like the others, if they visit more tiles than
-   ``floor(t / (2 W))``, ``t`` the tiles of all families of the batch; ``F`` their
+   ``floor((2 t + 5 U) / (4 W))``, ``t`` the
+   tiles of all families of the batch, ``U`` those of more than 32 rows; ``F`` their
    number (token tiles times head groups), ``L = 4 W`` the wavefront slots.  If all of
    them have the same ``nb``: ``S = ceil(nb / k)`` for the ``k`` that minimises
    ``ceil(F k / L) * (ceil(nb / k) + 1)`` over ``k = 1 .. nb``, smallest ``k``

@@ -43,12 +43,14 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 
 constexpr int kD = 128;          // head dim
 constexpr int kB = 128;          // keys per K/V tile (one or more pages of the block table)
 constexpr int kTileBytes = kB * kD * 2;   // one K or V tile of one KV head
 constexpr int kThreads = 256;        // 4 wavefronts: one per SIMD
 constexpr int kMergeThreads = 256, kMergeRows = kMergeThreads / 32;     // rows of a family merged by one workgroup
+constexpr int64_t kDeepTiles = 10;
 constexpr float kPrescaleMaxC = 0.25f;    // largest c = scale * log2(e) that is folded into Q (wide units)
 // Dynamic assignment: the cursor of the shared list, kDoneGroups counts of finished workgroups and the
 // count of finished groups, kCounterStride ints (one 128-byte line) apart.
@@ -74,8 +76,9 @@ struct RunParams {
   uint16_t* out;
   float* ws;
   int64_t q_ts, q_hs, kv_bs, kv_hs, kv_ts, o_ts, o_hs;
-  int32_t max_blocks, group, num_workers;
+  int32_t max_blocks, num_workers;
   int32_t free_workers;              // workers without units of their own (plan with a shared list)
+  int32_t narrow_depth;              // slices a wavefront keeps in flight (see process_solo)
   int32_t num_units;                 // all units, the shared list of XY_ASSIGN_DYNAMIC included
   int32_t* counters;                 // plan with a shared list: its cursor and the finished-workgroup counts (kCounterStride apart); else null
   int32_t page_shift, page_mask;     // log2 of the tokens per block-table entry (page), and that size - 1
@@ -91,6 +94,15 @@ __device__ __forceinline__ const XY_CONST T* as_const(const T* ptr) {
   return (const XY_CONST T*)ptr;
 }
 
+// Pointers that reach the kernel through memory (the arguments as the narrow phase reads them) are generic ones to the
+// compiler: their loads become flat ones, which count with the scalar and LDS requests and were waited for, Q included,
+// before a unit's first K/V address was known.
+#define XY_GLOBAL __attribute__((address_space(1)))
+template <typename T>
+__device__ __forceinline__ XY_GLOBAL T* as_global(T* ptr) {
+  return (XY_GLOBAL T*)ptr;
+}
+
 template <typename T>     // whole-struct copy out of a read-only table, word by word
 __device__ __forceinline__ T load_const(const T* ptr) {
   static_assert(sizeof(T) % 4 == 0, "word-sized records only");
@@ -100,6 +112,16 @@ __device__ __forceinline__ T load_const(const T* ptr) {
 #pragma unroll
   for (unsigned i = 0; i < sizeof(T) / 4; ++i) dst[i] = src[i];
   return out;
+}
+
+// A unit record in registers, all of it: left to itself the compiler reads it field by field where a field is first
+// used, one round trip after another.
+__device__ __forceinline__ XyDevUnit load_unit(const XyDevUnit* at) {
+  XyDevUnit u = load_const(at);
+  asm volatile("" : "+s"(u.seq), "+s"(u.head_begin), "+s"(u.head_count), "+s"(u.q_begin), "+s"(u.q_count), "+s"(u.kv_begin),
+                    "+s"(u.kv_end), "+s"(u.flags), "+s"(u.ws_offset), "+s"(u.mask_off), "+s"(u.q_len), "+s"(u.ctx_len),
+                    "+s"(u.token_start), "+s"(u.kv_head));
+  return u;
 }
 
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
@@ -252,17 +274,6 @@ __device__ __forceinline__ void zero_tail_rows(unsigned slice_addr, int first_ro
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // before the hand-issued fragment reads that follow
 }
 
-// Element offset (inside the K or V cache, before the KV head is added) of key row j of a sequence:
-// page seq_table[j / page size], slot j % page size (paper section 4.1.1).  Sixteen consecutive rows
-// starting at a multiple of 16 always share a page (pages hold 16, 32, 64 or 128 tokens).  Rows past
-// the sequence's last page are never visible; they are redirected to the last page so that whatever
-// lands in LDS for them is ordinary finite cache content.
-__device__ __forceinline__ int64_t kv_row_offset(const XY_CONST int32_t* seq_table, int j, int last_page,
-                                                 const RunParams& p) {
-  const int page = min(j >> p.page_shift, last_page);
-  return (int64_t)seq_table[page] * p.kv_bs + (int64_t)(j & p.page_mask) * p.kv_ts;
-}
-
 // ---- per-lane description of the query rows a wavefront owns -------------------------
 template <int NT>
 struct Rows {
@@ -281,7 +292,7 @@ __device__ __forceinline__ UnitCtx make_ctx(const RunParams& p, const XyDevUnit&
   UnitCtx c;
   c.hc = u.head_count;
   c.rows = u.q_count * u.head_count;
-  c.kvh = u.head_begin / p.group;
+  c.kvh = u.kv_head;
   c.ctx = u.ctx_len;
   c.wpr = (u.q_len + 31) >> 5;
   c.tree = (u.flags >> 2) & 1;
@@ -311,30 +322,16 @@ __device__ __forceinline__ int64_t row_bytes(const RowIndex& r, int64_t ts, int6
   return 2 * (r.tl * ts + r.hl * hs);
 }
 
-// Row bookkeeping and Q fragments (B operand of S^T = K Q^T: lane (col, half) holds
-// d = 16*ks + 8*half .. +7 of its row).  Padding lanes read a real row; their results are dropped.
-template <int NT>
-__device__ __forceinline__ void setup_rows(const RunParams& p, const XyDevUnit& u, const UnitCtx& c, int row_base, int col, int half, Rows<NT>& r,
-                                           bf16x8 (&qf)[NT][8]) {
-#pragma unroll
-  for (int rt = 0; rt < NT; ++rt) {
-    const int rho = row_base + 32 * rt + col;
-    r.valid[rt] = rho < c.rows;
-    const int rc = max(0, min(rho, c.rows - 1));
-    const int tl = rc / c.hc, hl = rc - tl * c.hc;
-    r.tok[rt] = u.q_begin + tl;
-    r.lim[rt] = r.valid[rt] ? c.ctx + r.tok[rt] + 1 : 0;
-    const uint16_t* qrow =
-        p.q + (int64_t)(u.token_start + r.tok[rt]) * p.q_ts + (int64_t)(u.head_begin + hl) * p.q_hs;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-      qf[rt][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qrow + 16 * ks + 8 * half));
-    r.mw0[rt] = r.mw1[rt] = 0;
-    if (c.tree && r.valid[rt]) {
-      const uint32_t* mrow = p.masks + u.mask_off + (int64_t)r.tok[rt] * c.wpr;
-      r.mw0[rt] = mrow[0];
-      if (c.wpr > 1) r.mw1[rt] = mrow[1];
-    }
+// Row bookkeeping of a unit of at most 32 rows: what a lane has to know of its row.
+__device__ __forceinline__ void setup_rows(const RunParams& p, const XyDevUnit& u, const UnitCtx& c, int col, float inv_hc, Rows<1>& r) {
+  r.valid[0] = col < c.rows;
+  r.tok[0] = u.q_begin + row_index(min(col, c.rows - 1), c.hc, inv_hc).tl;
+  r.lim[0] = r.valid[0] ? c.ctx + r.tok[0] + 1 : 0;
+  r.mw0[0] = r.mw1[0] = 0;
+  if (c.tree && r.valid[0]) {
+    const XY_GLOBAL uint32_t* mrow = as_global(p.masks + u.mask_off + (int64_t)r.tok[0] * c.wpr);
+    r.mw0[0] = mrow[0];
+    if (c.wpr > 1) r.mw1[0] = mrow[1];
   }
 }
 
@@ -548,10 +545,10 @@ __device__ __forceinline__ void store_partial(const RunParams& p, const XyDevUni
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       const f32x4 x = {oacc[dt][4 * a], oacc[dt][4 * a + 1], oacc[dt][4 * a + 2], oacc[dt][4 * a + 3]};
-      *reinterpret_cast<f32x4*>(w + (size_t)((8 * dt + 2 * a) * rows * 16) + lane_off) = x;
+      *as_global(reinterpret_cast<f32x4*>(w + (size_t)((8 * dt + 2 * a) * rows * 16) + lane_off)) = x;
     }
   if (half == 0) {
-    float* ml = reinterpret_cast<float*>(w) + (int64_t)rows * kD + rho;
+    XY_GLOBAL float* ml = as_global(reinterpret_cast<float*>(w) + (int64_t)rows * kD + rho);
     ml[0] = m2;
     ml[rows] = l_tot;
   }
@@ -575,10 +572,9 @@ __device__ __forceinline__ void finish_unit(const RunParams& p, const XyDevUnit&
   for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
-      uint2 w2;
-      w2.x = pack_bf16(st.oacc[0][dt][4 * a] * inv, st.oacc[0][dt][4 * a + 1] * inv);
-      w2.y = pack_bf16(st.oacc[0][dt][4 * a + 2] * inv, st.oacc[0][dt][4 * a + 3] * inv);
-      *reinterpret_cast<uint2*>(o + 32 * dt + 8 * a + 4 * half) = w2;
+      const u32x2 w2 = {pack_bf16(st.oacc[0][dt][4 * a] * inv, st.oacc[0][dt][4 * a + 1] * inv),
+                        pack_bf16(st.oacc[0][dt][4 * a + 2] * inv, st.oacc[0][dt][4 * a + 3] * inv)};
+      *as_global(reinterpret_cast<u32x2*>(o + 32 * dt + 8 * a + 4 * half)) = w2;
     }
 }
 
@@ -1204,50 +1200,121 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
 }
 
 // A unit with at most 32 rows (decode, short verify; bandwidth-bound): ONE wavefront processes the
-// whole unit on its own, streaming 32-key slices through a private 16 KB ring (a K slot and a V slot,
-// each refilled as soon as it has been consumed; a second slice in flight per wavefront was measured
-// and gains nothing).  No barrier, no cross-wavefront merge: four such
+// whole unit on its own, streaming 32-key slices through a private ring of one or two slices (K and V slots, each
+// refilled as soon as it has been consumed).  No barrier, no cross-wavefront merge: four such
 // units are in flight per CU and hide each other's latencies.
+// Two slices (narrow_depth) where a launch has at most kDeepTiles tiles per wavefront: with every wavefront at work
+// the card's bandwidth is the bound and 16 KB each are enough, but a wavefront whose neighbours have run out of work waits
+// for memory in every slice, and that is the end of every launch.  8 decodes x 32 KV heads on 2-6k tokens (7.5 tiles per
+// wavefront) 95.4 -> 90.5 us with two; 128 trees on 512-4096 tokens (14 tiles) 153.0 -> 154.7 us, 128 decodes on
+// 2-16k (54 tiles) 553.7 -> 557.2 us, so those keep one.
 __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit& u,
                                              unsigned char* smem, const LaneOffsets& lo, const DmaOffsets& dof) {
   constexpr int NT = 1;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const UnitCtx c = make_ctx(p, u);
-  Rows<NT> r;
-  bf16x8 qf[NT][8];
-  setup_rows<NT>(p, u, c, 0, col, half, r, qf);
   const int mask_from = c.tree ? c.ctx : c.ctx + u.q_begin + 1;
-  UnitState st;
-  zero_state<NT>(st.oacc, st.m_ref, st.l_part);
-
   const XY_CONST int32_t* table = as_const(p.block_table) + (int64_t)u.seq * p.max_blocks;
   const int last_page = (u.ctx_len + u.q_len - 1) >> p.page_shift;
   const int64_t head_off = (int64_t)c.kvh * p.kv_hs;
   const int jfirst = u.kv_begin * kB;
   const int nsteps = (min(u.kv_end * kB, c.key_end) - jfirst + 31) >> 5;
-  unsigned char* ring = smem + wave * 16384;        // [K slot | V slot]
-  const unsigned kaddr = lds_addr(ring), vaddr = kaddr + 8192;
+  unsigned char* ring = smem + wave * 32768;        // one or two slices of [K 8 KB | V 8 KB]
+  const int depth = p.narrow_depth;
+  const unsigned ring_addr = lds_addr(ring);
   // a 32-key slice starting at key j: two runs of sixteen rows, each inside one page; eight
   // instructions per tensor, which is what the waits below count
-  auto load_slice = [&](const int j, const bool want_k, const bool want_v) {
-    const int64_t b0 = kv_row_offset(table, j, last_page, p) + head_off;
-    const int64_t b1 = kv_row_offset(table, j + 16, last_page, p) + head_off;
-    load_rows_async<4>(p.k + b0, p.v + b0, p.kv_ts, 0, ring, ring + 8192, dof, want_k, want_v);
-    load_rows_async<4>(p.k + b1, p.v + b1, p.kv_ts, 0, ring + 4096, ring + 8192 + 4096, dof, want_k, want_v);
+  struct Slice {
+    int64_t run[2];
   };
-  load_slice(jfirst, true, false);          // issue order K, V
-  load_slice(jfirst, false, true);
+  // page-table entries of the two runs of slice t: asked for early (entries), turned into addresses later (locate)
+  struct Entries {
+    int e[2];
+  };
+  auto entries = [&](const int t) {
+    Entries n;
+#pragma unroll
+    for (int g = 0; g < 2; ++g) n.e[g] = table[min((jfirst + 32 * t + 16 * g) >> p.page_shift, last_page)];
+    return n;
+  };
+  const Entries entries0 = entries(0), entries1 = entries(1);
+  Rows<NT> r;
+  bf16x8 qf[NT][8];
+  const float inv_hc = __builtin_amdgcn_rcpf((float)c.hc);
+  setup_rows(p, u, c, col, inv_hc, r);
+  UnitState st;
+  zero_state<NT>(st.oacc, st.m_ref, st.l_part);
+  auto locate = [&](const int t, const Entries& n) {
+    Slice at;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+      at.run[g] = (int64_t)n.e[g] * p.kv_bs + (int64_t)((jfirst + 32 * t + 16 * g) & p.page_mask) * p.kv_ts + head_off;
+    return at;
+  };
+  auto load_slice = [&](const Slice& at, const int t, const bool want_k, const bool want_v) {
+    unsigned char* slot = ring + (t & (depth - 1)) * 16384;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+      load_rows_async<4>(p.k + at.run[g], p.v + at.run[g], p.kv_ts, 0, slot + 4096 * g, slot + 8192 + 4096 * g, dof, want_k, want_v);
+  };
+  // Q goes through LDS as in the wide units (whole rows, 16-byte chunks swizzled by the low four bits of the row), and
+  // not only for that: a load whose result the compiler sees would be waited for with everything that is in flight.
+  // It waits where V of the second slice comes to lie, which is asked for when Q has been read.
+  unsigned char* const q_buf = ring + 16384 + 8192;
+  {
+    const int sub = lane >> 4, pos = lane & 15;             // a load moves four rows: row, 16-byte chunk
+    const char* q0 = reinterpret_cast<const char*>(p.q + (int64_t)(u.token_start + u.q_begin) * p.q_ts + (int64_t)u.head_begin * p.q_hs);
+    auto load_q = [&](const char* from, const int e) {
+      __builtin_amdgcn_global_load_lds((const XY_GLOBAL void*)from, (__attribute__((address_space(3))) void*)(q_buf + 1024 * e), 16, 0, 0);
+    };
+    auto q_row = [&](const int e) { return q0 + row_bytes<false>(row_index(min(4 * e + sub, c.rows - 1), c.hc, inv_hc), p.q_ts, p.q_hs); };
+    // the mask words are waited for here: behind a load to LDS the compiler can only wait for everything in flight
+    if (c.tree) asm volatile("" : "+v"(r.mw0[0]), "+v"(r.mw1[0]));
+    if ((c.hc == 4 || c.hc <= 2) && (c.rows & 3) == 0) {                 // whole groups of four, 4 / hc tokens further each
+      const char* from = q_row(0);
+      const int64_t step = (c.hc == 4 ? 2 : c.hc == 2 ? 4 : 8) * p.q_ts;      // bytes
+      const int chunk = (pos ^ sub) << 4;
+      for (int e = 0; 4 * e < c.rows; ++e, from += step) load_q(from + (chunk ^ ((e & 3) << 6)), e);
+    } else {
+      for (int e = 0; 4 * e < c.rows; ++e) load_q(q_row(e) + ((pos ^ ((4 * e + sub) & 15)) << 4), e);
+    }
+    const Slice first = locate(0, entries0), second = locate(1, entries1);
+    load_slice(first, 0, true, false);          // issue order K, V
+    load_slice(first, 0, false, true);
+    const bool two = depth == 2 && nsteps > 1;
+    if (two) {
+      load_slice(second, 1, true, false);
+      wait_vmcnt<24>();                         // Q has landed
+    } else {
+      wait_vmcnt<16>();
+    }
+    const int row = min(col, c.rows - 1);
+    const unsigned qaddr = lds_addr(q_buf) + row * 256;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qf[0][ks] = lds_read_b128<0>(qaddr + (((2 * ks + half) ^ (row & 15)) << 4));
+    lds_wait<4>(qf[0][0], qf[0][1], qf[0][2], qf[0][3]);
+    lds_wait<0>(qf[0][4], qf[0][5], qf[0][6], qf[0][7]);
+    if (two) load_slice(second, 1, false, true);
+  }
 #pragma unroll 1
   for (int t = 0; t < nsteps; ++t) {
-    wait_vmcnt<8>();                          // K(t) has landed; only V(t) may still be in flight
+    const unsigned kaddr = ring_addr + (t & (depth - 1)) * 16384, vaddr = kaddr + 8192;
+    const int left = nsteps - 1 - t;          // slices behind this one: depth - 1 of them in flight
+    Entries ahead = entries(t + depth);       // arrive while K is waited for
+    if (depth == 2 && left > 0) wait_vmcnt<24>();      // K(t) has landed
+    else wait_vmcnt<8>();
+    asm volatile("" : "+s"(ahead.e[0]), "+s"(ahead.e[1]));      // here, not among the fragment reads that follow
+    const Slice next = locate(t + depth, ahead);
     f32x16 s[NT];
     VFrags vf;
     qk_step<NT>(kaddr, lo, qf, s);            // all K reads have completed when this returns
-    const int tn = t + 1;
-    if (tn < nsteps) {        // K slot is free again: refill it with the next slice
-      load_slice(jfirst + 32 * tn, true, false);
-      wait_vmcnt<8>();        // V(t) has landed; the K refill stays in flight
+    if (left >= depth) {      // the K slot is free again
+      load_slice(next, t, true, false);
+      if (depth == 2) wait_vmcnt<24>();       // V(t) has landed
+      else wait_vmcnt<8>();
+    } else if (left > 0) {
+      wait_vmcnt<16>();
     } else {
       wait_vmcnt<0>();
       const int last_keys = min(u.kv_end * kB, c.key_end) - jfirst - 32 * t;      // keys of the last step: 1 .. 32
@@ -1258,7 +1325,7 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
     if (j + 32 > mask_from) mask_step<NT>(p, c, r, j + 8 * half, s);
     softmax_step<NT>(p.c, s, st.m_ref, st.l_part, st.oacc);
     pv_step<NT>(vaddr, lo, vf, s, st.oacc);   // all V reads have completed when this returns
-    if (tn < nsteps) load_slice(jfirst + 32 * tn, false, true);
+    if (left >= depth) load_slice(next, t, false, true);
   }
   finish_unit(p, u, c, r, st, col, half);
 }
@@ -1312,7 +1379,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     if ((threadIdx.x & 63) == 0) got = atomicAdd(&cursor, 1);
     const int i = __builtin_amdgcn_readfirstlane(got);
     if (i >= end) break;
-    const XyDevUnit u = load_const(pn.units + i);
+    const XyDevUnit u = load_unit(pn.units + i);
     if (u.q_count * u.head_count > 32) continue;
     process_solo(pn, u, smem, lo, dof);
   }
@@ -1340,7 +1407,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     while (true) {
       const int i = shared_begin + next;
       if (i >= pn.num_units) break;
-      const XyDevUnit u = load_const(pn.units + i);
+      const XyDevUnit u = load_unit(pn.units + i);
       process_solo(pn, u, smem, lo, dof);
       if (!any_left) break;
       int got = 0;
@@ -1503,12 +1570,15 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
   }
   unsigned char* h = static_cast<unsigned char*>(plan->h_stage);
   XyDevUnit* du = reinterpret_cast<XyDevUnit*>(h + off_units);
+  const int32_t group = plan->cfg.num_q_heads / plan->cfg.num_kv_heads;
+  plan->narrow_tiles = 0;
   for (size_t i = 0; i < plan->units.size(); ++i) {
     const xy_work_unit& u = plan->units[i];
     const xy_seq_desc& sd = plan->descs[u.seq];
+    if (u.q_count * u.head_count <= 32) plan->narrow_tiles += u.kv_block_end - u.kv_block_begin;
     du[i] = XyDevUnit{u.seq, u.head_begin, u.head_count, u.q_begin, u.q_count,
                       u.kv_block_begin, u.kv_block_end, u.kind_flags, u.ws_offset, sd.mask_word_offset,
-                      sd.query_len, sd.context_len, plan->token_start[u.seq], 0};
+                      sd.query_len, sd.context_len, plan->token_start[u.seq], u.head_begin / group};
   }
   memcpy(h + off_offsets, plan->worker_offsets.data(), plan->worker_offsets.size() * sizeof(int32_t));
   // behind the offsets: a worker's number among the workers that have no units of their own, -1 where it has some
@@ -1612,10 +1682,10 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
   p.max_blocks = plan->cfg.max_blocks_per_seq;
   p.page_mask = plan->cfg.block_size - 1;
   p.page_shift = plan->cfg.block_size == 16 ? 4 : plan->cfg.block_size == 32 ? 5 : plan->cfg.block_size == 64 ? 6 : 7;
-  p.group = plan->cfg.num_q_heads / plan->cfg.num_kv_heads;
   p.num_workers = plan->cfg.num_workers;
   p.free_workers = plan->free_workers;
   p.num_units = (int32_t)plan->units.size();
+  p.narrow_depth = plan->narrow_tiles <= kDeepTiles * (kThreads / 64) * plan->cfg.num_workers ? 2 : 1;
   p.counters = static_cast<int32_t*>(plan->d_counters);
   p.c = softmax_scale * 1.4426950408889634f;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);

@@ -11,7 +11,7 @@
 struct XyDevUnit {
   int32_t seq, head_begin, head_count, q_begin, q_count, kv_begin, kv_end, flags;
   int64_t ws_offset, mask_off;
-  int32_t q_len, ctx_len, token_start, reserved;
+  int32_t q_len, ctx_len, token_start, kv_head;
 };
 static_assert(sizeof(XyDevUnit) == 64, "one aligned scalar load");
 
@@ -58,6 +58,7 @@ struct xy_attn_plan {
   int64_t workspace_floats = 0;
   int64_t merge_groups = 0;                 // workgroups of the merge pass (of the tables last copied to the GPU)
   int32_t free_workers = 0;                 // workers without units of their own (of the tables last copied to the GPU)
+  int64_t narrow_tiles = 0;                 // K/V tiles of the units of at most 32 rows (of the tables last copied to the GPU)
   bool has_tree = false;
   XyPlanScratch scratch;
   // Device copy of the tables (owned): one arena on one device and a pinned staging buffer of the same size,

@@ -112,3 +112,15 @@ def test_wide_units_far_strides_of_q_and_out(gpu, dim):
             assert np.array_equal(out.float().cpu().numpy(), want), stride
     finally:
         db.close()
+
+
+@pytest.mark.parametrize("hq,hkv,tokens", [(1, 1, 1), (4, 1, 1), (3, 1, 2), (5, 1, 6), (8, 1, 4), (31, 1, 1), (32, 1, 1), (4, 2, 3)])
+def test_narrow_units_of_few_slices(gpu, hq, hkv, tokens):
+    """A narrow unit keeps one or two 32-key slices in flight (two up to ten tiles per wavefront of the launch), Q waits
+    where the second one's V comes to lie: units of one, two and three slices, ends inside a slice and right at one, rows
+    from one to 32 in groups of four; the last batch has more than ten tiles for each wavefront of its one worker."""
+    specs = [W.SeqSpec(tokens, max(0, keys - tokens), V) for keys in (tokens, 31, 32, 33, 63, 64, 65, 95, 96, 97, 129, 200, 300)]
+    run_and_check(gpu, W.make_custom(specs, hq, hkv, 11 * hq + tokens), f"{hq}/{hkv} heads, {tokens} tokens", split_kv_blocks=0)
+    run_and_check(gpu, W.make_custom(specs, hq, hkv, 12 * hq + tokens), f"{hq}/{hkv} heads, {tokens} tokens, split", split_kv_blocks=1)
+    run_and_check(gpu, W.make_custom(specs * 3, hq, hkv, 13 * hq + tokens), f"{hq}/{hkv} heads, {tokens} tokens, one slice",
+                  split_kv_blocks=0, num_workers=1)

@@ -1206,7 +1206,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
 // Two slices (narrow_depth) where a launch has at most kDeepTiles tiles per wavefront: with every wavefront at work
 // the card's bandwidth is the bound and 16 KB each are enough, but a wavefront whose neighbours have run out of work waits
 // for memory in every slice, and that is the end of every launch.  8 decodes x 32 KV heads on 2-6k tokens (7.5 tiles per
-// wavefront) 95.4 -> 90.5 us with two; 128 trees on 512-4096 tokens (14 tiles) 153.0 -> 154.7 us, 128 decodes on
+// wavefront) 94.8 -> 92.0 us with two; 128 trees on 512-4096 tokens (14 tiles) 153.0 -> 154.7 us, 128 decodes on
 // 2-16k (54 tiles) 553.7 -> 557.2 us, so those keep one.
 __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit& u,
                                              unsigned char* smem, const LaneOffsets& lo, const DmaOffsets& dof) {

@@ -1057,6 +1057,8 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   };
   bool exact = true;
   if (active) {
+    // iteration 0 multiplies V of step 0 already (by zeros, see below): cleared first where that is the last step
+    if (nsteps == 1) zero_tail_rows(k_slice(0) + 16384, min(u.kv_end * kB, c.key_end) - jfirst, lane);
     // S^T of step 0 against reference 0, then iteration 0 (exact prefix, no previous step)
 #pragma unroll
     for (int i = 0; i < 8; ++i) request_k(k_slice(0), i);
@@ -1076,7 +1078,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
       pb[rt][0] = pb[rt][1] = bf16x8{};
       asm volatile("" : "+v"(pb[rt][0]), "+v"(pb[rt][1]));
     }
-    // iteration 0 has no previous step: its probabilities are zero and meet V of step 0, which is finite
+    // iteration 0 has no previous step: its probabilities are zero and meet V of step 0 (keys of the unit, or zeros)
     exact = iterate(true, -1, 0, k_slice(1), k_slice(0) + 16384, k_slice(2), sa, sb, pb, pa);
   }
   const int hshift = wave < 2 ? 5 : 4;

@@ -124,3 +124,44 @@ def test_narrow_units_of_few_slices(gpu, hq, hkv, tokens):
     run_and_check(gpu, W.make_custom(specs, hq, hkv, 12 * hq + tokens), f"{hq}/{hkv} heads, {tokens} tokens, split", split_kv_blocks=1)
     run_and_check(gpu, W.make_custom(specs * 3, hq, hkv, 13 * hq + tokens), f"{hq}/{hkv} heads, {tokens} tokens, one slice",
                   split_kv_blocks=0, num_workers=1)
+
+
+def _poison(b):
+    """NaN and infinities in every slot of the caches that no sequence of the batch owns."""
+    patterns = np.array([0x7FC0, 0x7F80, 0xFF80, 0xFFC1], dtype=np.uint16)
+    bs = b.block_size
+    owned = np.zeros((b.k_cache.shape[0], bs), dtype=bool)
+    for i, (q, c, *_rest) in enumerate(b.seqs):
+        for j in range(c + q):
+            owned[b.block_table[i, j // bs], j % bs] = True
+    blk, slot = np.nonzero(~owned)
+    fill = patterns[(blk + slot)[:, None, None] % 4]
+    b.k_cache[blk, :, slot] = fill
+    b.v_cache[blk, :, slot] = fill[::-1]
+
+
+@pytest.mark.parametrize("bs", [16, 32, 128])
+@pytest.mark.parametrize("hq", [4, 8])
+def test_wide_units_of_less_than_one_step_ignore_what_lies_behind_them(gpu, bs, hq):
+    """A wide unit of fewer than 32 keys has one step, which is its first and its last: V rows behind the last key must
+    not meet the zero probabilities of the step before the first (0 x NaN).  Prompts from nothing, a tree of 20 tokens,
+    the last piece of a cut family with 1, 17 and 31 keys; one step and one key more."""
+    tree20 = W.random_tree(np.random.default_rng(3), 20)
+    whole = [W.SeqSpec(n, 0, P) for n in (9, 20, 31, 32, 33)] + [W.SeqSpec(20, 0, V, W.MASK_TREE, tree20), W.SeqSpec(20, 5, V)]
+    cut = [W.SeqSpec(20, 128 + last - 20, V) for last in (1, 17, 31, 32, 33)] + [W.SeqSpec(40, 128 + 17 - 40, V)]
+    for name, specs, cfg in (("whole", whole, dict(verify_tile_tokens=256 // hq, split_kv_blocks=0)),
+                             ("cut", cut, dict(verify_tile_tokens=256 // hq, split_kv_blocks=1))):
+        b = W.make_custom(specs, hq, 1, 60 + hq, block_size=bs)
+        db = gpu.DeviceBatch(b, **cfg)
+        base = db.run_numpy()
+        db.close()
+        _poison(b)
+
+        def plan_check(units, _offs, _merges):
+            rows = units["q_count"] * units["head_count"]
+            keys = np.array([min(128 * u["kv_block_end"], b.seqs[u["seq"]][0] + b.seqs[u["seq"]][1]) - 128 * u["kv_block_begin"] for u in units])
+            assert ((rows > 32) & (keys < 32)).sum() >= 3
+        run_and_check(gpu, b, f"{name}, {hq} heads, pages of {bs}", plan_check, **cfg)
+        db = gpu.DeviceBatch(b, **cfg)
+        assert np.array_equal(db.run_numpy(), base), name
+        db.close()

@@ -1460,10 +1460,16 @@ __device__ __forceinline__ void merge_pieces(const float* acc_row, const float* 
     l[i] = l_row[at];
     acc[i] = *reinterpret_cast<const f32x4*>(acc_row + at);
   }
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(m[i]), "+v"(l[i]), "+v"(acc[i]));      // loads stay together, above the selects
   float m_new = m_run;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    if (s0 + i >= num_splits) m[i] = -INFINITY;
+    if (s0 + i >= num_splits) {             // all of it: a factor of zero does not remove an infinity
+      m[i] = -INFINITY;
+      l[i] = 0.f;
+      acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     m_new = fmaxf(m_new, m[i]);
   }
   const float keep = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);

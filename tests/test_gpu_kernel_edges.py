@@ -165,3 +165,22 @@ def test_wide_units_of_less_than_one_step_ignore_what_lies_behind_them(gpu, bs, 
         db = gpu.DeviceBatch(b, **cfg)
         assert np.array_equal(db.run_numpy(), base), name
         db.close()
+
+
+@pytest.mark.parametrize("pieces", [2, 3, 4, 5, 6, 7, 8, 9, 11, 13])
+def test_merge_pass_keeps_an_infinity_of_the_last_piece(gpu, pieces):
+    """The merge pass fills its batches of two, four or eight pieces up: what stands in for a piece must not turn an
+    infinite accumulator into a NaN (0 x Inf).  One decode row, an infinite V element at its last key."""
+    b = W.make_custom([W.SeqSpec(1, 128 * pieces - 2, D_)], 1, 1, 300 + pieces)
+    last = b.seqs[0][1]
+    b.v_cache[b.block_table[0, last // 128], 0, last % 128, 5] = 0x7F80
+    db = gpu.DeviceBatch(b, split_kv_blocks=1)
+    try:
+        got = db.run_numpy()
+    finally:
+        db.close()
+    ref = A.attention_oracle(b.seqs, b.q, b.k_cache, b.v_cache, b.block_table, b.tree_masks, num_q_heads=1, num_kv_heads=1,
+                             block_size=b.block_size, scale=b.scale)
+    assert np.isposinf(ref[0, 0, 5]) and np.isposinf(got[0, 0, 5])
+    others = np.arange(128) != 5
+    assert np.abs(got[0, 0, others] - ref[0, 0, others]).max() <= MAX_ABS

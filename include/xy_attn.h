@@ -97,8 +97,9 @@ typedef struct {
  * 4.2.1 across workers) is sized to the batch.  Units of at most 32 rows are processed one per wavefront,
  * L = 4 * num_workers wavefronts in all.  Let F be the number of families of at most 32 rows (token tiles x head
  * groups; PREFILL ones, the last tokens of a prompt, count and are cut only if they visit more tiles than
- * floor((2 t + 5 U) / (4 num_workers)), t the tiles of all families, U those of more than 32 rows) and nb the number
- * of 128-key tiles a family visits.
+ * floor((2 t + 5 U) / (4 num_workers)), t the tiles of all families, U those of more than 32 rows; and not at all where
+ * the partial results of the batch would then exceed XY_STATIC_WORKSPACE_BYTES and would not otherwise) and nb the
+ * number of 128-key tiles a family visits.
  *  - All such families visit the same nb: each is cut into k pieces, k minimising
  *    ceil(F k / L) * (ceil(nb / k) + 1) (rounds of wavefront slots x tiles per piece, a piece costing about
  *    one tile on top of its own for set-up, partial result and merge) over k = 1 .. nb, the smallest such

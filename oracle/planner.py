@@ -30,7 +30,10 @@ Rules
    families are those of at most 32 rows; PREFILL ones (the last tokens of a
    prompt) count, and are cut like the others, if they visit more tiles than
    ``floor((2 t + 5 U) / (4 W))``, ``t`` the
-   tiles of all families of the batch, ``U`` those of more than 32 rows; ``F`` their
+   tiles of all families of the batch, ``U`` those of more than 32 rows; where
+   the partial results of the whole batch would then exceed
+   XY_STATIC_WORKSPACE_BYTES and would not without, no PREFILL one counts or
+   is cut; ``F`` their
    number (token tiles times head groups), ``L = 4 W`` the wavefront slots.  If all of
    them have the same ``nb``: ``S = ceil(nb / k)`` for the ``k`` that minimises
    ``ceil(F k / L) * (ceil(nb / k) + 1)`` over ``k = 1 .. nb``, smallest ``k``
@@ -102,6 +105,7 @@ KV_TILE = 128
 SPLIT_AUTO = -1          # split_kv_blocks value that sizes the K/V split to the batch
 STATIC_WORKSPACE_FLOATS = 64 * 1024 * 1024 // 4      # what the library's own workspace holds
 TILE_AUTO = -1           # verify_tile_tokens value that picks the token tile per sequence
+NEVER = 1 << 62          # a number of tiles no family visits
 NARROW_ROWS = 32         # units of at most this many rows are processed one per wavefront
 CHIPLETS = 8             # L2 domains of the GPU: workers [x W / 8, (x + 1) W / 8) run on domain x when 8 divides W
 
@@ -135,8 +139,20 @@ def _ceil_div(a, b):
     return -(-a // b)
 
 
-def _narrow_tile_pieces(nb, size):
-    return _ceil_div(nb, size) if nb > size else 1
+def _slab(rows, d):
+    """fp32 elements of a partial result (rule 6)."""
+    return _ceil_div(rows * (d + 2), 4) * 4
+
+
+def _narrow_split(narrow, slots):
+    """Split size of the narrow families that may be cut: one (tiles, rows, is prefill) per family."""
+    lengths = {x[0] for x in narrow}
+    if len(lengths) == 1:
+        nb, families = narrow[0][0], len(narrow)
+        best_k = min(range(1, nb + 1), key=lambda k: (_ceil_div(families * k, slots) * (_ceil_div(nb, k) + 1), k))
+        return _ceil_div(nb, best_k)
+    share = _ceil_div(sum(x[0] for x in narrow), slots)
+    return min(max(share, 2), max(16, min(64, 2 * share // 5)))
 
 
 def _wide_pieces(nb, prefill, size, floor):
@@ -173,7 +189,7 @@ def _wide_cut(wide, narrow_tiles, narrow_load, narrow_ws, w, d, cost_floor):
         return sum(_wide_pieces(nb, pre, size, floor) for nb, _r, pre in wide)
 
     def fits(size, floor):
-        ws = sum(_wide_pieces(nb, pre, size, floor) * (_ceil_div(rows * (d + 2), 4) * 4)
+        ws = sum(_wide_pieces(nb, pre, size, floor) * _slab(rows, d)
                  for nb, rows, pre in wide if _wide_pieces(nb, pre, size, floor) > 1)
         return ws <= STATIC_WORKSPACE_FLOATS - narrow_ws
 
@@ -239,22 +255,23 @@ def plan_oracle(cfg, seqs):
                 narrow_load += max(rows, cfg["cost_row_floor"]) * nb * (hq // hc)
                 narrow_tiles += nb * (hq // hc)
                 narrow += [(nb, rows, kind == PREFILL)] * (hq // hc)
-        prefill_whole = (2 * sum(x[0] for x in wide) + 5 * len(wide) + 2 * narrow_tiles) // (4 * w)
-        narrow = [x for x in narrow if not x[2] or x[0] > prefill_whole]
-        slots = 4 * w
-        if len({x[0] for x in narrow}) == 1:
-            nb, families = narrow[0][0], len(narrow)
-            best_k = min(range(1, nb + 1), key=lambda k: (_ceil_div(families * k, slots) * (_ceil_div(nb, k) + 1), k))
-            split_narrow = _ceil_div(nb, best_k)
-        else:
-            share = _ceil_div(sum(x[0] for x in narrow), slots)
-            split_narrow = min(max(share, 2), max(16, min(64, 2 * share // 5)))
         split_wide = 16
-        narrow_ws = 0
-        for nb, rows, _pre in narrow:
-            k = _narrow_tile_pieces(nb, split_narrow)
-            narrow_ws += k * (_ceil_div(rows * (d + 2), 4) * 4) if k > 1 else 0
-        wide_size, wide_floor = _wide_cut(wide, narrow_tiles, narrow_load, narrow_ws, w, d, cfg["cost_row_floor"])
+
+        def choose(whole):
+            """(fits XY_STATIC_WORKSPACE_BYTES, narrow size, wide size, wide floor), PREFILL whole up to that many tiles."""
+            may_cut = [x for x in narrow if not x[2] or x[0] > whole]
+            size = _narrow_split(may_cut, 4 * w)
+            ws = sum(_ceil_div(nb, size) * _slab(rows, d) for nb, rows, _pre in may_cut if nb > size)
+            wide_cut = _wide_cut(wide, narrow_tiles, narrow_load, ws, w, d, cfg["cost_row_floor"])
+            for nb, rows, pre in wide:
+                k = _wide_pieces(nb, pre, *wide_cut)
+                ws += k * _slab(rows, d) if k > 1 else 0
+            return ws <= STATIC_WORKSPACE_FLOATS, size, *wide_cut
+
+        prefill_whole = (2 * sum(x[0] for x in wide) + 5 * len(wide) + 2 * narrow_tiles) // (4 * w)
+        if not choose(prefill_whole)[0] and choose(NEVER)[0]:
+            prefill_whole = NEVER
+        _, split_narrow, wide_size, wide_floor = choose(prefill_whole)
     for i, (ql, c, kind, mk, _off) in enumerate(seqs):
         if kind == PREFILL:
             tile, hc = cfg["prefill_tile_tokens"], cfg["prefill_heads_per_unit"]
@@ -273,7 +290,7 @@ def plan_oracle(cfg, seqs):
                     may_split = kind != PREFILL or (cfg["split_kv_blocks"] == SPLIT_AUTO and rows <= NARROW_ROWS
                                                     and nb > prefill_whole)
                     k = _ceil_div(nb, s) if (may_split and s > 0 and nb > s) else 1
-                slab = _ceil_div(rows * (d + 2), 4) * 4
+                slab = _slab(rows, d)
                 base = -1
                 if k > 1:
                     base = ws_floats

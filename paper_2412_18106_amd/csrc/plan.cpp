@@ -10,6 +10,7 @@
 // Update stage (section 4.2.1).
 #include <algorithm>
 #include <cstring>
+#include <iterator>
 #include <new>
 #include <numeric>
 #include <utility>
@@ -49,6 +50,43 @@ inline int64_t wide_piece_min(int64_t nb) {
 using XyTileClass = XyPlanScratch::TileClass;
 
 inline int64_t slab_floats(int64_t rows, int64_t d) { return ((rows * (d + 2) + 3) / 4) * 4; }
+
+// XY_SPLIT_AUTO: the split size of the families of at most kNarrowRows rows that may be cut
+int32_t narrow_split_size(const std::vector<XyTileClass>& narrow, const int64_t slots) {
+  int64_t tiles = 0;
+  bool uniform = true;
+  for (const XyTileClass& w : narrow) {
+    tiles += w.nb * w.count;
+    uniform = uniform && w.nb == narrow[0].nb;
+  }
+  if (uniform && !narrow.empty()) {
+    // equal families: pieces per family that minimise (rounds of slots) x (tiles per piece + what a
+    // piece costs on top of its tiles: set-up, partial result and its share of the merge, about one tile)
+    const int64_t first_nb = narrow[0].nb, families = tiles / first_nb;
+    int64_t best_k = 1, best = ceil_div(families, slots) * (first_nb + kAutoSplitPieceOverhead);
+    for (int64_t k = 2; k <= first_nb; ++k) {
+      const int64_t piece = ceil_div(first_nb, k);
+      const int64_t score = ceil_div(families * k, slots) * (piece + kAutoSplitPieceOverhead);
+      if (score < best) {
+        best = score;
+        best_k = k;
+      }
+    }
+    return (int32_t)ceil_div(first_nb, best_k);
+  }
+  const int64_t share = ceil_div(tiles, slots);
+  const int64_t most = std::max<int64_t>(kAutoSplitMaxSmall, std::min<int64_t>(kAutoSplitMaxLarge, 2 * share / 5));
+  return (int32_t)std::min<int64_t>(std::max<int64_t>(share, kAutoSplitMin), most);
+}
+
+int64_t narrow_workspace(const std::vector<XyTileClass>& narrow, const int64_t split, const int64_t d) {
+  int64_t ws = 0;
+  for (const XyTileClass& w : narrow) {
+    const int64_t k = ceil_div(w.nb, split);
+    if (k > 1) ws += w.count * k * slab_floats(w.rows, d);
+  }
+  return ws;
+}
 
 // How XY_SPLIT_AUTO cuts the wide families: pieces of at most `size` tiles (0: as the stage says, PREFILL whole and
 // VERIFY at kAutoSplitWide), none shorter than wide_piece_min where `floor` is set.
@@ -258,89 +296,70 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
           }
         }
       }
-      // The last tokens of a prompt may be a narrow PREFILL family.  One that visits more tiles than half a worker's
-      // mean load is cut like the others: a wavefront on its own takes about a microsecond per 32 keys and comes to it
-      // behind the wide units (8 families of 94 tiles beside 23 tiles of wide work a worker 394 -> 103 us, 2 of 19
-      // beside 24 142 -> 105 us); a shorter one fills a gap (8 of 7 beside 15: 65 us whole, 74 cut).
-      prefill_whole_tiles = (2 * wide_tiles + kWideUnitHalves * wide_families + 2 * narrow_tiles) / (4 * (int64_t)c.num_workers);
-      narrow.erase(std::remove_if(narrow.begin(), narrow.end(), [&](const XyTileClass& w) {
-        return w.prefill && w.nb <= prefill_whole_tiles;
-      }), narrow.end());
-      int64_t split_tiles = 0;
-      bool uniform = true;
-      for (const XyTileClass& w : narrow) {
-        split_tiles += w.nb * w.count;
-        uniform = uniform && w.nb == narrow[0].nb;
-      }
-      const int64_t slots = (int64_t)kNarrowSlotsPerWorker * c.num_workers;
-      if (uniform && !narrow.empty()) {
-        // equal families: pieces per family that minimise (rounds of slots) x (tiles per piece + what a
-        // piece costs on top of its tiles: set-up, partial result and its share of the merge, about one tile)
-        const int64_t first_nb = narrow[0].nb, families = split_tiles / first_nb;
-        int64_t best_k = 1, best = ceil_div(families, slots) * (first_nb + kAutoSplitPieceOverhead);
-        for (int64_t k = 2; k <= first_nb; ++k) {
-          const int64_t piece = ceil_div(first_nb, k);
-          const int64_t cost = ceil_div(families * k, slots) * (piece + kAutoSplitPieceOverhead);
-          if (cost < best) {
-            best = cost;
-            best_k = k;
-          }
-        }
-        split_narrow = (int32_t)ceil_div(first_nb, best_k);
-      } else {
-        const int64_t share = ceil_div(split_tiles, slots);
-        const int64_t most = std::max<int64_t>(kAutoSplitMaxSmall, std::min<int64_t>(kAutoSplitMaxLarge, 2 * share / 5));
-        split_narrow = (int32_t)std::min<int64_t>(std::max<int64_t>(share, kAutoSplitMin), most);
-      }
-      split_wide = kAutoSplitWide;
-
-      // The wide families are cut along K/V, PREFILL included, where whole ones would leave workers idle.
-      if (wide_families > 0) {
-        // Partial results beyond what xy_attn_run_static holds are not made for the sake of balance.
-        int64_t narrow_ws = 0;
-        for (const XyTileClass& w : narrow) {
-          const int64_t k = ceil_div(w.nb, split_narrow);
-          if (k > 1) narrow_ws += w.count * k * slab_floats(w.rows, D);
-        }
-        const int64_t most = XY_STATIC_WORKSPACE_BYTES / (int64_t)sizeof(float) - narrow_ws;
-        const int64_t W = c.num_workers;
+      // The wide families are cut along K/V, PREFILL included, where whole ones would leave workers idle; partial results
+      // beyond `most` floats are not made for the sake of balance.
+      const int64_t W = c.num_workers;
+      auto wide_cut = [&](const int64_t most) -> WideCut {
+        if (wide_families == 0) return WideCut{};
         if (2 * wide_families <= W) {
           // Few of them, and so little narrow work that the other workers would be done with it before a wide
           // family is (a prefill chunk with no or few decodes beside it): at most one piece per worker, all of about
           // the same length whatever the lengths of the families, no shorter than a worker's share of the wide and half
           // of the narrow work, on few enough workers to leave half of what the narrow work would take to it, and no
           // shorter than the longest of the units that stay whole.  Loads as in the cost model, max(rows, floor) x tiles.
-          if (narrow_total * 2 < wide_max * (W - wide_families)) {
-            const int64_t wide_load = wide_tiles * tile_load, both = wide_load + narrow_total / 2;
-            cut = WideCut{wide_size_for(wide, ceil_div(both, W * tile_load), wide_longest, ceil_div(W + ceil_div(W * wide_load, both), 2), true), true};
-            int64_t whole = 0;
-            for (const XyTileClass& w : wide)
-              if (cut.pieces(w) == 1) whole = std::max(whole, w.nb);
-            cut.size = std::max(cut.size, whole);
-            while (cut.size < wide_longest && wide_workspace(wide, cut, D) > most) cut.size *= 2;
-          }
-        } else {
-          // More: the cut of the shortest estimated time among those that fill the workers once, twice, ... with
-          // whole units as the other choice; taken if a fifth shorter (the estimate knows nothing of the caches).
-          // Whole units are within a quarter of the mean anyway where none is longer than a quarter of it.
-          const int64_t mean = ceil_div(2 * wide_tiles + kWideUnitHalves * wide_families + 2 * narrow_tiles, W);
-          if (4 * (2 * wide_longest + kWideUnitHalves) > mean) {
-            const int64_t whole = wide_estimate(wide, WideCut{}, W, narrow_tiles, plan->scratch);
-            int64_t best = whole * 4 / 5 + 1;
-            const int64_t first = ceil_div(wide_families, W);
-            for (int64_t rounds = first; rounds < first + 3; ++rounds) {
-              const int64_t share = std::max(kAutoSplitWideMin, ceil_div(wide_tiles, rounds * W));
-              const WideCut other{wide_size_for(wide, share, wide_longest, rounds * W, false), false};
-              if (other.size >= wide_longest || wide_workspace(wide, other, D) > most) continue;
-              const int64_t t = wide_estimate(wide, other, W, narrow_tiles, plan->scratch);
-              if (t < best) {
-                best = t;
-                cut = other;
-              }
-            }
+          if (narrow_total * 2 >= wide_max * (W - wide_families)) return WideCut{};
+          const int64_t wide_load = wide_tiles * tile_load, both = wide_load + narrow_total / 2;
+          WideCut cut{wide_size_for(wide, ceil_div(both, W * tile_load), wide_longest, ceil_div(W + ceil_div(W * wide_load, both), 2), true), true};
+          int64_t whole = 0;
+          for (const XyTileClass& w : wide)
+            if (cut.pieces(w) == 1) whole = std::max(whole, w.nb);
+          cut.size = std::max(cut.size, whole);
+          while (cut.size < wide_longest && wide_workspace(wide, cut, D) > most) cut.size *= 2;
+          return cut;
+        }
+        // More: the cut of the shortest estimated time among those that fill the workers once, twice, ... with
+        // whole units as the other choice; taken if a fifth shorter (the estimate knows nothing of the caches).
+        // Whole units are within a quarter of the mean anyway where none is longer than a quarter of it.
+        const int64_t mean = ceil_div(2 * wide_tiles + kWideUnitHalves * wide_families + 2 * narrow_tiles, W);
+        if (4 * (2 * wide_longest + kWideUnitHalves) <= mean) return WideCut{};
+        const int64_t whole = wide_estimate(wide, WideCut{}, W, narrow_tiles, plan->scratch);
+        int64_t best = whole * 4 / 5 + 1;
+        WideCut cut;
+        const int64_t first = ceil_div(wide_families, W);
+        for (int64_t rounds = first; rounds < first + 3; ++rounds) {
+          const int64_t share = std::max(kAutoSplitWideMin, ceil_div(wide_tiles, rounds * W));
+          const WideCut other{wide_size_for(wide, share, wide_longest, rounds * W, false), false};
+          if (other.size >= wide_longest || wide_workspace(wide, other, D) > most) continue;
+          const int64_t t = wide_estimate(wide, other, W, narrow_tiles, plan->scratch);
+          if (t < best) {
+            best = t;
+            cut = other;
           }
         }
-      }
+        return cut;
+      };
+      // The last tokens of a prompt may be a narrow PREFILL family.  One that visits more tiles than half a worker's
+      // mean load is cut like the others: a wavefront on its own takes about a microsecond per 32 keys and comes to it
+      // behind the wide units (8 families of 94 tiles beside 23 tiles of wide work a worker 394 -> 103 us, 2 of 19
+      // beside 24 142 -> 105 us); a shorter one fills a gap (8 of 7 beside 15: 65 us whole, 74 cut).
+      std::vector<XyTileClass>& may_cut = plan->scratch.may_cut;
+      const int64_t most = XY_STATIC_WORKSPACE_BYTES / (int64_t)sizeof(float);
+      auto fits = [&](const int64_t whole_tiles) {      // sets every split size; whether xy_attn_run_static holds the partials
+        prefill_whole_tiles = whole_tiles;
+        may_cut.clear();
+        std::copy_if(narrow.begin(), narrow.end(), std::back_inserter(may_cut), [&](const XyTileClass& w) {
+          return !w.prefill || w.nb > whole_tiles;
+        });
+        split_narrow = narrow_split_size(may_cut, (int64_t)kNarrowSlotsPerWorker * W);
+        const int64_t narrow_ws = narrow_workspace(may_cut, split_narrow, D);
+        cut = wide_cut(most - narrow_ws);
+        return narrow_ws + wide_workspace(wide, cut, D) <= most;
+      };
+      // A batch that xy_attn_run_static takes with these families whole is not cut beyond what it holds (350 of them with
+      // 2000 tiles each would be in 29 pieces each, 162 MiB); one that it refuses either way is cut.
+      const int64_t half_mean = (2 * wide_tiles + kWideUnitHalves * wide_families + 2 * narrow_tiles) / (4 * W);
+      if (!fits(half_mean) && !fits(INT64_MAX)) fits(half_mean);
+      split_wide = kAutoSplitWide;
     }
 
     // --- decomposition (section 3.2.1) + K/V split -------------------------

@@ -42,7 +42,7 @@ struct XyPlanScratch {
     int64_t nb, count, rows;                // K/V tiles; families (head groups); rows of a family
     bool prefill;
   };
-  std::vector<TileClass> wide, narrow;      // token tiles of more than 32 rows, of at most 32
+  std::vector<TileClass> wide, narrow, may_cut;     // token tiles of more than 32 rows, of at most 32, those of them that may be cut
   std::vector<std::pair<int64_t, int64_t>> sizes, loads;
 };
 

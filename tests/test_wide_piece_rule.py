@@ -53,6 +53,23 @@ def test_partial_results_stay_within_the_library_workspace():
     compare(cfg, seqs)
 
 
+@pytest.mark.parametrize("seqs", [
+    [(8, 256000 - 8, X.XY_PREFILL, 0, 0)] * 44,                                             # 352 families in 29 pieces: 162 MiB
+    [(8, 256000 - 8, X.XY_PREFILL, 0, 0)] * 40 + [(8, 256000 - 8, X.XY_VERIFY, 0, 0)] * 3,
+    # five tails beside verify families of 160 rows on 9 x 16 tiles, 57 MiB of partials of their own
+    [(8, 300000 - 8, X.XY_PREFILL, 0, 0)] * 5 + [(40, 144 * 128 - 40, X.XY_VERIFY, 0, 0)] * 10 + [(1, 40 * 128, X.XY_DECODE, 0, 0)] * 5])
+def test_cut_prompt_tails_stay_within_the_library_workspace(seqs):
+    # the last 8 tokens of a prompt are families of 32 rows; whole, they need no workspace, and no batch that
+    # xy_attn_run_static takes that way is pushed beyond what it holds by cutting them
+    cfg = X.xy_attn_default_config(32, 8, 4096)
+    units = compare(cfg, seqs)
+    assert 4 * PL.plan_oracle(cfg.as_dict(), seqs)[3] <= X.XY_STATIC_WORKSPACE_BYTES
+    assert set(units["num_splits"][units["kind_flags"] == X.XY_PREFILL].tolist()) == {1}
+    # a few of them, where the partials fit, are cut as before
+    units = compare(cfg, seqs[:1] + [(1, 300, X.XY_DECODE, 0, 0)])
+    assert units["num_splits"].max() > 1
+
+
 @pytest.mark.parametrize("seed", range(40))
 def test_both_planners_agree_on_drawn_batches_with_wide_families(seed):
     rng = random.Random(seed)

@@ -326,11 +326,12 @@ def xy_attn_copy_block_rows(copies, num_kv_heads, k_cache, v_cache, stream=None)
     """copies: list of (src_block, dst_block, rows): the copy-on-write copies of a step (see xy_attn.h)."""
     if not copies:
         return
+    records = list(map(tuple, copies))      # each read once: a record may be an iterator
     try:
-        flat = [int(x) for src, dst, rows in copies for x in (src, dst, rows)]
+        flat = [int(x) for src, dst, rows in records for x in (src, dst, rows)]
         arr = struct.pack(f"{len(flat)}i", *flat)       # xy_kv_copy records
     except (ValueError, struct.error):      # fields left out, too many of them or beyond 32 bits: the record's own rules
-        arr = (xy_kv_copy * len(copies))(*[xy_kv_copy(*map(int, c)) for c in copies])
+        arr = (xy_kv_copy * len(records))(*[xy_kv_copy(*map(int, r)) for r in records])
     _check(_lib.xy_attn_copy_block_rows(arr, len(copies), int(num_kv_heads), _ptr(k_cache), _ptr(v_cache),
                                         k_cache.stride(0), k_cache.stride(1), k_cache.stride(2),
                                         _stream(stream)))

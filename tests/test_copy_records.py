@@ -24,6 +24,17 @@ def test_records_are_those_of_the_structure(monkeypatch, copies):
     assert seen == [bytes(want)]
 
 
+def test_records_that_can_be_read_only_once(monkeypatch):
+    seen = []
+    monkeypatch.setattr(X, "_lib", type("L", (), {"xy_attn_copy_block_rows": staticmethod(
+        lambda arr, n, *rest: seen.append(bytes(arr)[:12 * n]) or 0)}))
+    monkeypatch.setattr(X, "_stream", lambda s: 0)
+    k = torch.zeros(2, 1, 16, 128, dtype=torch.bfloat16)
+    for copies in ([(1, 2, 3), (4, 5)], [(1, 2)], [(2**31, 0, 1)], [(1, 2, 3)]):
+        X.xy_attn_copy_block_rows([iter(c) for c in copies], 1, k, k)
+        assert seen.pop() == bytes((X.xy_kv_copy * len(copies))(*[X.xy_kv_copy(*c) for c in copies]))
+
+
 def test_a_copy_of_four_fields_is_refused():
     k = torch.zeros(2, 1, 16, 128, dtype=torch.bfloat16)
     for copies in ([(1, 2, 3, 4)], [(1, 2), (3, 4, 5, 6)]):

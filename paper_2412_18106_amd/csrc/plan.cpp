@@ -309,7 +309,8 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
           // shorter than the longest of the units that stay whole.  Loads as in the cost model, max(rows, floor) x tiles.
           if (narrow_total * 2 >= wide_max * (W - wide_families)) return WideCut{};
           const int64_t wide_load = wide_tiles * tile_load, both = wide_load + narrow_total / 2;
-          WideCut cut{wide_size_for(wide, ceil_div(both, W * tile_load), wide_longest, ceil_div(W + ceil_div(W * wide_load, both), 2), true), true};
+          const int64_t workers = (int64_t)(((__int128)W * wide_load + both - 1) / both);      // the wide work's share of them
+          WideCut cut{wide_size_for(wide, ceil_div(both, W * tile_load), wide_longest, ceil_div(W + workers, 2), true), true};
           int64_t whole = 0;
           for (const XyTileClass& w : wide)
             if (cut.pieces(w) == 1) whole = std::max(whole, w.nb);

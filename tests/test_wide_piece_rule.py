@@ -53,6 +53,15 @@ def test_partial_results_stay_within_the_library_workspace():
     compare(cfg, seqs)
 
 
+@pytest.mark.parametrize("floor", [128, 2**31 - 1])
+@pytest.mark.parametrize("families", [1, 11, 21, 40])
+def test_loads_beyond_64_bits_times_the_workers(floor, families):
+    # workers x load of the wide families passes 2^63 from 11 families of 100000 tiles on (2^12 x 2^31 x 10^5 each)
+    cfg = X.xy_attn_default_config(4, 1, 100000, num_workers=4096, cost_row_floor=floor, assign_policy=1)
+    units = compare(cfg, [(64, 128 * 100000 - 64, X.XY_PREFILL, 0, 0)] * families + [(1, 12800 * 64 - 1, X.XY_DECODE, 0, 0)])
+    assert (units["seq"] < families).sum() > families
+
+
 @pytest.mark.parametrize("seqs", [
     [(8, 256000 - 8, X.XY_PREFILL, 0, 0)] * 44,                                             # 352 families in 29 pieces: 162 MiB
     [(8, 256000 - 8, X.XY_PREFILL, 0, 0)] * 40 + [(8, 256000 - 8, X.XY_VERIFY, 0, 0)] * 3,

@@ -50,6 +50,7 @@ constexpr int kB = 128;          // keys per K/V tile (one or more pages of the 
 constexpr int kTileBytes = kB * kD * 2;   // one K or V tile of one KV head
 constexpr int kThreads = 256;        // 4 wavefronts: one per SIMD
 constexpr int kMergeThreads = 256, kMergeRows = kMergeThreads / 32;     // rows of a family merged by one workgroup
+constexpr int64_t kMergeGrid = 1 << 22;      // workgroups of one launch (a launch of 2^32 threads or more runs those modulo 2^32, without an error)
 constexpr int64_t kDeepTiles = 10;
 constexpr float kPrescaleMaxC = 0.25f;    // largest c = scale * log2(e) that is folded into Q (wide units)
 // Dynamic assignment: the cursor of the shared list, kDoneGroups counts of finished workgroups and the
@@ -1702,10 +1703,13 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
     if (hipGetLastError() != hipSuccess) return XY_ERR_HIP;
   }
   if ((phases & XY_PHASE_MERGE) && !plan->merges.empty()) {
-    hipLaunchKernelGGL(xy_attn_merge_kernel, dim3((unsigned)plan->merge_groups), dim3(kMergeThreads), 0, stream,
-                       static_cast<const XyDevMergeRows*>(plan->d_merges), static_cast<const float*>(workspace), p.out,
-                       o_ts, o_hs);
-    if (hipGetLastError() != hipSuccess) return XY_ERR_HIP;
+    for (int64_t first = 0; first < plan->merge_groups; first += kMergeGrid) {
+      const int64_t groups = std::min(kMergeGrid, plan->merge_groups - first);
+      hipLaunchKernelGGL(xy_attn_merge_kernel, dim3((unsigned)groups), dim3(kMergeThreads), 0, stream,
+                         static_cast<const XyDevMergeRows*>(plan->d_merges) + first, static_cast<const float*>(workspace),
+                         p.out, o_ts, o_hs);
+      if (hipGetLastError() != hipSuccess) return XY_ERR_HIP;
+    }
   }
   return XY_OK;
 }

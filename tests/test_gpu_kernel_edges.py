@@ -184,3 +184,32 @@ def test_merge_pass_keeps_an_infinity_of_the_last_piece(gpu, pieces):
     assert np.isposinf(ref[0, 0, 5]) and np.isposinf(got[0, 0, 5])
     others = np.arange(128) != 5
     assert np.abs(got[0, 0, others] - ref[0, 0, others]).max() <= MAX_ABS
+
+
+def test_merge_pass_of_more_workgroups_than_one_launch_takes(gpu):
+    """A launch has fewer than 2^32 threads, 2^24 workgroups of the merge pass: 257 decodes of 65536 heads on two tiles
+    each are 2^24 + 65536 families of one row.  Every head reads the same K/V and every token has the same Q rows (strides
+    of zero), so that the result is the same for every token."""
+    import torch
+    from paper_2412_18106_amd import binding as X
+    heads, n, keys = 65536, 257, 129
+    cfg = X.xy_attn_default_config(heads, heads, 2, split_kv_blocks=1, assign_policy=X.XY_ASSIGN_SNAKE)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    q1 = torch.empty(heads, 128, dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    k1, v1 = (torch.empty(2, 1, 128, 128, dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(2))
+    out = torch.full((n, heads, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    table = torch.tensor([[1, 0]] * n, dtype=torch.int32, device="cuda")
+    plan = X.xy_attn_plan_create(cfg, [(1, keys - 1, X.XY_DECODE, 0, 0)] * n)
+    try:
+        ws = torch.empty(X.xy_attn_plan_workspace_bytes(plan), dtype=torch.uint8, device="cuda")
+        X.xy_attn_run(plan, q1.expand(n, heads, 128), k1.expand(2, heads, 128, 128), v1.expand(2, heads, 128, 128), table, None,
+                      out, ws, 128 ** -0.5)
+        torch.cuda.synchronize()
+    finally:
+        X.xy_attn_plan_destroy(plan)
+    k, v = (torch.cat([x[1, 0], x[0, 0, :1]]).float() for x in (k1, v1))
+    ref = torch.softmax((q1.float() @ k.t().contiguous()) * 128 ** -0.5, -1) @ v
+    err = (out[0].float() - ref).abs()
+    assert float(err.max()) <= MAX_ABS and float(err.mean()) <= MEAN_ABS      # (a NaN fails both)
+    assert all(torch.equal(out[i], out[0]) for i in range(1, n))

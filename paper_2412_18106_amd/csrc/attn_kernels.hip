@@ -50,7 +50,8 @@ constexpr int kB = 128;          // keys per K/V tile (one or more pages of the 
 constexpr int kTileBytes = kB * kD * 2;   // one K or V tile of one KV head
 constexpr int kThreads = 256;        // 4 wavefronts: one per SIMD
 constexpr int kMergeThreads = 256, kMergeRows = kMergeThreads / 32;     // rows of a family merged by one workgroup
-constexpr int64_t kMergeGrid = 1 << 22;      // workgroups of one launch (a launch of 2^32 threads or more runs those modulo 2^32, without an error)
+// workgroups of one launch (a launch of 2^32 threads or more runs those modulo 2^32, without an error)
+constexpr int64_t kMergeGrid = 1 << 22, kAppendGrid = 1 << 22;
 constexpr int64_t kDeepTiles = 10;
 constexpr float kPrescaleMaxC = 0.25f;    // largest c = scale * log2(e) that is folded into Q (wide units)
 // Dynamic assignment: the cursor of the shared list, kDoneGroups counts of finished workgroups and the
@@ -1726,8 +1727,8 @@ __global__ __launch_bounds__(256) void xy_attn_append_kernel(const XyDevSeq* __r
                                                              uint16_t* __restrict__ v_cache, int64_t kv_bs,
                                                              int64_t kv_hs, int64_t kv_ts,
                                                              const int32_t* __restrict__ block_table,
-                                                             int max_blocks, int page_shift) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+                                                             int max_blocks, int page_shift, int64_t first) {
+  const int64_t idx = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int chunk = (int)(idx & 15), is_v = (int)((idx >> 4) & 1);
   const int64_t row = idx >> 5;                     // token * Hkv + kv head
   const int64_t t = row / num_kv_heads;
@@ -1763,15 +1764,17 @@ extern "C" int xy_attn_append_kv(xy_attn_plan* plan, const void* k_new, const vo
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev != plan->device) return XY_ERR_ARG;
   const int64_t threads = plan->total_tokens * plan->cfg.num_kv_heads * 32;
-  const unsigned blocks = (unsigned)((threads + 255) / 256);
-  hipLaunchKernelGGL(xy_attn_append_kernel, dim3(blocks), dim3(256), 0, static_cast<hipStream_t>(hip_stream),
-                     static_cast<const XyDevSeq*>(plan->d_seqs), plan->num_seqs, plan->total_tokens,
-                     plan->cfg.num_kv_heads, static_cast<const uint16_t*>(k_new),
-                     static_cast<const uint16_t*>(v_new), n_ts, n_hs, static_cast<uint16_t*>(k_cache),
-                     static_cast<uint16_t*>(v_cache), kv_bs, kv_hs, kv_ts, block_table,
-                     plan->cfg.max_blocks_per_seq,
-                     plan->cfg.block_size == 16 ? 4 : plan->cfg.block_size == 32 ? 5 : plan->cfg.block_size == 64 ? 6 : 7);
-  if (hipGetLastError() != hipSuccess) return XY_ERR_HIP;
+  for (int64_t first = 0; first < threads; first += kAppendGrid * 256) {
+    const int64_t blocks = std::min(kAppendGrid, (threads - first + 255) / 256);
+    hipLaunchKernelGGL(xy_attn_append_kernel, dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(hip_stream),
+                       static_cast<const XyDevSeq*>(plan->d_seqs), plan->num_seqs, plan->total_tokens,
+                       plan->cfg.num_kv_heads, static_cast<const uint16_t*>(k_new),
+                       static_cast<const uint16_t*>(v_new), n_ts, n_hs, static_cast<uint16_t*>(k_cache),
+                       static_cast<uint16_t*>(v_cache), kv_bs, kv_hs, kv_ts, block_table,
+                       plan->cfg.max_blocks_per_seq,
+                       plan->cfg.block_size == 16 ? 4 : plan->cfg.block_size == 32 ? 5 : plan->cfg.block_size == 64 ? 6 : 7, first);
+    if (hipGetLastError() != hipSuccess) return XY_ERR_HIP;
+  }
   return XY_OK;
 }
 

@@ -174,3 +174,26 @@ def test_append_errors_and_empty_plan(gpu):
     assert X._lib.xy_attn_append_kv(plan, None, None, 0, 0, None, None, 0, 0, 0, None, None) == 0
     X.xy_attn_plan_destroy(plan)
     torch.cuda.synchronize()
+
+
+def test_append_of_more_threads_than_one_launch_takes(gpu):
+    """A launch has fewer than 2^32 threads: 131200 tokens of 1024 KV heads are 2^32 of them and 4 million more (32 per
+    row).  The new rows are the same for every token (token stride zero) and all pages but the last are one block, so
+    that the pass needs little memory; the last page is a block of its own, which only the last tokens write."""
+    import torch
+    from paper_2412_18106_amd import binding as X
+    heads, pages = 1024, 1025
+    tokens = 128 * pages
+    new = torch.randint(-2**15, 2**15, (2, heads, 128), dtype=torch.int16, device="cuda").view(torch.bfloat16)
+    k, v = (torch.zeros(3, heads, 128, 128, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    table = torch.tensor([[0] * (pages - 1) + [2]], dtype=torch.int32, device="cuda")
+    cfg = X.xy_attn_default_config(heads, heads, pages, split_kv_blocks=0, assign_policy=X.XY_ASSIGN_SNAKE)
+    plan = X.xy_attn_plan_create(cfg, [(tokens, 0, X.XY_PREFILL, 0, 0)])
+    try:
+        X.xy_attn_append_kv(plan, new[0].expand(tokens, heads, 128), new[1].expand(tokens, heads, 128), k, v, table)
+        torch.cuda.synchronize()
+    finally:
+        X.xy_attn_plan_destroy(plan)
+    for cache, rows in ((k, new[0]), (v, new[1])):
+        bits, want = cache.view(torch.int16), rows.view(torch.int16)[:, None, :].expand(heads, 128, 128)
+        assert torch.equal(bits[0], want) and torch.equal(bits[2], want) and not bits[1].any()

@@ -10,6 +10,7 @@
 // Update stage (section 4.2.1).
 #include <algorithm>
 #include <cstring>
+#include <functional>
 #include <iterator>
 #include <new>
 #include <numeric>
@@ -127,12 +128,12 @@ int64_t wide_size_for(const std::vector<XyTileClass>& wide, int64_t lo, int64_t 
 }
 
 // Time of the launch in half tiles if the pieces go, longest first, to the worker that is free first and the narrow
-// work (a narrow tile counted as a wide one) fills what is left.  Equal pieces and equally loaded workers are
+// work (a narrow tile counted as a wide one) fills what is left.  Equal pieces and workers that are loaded alike are
 // handled together.
 int64_t wide_estimate(const std::vector<XyTileClass>& wide, const WideCut& cut, int64_t workers, int64_t narrow_tiles,
                       XyPlanScratch& scratch) {
   auto& sizes = scratch.sizes;          // (cost, pieces)
-  auto& loads = scratch.loads;          // (load, workers), load ascending
+  auto& loads = scratch.loads;          // (load, workers): a heap, smallest load first
   sizes.clear();
   bool any_cut = false;
   int64_t total = 0;
@@ -145,18 +146,24 @@ int64_t wide_estimate(const std::vector<XyTileClass>& wide, const WideCut& cut, 
   }
   std::sort(sizes.begin(), sizes.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
   loads.assign(1, {0, workers});
+  int64_t largest = 0;
   for (const auto& [cost, pieces] : sizes) {
     for (int64_t left = pieces; left > 0;) {
-      const int64_t load = loads.front().first + cost, n = std::min(left, loads.front().second);
+      std::pop_heap(loads.begin(), loads.end(), std::greater<>());
+      const int64_t load = loads.back().first + cost, n = std::min(left, loads.back().second);
+      largest = std::max(largest, load);
       left -= n;
-      if (n == loads.front().second) loads.erase(loads.begin());
-      else loads.front().second -= n;
-      auto at = std::lower_bound(loads.begin(), loads.end(), load, [](const auto& x, int64_t l) { return x.first < l; });
-      if (at != loads.end() && at->first == load) at->second += n;
-      else loads.insert(at, {load, n});
+      if (n == loads.back().second) {
+        loads.back().first = load;
+      } else {
+        loads.back().second -= n;
+        std::push_heap(loads.begin(), loads.end(), std::greater<>());
+        loads.emplace_back(load, n);
+      }
+      std::push_heap(loads.begin(), loads.end(), std::greater<>());
     }
   }
-  return std::max(loads.back().first + (any_cut ? kWideMergeHalves : 0), ceil_div(total + 2 * narrow_tiles, workers));
+  return std::max(largest + (any_cut ? kWideMergeHalves : 0), ceil_div(total + 2 * narrow_tiles, workers));
 }
 
 // XY_ASSIGN_DYNAMIC without a unit of more than 32 rows: a shared list only if some unit visits more tiles than this
@@ -283,7 +290,8 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
           const int64_t last_excl = tree ? (int64_t)s.context_len + s.query_len : (int64_t)s.context_len + qb + qc;
           const int64_t nb = ceil_div(last_excl, kKvTile), load = std::max<int64_t>(rows, c.cost_row_floor) * nb;
           if (rows > kNarrowRows) {
-            wide.push_back(XyTileClass{nb, count, rows, pre});
+            if (!wide.empty() && wide.back().nb == nb && wide.back().rows == rows && wide.back().prefill == pre) wide.back().count += count;
+            else wide.push_back(XyTileClass{nb, count, rows, pre});
             wide_families += count;
             wide_tiles += nb * count;
             wide_longest = std::max(wide_longest, nb);
@@ -326,6 +334,7 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         const int64_t whole = wide_estimate(wide, WideCut{}, W, narrow_tiles, plan->scratch);
         int64_t best = whole * 4 / 5 + 1;
         WideCut cut;
+        if (best <= mean) return cut;       // no estimate is below the mean load
         const int64_t first = ceil_div(wide_families, W);
         for (int64_t rounds = first; rounds < first + 3; ++rounds) {
           const int64_t share = std::max(kAutoSplitWideMin, ceil_div(wide_tiles, rounds * W));
@@ -567,11 +576,11 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         }
         first[hole] = e;
       };
-      int64_t wide_units = 0;
+      int64_t wide_units = 0, assigned = 0, costliest = 0;
       auto assign = [&](std::vector<int32_t>& to, const bool by_chip) {       // returns the largest load of a worker
         heap.resize(W);
         for (int32_t w = 0; w < W; ++w) heap[w] = Entry(0, w);
-        wide_units = 0;
+        wide_units = assigned = costliest = 0;
         int64_t largest = 0;
         for (int64_t pos = 0; pos < (int64_t)order.size(); ++pos) {
           const xy_work_unit& u = fam[order[pos]];
@@ -581,6 +590,8 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
             continue;
           }
           wide_units += !narrow;
+          assigned += u.cost;
+          costliest = std::max(costliest, u.cost);
           int64_t h = 0;
           if (!narrow && by_chip) {
             h = chip_of_group[group_key(u)];
@@ -596,8 +607,10 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
       };
       const int64_t largest = assign(worker_of, !chip_of_group.empty());
       // A short list (two units a worker or fewer): chiplets that are level in load need not be level in units, and a
-      // worker with one unit more than the others is then most of the launch.
-      if (!chip_of_group.empty() && wide_units > 0 && wide_units <= 2 * W) {
+      // worker with one unit more than the others is then most of the launch.  (No placement has a largest load below
+      // the costliest unit or the mean: where that is near enough, the other one is not worked out.)
+      if (!chip_of_group.empty() && wide_units > 0 && wide_units <= 2 * W &&
+          largest * 100 > std::max(costliest, ceil_div(assigned, W)) * 103) {
         std::vector<int32_t>& plain = plan->scratch.other_worker_of;
         plain.resize(fam.size());
         if (largest * 100 > assign(plain, false) * 103) worker_of.swap(plain);

@@ -527,6 +527,8 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
       const int64_t per_chip = (W % kChiplets == 0) ? W / kChiplets : 0;
       std::vector<int32_t>& chip_of_group = plan->scratch.chip_of_group;
       chip_of_group.clear();
+      std::vector<int64_t>& by_cost = plan->scratch.by_cost;      // the groups, heaviest first
+      by_cost.clear();
       const int64_t group_heads = c.num_q_heads / c.num_kv_heads;
       auto group_key = [&](const xy_work_unit& u) { return (int64_t)u.seq * c.num_kv_heads + u.head_begin / group_heads; };
       if (per_chip > 0) {
@@ -539,8 +541,6 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
             group_cost[group_key(u)] += u.cost;
             total += u.cost;
           }
-        std::vector<int64_t>& by_cost = plan->scratch.by_cost;
-        by_cost.clear();
         for (int64_t g = 0; g < ngroups; ++g)
           if (group_cost[g] > 0) by_cost.push_back(g);
         std::stable_sort(by_cost.begin(), by_cost.end(),
@@ -559,61 +559,71 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
       // one heap per chiplet (one in all without chiplets), side by side in one array; the least-loaded worker
       // overall is the best top.  Workers in index order with no load yet are a heap already.
       const int64_t nheaps = per_chip > 0 ? kChiplets : 1, per_heap = per_chip > 0 ? per_chip : W;
-      std::vector<Entry>& heap = plan->scratch.heap;
-      auto top = [&](int64_t h) -> Entry& { return heap[h * per_heap]; };
-      auto add_to_top = [&](int64_t h, int64_t cost) {        // the top worker takes a unit and sinks to its new place
-        Entry* first = heap.data() + h * per_heap;
-        Entry e = first[0];
-        e.first += cost;
-        int64_t hole = 0;
-        for (;;) {
-          int64_t child = 2 * hole + 1;
-          if (child >= per_heap) break;
-          if (child + 1 < per_heap && first[child + 1] < first[child]) ++child;
-          if (!(first[child] < e)) break;
-          first[hole] = first[child];
-          hole = child;
-        }
-        first[hole] = e;
-      };
-      int64_t wide_units = 0, assigned = 0, costliest = 0;
-      auto assign = [&](std::vector<int32_t>& to, const bool by_chip) {       // returns the largest load of a worker
-        heap.resize(W);
+      plan->scratch.heap.resize(W);
+      auto assign = [&](int32_t* const to, const bool by_chip) {
+        // (its own copies: what is captured would be read again behind every store to the heaps)
+        Entry* const heap = plan->scratch.heap.data();
+        const int64_t heaps = nheaps, size = per_heap, units = (int64_t)fam.size();
+        const xy_work_unit* const unit = fam.data();
+        const int32_t* const sorted = order.data();
+        const bool shared_list = share;
+        auto top = [heap, size](int64_t h) -> Entry& { return heap[h * size]; };
+        auto add_to_top = [heap, size](int64_t h, int64_t cost) {        // the top worker takes a unit and sinks to its new place
+          Entry* first = heap + h * size;
+          Entry e = first[0];
+          e.first += cost;
+          int64_t hole = 0;
+          for (;;) {
+            int64_t child = 2 * hole + 1;
+            if (child >= size) break;
+            if (child + 1 < size && first[child + 1] < first[child]) ++child;
+            if (!(first[child] < e)) break;
+            first[hole] = first[child];
+            hole = child;
+          }
+          first[hole] = e;
+        };
         for (int32_t w = 0; w < W; ++w) heap[w] = Entry(0, w);
-        wide_units = assigned = costliest = 0;
-        int64_t largest = 0;
-        for (int64_t pos = 0; pos < (int64_t)order.size(); ++pos) {
-          const xy_work_unit& u = fam[order[pos]];
+        for (int64_t pos = 0; pos < units; ++pos) {
+          const xy_work_unit& u = unit[sorted[pos]];
           const bool narrow = (int64_t)u.q_count * u.head_count <= kNarrowRows;
-          if (share && narrow) {
+          if (shared_list && narrow) {
             to[pos] = kShared;
             continue;
           }
-          wide_units += !narrow;
-          assigned += u.cost;
-          costliest = std::max(costliest, u.cost);
           int64_t h = 0;
           if (!narrow && by_chip) {
             h = chip_of_group[group_key(u)];
           } else {
-            for (int64_t x = 1; x < nheaps; ++x)
+            for (int64_t x = 1; x < heaps; ++x)
               if (top(x) < top(h)) h = x;
           }
           to[pos] = top(h).second;
-          largest = std::max(largest, top(h).first + u.cost);
           add_to_top(h, u.cost);
         }
-        return largest;
       };
-      const int64_t largest = assign(worker_of, !chip_of_group.empty());
+      auto largest = [&] { return std::max_element(plan->scratch.heap.begin(), plan->scratch.heap.end())->first; };      // load of a worker
+      assign(worker_of.data(), !chip_of_group.empty());
       // A short list (two units a worker or fewer): chiplets that are level in load need not be level in units, and a
       // worker with one unit more than the others is then most of the launch.  (No placement has a largest load below
       // the costliest unit or the mean: where that is near enough, the other one is not worked out.)
-      if (!chip_of_group.empty() && wide_units > 0 && wide_units <= 2 * W &&
-          largest * 100 > std::max(costliest, ceil_div(assigned, W)) * 103) {
-        std::vector<int32_t>& plain = plan->scratch.other_worker_of;
-        plain.resize(fam.size());
-        if (largest * 100 > assign(plain, false) * 103) worker_of.swap(plain);
+      int64_t wide_units = 0, assigned = 0, costliest = 0;
+      if (!chip_of_group.empty() && !by_cost.empty())
+        for (const xy_work_unit& u : fam) {
+          const bool narrow = (int64_t)u.q_count * u.head_count <= kNarrowRows;
+          wide_units += !narrow;
+          if (share && narrow) continue;
+          assigned += u.cost;
+          costliest = std::max(costliest, u.cost);
+        }
+      if (wide_units > 0 && wide_units <= 2 * W) {
+        const int64_t by_chip = largest();
+        if (by_chip * 100 > std::max(costliest, ceil_div(assigned, W)) * 103) {
+          std::vector<int32_t>& plain = plan->scratch.other_worker_of;
+          plain.resize(fam.size());
+          assign(plain.data(), false);
+          if (by_chip * 100 > largest() * 103) worker_of.swap(plain);
+        }
       }
     }
     for (int64_t pos = 0; pos < (int64_t)order.size(); ++pos)

@@ -1453,6 +1453,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
 template <int N>      // pieces [s0, s0 + N), those from num_splits on counted as empty
 __device__ __forceinline__ void merge_pieces(const float* acc_row, const float* m_row, const float* l_row, int64_t slab,
                                              int s0, int num_splits, float& m_run, float& den, f32x4& num) {
+  constexpr int kCertain = N / 2 + (N > 2);      // more pieces than half a batch, or the next smaller one would do
   float m[N], l[N];
   f32x4 acc[N];
 #pragma unroll
@@ -1462,16 +1463,10 @@ __device__ __forceinline__ void merge_pieces(const float* acc_row, const float* 
     l[i] = l_row[at];
     acc[i] = *reinterpret_cast<const f32x4*>(acc_row + at);
   }
-#pragma unroll
-  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(m[i]), "+v"(l[i]), "+v"(acc[i]));      // loads stay together, above the selects
   float m_new = m_run;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    if (s0 + i >= num_splits) {             // all of it: a factor of zero does not remove an infinity
-      m[i] = -INFINITY;
-      l[i] = 0.f;
-      acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    if (s0 + i >= num_splits) m[i] = -INFINITY;
     m_new = fmaxf(m_new, m[i]);
   }
   const float keep = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
@@ -1479,6 +1474,13 @@ __device__ __forceinline__ void merge_pieces(const float* acc_row, const float* 
   num *= keep;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
+    if (i >= kCertain) {    // may be empty: all of it is zero then, a factor of zero would not remove an infinity
+      asm volatile("" : "+v"(l[i]), "+v"(acc[i]));      // (the loads stay where they are, not in a branch of their own)
+      if (s0 + i >= num_splits) {
+        l[i] = 0.f;
+        acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
     const float f = m[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[i] - m_new);
     num += f * acc[i];
     den += f * l[i];

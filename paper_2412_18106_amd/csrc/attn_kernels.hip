@@ -52,6 +52,17 @@ constexpr int kThreads = 256;        // 4 wavefronts: one per SIMD
 constexpr int kMergeThreads = 256, kMergeRows = kMergeThreads / 32;     // rows of a family merged by one workgroup
 // workgroups of one launch (a launch of 2^32 threads or more runs those modulo 2^32, without an error)
 constexpr int64_t kMergeGrid = 1 << 22, kAppendGrid = 1 << 22;
+// How a launch processes its units of at most 32 rows, by what they are on average over the
+// launch; wavefronts are four per worker.  A unit on two slices costs some 200 instructions more than a short one, which
+// a lone wavefront pays for with 0.3 us, and gains where it waits for memory in every slice, with its neighbours idle.
+// Decodes of 32 heads in 8, each a unit of its own, us short / two slices: 4 slices 7.1 / 7.3 (8 units), 9.3 / 9.2 (512),
+// 24.4 / 24.7 (2048), 47.9 / 49.2 (4096); 1 and 2 slices 2 to 13 % less short; 8 slices 11.3 / 10.8, 14.5 / 13.6 up to a
+// unit for every second wavefront, 22.4 / 22.5 at one each, 89.4 / 91.6 at four: so up to four slices a unit are short,
+// up to eight where there are more units than wavefronts.  Units of 32 rows, whose Q is eight times as much: 4096 of them
+// 42.1 / 44.8 with 2 slices, 66.4 / 65.7 with 4: up to two slices above 16 rows a unit.
+constexpr int64_t kShortSlices = 4, kShortSlicesManyUnits = 8, kShortSlicesManyRows = 2, kManyRows = 16;
+// Longer ones: two slices in flight up to kDeepTiles tiles a wavefront, one beyond (see process_solo; measured at 7.5
+// tiles, 3 % in favour of two, and at 14, 1 % against).
 constexpr int64_t kDeepTiles = 10;
 constexpr float kPrescaleMaxC = 0.25f;    // largest c = scale * log2(e) that is folded into Q (wide units)
 // Dynamic assignment: the cursor of the shared list, kDoneGroups counts of finished workgroups and the
@@ -274,6 +285,17 @@ __device__ __forceinline__ void zero_tail_rows(unsigned slice_addr, int first_ro
     addr += 1024u;
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // before the hand-issued fragment reads that follow
+}
+
+// Element offset (inside the K or V cache, before the KV head is added) of key row j of a sequence:
+// page seq_table[j / page size], slot j % page size (paper section 4.1.1).  Sixteen consecutive rows
+// starting at a multiple of 16 always share a page (pages hold 16, 32, 64 or 128 tokens).  Rows past
+// the sequence's last page are never visible; they are redirected to the last page so that whatever
+// lands in LDS for them is ordinary finite cache content.
+__device__ __forceinline__ int64_t kv_row_offset(const XY_CONST int32_t* seq_table, int j, int last_page,
+                                                 const RunParams& p) {
+  const int page = min(j >> p.page_shift, last_page);
+  return (int64_t)seq_table[page] * p.kv_bs + (int64_t)(j & p.page_mask) * p.kv_ts;
 }
 
 // ---- per-lane description of the query rows a wavefront owns -------------------------
@@ -1211,7 +1233,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
 // the card's bandwidth is the bound and 16 KB each are enough, but a wavefront whose neighbours have run out of work waits
 // for memory in every slice, and that is the end of every launch.  8 decodes x 32 KV heads on 2-6k tokens (7.5 tiles per
 // wavefront) 94.8 -> 92.0 us with two; 128 trees on 512-4096 tokens (14 tiles) 153.0 -> 154.7 us, 128 decodes on
-// 2-16k (54 tiles) 553.7 -> 557.2 us, so those keep one.
+// 2-16k (54 tiles) 553.7 -> 557.2 us, so those keep one.  Launches of short units take process_short instead.
 __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit& u,
                                              unsigned char* smem, const LaneOffsets& lo, const DmaOffsets& dof) {
   constexpr int NT = 1;
@@ -1334,10 +1356,81 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
   finish_unit(p, u, c, r, st, col, half);
 }
 
+// A unit of at most 32 rows in a launch of short ones (kShortSlices): one slice at a time, Q straight into registers and
+// no address worked out before its turn.  Such a unit is bound by the instructions of a lone wavefront and by the three
+// round trips to memory that follow each other (record, page table, K/V); what process_solo does on top pays off from the
+// fifth slice on.  512 decodes on 10-32 keys x 8 KV heads (one slice each) 22.5 -> 20.6 us.
+__device__ __forceinline__ void process_short(const RunParams& p, const XyDevUnit& u,
+                                              unsigned char* smem, const LaneOffsets& lo, const DmaOffsets& dof) {
+  constexpr int NT = 1;
+  const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const UnitCtx c = make_ctx(p, u);
+  Rows<NT> r;
+  bf16x8 qf[NT][8];
+  const int rc = min(col, c.rows - 1), tl = rc / c.hc, hl = rc - tl * c.hc;
+  r.valid[0] = col < c.rows;
+  r.tok[0] = u.q_begin + tl;
+  r.lim[0] = r.valid[0] ? c.ctx + r.tok[0] + 1 : 0;
+  const uint16_t* qrow = p.q + (int64_t)(u.token_start + r.tok[0]) * p.q_ts + (int64_t)(u.head_begin + hl) * p.q_hs + 8 * half;
+#pragma unroll
+  for (int ks = 0; ks < 8; ++ks) qf[0][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qrow + 16 * ks));
+  r.mw0[0] = r.mw1[0] = 0;
+  if (c.tree && r.valid[0]) {
+    const uint32_t* mrow = p.masks + u.mask_off + (int64_t)r.tok[0] * c.wpr;
+    r.mw0[0] = mrow[0];
+    if (c.wpr > 1) r.mw1[0] = mrow[1];
+  }
+  const int mask_from = c.tree ? c.ctx : c.ctx + u.q_begin + 1;
+  UnitState st;
+  zero_state<NT>(st.oacc, st.m_ref, st.l_part);
+  const XY_CONST int32_t* table = as_const(p.block_table) + (int64_t)u.seq * p.max_blocks;
+  const int last_page = (u.ctx_len + u.q_len - 1) >> p.page_shift;
+  const int64_t head_off = (int64_t)c.kvh * p.kv_hs;
+  const int jfirst = u.kv_begin * kB;
+  const int nsteps = (min(u.kv_end * kB, c.key_end) - jfirst + 31) >> 5;
+  unsigned char* ring = smem + wave * 32768;        // [K slot | V slot]
+  const unsigned kaddr = lds_addr(ring), vaddr = kaddr + 8192;
+  auto load_slice = [&](const int j, const bool want_k, const bool want_v) {      // eight instructions per tensor
+    const int64_t b0 = kv_row_offset(table, j, last_page, p) + head_off;
+    const int64_t b1 = kv_row_offset(table, j + 16, last_page, p) + head_off;
+    load_rows_async<4>(p.k + b0, p.v + b0, p.kv_ts, 0, ring, ring + 8192, dof, want_k, want_v);
+    load_rows_async<4>(p.k + b1, p.v + b1, p.kv_ts, 0, ring + 4096, ring + 8192 + 4096, dof, want_k, want_v);
+  };
+  load_slice(jfirst, true, false);          // issue order K, V
+  load_slice(jfirst, false, true);
+#pragma unroll 1
+  for (int t = 0; t < nsteps; ++t) {
+    wait_vmcnt<8>();                          // K(t) has landed; only V(t) may still be in flight
+    f32x16 s[NT];
+    VFrags vf;
+    qk_step<NT>(kaddr, lo, qf, s);            // all K reads have completed when this returns
+    const int tn = t + 1;
+    if (tn < nsteps) {        // K slot is free again: refill it with the next slice
+      load_slice(jfirst + 32 * tn, true, false);
+      wait_vmcnt<8>();        // V(t) has landed; the K refill stays in flight
+    } else {
+      wait_vmcnt<0>();
+      const int last_keys = min(u.kv_end * kB, c.key_end) - jfirst - 32 * t;      // keys of the last step: 1 .. 32
+      if (last_keys < 32) zero_tail_rows(vaddr, last_keys, lane);
+    }
+    v_fetch<0>(vaddr, lo, vf);                // the first V fragments arrive while the softmax runs
+    const int j = jfirst + 32 * t;
+    if (j + 32 > mask_from) mask_step<NT>(p, c, r, j + 8 * half, s);
+    softmax_step<NT>(p.c, s, st.m_ref, st.l_part, st.oacc);
+    pv_step<NT>(vaddr, lo, vf, s, st.oacc);   // all V reads have completed when this returns
+    if (tn < nsteps) load_slice(jfirst + 32 * tn, false, true);
+  }
+  finish_unit(p, u, c, r, st, col, half);
+}
+
 // Every workgroup is one worker of the Task-Table (paper section 3.3).  It first works through the
 // wide units of its list together, then its four wavefronts draw the remaining (bandwidth-bound)
 // units of the same list one by one from a shared cursor, each wavefront finishing whole units
 // on its own.
+// SHORT: how its units of at most 32 rows are processed (kShortSlices); a kernel for each, since the two in one disturb each
+// other's registers (short units 3 to 5 %, launches on two slices up to 2 %).
+template <bool SHORT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void xy_attn_units_kernel(RunParams p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kTileBytes];
   __shared__ int cursor, first_draw;
@@ -1385,7 +1478,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     if (i >= end) break;
     const XyDevUnit u = load_unit(pn.units + i);
     if (u.q_count * u.head_count > 32) continue;
-    process_solo(pn, u, smem, lo, dof);
+    if (SHORT) process_short(pn, u, smem, lo, dof);
+    else process_solo(pn, u, smem, lo, dof);
   }
   if (pn.counters) {
     // The shared list of narrow units (dynamic assignment): every wavefront of every workgroup draws the
@@ -1412,7 +1506,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
       const int i = shared_begin + next;
       if (i >= pn.num_units) break;
       const XyDevUnit u = load_unit(pn.units + i);
-      process_solo(pn, u, smem, lo, dof);
+      if (SHORT) process_short(pn, u, smem, lo, dof);
+      else process_solo(pn, u, smem, lo, dof);
       if (!any_left) break;
       int got = 0;
       if ((threadIdx.x & 63) == 0) got = slots + atomicAdd(pn.counters, 1);
@@ -1583,11 +1678,9 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
   unsigned char* h = static_cast<unsigned char*>(plan->h_stage);
   XyDevUnit* du = reinterpret_cast<XyDevUnit*>(h + off_units);
   const int32_t group = plan->cfg.num_q_heads / plan->cfg.num_kv_heads;
-  plan->narrow_tiles = 0;
   for (size_t i = 0; i < plan->units.size(); ++i) {
     const xy_work_unit& u = plan->units[i];
     const xy_seq_desc& sd = plan->descs[u.seq];
-    if (u.q_count * u.head_count <= 32) plan->narrow_tiles += u.kv_block_end - u.kv_block_begin;
     du[i] = XyDevUnit{u.seq, u.head_begin, u.head_count, u.q_begin, u.q_count,
                       u.kv_block_begin, u.kv_block_end, u.kind_flags, u.ws_offset, sd.mask_word_offset,
                       sd.query_len, sd.context_len, plan->token_start[u.seq], u.head_begin / group};
@@ -1697,12 +1790,17 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
   p.num_workers = plan->cfg.num_workers;
   p.free_workers = plan->free_workers;
   p.num_units = (int32_t)plan->units.size();
-  p.narrow_depth = plan->narrow_tiles <= kDeepTiles * (kThreads / 64) * plan->cfg.num_workers ? 2 : 1;
+  const int64_t wavefronts = (int64_t)(kThreads / 64) * plan->cfg.num_workers;
+  const int64_t short_slices = plan->narrow_rows > kManyRows * plan->narrow_units ? kShortSlicesManyRows
+                               : plan->narrow_units > wavefronts ? kShortSlicesManyUnits : kShortSlices;
+  const bool short_units = plan->narrow_units > 0 && plan->narrow_slices <= short_slices * plan->narrow_units;
+  p.narrow_depth = plan->narrow_tiles <= kDeepTiles * wavefronts ? 2 : 1;
   p.counters = static_cast<int32_t*>(plan->d_counters);
   p.c = softmax_scale * 1.4426950408889634f;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (phases & XY_PHASE_UNITS) {
-    hipLaunchKernelGGL(xy_attn_units_kernel, dim3(plan->cfg.num_workers), dim3(kThreads), 0, stream, p);
+    if (short_units) hipLaunchKernelGGL(xy_attn_units_kernel<true>, dim3(plan->cfg.num_workers), dim3(kThreads), 0, stream, p);
+    else hipLaunchKernelGGL(xy_attn_units_kernel<false>, dim3(plan->cfg.num_workers), dim3(kThreads), 0, stream, p);
     if (hipGetLastError() != hipSuccess) return XY_ERR_HIP;
   }
   if ((phases & XY_PHASE_MERGE) && !plan->merges.empty()) {

@@ -24,7 +24,7 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Units visit K/V in tiles of 128 keys (the kernel's tile); a tile is 128 / block_size consecutive
 // entries of the sequence's block-table row.
-constexpr int64_t kKvTile = 128;
+constexpr int64_t kKvTile = 128, kKvSlice = 32;
 // XY_SPLIT_AUTO: units of at most kNarrowRows rows are processed one per wavefront, kNarrowSlotsPerWorker
 // wavefronts per worker (the unit kernel's workgroup size / 64)
 constexpr int64_t kNarrowRows = 32;
@@ -268,6 +268,7 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
     plan->merges.clear();
     plan->workspace_floats = 0;
     plan->has_tree = false;
+    plan->narrow_units = plan->narrow_rows = plan->narrow_tiles = plan->narrow_slices = 0;
 
     // --- size of the K/V split (see XY_SPLIT_AUTO) ---------------------------
     int32_t split_narrow = c.split_kv_blocks, split_wide = c.split_kv_blocks;
@@ -410,6 +411,12 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         const int64_t slab = slab_floats(rows, D);   // keeps every partial 16-byte aligned
         // piece p covers tiles [floor(p nb / k), floor((p + 1) nb / k)): walked with a running remainder
         const int32_t whole = nb / k, rest = nb % k;
+        if (rows <= kNarrowRows) {
+          plan->narrow_units += (int64_t)k * head_groups;
+          plan->narrow_rows += (int64_t)k * head_groups * rows;
+          plan->narrow_tiles += (int64_t)nb * head_groups;
+          plan->narrow_slices += ceil_div(last_excl, kKvSlice) * head_groups;      // (pieces end at whole tiles)
+        }
         const int64_t unit_rows = std::max<int64_t>(rows, c.cost_row_floor);
         const size_t at = fam.size();
         fam.resize(at + (size_t)k * head_groups);

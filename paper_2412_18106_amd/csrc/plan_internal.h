@@ -58,7 +58,7 @@ struct xy_attn_plan {
   int64_t workspace_floats = 0;
   int64_t merge_groups = 0;                 // workgroups of the merge pass (of the tables last copied to the GPU)
   int32_t free_workers = 0;                 // workers without units of their own (of the tables last copied to the GPU)
-  int64_t narrow_tiles = 0;                 // K/V tiles of the units of at most 32 rows (of the tables last copied to the GPU)
+  int64_t narrow_units = 0, narrow_rows = 0, narrow_tiles = 0, narrow_slices = 0;     // units of at most 32 rows, their rows, K/V tiles and 32-key slices
   bool has_tree = false;
   XyPlanScratch scratch;
   // Device copy of the tables (owned): one arena on one device and a pinned staging buffer of the same size,

@@ -116,13 +116,13 @@ def test_wide_units_far_strides_of_q_and_out(gpu, dim):
 
 @pytest.mark.parametrize("hq,hkv,tokens", [(1, 1, 1), (4, 1, 1), (3, 1, 2), (5, 1, 6), (8, 1, 4), (31, 1, 1), (32, 1, 1), (4, 2, 3)])
 def test_narrow_units_of_few_slices(gpu, hq, hkv, tokens):
-    """A narrow unit keeps one or two 32-key slices in flight (two up to ten tiles per wavefront of the launch), Q waits
-    where the second one's V comes to lie: units of one, two and three slices, ends inside a slice and right at one, rows
-    from one to 32 in groups of four; the last batch has more than ten tiles for each wavefront of its one worker."""
+    """Narrow units of one, two, three and more 32-key slices, ends inside a slice and right at one, rows from one to 32 in
+    groups of four; whole, cut, and three times as many through one worker (the ways a launch can take are in
+    test_ways_of_processing_narrow_units)."""
     specs = [W.SeqSpec(tokens, max(0, keys - tokens), V) for keys in (tokens, 31, 32, 33, 63, 64, 65, 95, 96, 97, 129, 200, 300)]
     run_and_check(gpu, W.make_custom(specs, hq, hkv, 11 * hq + tokens), f"{hq}/{hkv} heads, {tokens} tokens", split_kv_blocks=0)
     run_and_check(gpu, W.make_custom(specs, hq, hkv, 12 * hq + tokens), f"{hq}/{hkv} heads, {tokens} tokens, split", split_kv_blocks=1)
-    run_and_check(gpu, W.make_custom(specs * 3, hq, hkv, 13 * hq + tokens), f"{hq}/{hkv} heads, {tokens} tokens, one slice",
+    run_and_check(gpu, W.make_custom(specs * 3, hq, hkv, 13 * hq + tokens), f"{hq}/{hkv} heads, {tokens} tokens, one worker",
                   split_kv_blocks=0, num_workers=1)
 
 
@@ -213,3 +213,34 @@ def test_merge_pass_of_more_workgroups_than_one_launch_takes(gpu):
     err = (out[0].float() - ref).abs()
     assert float(err.max()) <= MAX_ABS and float(err.mean()) <= MEAN_ABS      # (a NaN fails both)
     assert all(torch.equal(out[i], out[0]) for i in range(1, n))
+
+
+@pytest.mark.parametrize("hq,hkv,tokens", [(1, 1, 1), (4, 1, 1), (5, 1, 6), (8, 1, 4), (4, 2, 8), (32, 1, 1)])
+@pytest.mark.parametrize("way", ["short", "two slices", "one slice"])
+def test_ways_of_processing_narrow_units(gpu, way, hq, hkv, tokens):
+    """Units of at most 32 rows are processed in one of three ways, by the average slices (32 keys) of a unit, the number of
+    units and their tiles (128 keys) per wavefront: up to four slices (eight where units outnumber the wavefronts, two
+    where they have more than 16 rows) short, else two slices in flight up to ten tiles a wavefront, else one.  Chains and trees that end inside a slice and right
+    at one, with a few long ones that move the averages; through the shared list and through the workers' own lists."""
+    tree = W.random_tree(np.random.default_rng(tokens), tokens)
+    most = 70 if way == "short" and tokens * (hq // hkv) > 16 else 200
+    specs = [W.SeqSpec(tokens, max(0, keys - tokens), V) for keys in (tokens, 31, 32, 33, 64, 95, 96, 97, 129, 200) if keys <= most]
+    specs += [W.SeqSpec(tokens, keys - tokens, V, W.MASK_TREE, tree) for keys in (40, 64, 97, 160) if keys <= most]
+    if way != "short":
+        specs += [W.SeqSpec(tokens, keys - tokens, V) for keys in (1500, 1600, 1679, 1697)]
+    workers = 1 if way == "one slice" else 64
+    b = W.make_custom(specs, hq, hkv, 17 * hq + tokens)
+
+    def plan_check(units, _offs, _merges):
+        n = len(units)
+        assert int((units["q_count"] * units["head_count"]).max()) <= 32
+        ends = [sum(b.seqs[u["seq"]][:2]) if b.seqs[u["seq"]][3] else b.seqs[u["seq"]][1] + u["q_begin"] + u["q_count"] for u in units]
+        slices = sum(-(-(min(128 * u["kv_block_end"], e) - 128 * u["kv_block_begin"]) // 32) for u, e in zip(units, ends))
+        tiles = int((units["kv_block_end"] - units["kv_block_begin"]).sum())
+        many_rows = int((units["q_count"] * units["head_count"]).sum()) > 16 * n
+        if slices <= (2 if many_rows else 8 if n > 4 * workers else 4) * n:
+            assert way == "short"
+        else:
+            assert way == ("two slices" if tiles <= 40 * workers else "one slice")
+    for policy in (1, 2):
+        run_and_check(gpu, b, f"{way}, policy {policy}", plan_check, split_kv_blocks=0, num_workers=workers, assign_policy=policy)

@@ -72,7 +72,7 @@ typedef struct {
                                      sequence (see XY_TILE_AUTO)                             */
   int32_t split_kv_blocks;        /* a DECODE / VERIFY unit visiting more 128-key K/V tiles than this
                                      is split along K/V; 0 = never; XY_SPLIT_AUTO = chosen per
-                                     batch (see XY_SPLIT_AUTO)                                */
+                                     batch, PREFILL units included (see XY_SPLIT_AUTO)        */
   int32_t cost_row_floor;         /* load = max(rows, floor) * tiles; 1 = the paper's
                                      tileSize x kvLen (section 3.3.1) in units of 128 keys   */
   int32_t assign_policy;          /* XY_ASSIGN_SNAKE: the paper's symmetric round-robin over the
@@ -114,7 +114,8 @@ typedef struct {
  *    2 N < M (num_workers - U), N the summed load max(rows, cost_row_floor) x nb of the families of at most 32 rows,
  *    M the largest load of a wide family, R its largest max(rows, cost_row_floor)): T is the smallest size from
  *    ceil(B / (num_workers R)), B = R sum nb + floor(N / 2), on at which they make at most
- *    ceil((num_workers + ceil(num_workers R sum nb / B)) / 2) pieces (others have the narrow work), a family being cut at max(T, m), m = min(8, max(2, ceil(nb / 4))), and whole where nb <= 4 (a piece costs about two and a half
+ *    ceil((num_workers + ceil(num_workers R sum nb / B)) / 2) pieces (others have the narrow work), a family being cut
+ *    at max(T, m), m = min(8, max(2, ceil(nb / 4))), and whole where nb <= 4 (a piece costs about two and a half
  *    tiles' time around its loop, the merge pass two more); T is then raised to the longest family that stays
  *    whole.
  *  - 2 U > num_workers and the longest costs more than a quarter of a worker's mean load: of the sizes that make at most
@@ -137,7 +138,9 @@ enum { XY_ASSIGN_SNAKE = 0, XY_ASSIGN_LEAST_LOADED = 1, XY_ASSIGN_DYNAMIC = 2 };
  * by summed load descending (ties: sequence, KV head ascending), go to the chiplet with the smallest load so far
  * (lowest index among equals); a unit goes to the least-loaded worker of its group's chiplet.  If the heaviest
  * chiplet ends more than 3 % above the mean load (max * 8 * 100 > total * 103) no groups are used and every
- * unit goes to the least-loaded worker overall. */
+ * unit goes to the least-loaded worker overall; nor are they with at most 2 num_workers such units where the largest
+ * load of a worker with the groups is more than 3 % above the largest without (largest * 100 > other * 103): chiplets
+ * that are level in load need not be level in units, and on a short list one unit more is most of the launch. */
 /* rows = tile tokens x heads per unit must be <= 256 for every kind. */
 
 /* One tiling unit (section 3.2.1) placed in the Task-Table (section 3.3.1). */
@@ -158,7 +161,10 @@ typedef struct {
  * (section 4.2.1, the Update stage's running max / sum, applied across units). */
 typedef struct {
   int32_t seq, head_begin, head_count, q_begin, q_count, num_splits;
-  int64_t ws_offset;              /* slab base: num_splits x [rows x head_dim acc | rows m | rows l] fp32 */
+  int64_t ws_offset;              /* slab base: num_splits slabs of fp32, each [head_dim / 4][rows][4] accumulators
+                                     (element d of row r at (d / 4 * rows + r) * 4 + d % 4), then rows references m
+                                     (log2 units, -inf: no visible key), then rows sums l, rounded up to a multiple
+                                     of 4; row r = token * head_count + head, acc and l relative to 2^m */
 } xy_merge_item;
 
 typedef struct xy_attn_plan xy_attn_plan; /* opaque, library-owned */

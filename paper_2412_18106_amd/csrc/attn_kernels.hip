@@ -681,12 +681,13 @@ __device__ __forceinline__ void scale_acc(f32x16& acc, const float alpha) {
 // and the PV MFMAs of step t - 1, as sixteen chunks of two MFMAs (one per row tile, sharing the chunk's
 // K or V fragment) with a few vector instructions and one LDS request behind each MFMA.
 // PRESCALE: Q carries the factor c = scale x log2(e), see the softmax notes inside.
-template <int NT, bool PRESCALE, bool ROWS_CONTIGUOUS>
+template <bool PRESCALE, bool ROWS_CONTIGUOUS>
 // force: the second pass over a unit whose optimistic pass overflowed (exact prefix in every iteration).  Returns
 // whether the unit has to be run again that way (only when force is false; nothing has been written then).
 __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit& u,
                                              unsigned char* smem, int* overflow_flags, const bool force,
                                              const LaneOffsets& lo, const DmaOffsets& dof) {
+  constexpr int NT = 2;      // row tiles of a wavefront; the gap tables below are made for two
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const UnitCtx c = make_ctx(p, u);
@@ -695,7 +696,6 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   const float inv_hc = __builtin_amdgcn_rcpf((float)c.hc);
   bf16x8 qf[NT][8];
   const int mask_from = c.tree ? c.ctx : c.ctx + u.q_begin + row_base / c.hc + 1;
-  const XY_CONST int32_t* table = as_const(p.block_table) + (int64_t)u.seq * p.max_blocks;
   const int last_page = (u.ctx_len + u.q_len - 1) >> p.page_shift;
   const int64_t head_off = (int64_t)c.kvh * p.kv_hs;
   const int jfirst = u.kv_begin * kB;
@@ -1454,11 +1454,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     // tolerance, with a scale so large that scores reach tens of log2 units it is not, and c stays in fp32.
     bool again;
     if (p.kv_ts == kD) {
-      if (p.c <= kPrescaleMaxC) again = process_wide<2, true, true>(p, u, smem, overflow_flags, force, lo, dof);
-      else again = process_wide<2, false, true>(p, u, smem, overflow_flags, force, lo, dof);
+      if (p.c <= kPrescaleMaxC) again = process_wide<true, true>(p, u, smem, overflow_flags, force, lo, dof);
+      else again = process_wide<false, true>(p, u, smem, overflow_flags, force, lo, dof);
     } else {
-      if (p.c <= kPrescaleMaxC) again = process_wide<2, true, false>(p, u, smem, overflow_flags, force, lo, dof);
-      else again = process_wide<2, false, false>(p, u, smem, overflow_flags, force, lo, dof);
+      if (p.c <= kPrescaleMaxC) again = process_wide<true, false>(p, u, smem, overflow_flags, force, lo, dof);
+      else again = process_wide<false, false>(p, u, smem, overflow_flags, force, lo, dof);
     }
     force = again;              // wavefront- and workgroup-uniform
     if (!again) ++i;

@@ -53,6 +53,20 @@ def test_partial_results_stay_within_the_library_workspace():
     compare(cfg, seqs)
 
 
+@pytest.mark.parametrize("heavy,counts", [(1030, [2, 1] * 8), (1031, [1] * 3 + [2] * 8 + [1] * 5)])
+def test_chiplet_groups_of_a_short_list_are_dropped_for_a_level_list(heavy, counts):
+    # Sixteen workers, two per chiplet; eight groups of three equal units (three heads of one KV head), seven groups of
+    # 1000 tiles a unit and one of `heavy`.  By chiplet a worker has two units: at most 2 heavy.  Without, the three
+    # heavy units have a worker each and no worker more than 2000.  2060 * 100 = 2000 * 103: kept; 2062: dropped.  The
+    # chiplets are within 3 % of their mean both times (1031: 3093 * 800 = 2474400 <= (3093 + 21000) * 103 = 2481579).
+    cfg = X.xy_attn_default_config(3, 1, 1031, num_workers=16, prefill_heads_per_unit=1, prefill_tile_tokens=128,
+                                   split_kv_blocks=0, cost_row_floor=1, assign_policy=1)
+    seqs = [(128, 128 * (heavy - 1), X.XY_PREFILL, 0, 0)] + [(128, 128 * 999, X.XY_PREFILL, 0, 0)] * 7
+    compare(cfg, seqs)
+    offs = PL.plan_oracle(cfg.as_dict(), seqs)[1]
+    assert [int(offs[w + 1] - offs[w]) for w in range(16)] == counts
+
+
 @pytest.mark.parametrize("floor", [128, 2**31 - 1])
 @pytest.mark.parametrize("families", [1, 11, 21, 40])
 def test_loads_beyond_64_bits_times_the_workers(floor, families):

@@ -67,6 +67,8 @@ constexpr int64_t kDeepTiles = 10;
 constexpr float kPrescaleMaxC = 0.25f;    // largest c = scale * log2(e) that is folded into Q (wide units)
 // Dynamic assignment: the cursor of the shared list, kDoneGroups counts of finished workgroups and the
 // count of finished groups, kCounterStride ints (one 128-byte line) apart.
+// XyDevUnit::flags: kind and mask in the low bits; rows of the family's partial results, the unit's first row among them
+constexpr int kSlabRowsShift = 8, kSlabFirstShift = 20;
 constexpr int kDoneGroups = 8;
 constexpr int kCounterStride = 32;
 constexpr float kLazyRescale = 8.0f;      // log2 units the running max may lag behind
@@ -76,6 +78,10 @@ constexpr float kLazyRescale = 8.0f;      // log2 units the running max may lag 
 #define XY_GAP_TABLE_EXP {0, 2, 4, 5, 6, 7, 8, 10, 11, 12, 13, 14, 14, 15, 16, 17, 18, 19, 21, 22, 22, 22, 24, 25, 26, 27, 28, 30, 30, 31, 32, 32, 32}
 #define XY_GAP_TABLE_CVT {0, 0, 0, 1, 1, 2, 3, 3, 3, 4, 5, 5, 5, 6, 7, 7, 8, 8, 8, 9, 9, 10, 10, 10, 11, 12, 13, 13, 13, 14, 15, 16, 16}
 #define XY_GAP_TABLE_ADD {0, 0, 1, 2, 2, 3, 5, 5, 7, 7, 9, 10, 11, 11, 13, 14, 15, 16, 17, 17, 18, 19, 20, 21, 22, 23, 25, 25, 26, 27, 29, 32, 32}
+// the same for a wavefront of one row tile: 16 gaps, 16 exponentials, 8 packings, 16 additions
+#define XY_GAP_TABLE_ONE_EXP {0, 3, 4, 6, 7, 8, 8, 10, 10, 12, 12, 13, 14, 16, 16, 16, 16}
+#define XY_GAP_TABLE_ONE_CVT {0, 0, 0, 1, 2, 3, 3, 3, 4, 4, 4, 5, 5, 6, 6, 8, 8}
+#define XY_GAP_TABLE_ONE_ADD {0, 0, 1, 2, 3, 5, 5, 5, 7, 8, 8, 9, 10, 11, 12, 15, 16}
 constexpr float kRowSumLimit = 18446744073709551616.f;      // 2^64: a wide unit whose row sums stay below was computed without overflow
 
 struct RunParams {
@@ -681,13 +687,28 @@ __device__ __forceinline__ void scale_acc(f32x16& acc, const float alpha) {
 // and the PV MFMAs of step t - 1, as sixteen chunks of two MFMAs (one per row tile, sharing the chunk's
 // K or V fragment) with a few vector instructions and one LDS request behind each MFMA.
 // PRESCALE: Q carries the factor c = scale x log2(e), see the softmax notes inside.
-template <bool PRESCALE, bool ROWS_CONTIGUOUS>
+// NT: row tiles of a wavefront, two as described, or one, where no unit of the launch has more than 128 rows: with two
+// such a unit leaves two of the four wavefronts without rows.  One tile means half the MFMAs, exponentials and rows to
+// load and store per wavefront and the same LDS requests, so a step takes 0.38 us instead of 0.58 (124 rows, 8 units
+// alone), and what stands around the loop 7.7 us instead of 9.9; 248 of them on 1 / 4 / 16 tiles 15.2 / 24.8 / 56.3 ->
+// 12.7 / 20.4 / 45.2 us, the last at 5.8 TB/s; four trees of 31 tokens on 10-20k keys, with merge pass, 64.6 -> 60.7 us.
+// K fragments asked for eight chunks ahead instead of four changed nothing.
+template <int NT>
+struct GapTables;
+template <>
+struct GapTables<2> {
+  static constexpr int kExp[33] = XY_GAP_TABLE_EXP, kCvt[33] = XY_GAP_TABLE_CVT, kAdd[33] = XY_GAP_TABLE_ADD;
+};
+template <>
+struct GapTables<1> {
+  static constexpr int kExp[17] = XY_GAP_TABLE_ONE_EXP, kCvt[17] = XY_GAP_TABLE_ONE_CVT, kAdd[17] = XY_GAP_TABLE_ONE_ADD;
+};
+template <bool PRESCALE, bool ROWS_CONTIGUOUS, int NT>
 // force: the second pass over a unit whose optimistic pass overflowed (exact prefix in every iteration).  Returns
 // whether the unit has to be run again that way (only when force is false; nothing has been written then).
 __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit& u,
                                              unsigned char* smem, int* overflow_flags, const bool force,
                                              const LaneOffsets& lo, const DmaOffsets& dof) {
-  constexpr int NT = 2;      // row tiles of a wavefront; the gap tables below are made for two
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const UnitCtx c = make_ctx(p, u);
@@ -699,7 +720,9 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   const int last_page = (u.ctx_len + u.q_len - 1) >> p.page_shift;
   const int64_t head_off = (int64_t)c.kvh * p.kv_hs;
   const int jfirst = u.kv_begin * kB;
-  const int nsteps = (min(u.kv_end * kB, c.key_end) - jfirst + 31) >> 5;
+  // (the first half of a unit's tokens may see nothing of the last piece: one step then, in which nothing is visible)
+  const int key_end = NT == 1 ? max(c.key_end, jfirst + 1) : c.key_end;
+  const int nsteps = (min(u.kv_end * kB, key_end) - jfirst + 31) >> 5;
   const float cs = p.c;
 
   // ---- softmax with the reference folded into the MFMA ------------------------------------------------
@@ -1012,9 +1035,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
     // anyway (LDS requests, waits, the K/V loads): about 24 cycles in every gap.  Scheduling barriers keep the
     // compiler from moving work between gaps.  The tables count, gap by gap, how many of the 32 exponentials,
     // 16 packings and 32 row-sum additions are done before that gap.
-    constexpr int kExp[33] = XY_GAP_TABLE_EXP;
-    constexpr int kCvt[33] = XY_GAP_TABLE_CVT;
-    constexpr int kAdd[33] = XY_GAP_TABLE_ADD;
+    typedef GapTables<NT> Gaps;
     auto exp_one = [&](const int j) {          // score j & 15 of row tile j >> 4
       e[j] = __builtin_amdgcn_exp2f(PRESCALE ? s_in[j >> 4][j & 15] : s_in[j >> 4][j & 15] * cs);
     };
@@ -1028,11 +1049,11 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
     };
     auto gap_work = [&](const int k) {
 #pragma unroll
-      for (int j = kExp[k]; j < kExp[k + 1]; ++j) exp_one(j);
+      for (int j = Gaps::kExp[k]; j < Gaps::kExp[k + 1]; ++j) exp_one(j);
 #pragma unroll
-      for (int g = kCvt[k]; g < kCvt[k + 1]; ++g) cvt_one(g);
+      for (int g = Gaps::kCvt[k]; g < Gaps::kCvt[k + 1]; ++g) cvt_one(g);
 #pragma unroll
-      for (int j = kAdd[k]; j < kAdd[k + 1]; ++j) add_one(j);
+      for (int j = Gaps::kAdd[k]; j < Gaps::kAdd[k + 1]; ++j) add_one(j);
     };
 #pragma unroll
     for (int ch = 0; ch < 16; ++ch) {
@@ -1082,7 +1103,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   bool exact = true;
   if (active) {
     // iteration 0 multiplies V of step 0 already (by zeros, see below): cleared first where that is the last step
-    if (nsteps == 1) zero_tail_rows(k_slice(0) + 16384, min(u.kv_end * kB, c.key_end) - jfirst, lane);
+    if (nsteps == 1) zero_tail_rows(k_slice(0) + 16384, min(u.kv_end * kB, key_end) - jfirst, lane);
     // S^T of step 0 against reference 0, then iteration 0 (exact prefix, no previous step)
 #pragma unroll
     for (int i = 0; i < 8; ++i) request_k(k_slice(0), i);
@@ -1142,7 +1163,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   if (active) {                 // PV of the last step
     lds_wait1<0>(kf[0]); lds_wait1<0>(kf[1]); lds_wait1<0>(kf[2]); lds_wait1<0>(kf[3]);
     const unsigned vaddr = k_slice(nsteps - 1) + 16384;
-    const int last_keys = min(u.kv_end * kB, c.key_end) - jfirst - 32 * (nsteps - 1);     // keys of the last step: 1 .. 32
+    const int last_keys = min(u.kv_end * kB, key_end) - jfirst - 32 * (nsteps - 1);     // keys of the last step: 1 .. 32
     if (last_keys < 32) zero_tail_rows(vaddr, last_keys, lane);
     bf16x8 p_last[NT][2];
 #pragma unroll
@@ -1190,7 +1211,8 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   if (u.ws_offset >= 0) {
 #pragma unroll
     for (int rt = 0; rt < NT; ++rt)
-      store_partial(p, u, c.rows, row_base + 32 * rt + col, r.valid[rt], half, oacc[rt],
+      store_partial(p, u, NT == 1 ? (u.flags >> kSlabRowsShift) & 0xfff : c.rows,       // the unit may be a half of its family
+                    (NT == 1 ? u.flags >> kSlabFirstShift : 0) + row_base + 32 * rt + col, r.valid[rt], half, oacc[rt],
                     m_ref[rt] == -INFINITY ? -INFINITY : m_ref[rt] * u2l, l_tot[rt]);
     return false;
   }
@@ -1430,7 +1452,8 @@ __device__ __forceinline__ void process_short(const RunParams& p, const XyDevUni
 // on its own.
 // SHORT: how its units of at most 32 rows are processed (kShortSlices); a kernel for each, since the two in one disturb each
 // other's registers (short units 3 to 5 %, launches on two slices up to 2 %).
-template <bool SHORT>
+// NT: row tiles of a wavefront on its wide units (process_wide).
+template <bool SHORT, int NT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void xy_attn_units_kernel(RunParams p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kTileBytes];
   __shared__ int cursor, first_draw;
@@ -1454,11 +1477,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     // tolerance, with a scale so large that scores reach tens of log2 units it is not, and c stays in fp32.
     bool again;
     if (p.kv_ts == kD) {
-      if (p.c <= kPrescaleMaxC) again = process_wide<true, true>(p, u, smem, overflow_flags, force, lo, dof);
-      else again = process_wide<false, true>(p, u, smem, overflow_flags, force, lo, dof);
+      if (p.c <= kPrescaleMaxC) again = process_wide<true, true, NT>(p, u, smem, overflow_flags, force, lo, dof);
+      else again = process_wide<false, true, NT>(p, u, smem, overflow_flags, force, lo, dof);
     } else {
-      if (p.c <= kPrescaleMaxC) again = process_wide<true, false>(p, u, smem, overflow_flags, force, lo, dof);
-      else again = process_wide<false, false>(p, u, smem, overflow_flags, force, lo, dof);
+      if (p.c <= kPrescaleMaxC) again = process_wide<true, false, NT>(p, u, smem, overflow_flags, force, lo, dof);
+      else again = process_wide<false, false, NT>(p, u, smem, overflow_flags, force, lo, dof);
     }
     force = again;              // wavefront- and workgroup-uniform
     if (!again) ++i;
@@ -1640,14 +1663,42 @@ __global__ __launch_bounds__(256) void xy_plan_copy_kernel(const uint4* __restri
   if (i < chunks) dst[i] = src[i];
 }
 
+// Units of more than kHalfRows rows that go to the GPU as two, by their tokens, for a worker each: all of them or none.
+// The kernel then holds one row tile a wavefront instead of two, which takes two thirds of the time for units
+// that are alone (64 tokens x 4 heads on 1 / 4 / 16 K/V tiles, 8 units: 12.6 / 19.6 / 47.5 -> 9.1 / 13.6 / 32.9 us), but
+// reads the K/V twice and keeps two workers busy: only where there are idle workers for all second halves, with a
+// wavefront left for every narrow unit (a suffix of 150-250 tokens beside 472 narrow units 254.9 -> 266.0 us for eight layers
+// and a chunk of 512 beside 1184 157 -> 164 us where there is not).  The plan the caller sees stays as it is.
+constexpr int32_t kHalfRows = 128, kXcds = 8;
+static int32_t first_half(const xy_work_unit& u) { return (u.q_count + 1) / 2; }
+static int64_t units_to_halve(const xy_attn_plan* plan) {
+  if (plan->units.empty()) return 0;
+  const int32_t W = plan->cfg.num_workers;
+  int64_t halved = 0;
+  int32_t idle = 0;
+  for (int32_t w = 0; w < W; ++w) {
+    idle += plan->worker_offsets[w] == plan->worker_offsets[w + 1];
+    for (int32_t i = plan->worker_offsets[w]; i < plan->worker_offsets[w + 1]; ++i) {
+      const xy_work_unit& u = plan->units[i];
+      if (u.q_count * u.head_count > kHalfRows) {
+        if (first_half(u) * u.head_count > kHalfRows) return 0;
+        ++halved;
+      }
+    }
+  }
+  return halved <= idle && plan->narrow_units <= (int64_t)(kThreads / 64) * (idle - halved) ? halved : 0;
+}
+
 static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return XY_ERR_HIP;
   if (plan->device >= 0 && plan->device != dev) return XY_ERR_ARG;      // the plan lives on another device
   auto round_up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const bool shared_list = plan->worker_offsets.back() < (int64_t)plan->units.size();
+  const int64_t halved = units_to_halve(plan);
+  const size_t num_units = plan->units.size() + halved;
   const size_t off_units = 0;
-  const size_t off_offsets = off_units + round_up(plan->units.size() * sizeof(XyDevUnit));
+  const size_t off_offsets = off_units + round_up(num_units * sizeof(XyDevUnit));
   const size_t off_seqs = off_offsets + round_up(2 * plan->worker_offsets.size() * sizeof(int32_t));
   const size_t off_merges = off_seqs + round_up((size_t)plan->num_seqs * sizeof(XyDevSeq));
   int64_t merge_groups = 0;       // workgroups of the merge pass
@@ -1678,19 +1729,59 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
   unsigned char* h = static_cast<unsigned char*>(plan->h_stage);
   XyDevUnit* du = reinterpret_cast<XyDevUnit*>(h + off_units);
   const int32_t group = plan->cfg.num_q_heads / plan->cfg.num_kv_heads;
-  for (size_t i = 0; i < plan->units.size(); ++i) {
-    const xy_work_unit& u = plan->units[i];
-    const xy_seq_desc& sd = plan->descs[u.seq];
-    du[i] = XyDevUnit{u.seq, u.head_begin, u.head_count, u.q_begin, u.q_count,
-                      u.kv_block_begin, u.kv_block_end, u.kind_flags, u.ws_offset, sd.mask_word_offset,
-                      sd.query_len, sd.context_len, plan->token_start[u.seq], u.head_begin / group};
-  }
-  memcpy(h + off_offsets, plan->worker_offsets.data(), plan->worker_offsets.size() * sizeof(int32_t));
+  const int32_t W = (int32_t)plan->worker_offsets.size() - 1;
+  int32_t* const offsets = reinterpret_cast<int32_t*>(h + off_offsets);
   // behind the offsets: a worker's number among the workers that have no units of their own, -1 where it has some
-  int32_t* rank = reinterpret_cast<int32_t*>(h + off_offsets) + plan->worker_offsets.size();
+  int32_t* const rank = offsets + W + 1;
+  std::vector<int32_t>& second_of = plan->scratch.cursor;      // worker -> the unit whose second half it gets, or -1
+  if (halved) {
+    second_of.assign(W, -1);                                    // (the planner left room for W)
+    // the second half goes to an idle worker of the same chiplet if there is one: both read the same K/V
+    const int32_t per_chip = W % kXcds == 0 ? W / kXcds : W;
+    std::vector<int32_t>& idle = plan->scratch.count;           // the next worker to look at, per chiplet
+    idle.assign(W / per_chip, 0);
+    auto next_idle = [&](const int32_t chip) {
+      for (int32_t& at = idle[chip]; at < per_chip; ++at) {
+        const int32_t w = chip * per_chip + at;
+        if (plan->worker_offsets[w] == plan->worker_offsets[w + 1] && second_of[w] < 0) return w;
+      }
+      return -1;
+    };
+    for (int32_t w = 0; w < W; ++w)
+      for (int32_t i = plan->worker_offsets[w]; i < plan->worker_offsets[w + 1]; ++i) {
+        if (plan->units[i].q_count * plan->units[i].head_count <= kHalfRows) continue;
+        int32_t to = next_idle(w / per_chip);
+        for (int32_t chip = 0; to < 0; ++chip) to = next_idle(chip);       // there are as many idle workers as halves
+        second_of[to] = i;
+      }
+  }
+  plan->wide_rows = 0;
   plan->free_workers = 0;
-  for (size_t w = 0; w + 1 < plan->worker_offsets.size(); ++w)
-    rank[w] = plan->worker_offsets[w + 1] == plan->worker_offsets[w] ? plan->free_workers++ : -1;
+  int32_t emitted = 0;
+  auto emit = [&](const xy_work_unit& u, const int32_t first_token, const int32_t tokens) {
+    const xy_seq_desc& sd = plan->descs[u.seq];
+    const int32_t flags = u.kind_flags | (u.q_count * u.head_count) << kSlabRowsShift | (first_token * u.head_count) << kSlabFirstShift;
+    du[emitted++] = XyDevUnit{u.seq, u.head_begin, u.head_count, u.q_begin + first_token, tokens,
+                              u.kv_block_begin, u.kv_block_end, flags, u.ws_offset, sd.mask_word_offset,
+                              sd.query_len, sd.context_len, plan->token_start[u.seq], u.head_begin / group};
+    plan->wide_rows = std::max(plan->wide_rows, tokens * u.head_count);
+  };
+  for (int32_t w = 0; w < W; ++w) {
+    offsets[w] = emitted;
+    if (plan->units.empty()) continue;          // (the offsets of a plan that could not be built are stale)
+    for (int32_t i = plan->worker_offsets[w]; i < plan->worker_offsets[w + 1]; ++i) {
+      const xy_work_unit& u = plan->units[i];
+      emit(u, 0, halved && u.q_count * u.head_count > kHalfRows ? first_half(u) : u.q_count);
+    }
+    if (halved && second_of[w] >= 0) {
+      const xy_work_unit& u = plan->units[second_of[w]];
+      emit(u, first_half(u), u.q_count - first_half(u));
+    }
+    rank[w] = emitted == offsets[w] ? plan->free_workers++ : -1;
+  }
+  offsets[W] = emitted;
+  for (size_t i = (size_t)plan->worker_offsets[W]; i < plan->units.size(); ++i) emit(plan->units[i], 0, plan->units[i].q_count);
+  plan->device_units = emitted;
   XyDevSeq* ds = reinterpret_cast<XyDevSeq*>(h + off_seqs);
   for (int32_t i = 0; i < plan->num_seqs; ++i) {
     const xy_seq_desc& s = plan->descs[i];
@@ -1789,7 +1880,7 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
   p.page_shift = plan->cfg.block_size == 16 ? 4 : plan->cfg.block_size == 32 ? 5 : plan->cfg.block_size == 64 ? 6 : 7;
   p.num_workers = plan->cfg.num_workers;
   p.free_workers = plan->free_workers;
-  p.num_units = (int32_t)plan->units.size();
+  p.num_units = plan->device_units;
   const int64_t wavefronts = (int64_t)(kThreads / 64) * plan->cfg.num_workers;
   const int64_t short_slices = plan->narrow_rows > kManyRows * plan->narrow_units ? kShortSlicesManyRows
                                : plan->narrow_units > wavefronts ? kShortSlicesManyUnits : kShortSlices;
@@ -1799,8 +1890,9 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
   p.c = softmax_scale * 1.4426950408889634f;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (phases & XY_PHASE_UNITS) {
-    if (short_units) hipLaunchKernelGGL(xy_attn_units_kernel<true>, dim3(plan->cfg.num_workers), dim3(kThreads), 0, stream, p);
-    else hipLaunchKernelGGL(xy_attn_units_kernel<false>, dim3(plan->cfg.num_workers), dim3(kThreads), 0, stream, p);
+    const auto kernel = plan->wide_rows > 128 ? (short_units ? xy_attn_units_kernel<true, 2> : xy_attn_units_kernel<false, 2>)
+                                              : (short_units ? xy_attn_units_kernel<true, 1> : xy_attn_units_kernel<false, 1>);
+    hipLaunchKernelGGL(kernel, dim3(plan->cfg.num_workers), dim3(kThreads), 0, stream, p);
     if (hipGetLastError() != hipSuccess) return XY_ERR_HIP;
   }
   if ((phases & XY_PHASE_MERGE) && !plan->merges.empty()) {

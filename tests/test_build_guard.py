@@ -169,6 +169,19 @@ def test_gap_tables_in_the_kernel_source_are_the_generated_ones():
         raise AssertionError("a packing in the gap of its own exponentials was accepted")
 
 
+def test_gap_tables_of_one_row_tile_in_the_kernel_source_are_the_generated_ones():
+    import os
+    import re
+    from paper_2412_18106_amd import gap_tables as G
+    tables = G.tables(1)
+    G.check(*tables, 1)
+    assert max(G.gap_costs(*tables, 1)) <= G.GAP_CAP_ONE
+    src = open(os.path.join(os.path.dirname(G.__file__), "csrc", "attn_kernels.hip")).read()
+    for name, table in zip(("EXP", "CVT", "ADD"), tables):
+        m = re.search(r"#define XY_GAP_TABLE_ONE_%s \{([^}]*)\}" % name, src)
+        assert m and [int(x) for x in m.group(1).split(",")] == table, name
+
+
 def test_library_stamp_tells_a_current_library_from_a_stale_one(tmp_path, monkeypatch):
     """The build writes the digest of the sources next to the library; the binding loads the library only when
     the digest of the tree still equals it."""

@@ -244,3 +244,48 @@ def test_ways_of_processing_narrow_units(gpu, way, hq, hkv, tokens):
             assert way == ("two slices" if tiles <= 40 * workers else "one slice")
     for policy in (1, 2):
         run_and_check(gpu, b, f"{way}, policy {policy}", plan_check, split_kv_blocks=0, num_workers=workers, assign_policy=policy)
+
+
+@pytest.mark.parametrize("scale", [None, 1.0])
+@pytest.mark.parametrize("hq,hkv", [(4, 1), (6, 2), (1, 1)])
+def test_units_of_more_than_32_rows_on_one_and_on_two_row_tiles(gpu, hq, hkv, scale):
+    """A wavefront holds one row tile where no unit of a launch has more than 128 rows, and units of more are handed out
+    as two halves where there are idle workers for the second ones; else it holds two.  Rows at the edges of tiles,
+    wavefronts and halves; a last piece of which the first half sees nothing; a tree; scores far above a row's first
+    reference (second pass) and, with scale 1, a factor that is not folded into Q; padded cache rows.  A row is computed
+    the same way either way: 256 workers (halves) and one worker (none idle) agree bit for bit."""
+    import torch
+    from paper_2412_18106_amd import binding as X
+    g = hq // hkv
+    rows = [33, 64, 65, 97, 128, 129, 192, 193, 255, 256]
+    tokens = sorted({max(33 // g + 1, min(256 // g, r // g)) for r in rows})
+    tree = W.random_tree(np.random.default_rng(3), 40)
+    specs = [W.SeqSpec(t, 70 + 31 * i, V) for i, t in enumerate(tokens)] + [W.SeqSpec(40, 75, V, W.MASK_TREE, tree)]
+    specs += [W.SeqSpec(64, c, V) for c in (0, 70, 134)]              # 64 tokens: the first 32 see no key of the last tile
+    b = W.make_custom(specs, hq, hkv, 50 + hq, **({} if scale is None else dict(scale=scale)))
+    k = W.bf16_bits_to_f32(b.k_cache)
+    for i, s in enumerate(specs[:4]):                                   # 300 log2 units above what its row has seen so far
+        pos, t0 = s.context_len - 3, sum(x.query_len for x in specs[:i])
+        q = W.bf16_bits_to_f32(b.q[t0 + s.query_len - 1, 0])
+        k[b.block_table[i, pos // 128], 0, pos % 128] = q * (300 / (b.scale * np.log2(np.e) * np.dot(q, q)))
+    if scale is not None:         # (folded into Q, the factor costs a score of 300 log2 units more than the tolerance)
+        b.k_cache[:] = W.f32_to_bf16_bits(k)
+    ref = A.attention_oracle(b.seqs, b.q, b.k_cache, b.v_cache, b.block_table, b.tree_masks, num_q_heads=hq,
+                             num_kv_heads=hkv, block_size=b.block_size, scale=b.scale)
+    for split in (0, 1):
+        outs = []
+        for workers in (256, 1):
+            db = gpu.DeviceBatch(b, num_workers=workers, split_kv_blocks=split, verify_tile_tokens=256 // g)
+            try:
+                outs.append(db.run_numpy())
+                views = []
+                for src in (db.k_cache, db.v_cache):
+                    views.append(torch.full((*src.shape[:3], 256), 3.0e4, dtype=torch.bfloat16, device="cuda")[..., :128])
+                    views[-1].copy_(src)
+                X.xy_attn_run(db.plan, db.q, *views, db.block_table, db.tree_masks, db.out, db.workspace, b.scale)
+                outs.append(db.out.float().cpu().numpy())
+            finally:
+                db.close()
+        err = np.abs(outs[0].astype(np.float64) - ref)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (split, err.max(), err.mean())
+        assert all(np.array_equal(o, outs[0]) for o in outs[1:]), split

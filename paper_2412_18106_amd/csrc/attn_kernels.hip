@@ -1909,8 +1909,11 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
 
 // ---- K/V append (section 4.1.1: the cache holds historical and newly generated tokens) --------
 // One thread moves one 16-byte chunk: thread index = ((token * Hkv + kv head) * 2 + (K | V)) * 16 + chunk.
-// The sixteen threads of a row read 256 contiguous bytes and write 256 contiguous bytes.  The owning
-// sequence of a token is found by bisection over the packed start positions.
+// The sixteen threads of a row read 256 contiguous bytes and write 256 contiguous bytes.  What a small step pays for is
+// the chain of dependent loads in front of the copy, so a wavefront finds the sequence of its token among the packed
+// start positions with one load for up to 64 sequences (two up to 4096), one lane each, instead of one per halving, and
+// asks for its row before that: 24 decodes and a suffix of 200 tokens 3.4 -> 2.9 us, 7800 prompt tokens (copy rate)
+// 12.5 -> 11.2 us.  Four probes a lane (256 sequences in one round trip) and 32-bit divisions changed nothing.
 __global__ __launch_bounds__(256) void xy_attn_append_kernel(const XyDevSeq* __restrict__ seqs, int num_seqs,
                                                              int64_t total_tokens, int num_kv_heads,
                                                              const uint16_t* __restrict__ k_new,
@@ -1921,22 +1924,34 @@ __global__ __launch_bounds__(256) void xy_attn_append_kernel(const XyDevSeq* __r
                                                              const int32_t* __restrict__ block_table,
                                                              int max_blocks, int page_shift, int64_t first) {
   const int64_t idx = first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int chunk = (int)(idx & 15), is_v = (int)((idx >> 4) & 1);
+  const int chunk = (int)(idx & 15), is_v = (int)((idx >> 4) & 1), lane = threadIdx.x & 63;
   const int64_t row = idx >> 5;                     // token * Hkv + kv head
   const int64_t t = row / num_kv_heads;
   const int g = (int)(row - t * num_kv_heads);
-  if (t >= total_tokens) return;
-  int lo = 0, hi = num_seqs - 1;                    // last sequence whose token_start <= t
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (seqs[mid].token_start <= t) lo = mid; else hi = mid - 1;
-  }
-  const XyDevSeq sq = seqs[lo];
+  const int64_t t0 = __shfl(t, 0);                  // the wavefront's first token (with one KV head it has two)
+  if (t0 >= total_tokens) return;
+  const bool live = t < total_tokens;
+  uint4 data = {0u, 0u, 0u, 0u};
+  if (live) data = *reinterpret_cast<const uint4*>((is_v ? v_new : k_new) + t * n_ts + (int64_t)g * n_hs + chunk * 8);
+  int lo = 0, left = num_seqs;                      // the last sequence whose token_start <= t0 is one of [lo, lo + left)
+  XyDevSeq sq;
+  int step;
+  do {
+    step = (left + 63) >> 6;
+    XyDevSeq probe = {0, INT32_MAX};
+    if (lane < (left + step - 1) / step) probe = seqs[lo + lane * step];
+    const int hit = __popcll(__builtin_amdgcn_ballot_w64(probe.token_start <= t0)) - 1;
+    lo += hit * step;
+    left = min(step, left - hit * step);
+    sq = XyDevSeq{__shfl(probe.ctx_len, hit), __shfl(probe.token_start, hit)};
+  } while (step > 1);
+  if (!live) return;
+  if (t != t0)
+    while (lo + 1 < num_seqs && seqs[lo + 1].token_start <= t) sq = seqs[++lo];
   const int j = sq.ctx_len + (int)(t - sq.token_start);          // key position of this token
   const int64_t block = block_table[(int64_t)lo * max_blocks + (j >> page_shift)];
-  const uint16_t* src = (is_v ? v_new : k_new) + t * n_ts + (int64_t)g * n_hs + chunk * 8;
   uint16_t* dst = (is_v ? v_cache : k_cache) + block * kv_bs + (int64_t)g * kv_hs + (int64_t)(j & ((1 << page_shift) - 1)) * kv_ts + chunk * 8;
-  *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+  *reinterpret_cast<uint4*>(dst) = data;
 }
 
 extern "C" int xy_attn_append_kv(xy_attn_plan* plan, const void* k_new, const void* v_new, int64_t n_ts,

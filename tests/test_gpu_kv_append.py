@@ -197,3 +197,33 @@ def test_append_of_more_threads_than_one_launch_takes(gpu):
     for cache, rows in ((k, new[0]), (v, new[1])):
         bits, want = cache.view(torch.int16), rows.view(torch.int16)[:, None, :].expand(heads, 128, 128)
         assert torch.equal(bits[0], want) and torch.equal(bits[2], want) and not bits[1].any()
+
+
+@pytest.mark.parametrize("hkv", [1, 2, 3])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 1000, 4096, 4097, 4161])
+def test_append_finds_the_sequence_of_a_token(gpu, n, hkv):
+    """A wavefront looks its token up among 64 start positions at a time: one level up to 64 sequences, two up to 4096,
+    three beyond, levels that end inside and at a lane; one KV head, where a wavefront has two tokens (of one or of two
+    sequences), and three, where tokens end inside a wavefront.  Every byte of the caches against a scatter on the host."""
+    import torch
+    from paper_2412_18106_amd import binding as X
+    rng = np.random.default_rng(n)
+    lens, ctx = rng.choice([1, 1, 1, 2, 3, 5], n), rng.integers(0, 20, n)
+    pages = 2
+    cfg = X.xy_attn_default_config(hkv, hkv, pages, block_size=16)
+    plan = X.xy_attn_plan_create(cfg, [(int(q), int(c), X.XY_VERIFY, 0, 0) for q, c in zip(lens, ctx)])
+    try:
+        table = torch.from_numpy(rng.permutation(pages * n).astype(np.int32).reshape(n, pages)).cuda()
+        new = torch.randint(-2**15, 2**15, (2, int(lens.sum()), hkv, 128), dtype=torch.int16, device="cuda")
+        caches = torch.randint(-2**15, 2**15, (2, pages * n, hkv, 16, 128), dtype=torch.int16, device="cuda")
+        want = caches.clone()
+        seq = np.repeat(np.arange(n), lens)
+        pos = np.concatenate([np.arange(c, c + q) for q, c in zip(lens, ctx)])
+        block = table.cpu().numpy()[seq, pos // 16]
+        want[:, torch.from_numpy(block).cuda().long(), :, torch.from_numpy(pos % 16).cuda().long()] = new.transpose(0, 1)
+        bf = [x.view(torch.bfloat16) for x in (new[0], new[1], caches[0], caches[1])]
+        X.xy_attn_append_kv(plan, *bf, table)
+        torch.cuda.synchronize()
+        assert torch.equal(caches, want)
+    finally:
+        X.xy_attn_plan_destroy(plan)

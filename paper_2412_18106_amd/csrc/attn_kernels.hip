@@ -67,7 +67,8 @@ constexpr int64_t kDeepTiles = 10;
 constexpr float kPrescaleMaxC = 0.25f;    // largest c = scale * log2(e) that is folded into Q (wide units)
 // Dynamic assignment: the cursor of the shared list, kDoneGroups counts of finished workgroups and the
 // count of finished groups, kCounterStride ints (one 128-byte line) apart.
-// XyDevUnit::flags: kind and mask in the low bits; rows of the family's partial results, the unit's first row among them
+// XyDevUnit::flags: kind and mask in the low bits; where wide units are on one row tile also the rows of the family's partial
+// results and the unit's first row among them
 constexpr int kSlabRowsShift = 8, kSlabFirstShift = 20;
 constexpr int kDoneGroups = 8;
 constexpr int kCounterStride = 32;
@@ -605,6 +606,70 @@ __device__ __forceinline__ void finish_unit(const RunParams& p, const XyDevUnit&
       const u32x2 w2 = {pack_bf16(st.oacc[0][dt][4 * a] * inv, st.oacc[0][dt][4 * a + 1] * inv),
                         pack_bf16(st.oacc[0][dt][4 * a + 2] * inv, st.oacc[0][dt][4 * a + 3] * inv)};
       *as_global(reinterpret_cast<u32x2*>(o + 32 * dt + 8 * a + 4 * half)) = w2;
+    }
+}
+
+// The wavefronts of a team have each seen some of the keys of one unit: their states meet in LDS (each in its own part
+// of the ring, 16-byte groups in register order) and every wavefront puts a share of the d tiles together, in the order of
+// the members whatever the order they arrive in.  Every wavefront of the workgroup comes here once.
+template <int TEAM>
+__device__ __forceinline__ void finish_team(const RunParams& p, const XyDevUnit& u, const UnitCtx& c, const Rows<1>& r, UnitState& st,
+                                            unsigned char* smem, const bool exists) {
+  constexpr int kTiles = 4 / TEAM;            // d tiles of a wavefront
+  const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5, wave = wave_id(), member = wave & (TEAM - 1);
+  mfma_results_ready(st.oacc[0][0], st.oacc[0][1], st.oacc[0][2], st.oacc[0][3]);
+  f32x4* const mine = reinterpret_cast<f32x4*>(smem + wave * 32768) + lane;
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      mine[64 * (4 * dt + a)] = f32x4{st.oacc[0][dt][4 * a], st.oacc[0][dt][4 * a + 1], st.oacc[0][dt][4 * a + 2], st.oacc[0][dt][4 * a + 3]};
+  mine[64 * 16] = f32x4{st.m_ref[0], st.l_part[0] + other_half(st.l_part[0]), 0.f, 0.f};
+  __syncthreads();
+  if (!exists || !r.valid[0]) return;
+  const f32x4* const first = reinterpret_cast<const f32x4*>(smem + (wave - member) * 32768) + lane;      // of member 0
+  constexpr int kNext = 32768 / 16;
+  float m[TEAM], l[TEAM], m_all = -INFINITY, l_all = 0.f;
+#pragma unroll
+  for (int i = 0; i < TEAM; ++i) {
+    const f32x4 ml = first[i * kNext + 64 * 16];
+    m[i] = ml[0];
+    l[i] = ml[1];
+    m_all = fmaxf(m_all, m[i]);
+  }
+  f32x4 o[kTiles][4] = {};
+#pragma unroll
+  for (int i = 0; i < TEAM; ++i) {
+    const float f = m[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m[i] - m_all) * p.c);
+    l_all += f * l[i];
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) o[k][a] += f * first[i * kNext + 64 * (4 * (kTiles * member + k) + a)];
+  }
+  if (u.ws_offset >= 0) {                     // as store_partial
+    char* w = reinterpret_cast<char*>(p.ws + u.ws_offset) + (unsigned)(half * c.rows + col) * 16u;
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k)
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+        *as_global(reinterpret_cast<f32x4*>(w + (8 * (kTiles * member + k) + 2 * a) * c.rows * 16)) = o[k][a];
+    if (half == 0 && member == 0) {
+      XY_GLOBAL float* ml = as_global(p.ws + u.ws_offset + (int64_t)c.rows * kD + col);
+      ml[0] = m_all == -INFINITY ? -INFINITY : m_all * p.c;
+      ml[c.rows] = l_all;
+    }
+    return;
+  }
+  const int tl = r.tok[0] - u.q_begin, hl = col - tl * c.hc;
+  const float inv = l_all > 0.f ? 1.f / l_all : 0.f;
+  uint16_t* out = p.out + (int64_t)(u.token_start + u.q_begin + tl) * p.o_ts + (int64_t)(u.head_begin + hl) * p.o_hs;
+#pragma unroll
+  for (int k = 0; k < kTiles; ++k)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const u32x2 w2 = {pack_bf16(o[k][a][0] * inv, o[k][a][1] * inv), pack_bf16(o[k][a][2] * inv, o[k][a][3] * inv)};
+      *as_global(reinterpret_cast<u32x2*>(out + 32 * (kTiles * member + k) + 8 * a + 4 * half)) = w2;
     }
 }
 
@@ -1256,8 +1321,11 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
 // for memory in every slice, and that is the end of every launch.  8 decodes x 32 KV heads on 2-6k tokens (7.5 tiles per
 // wavefront) 94.8 -> 92.0 us with two; 128 trees on 512-4096 tokens (14 tiles) 153.0 -> 154.7 us, 128 decodes on
 // 2-16k (54 tiles) 553.7 -> 557.2 us, so those keep one.  Launches of short units take process_short instead.
-__device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit& u,
-                                             unsigned char* smem, const LaneOffsets& lo, const DmaOffsets& dof) {
+// TEAM: wavefronts that share the unit (see finish_team), each with every TEAM-th slice from its place in the team on;
+// exists: whether the team has a unit at all.
+template <int TEAM>
+__device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit& u, unsigned char* smem, const LaneOffsets& lo,
+                                             const DmaOffsets& dof, const bool exists = true) {
   constexpr int NT = 1;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1267,7 +1335,9 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
   const int last_page = (u.ctx_len + u.q_len - 1) >> p.page_shift;
   const int64_t head_off = (int64_t)c.kvh * p.kv_hs;
   const int jfirst = u.kv_begin * kB;
-  const int nsteps = (min(u.kv_end * kB, c.key_end) - jfirst + 31) >> 5;
+  const int slices = (min(u.kv_end * kB, c.key_end) - jfirst + 31) >> 5, member = wave & (TEAM - 1);
+  const int nsteps = TEAM == 1 ? slices : exists ? (slices - member + TEAM - 1) / TEAM : 0;      // of this wavefront
+  auto key_of = [&](const int t) { return jfirst + 32 * (TEAM * t + member); };                 // first key of its step t
   unsigned char* ring = smem + wave * 32768;        // one or two slices of [K 8 KB | V 8 KB]
   const int depth = p.narrow_depth;
   const unsigned ring_addr = lds_addr(ring);
@@ -1283,10 +1353,14 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
   auto entries = [&](const int t) {
     Entries n;
 #pragma unroll
-    for (int g = 0; g < 2; ++g) n.e[g] = table[min((jfirst + 32 * t + 16 * g) >> p.page_shift, last_page)];
+    for (int g = 0; g < 2; ++g) n.e[g] = table[min((key_of(t) + 16 * g) >> p.page_shift, last_page)];
     return n;
   };
-  const Entries entries0 = entries(0), entries1 = entries(1);
+  Entries entries0 = {}, entries1 = {};
+  if (TEAM == 1 || nsteps > 0) {
+    entries0 = entries(0);
+    entries1 = entries(1);
+  }
   Rows<NT> r;
   bf16x8 qf[NT][8];
   const float inv_hc = __builtin_amdgcn_rcpf((float)c.hc);
@@ -1297,7 +1371,7 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
     Slice at;
 #pragma unroll
     for (int g = 0; g < 2; ++g)
-      at.run[g] = (int64_t)n.e[g] * p.kv_bs + (int64_t)((jfirst + 32 * t + 16 * g) & p.page_mask) * p.kv_ts + head_off;
+      at.run[g] = (int64_t)n.e[g] * p.kv_bs + (int64_t)((key_of(t) + 16 * g) & p.page_mask) * p.kv_ts + head_off;
     return at;
   };
   auto load_slice = [&](const Slice& at, const int t, const bool want_k, const bool want_v) {
@@ -1310,7 +1384,7 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
   // not only for that: a load whose result the compiler sees would be waited for with everything that is in flight.
   // It waits where V of the second slice comes to lie, which is asked for when Q has been read.
   unsigned char* const q_buf = ring + 16384 + 8192;
-  {
+  if (TEAM == 1 || nsteps > 0) {
     const int sub = lane >> 4, pos = lane & 15;             // a load moves four rows: row, 16-byte chunk
     const char* q0 = reinterpret_cast<const char*>(p.q + (int64_t)(u.token_start + u.q_begin) * p.q_ts + (int64_t)u.head_begin * p.q_hs);
     auto load_q = [&](const char* from, const int e) {
@@ -1365,17 +1439,18 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
       wait_vmcnt<16>();
     } else {
       wait_vmcnt<0>();
-      const int last_keys = min(u.kv_end * kB, c.key_end) - jfirst - 32 * t;      // keys of the last step: 1 .. 32
+      const int last_keys = min(u.kv_end * kB, c.key_end) - key_of(t);      // keys of the last step: 1 .. 32
       if (last_keys < 32) zero_tail_rows(vaddr, last_keys, lane);
     }
     v_fetch<0>(vaddr, lo, vf);                // the first V fragments arrive while the softmax runs
-    const int j = jfirst + 32 * t;
+    const int j = key_of(t);
     if (j + 32 > mask_from) mask_step<NT>(p, c, r, j + 8 * half, s);
     softmax_step<NT>(p.c, s, st.m_ref, st.l_part, st.oacc);
     pv_step<NT>(vaddr, lo, vf, s, st.oacc);   // all V reads have completed when this returns
     if (left >= depth) load_slice(next, t, false, true);
   }
-  finish_unit(p, u, c, r, st, col, half);
+  if constexpr (TEAM == 1) finish_unit(p, u, c, r, st, col, half);
+  else finish_team<TEAM>(p, u, c, r, st, smem, exists);
 }
 
 // A unit of at most 32 rows in a launch of short ones (kShortSlices): one slice at a time, Q straight into registers and
@@ -1450,10 +1525,12 @@ __device__ __forceinline__ void process_short(const RunParams& p, const XyDevUni
 // wide units of its list together, then its four wavefronts draw the remaining (bandwidth-bound)
 // units of the same list one by one from a shared cursor, each wavefront finishing whole units
 // on its own.
-// SHORT: how its units of at most 32 rows are processed (kShortSlices); a kernel for each, since the two in one disturb each
-// other's registers (short units 3 to 5 %, launches on two slices up to 2 %).
+// NARROW: how its units of at most 32 rows are processed (kSolo, kShort: kShortSlices; 2 or 4: by a team of so many
+// wavefronts each, see narrow_team); a kernel for each, since the ways in one disturb each other's registers (short units
+// 3 to 5 %, launches on two slices up to 2 %).
 // NT: row tiles of a wavefront on its wide units (process_wide).
-template <bool SHORT, int NT>
+constexpr int kSolo = 0, kShort = 1;
+template <int NARROW, int NT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void xy_attn_units_kernel(RunParams p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kTileBytes];
   __shared__ int cursor, first_draw;
@@ -1461,7 +1538,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
   // consecutive workgroup ids land on different XCDs; give each XCD a contiguous range of workers
   int worker = blockIdx.x;
   if ((p.num_workers & 7) == 0) worker = (blockIdx.x & 7) * (p.num_workers >> 3) + (blockIdx.x >> 3);
-  const int begin = as_const(p.worker_offsets)[worker], end = as_const(p.worker_offsets)[worker + 1];
+  constexpr bool kTeams = NARROW > 1;
+  const bool no_lists = kTeams && p.free_workers == p.num_workers;       // teams only: nothing to look up
+  int begin = 0, end = 0;
+  if (!no_lists) {
+    begin = as_const(p.worker_offsets)[worker];
+    end = as_const(p.worker_offsets)[worker + 1];
+  }
   const LaneOffsets lo = make_lane_offsets(threadIdx.x & 63);
   const DmaOffsets dof = make_dma_offsets(threadIdx.x & 63, p.kv_ts);
   if (threadIdx.x == 0) cursor = begin;
@@ -1493,6 +1576,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
   const XY_CONST RunParams* args = (const XY_CONST RunParams*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(args));
   const RunParams pn = load_const((const RunParams*)args);
+  if constexpr (kTeams) {
+    // one unit for every team of the workers without wide units, none drawn: consecutive ones on different chiplets
+    if (begin < end) return;
+    const int teams_begin = no_lists ? 0 : as_const(pn.worker_offsets)[pn.num_workers];
+    const int rank = no_lists ? blockIdx.x : as_const(pn.worker_offsets)[pn.num_workers + 1 + worker];
+    const int i = teams_begin + rank + pn.free_workers * (wave_id() / NARROW);
+    const bool exists = i < pn.num_units;
+    const XyDevUnit u = load_unit(pn.units + (exists ? i : teams_begin));
+    process_solo<NARROW>(pn, u, smem, lo, dof, exists);
+    return;
+  }
 #pragma unroll 1
   while (true) {
     int got = 0;
@@ -1501,8 +1595,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     if (i >= end) break;
     const XyDevUnit u = load_unit(pn.units + i);
     if (u.q_count * u.head_count > 32) continue;
-    if (SHORT) process_short(pn, u, smem, lo, dof);
-    else process_solo(pn, u, smem, lo, dof);
+    if (NARROW == kShort) process_short(pn, u, smem, lo, dof);
+    else process_solo<1>(pn, u, smem, lo, dof);
   }
   if (pn.counters) {
     // The shared list of narrow units (dynamic assignment): every wavefront of every workgroup draws the
@@ -1529,8 +1623,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
       const int i = shared_begin + next;
       if (i >= pn.num_units) break;
       const XyDevUnit u = load_unit(pn.units + i);
-      if (SHORT) process_short(pn, u, smem, lo, dof);
-      else process_solo(pn, u, smem, lo, dof);
+      if (NARROW == kShort) process_short(pn, u, smem, lo, dof);
+      else process_solo<1>(pn, u, smem, lo, dof);
       if (!any_left) break;
       int got = 0;
       if ((threadIdx.x & 63) == 0) got = slots + atomicAdd(pn.counters, 1);
@@ -1671,22 +1765,51 @@ __global__ __launch_bounds__(256) void xy_plan_copy_kernel(const uint4* __restri
 // and a chunk of 512 beside 1184 157 -> 164 us where there is not).  The plan the caller sees stays as it is.
 constexpr int32_t kHalfRows = 128, kXcds = 8;
 static int32_t first_half(const xy_work_unit& u) { return (u.q_count + 1) / 2; }
-static int64_t units_to_halve(const xy_attn_plan* plan) {
-  if (plan->units.empty()) return 0;
-  const int32_t W = plan->cfg.num_workers;
-  int64_t halved = 0;
-  int32_t idle = 0;
-  for (int32_t w = 0; w < W; ++w) {
-    idle += plan->worker_offsets[w] == plan->worker_offsets[w + 1];
-    for (int32_t i = plan->worker_offsets[w]; i < plan->worker_offsets[w + 1]; ++i) {
-      const xy_work_unit& u = plan->units[i];
-      if (u.q_count * u.head_count > kHalfRows) {
-        if (first_half(u) * u.head_count > kHalfRows) return 0;
+// Wavefronts that share a narrow unit, for launches that have fewer such units than wavefronts: four while every unit can
+// have a worker without wide units to itself, two while half of one, else none.  Unit kernel, us, one wavefront a unit / team (decodes of 32 heads
+// in 8, caches cold):
+//   units   2 slices (64 keys)    4            8            16           63
+//   8       5.7 / 5.8             8.3 / 6.5    11.2 / 8.4   18.2 / 10.4  60.2 / 23.7
+//   224     6.8 / 6.8             8.6 / 8.1    12.2 / 10.6  19.4 / 14.1  61.4 / 39.1
+//   256     6.0 / 6.9             8.3 / 8.4    12.4 / 11.2  19.5 / 15.5  62.0 / 43.9
+//   264     7.1 / 7.4 (two)       9.1 / 9.8    12.9 / 12.4  20.1 / 19.2  62.2 / 59.0
+//   512     7.5 / 8.3             10.2 / 11.4  15.6 / 15.1  25.9 / 24.8  85.3 / 84.5
+// so a team of four takes units of three slices and more on average, a team of two those of eight.
+constexpr int64_t kTeamOf4Slices = 3, kTeamOf2Slices = 8;
+static bool is_narrow(const xy_work_unit& u) { return u.q_count * u.head_count <= 32; }
+
+struct XyLayout {
+  int64_t halved;       // units handed out as two halves
+  int32_t team;         // wavefronts that share a narrow unit, 2 or 4, or 0
+};
+static XyLayout layout_of(const xy_attn_plan* plan) {
+  const int64_t units = plan->narrow_units, slices = plan->narrow_slices, W = plan->cfg.num_workers;
+  if (plan->units.empty()) return {0, 0};
+  int64_t halved = 0, idle = W, free = W;       // workers without units, without wide units
+  bool divisible = true;
+  if (units < (int64_t)plan->units.size()) {
+    const xy_work_unit* const u = plan->units.data();
+    const int32_t* const offsets = plan->worker_offsets.data();
+    for (int64_t w = 0; w < W; ++w) idle -= offsets[w + 1] > offsets[w];
+    for (int64_t w = 0; w < W; ++w) {
+      int32_t wide = 0;
+      for (int32_t i = offsets[w]; i < offsets[w + 1]; ++i) {
+        const int32_t rows = u[i].q_count * u[i].head_count;
+        wide += rows > 32;
+        if (rows <= kHalfRows) continue;
         ++halved;
+        divisible &= first_half(u[i]) * u[i].head_count <= kHalfRows;
       }
+      free -= wide > 0;
+      if (halved > idle) return {0, 0};
     }
+    if (halved && (!divisible || halved > idle || units > (int64_t)(kThreads / 64) * (idle - halved))) return {0, 0};
+    free -= halved;
   }
-  return halved <= idle && plan->narrow_units <= (int64_t)(kThreads / 64) * (idle - halved) ? halved : 0;
+  // (the kernels with teams hold one row tile: no unit has more than kHalfRows rows here)
+  const int32_t team = units == 0 ? 0 : units <= free ? (slices >= kTeamOf4Slices * units ? 4 : 0)
+                       : units <= 2 * free && slices >= kTeamOf2Slices * units ? 2 : 0;
+  return {halved, team};
 }
 
 static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
@@ -1695,7 +1818,7 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
   if (plan->device >= 0 && plan->device != dev) return XY_ERR_ARG;      // the plan lives on another device
   auto round_up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const bool shared_list = plan->worker_offsets.back() < (int64_t)plan->units.size();
-  const int64_t halved = units_to_halve(plan);
+  const auto [halved, team] = layout_of(plan);
   const size_t num_units = plan->units.size() + halved;
   const size_t off_units = 0;
   const size_t off_offsets = off_units + round_up(num_units * sizeof(XyDevUnit));
@@ -1755,32 +1878,44 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
         second_of[to] = i;
       }
   }
-  plan->wide_rows = 0;
-  plan->free_workers = 0;
-  int32_t emitted = 0;
-  auto emit = [&](const xy_work_unit& u, const int32_t first_token, const int32_t tokens) {
-    const xy_seq_desc& sd = plan->descs[u.seq];
-    const int32_t flags = u.kind_flags | (u.q_count * u.head_count) << kSlabRowsShift | (first_token * u.head_count) << kSlabFirstShift;
-    du[emitted++] = XyDevUnit{u.seq, u.head_begin, u.head_count, u.q_begin + first_token, tokens,
-                              u.kv_block_begin, u.kv_block_end, flags, u.ws_offset, sd.mask_word_offset,
-                              sd.query_len, sd.context_len, plan->token_start[u.seq], u.head_begin / group};
-    plan->wide_rows = std::max(plan->wide_rows, tokens * u.head_count);
+  int32_t emitted = 0, free_workers = 0;
+  const xy_work_unit* const units = plan->units.data();
+  const xy_seq_desc* const descs = plan->descs.data();
+  const int32_t *const starts = plan->token_start.data(), *const lists = plan->worker_offsets.data();
+  auto record = [=](const xy_work_unit& u, const int32_t q_begin, const int32_t q_count, const int32_t flags) {
+    const xy_seq_desc& sd = descs[u.seq];
+    return XyDevUnit{u.seq, u.head_begin, u.head_count, q_begin, q_count, u.kv_block_begin, u.kv_block_end, flags, u.ws_offset,
+                     sd.mask_word_offset, sd.query_len, sd.context_len, starts[u.seq], u.head_begin / group};
   };
-  for (int32_t w = 0; w < W; ++w) {
-    offsets[w] = emitted;
-    if (plan->units.empty()) continue;          // (the offsets of a plan that could not be built are stale)
-    for (int32_t i = plan->worker_offsets[w]; i < plan->worker_offsets[w + 1]; ++i) {
-      const xy_work_unit& u = plan->units[i];
-      emit(u, 0, halved && u.q_count * u.head_count > kHalfRows ? first_half(u) : u.q_count);
+  plan->row_tiles = !halved && plan->most_rows > kHalfRows ? 2 : 1;
+  if (team || (plan->row_tiles == 1 && plan->most_rows > 32)) {
+    auto emit = [&](const xy_work_unit& u, const int32_t first_token, const int32_t tokens) {
+      const int32_t flags = u.kind_flags | (u.q_count * u.head_count) << kSlabRowsShift | (first_token * u.head_count) << kSlabFirstShift;
+      du[emitted++] = record(u, u.q_begin + first_token, tokens, flags);
+    };
+    for (int32_t w = 0; w < W; ++w) {
+      offsets[w] = emitted;
+      for (int32_t i = lists[w]; i < lists[w + 1]; ++i) {
+        if (team && is_narrow(units[i])) continue;
+        emit(units[i], 0, halved && units[i].q_count * units[i].head_count > kHalfRows ? first_half(units[i]) : units[i].q_count);
+      }
+      if (halved && second_of[w] >= 0) {
+        const xy_work_unit& u = units[second_of[w]];
+        emit(u, first_half(u), u.q_count - first_half(u));
+      }
     }
-    if (halved && second_of[w] >= 0) {
-      const xy_work_unit& u = plan->units[second_of[w]];
-      emit(u, first_half(u), u.q_count - first_half(u));
-    }
-    rank[w] = emitted == offsets[w] ? plan->free_workers++ : -1;
+    offsets[W] = emitted;
+    // the shared list; with teams every narrow unit is on it
+    for (size_t i = team ? 0 : (size_t)lists[W]; i < plan->units.size(); ++i)
+      if (!team || is_narrow(units[i])) emit(units[i], 0, units[i].q_count);
+  } else {
+    emitted = (int32_t)plan->units.size();
+    for (int32_t i = 0; i < emitted; ++i) du[i] = record(units[i], units[i].q_begin, units[i].q_count, units[i].kind_flags);
+    memcpy(offsets, lists, plan->worker_offsets.size() * sizeof(int32_t));
   }
-  offsets[W] = emitted;
-  for (size_t i = (size_t)plan->worker_offsets[W]; i < plan->units.size(); ++i) emit(plan->units[i], 0, plan->units[i].q_count);
+  for (int32_t w = 0; w < W; ++w) rank[w] = offsets[w + 1] == offsets[w] ? free_workers++ : -1;
+  plan->narrow_team = team;
+  plan->free_workers = free_workers;
   plan->device_units = emitted;
   XyDevSeq* ds = reinterpret_cast<XyDevSeq*>(h + off_seqs);
   for (int32_t i = 0; i < plan->num_seqs; ++i) {
@@ -1885,14 +2020,18 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
   const int64_t short_slices = plan->narrow_rows > kManyRows * plan->narrow_units ? kShortSlicesManyRows
                                : plan->narrow_units > wavefronts ? kShortSlicesManyUnits : kShortSlices;
   const bool short_units = plan->narrow_units > 0 && plan->narrow_slices <= short_slices * plan->narrow_units;
-  p.narrow_depth = plan->narrow_tiles <= kDeepTiles * wavefronts ? 2 : 1;
+  p.narrow_depth = plan->narrow_team || plan->narrow_tiles <= kDeepTiles * wavefronts ? 2 : 1;
   p.counters = static_cast<int32_t*>(plan->d_counters);
   p.c = softmax_scale * 1.4426950408889634f;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (phases & XY_PHASE_UNITS) {
-    const auto kernel = plan->wide_rows > 128 ? (short_units ? xy_attn_units_kernel<true, 2> : xy_attn_units_kernel<false, 2>)
-                                              : (short_units ? xy_attn_units_kernel<true, 1> : xy_attn_units_kernel<false, 1>);
-    hipLaunchKernelGGL(kernel, dim3(plan->cfg.num_workers), dim3(kThreads), 0, stream, p);
+    const auto kernel = plan->narrow_team == 4 ? xy_attn_units_kernel<4, 1>
+                        : plan->narrow_team == 2 ? xy_attn_units_kernel<2, 1>
+                        : plan->row_tiles == 2 ? (short_units ? xy_attn_units_kernel<kShort, 2> : xy_attn_units_kernel<kSolo, 2>)
+                                                : (short_units ? xy_attn_units_kernel<kShort, 1> : xy_attn_units_kernel<kSolo, 1>);
+    // teams without wide units need no workgroup more than there are units
+    const int32_t workgroups = plan->narrow_team && p.free_workers == p.num_workers ? std::min(p.num_workers, p.num_units) : p.num_workers;
+    hipLaunchKernelGGL(kernel, dim3(workgroups), dim3(kThreads), 0, stream, p);
     if (hipGetLastError() != hipSuccess) return XY_ERR_HIP;
   }
   if ((phases & XY_PHASE_MERGE) && !plan->merges.empty()) {

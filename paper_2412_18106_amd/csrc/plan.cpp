@@ -268,6 +268,7 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
     plan->merges.clear();
     plan->workspace_floats = 0;
     plan->has_tree = false;
+    plan->most_rows = 0;
     plan->narrow_units = plan->narrow_rows = plan->narrow_tiles = plan->narrow_slices = 0;
 
     // --- size of the K/V split (see XY_SPLIT_AUTO) ---------------------------
@@ -404,6 +405,7 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         const int32_t nb = (int32_t)ceil_div(last_excl, kKvTile);   // 128-key tiles, whatever the page size
         // pieces of a family and their size: the same for every head group of the token tile
         const int64_t rows = (int64_t)qc * hc;
+        plan->most_rows = std::max(plan->most_rows, (int32_t)rows);
         int32_t k = 1;
         const int32_t split = rows <= kNarrowRows ? split_narrow : split_wide;
         if (rows > kNarrowRows && cut.size > 0) k = (int32_t)cut.pieces(XyTileClass{nb, head_groups, rows, prefill});

@@ -59,7 +59,9 @@ struct xy_attn_plan {
   int64_t merge_groups = 0;                 // workgroups of the merge pass (of the tables last copied to the GPU)
   int32_t free_workers = 0;                 // workers without units of their own (of the tables last copied to the GPU)
   int32_t device_units = 0;                 // records of units (of the tables last copied to the GPU)
-  int32_t wide_rows = 0;                    // most rows of a unit (of the tables last copied to the GPU)
+  int32_t narrow_team = 0;                  // wavefronts that share a narrow unit, 2 or 4; else 0 (of the tables last copied to the GPU)
+  int32_t row_tiles = 2;                    // of a wavefront on a wide unit (of the tables last copied to the GPU)
+  int32_t most_rows = 0;                    // most rows of a unit
   int64_t narrow_units = 0, narrow_rows = 0, narrow_tiles = 0, narrow_slices = 0;     // units of at most 32 rows, their rows, K/V tiles and 32-key slices
   bool has_tree = false;
   XyPlanScratch scratch;

@@ -289,3 +289,50 @@ def test_units_of_more_than_32_rows_on_one_and_on_two_row_tiles(gpu, hq, hkv, sc
         err = np.abs(outs[0].astype(np.float64) - ref)
         assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (split, err.max(), err.mean())
         assert all(np.array_equal(o, outs[0]) for o in outs[1:]), split
+
+
+@pytest.mark.parametrize("hq,hkv,tokens", [(1, 1, 1), (4, 1, 1), (5, 1, 6), (8, 1, 4), (4, 2, 8), (31, 1, 1)])
+@pytest.mark.parametrize("team,wide", [(4, False), (4, True), (2, False), (2, True)])
+def test_teams_of_wavefronts_on_narrow_units(gpu, team, wide, hq, hkv, tokens):
+    """Several wavefronts share a narrow unit where there are fewer of them than workers without wide units (four each) or
+    than twice as many (two), every wavefront with every fourth or second slice: units of fewer slices than members (the
+    others come with nothing), ends inside a slice and right at one, trees, one to 32 rows, whole and cut, beside a wide
+    unit and without, NaN and infinities in the slots nobody owns, three launches alike."""
+    tree = W.random_tree(np.random.default_rng(tokens), tokens)
+    specs = [W.SeqSpec(tokens, max(0, keys - tokens), V) for keys in (tokens, 31, 32, 33, 64, 95, 97, 129, 200, 700, 1055, 1100)]
+    specs += [W.SeqSpec(tokens, keys - tokens, V, W.MASK_TREE, tree) for keys in (40, 97, 160, 1500)]
+    if wide:
+        specs.insert(5, W.SeqSpec(128 // (hq // hkv), 77, P))
+    b = W.make_custom(specs, hq, hkv, 23 * hq + tokens)
+    g, seqs = hq // hkv, len(specs) - wide
+    for split in (0, 8):
+        units = sum(-(-tokens // max(1, 32 // g)) * hkv * (-(-(-(-(s.context_len + s.query_len) // 128)) // split) if split else 1)
+                    for s in specs if s.query_len == tokens and s.kind != P)
+        workers = (units if team == 4 else (units + 1) // 2) + wide * hkv
+        cfg = dict(split_kv_blocks=split, num_workers=workers)
+
+        def plan_check(u, _offs, _merges):
+            narrow = u[u["q_count"] * u["head_count"] <= 32]
+            slices = 0
+            for x in narrow:
+                q, c, _kind, mask, _off = b.seqs[x["seq"]]
+                end = c + q if mask else c + x["q_begin"] + x["q_count"]
+                slices += -(-(min(128 * x["kv_block_end"], end) - 128 * x["kv_block_begin"]) // 32)
+            free = workers - (len(u) - len(narrow))
+            assert (free if team == 2 else 0) < len(narrow) <= (free if team == 4 else 2 * free)
+            assert slices >= (3 if team == 4 else 8) * len(narrow)
+        db = gpu.DeviceBatch(b, **cfg)
+        try:
+            first = db.run_numpy()
+            assert all(np.array_equal(db.run_numpy(), first) for _ in range(2))
+        finally:
+            db.close()
+        saved = b.k_cache.copy(), b.v_cache.copy()
+        _poison(b)
+        db = gpu.DeviceBatch(b, **cfg)
+        try:
+            assert np.array_equal(db.run_numpy(), first)
+        finally:
+            db.close()
+        b.k_cache[:], b.v_cache[:] = saved
+        run_and_check(gpu, b, f"team of {team}, split {split}", plan_check, **cfg)

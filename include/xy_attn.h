@@ -80,7 +80,9 @@ typedef struct {
                                      sorted unit goes to the worker with the smallest load so far
                                      (lowest index on ties); XY_ASSIGN_DYNAMIC: units of more
                                      than 32 rows as with XY_ASSIGN_LEAST_LOADED (among
-                                     themselves), units of at most 32 rows are not assigned at
+                                     themselves; with cost_row_floor >= 128 sorted and placed by
+                                     the time they take, 2 tiles + 5 whatever their rows, instead
+                                     of their load), units of at most 32 rows are not assigned at
                                      all: they form one list in sorted order behind the workers'
                                      lists (worker_offsets[W] is where it starts) and the
                                      wavefronts of all workers draw from it at run time; when

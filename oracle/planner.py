@@ -82,7 +82,9 @@ Rules
    ``2 W`` units of more than 32 rows, if the largest load of a worker with it
    exceeds 1.03 times the largest without.
    ``assign_policy`` 2 (dynamic): units of more than 32 rows are assigned as
-   with policy 1, counting only their own costs; units of at most 32 rows are
+   with policy 1 among themselves, where ``cost_row_floor >= 128`` with
+   ``2 * blocks + 5`` (a unit's time, whatever its rows) instead of the cost, in
+   the sort as well; units of at most 32 rows are
    emitted behind all workers' lists, in sorted order, as one shared list that
    starts at ``worker_offsets[W]``.  When no unit has more than 32 rows and
    either all costs are equal or no unit visits more than 2 K/V tiles, policy
@@ -302,8 +304,12 @@ def plan_oracle(cfg, seqs):
                     off = -1 if k == 1 else base + p * slab
                     fam_units.append((i, head_begin, hc, q_begin, q_count, lo, hi, p, k,
                                       kind | (mk << 2), cost, off))
+    by_time = cfg.get("assign_policy", 0) == 2 and cfg["cost_row_floor"] >= 128
+
+    def load_of(u):
+        return 2 * (u[6] - u[5]) + 5 if by_time and u[2] * u[4] > NARROW_ROWS else u[10]
     order = sorted(range(len(fam_units)),
-                   key=lambda x: (-fam_units[x][10], fam_units[x][0], fam_units[x][1],
+                   key=lambda x: (-load_of(fam_units[x]), fam_units[x][0], fam_units[x][1],
                                   fam_units[x][3], fam_units[x][7]))
     per_worker = [[] for _ in range(w)]
     shared = []                 # policy 2: the narrow units, for all workers
@@ -325,7 +331,7 @@ def plan_oracle(cfg, seqs):
             for u in fam_units:
                 if u[2] * u[4] > NARROW_ROWS:
                     key = u[0] * hkv + u[1] // group
-                    group_cost[key] = group_cost.get(key, 0) + u[10]
+                    group_cost[key] = group_cost.get(key, 0) + load_of(u)
             chip_load = [0] * CHIPLETS
             chip_of_group = {}
             for key in sorted(group_cost, key=lambda g: (-group_cost[g], g)):
@@ -349,7 +355,7 @@ def plan_oracle(cfg, seqs):
                 else:
                     k = int(np.argmin(load))          # first index of the minimum
                 lists[k].append(u)
-                load[k] += u[10]
+                load[k] += load_of(u)
             return lists, shared_list, int(load.max()), wide_units
 
         per_worker, shared, largest, wide_units = assign(chip_of_group)

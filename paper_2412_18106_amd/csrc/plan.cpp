@@ -470,6 +470,16 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
     // tie order (their places) and then sorted by cost with a stable byte-wise radix sort, lowest byte first,
     // over the bytes of the cost in which any two units differ (two or three passes for real batches; a
     // comparison sort of the same list costs three to four times as much, most of it mispredicted branches).
+    // XY_ASSIGN_DYNAMIC sorts and places the units of more than 32 rows (among themselves: the others are on the shared
+    // list then) by the time they take, 2 tiles + 5 in half tiles whatever their rows, unless a cost_row_floor below
+    // kRowFloorByTime asks for a cost by rows.  By cost, units of 80 rows count for a third of those of 256, and what
+    // stands around a unit's loop for nothing: largest load of a worker over the mean, by time, 1.54 -> 1.07 for 392 units of
+    // 76 to 256 rows, 1.43 -> 1.14 for 424, 1.12 -> 1.06 for eight prompts of 60 to 4000 tokens.
+    constexpr int32_t kRowFloorByTime = 128;
+    const bool by_time = c.assign_policy == XY_ASSIGN_DYNAMIC && c.cost_row_floor >= kRowFloorByTime;
+    auto load_of = [by_time](const xy_work_unit& u) -> int64_t {
+      return by_time && (int64_t)u.q_count * u.head_count > kNarrowRows ? 2 * (int64_t)(u.kv_block_end - u.kv_block_begin) + kWideUnitHalves : u.cost;
+    };
     const size_t n = fam.size();
     std::vector<int32_t>&order = plan->scratch.order, &other = plan->scratch.order_tmp;
     std::vector<uint64_t>& key = plan->scratch.key;
@@ -479,7 +489,7 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
     uint64_t differ = 0;
     for (size_t x = 0; x < n; ++x) {
       order[place[x]] = (int32_t)x;
-      key[x] = ~(uint64_t)fam[x].cost;              // ascending key = descending cost
+      key[x] = ~(uint64_t)load_of(fam[x]);          // ascending key = descending load
       differ |= key[x] ^ key[0];
     }
     for (int shift = 0; shift < 64; shift += 8) {
@@ -547,8 +557,8 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         int64_t total = 0;
         for (const xy_work_unit& u : fam)
           if ((int64_t)u.q_count * u.head_count > kNarrowRows) {
-            group_cost[group_key(u)] += u.cost;
-            total += u.cost;
+            group_cost[group_key(u)] += load_of(u);
+            total += load_of(u);
           }
         for (int64_t g = 0; g < ngroups; ++g)
           if (group_cost[g] > 0) by_cost.push_back(g);
@@ -608,7 +618,7 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
               if (top(x) < top(h)) h = x;
           }
           to[pos] = top(h).second;
-          add_to_top(h, u.cost);
+          add_to_top(h, load_of(u));
         }
       };
       auto largest = [&] { return std::max_element(plan->scratch.heap.begin(), plan->scratch.heap.end())->first; };      // load of a worker
@@ -622,8 +632,8 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
           const bool narrow = (int64_t)u.q_count * u.head_count <= kNarrowRows;
           wide_units += !narrow;
           if (share && narrow) continue;
-          assigned += u.cost;
-          costliest = std::max(costliest, u.cost);
+          assigned += load_of(u);
+          costliest = std::max(costliest, load_of(u));
         }
       if (wide_units > 0 && wide_units <= 2 * W) {
         const int64_t by_chip = largest();

@@ -279,3 +279,23 @@ def test_thresholds_of_the_plan_rules_match_on_both_sides():
                                         **{k: v for k, v in c.items()
                                            if k not in ("num_q_heads", "num_kv_heads", "max_blocks_per_seq")})
         compare(cfgc, seqs)
+
+
+@pytest.mark.parametrize("floor,policy,rows,tiles", [
+    # one prompt of 128 rows and three of 40, eight tiles each, two workers: the same time (21), two and two; by cost, 1024
+    # against 320 each, the first has a worker to itself
+    (128, 2, [[0, 2], [1, 3]], [[0, 4, 6], [1, 2, 3, 5]]),
+    (200, 2, [[0, 2], [1, 3]], [[0, 4, 6], [1, 2, 3, 5]]),
+    # one of eight tiles and six of one: 21 against 7 each; by cost 8 against 1 each
+    (127, 2, [[0], [1, 2, 3]], [[0], [1, 2, 3, 4, 5, 6]]),
+    (1, 1, [[0], [1, 2, 3]], [[0], [1, 2, 3, 4, 5, 6]])])
+def test_wide_units_are_placed_by_their_time(floor, policy, rows, tiles):
+    cfg = X.xy_attn_default_config(1, 1, 64, num_workers=2, prefill_tile_tokens=128, split_kv_blocks=0,
+                                   cost_row_floor=floor, assign_policy=policy)
+    for seqs, want in (([(128, 7 * 128, 0, 0, 0)] + [(40, 8 * 128 - 40, 0, 0, 0)] * 3, rows),
+                       ([(128, 7 * 128, 0, 0, 0)] + [(128, 0, 0, 0, 0)] * 6, tiles)):
+        compare(cfg, seqs)
+        units, offs, _, _ = PL.plan_oracle(cfg.as_dict(), seqs)
+        if floor == 127 and want is rows:
+            continue            # 1024 against 1016 each: levels as by time
+        assert [[int(x) for x in units["seq"][offs[w]:offs[w + 1]]] for w in range(2)] == want

@@ -109,7 +109,9 @@ typedef struct {
  *  - Otherwise, with s = ceil(B / L) one wavefront's share of the tiles B of all these families together, the
  *    split size is min(max(s, 2), max(16, min(64, floor(2 s / 5)))): the share itself for small batches, 16
  *    tiles up to a share of 40, then two fifths of the share (about three pieces per wavefront, which the shared
- *    list still evens out, each piece costing about a tile and a half beyond its own), at most 64.
+ *    list still evens out, each piece costing about a tile and a half beyond its own), at most 64.  Where s <= 16 and
+ *    the batch has no other families, it is the smallest size from max(s, 2) to max(s + 1, floor(5 s / 4)) that
+ *    makes at most L pieces (one for each wavefront instead of a few more), if there is one.
  * Wide families (more than 32 rows): DECODE / VERIFY ones are split at 16 tiles, PREFILL ones are whole, unless that
  * leaves workers idle; then all of them, PREFILL too, are cut at T tiles (U = their number, nb their tiles):
  *  - 2 U <= num_workers and little else to do (a prefill chunk with no or few decodes beside it:

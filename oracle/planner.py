@@ -39,7 +39,9 @@ Rules
    ``ceil(F k / L) * (ceil(nb / k) + 1)`` over ``k = 1 .. nb``, smallest ``k``
    on ties (the ``+ 1`` is what a piece costs beyond its tiles).  Otherwise
    ``S = min(max(s, 2), max(16, min(64, floor(2 s / 5))))`` with
-   ``s = ceil(B / L)`` and ``B`` the sum of their ``nb``.
+   ``s = ceil(B / L)`` and ``B`` the sum of their ``nb``; where ``s <= 16`` and
+   the batch has no other families, the smallest ``S`` from ``max(s, 2)`` to
+   ``max(s + 1, floor(5 s / 4))`` that makes at most ``L`` pieces, if there is one.
    Wide families (more than 32 rows) of a DECODE / VERIFY sequence use ``S =
    16``, PREFILL ones are whole, unless a cut size ``T`` for all wide families,
    PREFILL too, is found.  ``U`` is the number of wide families:
@@ -146,14 +148,19 @@ def _slab(rows, d):
     return _ceil_div(rows * (d + 2), 4) * 4
 
 
-def _narrow_split(narrow, slots):
-    """Split size of the narrow families that may be cut: one (tiles, rows, is prefill) per family."""
+def _narrow_split(narrow, slots, alone):
+    """Split size of the narrow families that may be cut: one (tiles, rows, is prefill) per family.  alone: whether
+    the batch has no others."""
     lengths = {x[0] for x in narrow}
     if len(lengths) == 1:
         nb, families = narrow[0][0], len(narrow)
         best_k = min(range(1, nb + 1), key=lambda k: (_ceil_div(families * k, slots) * (_ceil_div(nb, k) + 1), k))
         return _ceil_div(nb, best_k)
     share = _ceil_div(sum(x[0] for x in narrow), slots)
+    if alone and share <= 16:
+        for size in range(max(share, 2), max(share + 1, 5 * share // 4) + 1):
+            if sum(_ceil_div(x[0], size) for x in narrow) <= slots:
+                return size
     return min(max(share, 2), max(16, min(64, 2 * share // 5)))
 
 
@@ -262,7 +269,7 @@ def plan_oracle(cfg, seqs):
         def choose(whole):
             """(fits XY_STATIC_WORKSPACE_BYTES, narrow size, wide size, wide floor), PREFILL whole up to that many tiles."""
             may_cut = [x for x in narrow if not x[2] or x[0] > whole]
-            size = _narrow_split(may_cut, 4 * w)
+            size = _narrow_split(may_cut, 4 * w, not wide and len(may_cut) == len(narrow))
             ws = sum(_ceil_div(nb, size) * _slab(rows, d) for nb, rows, _pre in may_cut if nb > size)
             wide_cut = _wide_cut(wide, narrow_tiles, narrow_load, ws, w, d, cfg["cost_row_floor"])
             for nb, rows, pre in wide:

@@ -34,6 +34,13 @@ constexpr int64_t kAutoSplitMin = 2, kAutoSplitPieceOverhead = 1;
 // two and a half pieces, at most two fifths of the share beyond (a piece costs about a tile and a half on top of
 // its own, and with some three pieces per wavefront the shared list still evens out), never more than 64
 constexpr int64_t kAutoSplitMaxSmall = 16, kAutoSplitMaxLarge = 64;
+// A share rounds to slightly more pieces than wavefronts as a rule, and the few left over are a second round at the pace of
+// a lone wavefront.  Where these families are the whole batch and the share is at most kAutoSplitMaxSmall, the size grows by up to a
+// quarter (at least one tile) if that makes one round of them.  Unit kernel and merge pass, us, share -> fitted size: 4 -> 5 59.3 -> 55.8,
+// 8 -> 9 (20 verify chains) 105.5 -> 93.2, 8 -> 10 91.3 -> 89.4, 10 -> 12 122.7 -> 114.7, 12 -> 13 149.9 -> 131.7, 14 -> 16
+// 173.9 -> 155.8, 15 -> 16 181.8 -> 163.4; further off it turns: 10 -> 13 110.3 -> 111.4, 14 -> 18 158.1 -> 159.7, 14 -> 32
+// 156.5 -> 184.7, and beyond that share 16 -> 30 232.6 -> 252.7.
+inline int64_t most_fitted(int64_t share) { return std::max(share + 1, 5 * share / 4); }
 constexpr int32_t kAutoSplitWide = 16;
 // Families of more than kNarrowRows rows (wide: a workgroup works on one unit at a time, whatever its rows, in time
 // proportional to its tiles).  A unit costs about two and a half tiles' time around its loop and a plan with cut
@@ -52,8 +59,8 @@ using XyTileClass = XyPlanScratch::TileClass;
 
 inline int64_t slab_floats(int64_t rows, int64_t d) { return ((rows * (d + 2) + 3) / 4) * 4; }
 
-// XY_SPLIT_AUTO: the split size of the families of at most kNarrowRows rows that may be cut
-int32_t narrow_split_size(const std::vector<XyTileClass>& narrow, const int64_t slots) {
+// XY_SPLIT_AUTO: the split size of the families of at most kNarrowRows rows that may be cut; alone: whether they are the batch
+int32_t narrow_split_size(const std::vector<XyTileClass>& narrow, const int64_t slots, const bool alone) {
   int64_t tiles = 0;
   bool uniform = true;
   for (const XyTileClass& w : narrow) {
@@ -76,6 +83,11 @@ int32_t narrow_split_size(const std::vector<XyTileClass>& narrow, const int64_t 
     return (int32_t)ceil_div(first_nb, best_k);
   }
   const int64_t share = ceil_div(tiles, slots);
+  for (int64_t size = std::max(share, kAutoSplitMin); alone && share <= kAutoSplitMaxSmall && size <= most_fitted(share); ++size) {
+    int64_t pieces = 0;
+    for (const XyTileClass& w : narrow) pieces += w.count * (((uint32_t)w.nb + (uint32_t)size - 1) / (uint32_t)size);
+    if (pieces <= slots) return (int32_t)size;
+  }
   const int64_t most = std::max<int64_t>(kAutoSplitMaxSmall, std::min<int64_t>(kAutoSplitMaxLarge, 2 * share / 5));
   return (int32_t)std::min<int64_t>(std::max<int64_t>(share, kAutoSplitMin), most);
 }
@@ -362,7 +374,7 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
         std::copy_if(narrow.begin(), narrow.end(), std::back_inserter(may_cut), [&](const XyTileClass& w) {
           return !w.prefill || w.nb > whole_tiles;
         });
-        split_narrow = narrow_split_size(may_cut, (int64_t)kNarrowSlotsPerWorker * W);
+        split_narrow = narrow_split_size(may_cut, (int64_t)kNarrowSlotsPerWorker * W, wide.empty() && may_cut.size() == narrow.size());
         const int64_t narrow_ws = narrow_workspace(may_cut, split_narrow, D);
         cut = wide_cut(most - narrow_ws);
         return narrow_ws + wide_workspace(wide, cut, D) <= most;

@@ -299,3 +299,19 @@ def test_wide_units_are_placed_by_their_time(floor, policy, rows, tiles):
         if floor == 127 and want is rows:
             continue            # 1024 against 1016 each: levels as by time
         assert [[int(x) for x in units["seq"][offs[w]:offs[w + 1]]] for w in range(2)] == want
+
+
+@pytest.mark.parametrize("tiles,wide,want", [
+    # four wavefronts; a share of 8 grows to 10 at most, of 3 to 4, of 16 to 20
+    ([20, 11], False, [10, 10, 5, 6]), ([11, 11, 10], False, [5, 6, 5, 6, 5, 5]), ([4, 4, 3], False, [4, 4, 3]),
+    ([20, 20, 20, 4], False, [20, 20, 20, 4]), ([20, 20, 20, 5], False, [10, 10] * 3 + [5]),
+    ([7, 9], False, [3, 4, 4, 5]),                      # five pieces of four, the share; four of five
+    ([20, 11], True, [6, 7, 7, 5, 6])])                 # beside a unit of 40 rows: the share
+def test_a_batch_of_narrow_families_fills_the_wavefronts_once(tiles, wide, want):
+    cfg = X.xy_attn_default_config(1, 1, 64, num_workers=1)
+    seqs = [(1, 128 * t - 1, 1, 0, 0) for t in tiles] + [(40, 0, 0, 0, 0)] * wide
+    compare(cfg, seqs)
+    units, _, _, _ = PL.plan_oracle(cfg.as_dict(), seqs)
+    got = sorted((int(u["seq"]), int(u["kv_block_begin"]), int(u["kv_block_end"] - u["kv_block_begin"]))
+                 for u in units if u["seq"] < len(tiles))
+    assert [x[2] for x in got] == want

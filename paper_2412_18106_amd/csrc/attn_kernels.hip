@@ -1782,26 +1782,30 @@ struct XyLayout {
   int64_t halved;       // units handed out as two halves
   int32_t team;         // wavefronts that share a narrow unit, 2 or 4, or 0
 };
-static XyLayout layout_of(const xy_attn_plan* plan) {
+// (leaves the halved units, worker and unit number of each, in scratch.count)
+static XyLayout layout_of(xy_attn_plan* plan) {
   const int64_t units = plan->narrow_units, slices = plan->narrow_slices, W = plan->cfg.num_workers;
   if (plan->units.empty()) return {0, 0};
   int64_t halved = 0, idle = W, free = W;       // workers without units, without wide units
   bool divisible = true;
+  std::vector<int32_t>& halves = plan->scratch.count;
+  halves.clear();
   if (units < (int64_t)plan->units.size()) {
     const xy_work_unit* const u = plan->units.data();
     const int32_t* const offsets = plan->worker_offsets.data();
-    for (int64_t w = 0; w < W; ++w) idle -= offsets[w + 1] > offsets[w];
     for (int64_t w = 0; w < W; ++w) {
+      if (offsets[w] == offsets[w + 1]) continue;
+      --idle;
       int32_t wide = 0;
       for (int32_t i = offsets[w]; i < offsets[w + 1]; ++i) {
         const int32_t rows = u[i].q_count * u[i].head_count;
         wide += rows > 32;
         if (rows <= kHalfRows) continue;
-        ++halved;
+        if (++halved > idle) return {0, 0};
+        halves.insert(halves.end(), {(int32_t)w, i});
         divisible &= first_half(u[i]) * u[i].head_count <= kHalfRows;
       }
       free -= wide > 0;
-      if (halved > idle) return {0, 0};
     }
     if (halved && (!divisible || halved > idle || units > (int64_t)(kThreads / 64) * (idle - halved))) return {0, 0};
     free -= halved;
@@ -1861,7 +1865,8 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
     second_of.assign(W, -1);                                    // (the planner left room for W)
     // the second half goes to an idle worker of the same chiplet if there is one: both read the same K/V
     const int32_t per_chip = W % kXcds == 0 ? W / kXcds : W;
-    std::vector<int32_t>& idle = plan->scratch.count;           // the next worker to look at, per chiplet
+    const std::vector<int32_t>& halves = plan->scratch.count;
+    std::vector<int32_t>& idle = plan->scratch.order;           // the next worker to look at, per chiplet
     idle.assign(W / per_chip, 0);
     auto next_idle = [&](const int32_t chip) {
       for (int32_t& at = idle[chip]; at < per_chip; ++at) {
@@ -1870,13 +1875,11 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
       }
       return -1;
     };
-    for (int32_t w = 0; w < W; ++w)
-      for (int32_t i = plan->worker_offsets[w]; i < plan->worker_offsets[w + 1]; ++i) {
-        if (plan->units[i].q_count * plan->units[i].head_count <= kHalfRows) continue;
-        int32_t to = next_idle(w / per_chip);
-        for (int32_t chip = 0; to < 0; ++chip) to = next_idle(chip);       // there are as many idle workers as halves
-        second_of[to] = i;
-      }
+    for (size_t x = 0; x < halves.size(); x += 2) {
+      int32_t to = next_idle(halves[x] / per_chip);
+      for (int32_t chip = 0; to < 0; ++chip) to = next_idle(chip);       // there are as many idle workers as halves
+      second_of[to] = halves[x + 1];
+    }
   }
   int32_t emitted = 0, free_workers = 0;
   const xy_work_unit* const units = plan->units.data();
@@ -1893,21 +1896,27 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
       const int32_t flags = u.kind_flags | (u.q_count * u.head_count) << kSlabRowsShift | (first_token * u.head_count) << kSlabFirstShift;
       du[emitted++] = record(u, u.q_begin + first_token, tokens, flags);
     };
+    const int32_t* const second = halved ? second_of.data() : nullptr;
     for (int32_t w = 0; w < W; ++w) {
       offsets[w] = emitted;
       for (int32_t i = lists[w]; i < lists[w + 1]; ++i) {
         if (team && is_narrow(units[i])) continue;
         emit(units[i], 0, halved && units[i].q_count * units[i].head_count > kHalfRows ? first_half(units[i]) : units[i].q_count);
       }
-      if (halved && second_of[w] >= 0) {
-        const xy_work_unit& u = units[second_of[w]];
+      if (second && second[w] >= 0) {
+        const xy_work_unit& u = units[second[w]];
         emit(u, first_half(u), u.q_count - first_half(u));
       }
     }
     offsets[W] = emitted;
     // the shared list; with teams every narrow unit is on it
-    for (size_t i = team ? 0 : (size_t)lists[W]; i < plan->units.size(); ++i)
-      if (!team || is_narrow(units[i])) emit(units[i], 0, units[i].q_count);
+    const int32_t all = (int32_t)plan->units.size();
+    if (team) {
+      for (int32_t i = 0; i < all; ++i)
+        if (is_narrow(units[i])) emit(units[i], 0, units[i].q_count);
+    } else {
+      for (int32_t i = lists[W]; i < all; ++i) du[emitted++] = record(units[i], units[i].q_begin, units[i].q_count, units[i].kind_flags);
+    }
   } else {
     emitted = (int32_t)plan->units.size();
     for (int32_t i = 0; i < emitted; ++i) du[i] = record(units[i], units[i].q_begin, units[i].q_count, units[i].kind_flags);

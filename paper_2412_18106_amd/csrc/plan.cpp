@@ -662,6 +662,8 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
     plan->worker_offsets.assign(W + 1, 0);
     for (int64_t w = 0; w < W; ++w) plan->worker_offsets[w + 1] = plan->worker_offsets[w] + count[w];
     plan->units.resize(fam.size());
+    plan->scratch.count.reserve(2 * W);        // the upload keeps lists in these
+    plan->scratch.order.reserve(W);
     std::vector<int32_t>& cursor = plan->scratch.cursor;
     cursor.assign(plan->worker_offsets.begin(), plan->worker_offsets.end() - 1);
     int32_t shared_cursor = plan->worker_offsets[W];        // the shared list follows the workers' lists

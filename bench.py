@@ -48,7 +48,7 @@ TRAFFIC = {"sources_sha256_16": "fabc76678e324823", "bytes": {2: 1279428608, 3: 
 
 def sources_digest():
     h = hashlib.sha256()
-    for rel in ("paper_2412_18106_amd/csrc/attn_kernels.hip", "paper_2412_18106_amd/csrc/plan.cpp"):
+    for rel in ("paper_2412_18106_amd/csrc/attn_kernels.hip", "paper_2412_18106_amd/csrc/plan.cpp", "paper_2412_18106_amd/csrc/layout.cpp"):
         with open(os.path.join(ROOT, rel), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -44,6 +44,26 @@ enum { XY_MIX_NONE = 0, XY_MIX_EVEN_4 = 1, XY_MIX_UNEVEN_8_0 = 2, XY_MIX_DOT2 = 
        XY_MIX_ATTENTION = 5 };
 int xy_probe_issue_mix(int32_t mix, int32_t iters, void* cycles, void* sink, void* hip_stream);
 
+/* How the units of a plan go to the GPU, worked out on the host as every upload does it (no GPU is touched; the plan that
+ * xy_attn_plan_get shows and what is on the GPU stay as they are). */
+typedef struct {
+  int32_t row_tiles;      /* 32-row tiles a wavefront holds on a unit of more than 32 rows: 2, or 1 where no unit is handed
+                             out with more than 128 rows */
+  int32_t halved;         /* units handed out as two halves, by their tokens, to a worker each */
+  int32_t narrow_team;    /* wavefronts that share a unit of at most 32 rows: 4 or 2, 0 where each takes a whole one */
+  int32_t narrow_short;   /* 1: a wavefront takes such units in the way made for short ones (without teams) */
+  int32_t narrow_depth;   /* else the 32-key slices it keeps in flight: 1 or 2 */
+  int32_t records;        /* units as they are handed out, second halves among them */
+} xy_probe_layout;
+/*   records  host, capacity records of 64 bytes, or NULL: int32 seq, first head, heads, first token, tokens, first and last + 1
+ *            K/V tile, kind | mask << 2 (| rows of its family's partial results << 8 | its first row among them << 20 with
+ *            teams, and with row_tiles = 1 on a worker's list), int64 ws_offset, mask_word_offset, int32 query_len,
+ *            context_len, first token of the sequence among the packed ones, KV head
+ *   lists    host, 2 num_workers + 1 entries, NULL with records: worker w owns records[lists[w] .. lists[w + 1]), the shared
+ *            list starts at lists[num_workers]; behind that, per worker, its number among those that own none, or -1
+ * Errors: XY_ERR_ARG, XY_ERR_CAPACITY (more records than that; *out is filled in). */
+int xy_probe_plan_layout(xy_attn_plan* plan, xy_probe_layout* out /* host */, void* records, int64_t capacity, int32_t* lists);
+
 #ifdef __cplusplus
 }
 #endif

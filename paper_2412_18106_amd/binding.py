@@ -75,6 +75,10 @@ class xy_chunk_entry(C.Structure):
     _fields_ = [("request", C.c_int32), ("kind", C.c_int32), ("query_len", C.c_int32), ("context_len", C.c_int32)]
 
 
+class xy_probe_layout(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("row_tiles", "halved", "narrow_team", "narrow_short", "narrow_depth", "records")]
+
+
 _plan_p = C.c_void_p
 _lib.xy_attn_default_config.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.POINTER(xy_attn_config)]
 _lib.xy_attn_plan_create.argtypes = [C.POINTER(xy_attn_config), C.c_void_p, C.c_int32, C.POINTER(_plan_p)]
@@ -111,6 +115,7 @@ _lib.xy_probe_stream_read.argtypes = [C.c_void_p, C.c_size_t, C.c_void_p, C.c_vo
 _lib.xy_probe_stream_read_once.argtypes = [C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p]
 _lib.xy_probe_mfma.argtypes = [C.c_int32, C.c_void_p, C.c_void_p]
 _lib.xy_probe_issue_mix.argtypes = [C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
+_lib.xy_probe_plan_layout.argtypes = [_plan_p, C.POINTER(xy_probe_layout), C.c_void_p, C.c_int64, C.c_void_p]
 _lib.xy_attn_plan_destroy.argtypes = [_plan_p]
 _lib.xy_attn_plan_destroy.restype = None
 _lib.xy_attn_strerror.argtypes = [C.c_int]
@@ -118,7 +123,7 @@ _lib.xy_attn_strerror.restype = C.c_char_p
 for _f in ("xy_attn_default_config", "xy_attn_plan_create", "xy_attn_plan_rebuild", "xy_attn_plan_get",
            "xy_attn_plan_workspace_bytes", "xy_attn_plan_upload", "xy_attn_plan_upload_async", "xy_attn_run", "xy_attn_run_phase",
            "xy_attn_run_static", "xy_attn_append_kv", "xy_attn_run_fused_qkv", "xy_probe_stream_read", "xy_probe_stream_read_once",
-           "xy_probe_mfma", "xy_probe_issue_mix", "xy_attn_copy_block_rows", "xy_serve_schedule_chunk", "xy_kv_create", "xy_kv_open",
+           "xy_probe_mfma", "xy_probe_issue_mix", "xy_probe_plan_layout", "xy_attn_copy_block_rows", "xy_serve_schedule_chunk", "xy_kv_create", "xy_kv_open",
            "xy_kv_extend", "xy_kv_block_row", "xy_kv_close", "xy_kv_stats"):
     getattr(_lib, _f).restype = C.c_int
 
@@ -126,7 +131,8 @@ EXPORTED = ("xy_attn_default_config", "xy_attn_plan_create", "xy_attn_plan_rebui
             "xy_attn_plan_workspace_bytes", "xy_attn_plan_upload", "xy_attn_plan_upload_async", "xy_attn_run", "xy_attn_run_phase",
             "xy_attn_run_static", "xy_attn_append_kv", "xy_attn_run_fused_qkv", "xy_attn_copy_block_rows",
             "xy_attn_plan_destroy", "xy_attn_strerror")
-EXPORTED_PROBE = ("xy_probe_stream_read", "xy_probe_stream_read_once", "xy_probe_mfma", "xy_probe_issue_mix")
+EXPORTED_PROBE = ("xy_probe_stream_read", "xy_probe_stream_read_once", "xy_probe_mfma", "xy_probe_issue_mix",
+                  "xy_probe_plan_layout")
 EXPORTED_SERVE = ("xy_serve_schedule_chunk", "xy_kv_create", "xy_kv_destroy", "xy_kv_open", "xy_kv_extend",
                   "xy_kv_block_row", "xy_kv_close", "xy_kv_stats")
 
@@ -320,6 +326,22 @@ def xy_probe_issue_mix(mix, iters, cycles, sink, stream=None):
     cycles: device int64 tensor of 1024 elements."""
     assert cycles.numel() >= 1024 and cycles.element_size() == 8
     _check(_lib.xy_probe_issue_mix(int(mix), int(iters), _ptr(cycles), _ptr(sink), _stream(stream)))
+
+
+_RECORD_DTYPE = np.dtype([(n, np.int32) for n in ("seq", "head_begin", "head_count", "q_begin", "q_count", "kv_block_begin",
+                                                  "kv_block_end", "flags")] +
+                         [("ws_offset", np.int64), ("mask_word_offset", np.int64)] +
+                         [(n, np.int32) for n in ("query_len", "context_len", "token_start", "kv_head")])
+
+
+def xy_probe_plan_layout(plan, num_workers):
+    """(xy_probe_layout, records, worker_offsets, ranks) of a plan: how its units are handed out (host only)."""
+    layout = xy_probe_layout()
+    _check(_lib.xy_probe_plan_layout(plan, C.byref(layout), None, 0, None))
+    records = np.zeros(max(1, layout.records), dtype=_RECORD_DTYPE)
+    lists = np.zeros(2 * num_workers + 1, dtype=np.int32)
+    _check(_lib.xy_probe_plan_layout(plan, C.byref(layout), records.ctypes.data, layout.records, lists.ctypes.data))
+    return layout, records[:layout.records], lists[:num_workers + 1], lists[num_workers + 1:]
 
 
 def xy_attn_copy_block_rows(copies, num_kv_heads, k_cache, v_cache, stream=None):

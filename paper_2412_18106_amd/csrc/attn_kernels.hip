@@ -52,24 +52,9 @@ constexpr int kThreads = 256;        // 4 wavefronts: one per SIMD
 constexpr int kMergeThreads = 256, kMergeRows = kMergeThreads / 32;     // rows of a family merged by one workgroup
 // workgroups of one launch (a launch of 2^32 threads or more runs those modulo 2^32, without an error)
 constexpr int64_t kMergeGrid = 1 << 22, kAppendGrid = 1 << 22;
-// How a launch processes its units of at most 32 rows, by what they are on average over the
-// launch; wavefronts are four per worker.  A unit on two slices costs some 200 instructions more than a short one, which
-// a lone wavefront pays for with 0.3 us, and gains where it waits for memory in every slice, with its neighbours idle.
-// Decodes of 32 heads in 8, each a unit of its own, us short / two slices: 4 slices 7.1 / 7.3 (8 units), 9.3 / 9.2 (512),
-// 24.4 / 24.7 (2048), 47.9 / 49.2 (4096); 1 and 2 slices 2 to 13 % less short; 8 slices 11.3 / 10.8, 14.5 / 13.6 up to a
-// unit for every second wavefront, 22.4 / 22.5 at one each, 89.4 / 91.6 at four: so up to four slices a unit are short,
-// up to eight where there are more units than wavefronts.  Units of 32 rows, whose Q is eight times as much: 4096 of them
-// 42.1 / 44.8 with 2 slices, 66.4 / 65.7 with 4: up to two slices above 16 rows a unit.
-constexpr int64_t kShortSlices = 4, kShortSlicesManyUnits = 8, kShortSlicesManyRows = 2, kManyRows = 16;
-// Longer ones: two slices in flight up to kDeepTiles tiles a wavefront, one beyond (see process_solo; measured at 7.5
-// tiles, 3 % in favour of two, and at 14, 1 % against).
-constexpr int64_t kDeepTiles = 10;
 constexpr float kPrescaleMaxC = 0.25f;    // largest c = scale * log2(e) that is folded into Q (wide units)
 // Dynamic assignment: the cursor of the shared list, kDoneGroups counts of finished workgroups and the
 // count of finished groups, kCounterStride ints (one 128-byte line) apart.
-// XyDevUnit::flags: kind and mask in the low bits; where wide units are on one row tile also the rows of the family's partial
-// results and the unit's first row among them
-constexpr int kSlabRowsShift = 8, kSlabFirstShift = 20;
 constexpr int kDoneGroups = 8;
 constexpr int kCounterStride = 32;
 constexpr float kLazyRescale = 8.0f;      // log2 units the running max may lag behind
@@ -1757,75 +1742,15 @@ __global__ __launch_bounds__(256) void xy_plan_copy_kernel(const uint4* __restri
   if (i < chunks) dst[i] = src[i];
 }
 
-// Units of more than kHalfRows rows that go to the GPU as two, by their tokens, for a worker each: all of them or none.
-// The kernel then holds one row tile a wavefront instead of two, which takes two thirds of the time for units
-// that are alone (64 tokens x 4 heads on 1 / 4 / 16 K/V tiles, 8 units: 12.6 / 19.6 / 47.5 -> 9.1 / 13.6 / 32.9 us), but
-// reads the K/V twice and keeps two workers busy: only where there are idle workers for all second halves, with a
-// wavefront left for every narrow unit (a suffix of 150-250 tokens beside 472 narrow units 254.9 -> 266.0 us for eight layers
-// and a chunk of 512 beside 1184 157 -> 164 us where there is not).  The plan the caller sees stays as it is.
-constexpr int32_t kHalfRows = 128, kXcds = 8;
-static int32_t first_half(const xy_work_unit& u) { return (u.q_count + 1) / 2; }
-// Wavefronts that share a narrow unit, for launches that have fewer such units than wavefronts: four while every unit can
-// have a worker without wide units to itself, two while half of one, else none.  Unit kernel, us, one wavefront a unit / team (decodes of 32 heads
-// in 8, caches cold):
-//   units   2 slices (64 keys)    4            8            16           63
-//   8       5.7 / 5.8             8.3 / 6.5    11.2 / 8.4   18.2 / 10.4  60.2 / 23.7
-//   224     6.8 / 6.8             8.6 / 8.1    12.2 / 10.6  19.4 / 14.1  61.4 / 39.1
-//   256     6.0 / 6.9             8.3 / 8.4    12.4 / 11.2  19.5 / 15.5  62.0 / 43.9
-//   264     7.1 / 7.4 (two)       9.1 / 9.8    12.9 / 12.4  20.1 / 19.2  62.2 / 59.0
-//   512     7.5 / 8.3             10.2 / 11.4  15.6 / 15.1  25.9 / 24.8  85.3 / 84.5
-// so a team of four takes units of three slices and more on average, a team of two those of eight.
-constexpr int64_t kTeamOf4Slices = 3, kTeamOf2Slices = 8;
-static bool is_narrow(const xy_work_unit& u) { return u.q_count * u.head_count <= 32; }
-
-struct XyLayout {
-  int64_t halved;       // units handed out as two halves
-  int32_t team;         // wavefronts that share a narrow unit, 2 or 4, or 0
-};
-// (leaves the halved units, worker and unit number of each, in scratch.count)
-static XyLayout layout_of(xy_attn_plan* plan) {
-  const int64_t units = plan->narrow_units, slices = plan->narrow_slices, W = plan->cfg.num_workers;
-  if (plan->units.empty()) return {0, 0};
-  int64_t halved = 0, idle = W, free = W;       // workers without units, without wide units
-  bool divisible = true;
-  std::vector<int32_t>& halves = plan->scratch.count;
-  halves.clear();
-  if (units < (int64_t)plan->units.size()) {
-    const xy_work_unit* const u = plan->units.data();
-    const int32_t* const offsets = plan->worker_offsets.data();
-    for (int64_t w = 0; w < W; ++w) {
-      if (offsets[w] == offsets[w + 1]) continue;
-      --idle;
-      int32_t wide = 0;
-      for (int32_t i = offsets[w]; i < offsets[w + 1]; ++i) {
-        const int32_t rows = u[i].q_count * u[i].head_count;
-        wide += rows > 32;
-        if (rows <= kHalfRows) continue;
-        if (++halved > idle) return {0, 0};
-        halves.insert(halves.end(), {(int32_t)w, i});
-        divisible &= first_half(u[i]) * u[i].head_count <= kHalfRows;
-      }
-      free -= wide > 0;
-    }
-    if (halved && (!divisible || halved > idle || units > (int64_t)(kThreads / 64) * (idle - halved))) return {0, 0};
-    free -= halved;
-  }
-  // (the kernels with teams hold one row tile: no unit has more than kHalfRows rows here)
-  const int32_t team = units == 0 ? 0 : units <= free ? (slices >= kTeamOf4Slices * units ? 4 : 0)
-                       : units <= 2 * free && slices >= kTeamOf2Slices * units ? 2 : 0;
-  return {halved, team};
-}
-
 static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return XY_ERR_HIP;
   if (plan->device >= 0 && plan->device != dev) return XY_ERR_ARG;      // the plan lives on another device
   auto round_up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   const bool shared_list = plan->worker_offsets.back() < (int64_t)plan->units.size();
-  const auto [halved, team] = layout_of(plan);
-  const size_t num_units = plan->units.size() + halved;
+  const XyLayout layout = xy_plan_layout(plan);
   const size_t off_units = 0;
-  const size_t off_offsets = off_units + round_up(num_units * sizeof(XyDevUnit));
+  const size_t off_offsets = off_units + round_up((size_t)layout.records * sizeof(XyDevUnit));
   const size_t off_seqs = off_offsets + round_up(2 * plan->worker_offsets.size() * sizeof(int32_t));
   const size_t off_merges = off_seqs + round_up((size_t)plan->num_seqs * sizeof(XyDevSeq));
   int64_t merge_groups = 0;       // workgroups of the merge pass
@@ -1854,78 +1779,8 @@ static int plan_copy_to_device(xy_attn_plan* plan, hipStream_t stream) {
     return XY_ERR_HIP;              // (the copy before this one has long finished in any sensible use)
   }
   unsigned char* h = static_cast<unsigned char*>(plan->h_stage);
-  XyDevUnit* du = reinterpret_cast<XyDevUnit*>(h + off_units);
-  const int32_t group = plan->cfg.num_q_heads / plan->cfg.num_kv_heads;
-  const int32_t W = (int32_t)plan->worker_offsets.size() - 1;
-  int32_t* const offsets = reinterpret_cast<int32_t*>(h + off_offsets);
-  // behind the offsets: a worker's number among the workers that have no units of their own, -1 where it has some
-  int32_t* const rank = offsets + W + 1;
-  std::vector<int32_t>& second_of = plan->scratch.cursor;      // worker -> the unit whose second half it gets, or -1
-  if (halved) {
-    second_of.assign(W, -1);                                    // (the planner left room for W)
-    // the second half goes to an idle worker of the same chiplet if there is one: both read the same K/V
-    const int32_t per_chip = W % kXcds == 0 ? W / kXcds : W;
-    const std::vector<int32_t>& halves = plan->scratch.count;
-    std::vector<int32_t>& idle = plan->scratch.order;           // the next worker to look at, per chiplet
-    idle.assign(W / per_chip, 0);
-    auto next_idle = [&](const int32_t chip) {
-      for (int32_t& at = idle[chip]; at < per_chip; ++at) {
-        const int32_t w = chip * per_chip + at;
-        if (plan->worker_offsets[w] == plan->worker_offsets[w + 1] && second_of[w] < 0) return w;
-      }
-      return -1;
-    };
-    for (size_t x = 0; x < halves.size(); x += 2) {
-      int32_t to = next_idle(halves[x] / per_chip);
-      for (int32_t chip = 0; to < 0; ++chip) to = next_idle(chip);       // there are as many idle workers as halves
-      second_of[to] = halves[x + 1];
-    }
-  }
-  int32_t emitted = 0, free_workers = 0;
-  const xy_work_unit* const units = plan->units.data();
-  const xy_seq_desc* const descs = plan->descs.data();
-  const int32_t *const starts = plan->token_start.data(), *const lists = plan->worker_offsets.data();
-  auto record = [=](const xy_work_unit& u, const int32_t q_begin, const int32_t q_count, const int32_t flags) {
-    const xy_seq_desc& sd = descs[u.seq];
-    return XyDevUnit{u.seq, u.head_begin, u.head_count, q_begin, q_count, u.kv_block_begin, u.kv_block_end, flags, u.ws_offset,
-                     sd.mask_word_offset, sd.query_len, sd.context_len, starts[u.seq], u.head_begin / group};
-  };
-  plan->row_tiles = !halved && plan->most_rows > kHalfRows ? 2 : 1;
-  if (team || (plan->row_tiles == 1 && plan->most_rows > 32)) {
-    auto emit = [&](const xy_work_unit& u, const int32_t first_token, const int32_t tokens) {
-      const int32_t flags = u.kind_flags | (u.q_count * u.head_count) << kSlabRowsShift | (first_token * u.head_count) << kSlabFirstShift;
-      du[emitted++] = record(u, u.q_begin + first_token, tokens, flags);
-    };
-    const int32_t* const second = halved ? second_of.data() : nullptr;
-    for (int32_t w = 0; w < W; ++w) {
-      offsets[w] = emitted;
-      for (int32_t i = lists[w]; i < lists[w + 1]; ++i) {
-        if (team && is_narrow(units[i])) continue;
-        emit(units[i], 0, halved && units[i].q_count * units[i].head_count > kHalfRows ? first_half(units[i]) : units[i].q_count);
-      }
-      if (second && second[w] >= 0) {
-        const xy_work_unit& u = units[second[w]];
-        emit(u, first_half(u), u.q_count - first_half(u));
-      }
-    }
-    offsets[W] = emitted;
-    // the shared list; with teams every narrow unit is on it
-    const int32_t all = (int32_t)plan->units.size();
-    if (team) {
-      for (int32_t i = 0; i < all; ++i)
-        if (is_narrow(units[i])) emit(units[i], 0, units[i].q_count);
-    } else {
-      for (int32_t i = lists[W]; i < all; ++i) du[emitted++] = record(units[i], units[i].q_begin, units[i].q_count, units[i].kind_flags);
-    }
-  } else {
-    emitted = (int32_t)plan->units.size();
-    for (int32_t i = 0; i < emitted; ++i) du[i] = record(units[i], units[i].q_begin, units[i].q_count, units[i].kind_flags);
-    memcpy(offsets, lists, plan->worker_offsets.size() * sizeof(int32_t));
-  }
-  for (int32_t w = 0; w < W; ++w) rank[w] = offsets[w + 1] == offsets[w] ? free_workers++ : -1;
-  plan->narrow_team = team;
-  plan->free_workers = free_workers;
-  plan->device_units = emitted;
+  plan->layout = layout;
+  plan->free_workers = xy_plan_hand_out(plan, layout, reinterpret_cast<XyDevUnit*>(h + off_units), reinterpret_cast<int32_t*>(h + off_offsets));
   XyDevSeq* ds = reinterpret_cast<XyDevSeq*>(h + off_seqs);
   for (int32_t i = 0; i < plan->num_seqs; ++i) {
     const xy_seq_desc& s = plan->descs[i];
@@ -2024,22 +1879,19 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
   p.page_shift = plan->cfg.block_size == 16 ? 4 : plan->cfg.block_size == 32 ? 5 : plan->cfg.block_size == 64 ? 6 : 7;
   p.num_workers = plan->cfg.num_workers;
   p.free_workers = plan->free_workers;
-  p.num_units = plan->device_units;
-  const int64_t wavefronts = (int64_t)(kThreads / 64) * plan->cfg.num_workers;
-  const int64_t short_slices = plan->narrow_rows > kManyRows * plan->narrow_units ? kShortSlicesManyRows
-                               : plan->narrow_units > wavefronts ? kShortSlicesManyUnits : kShortSlices;
-  const bool short_units = plan->narrow_units > 0 && plan->narrow_slices <= short_slices * plan->narrow_units;
-  p.narrow_depth = plan->narrow_team || plan->narrow_tiles <= kDeepTiles * wavefronts ? 2 : 1;
+  p.num_units = plan->layout.records;
+  p.narrow_depth = plan->layout.depth;
   p.counters = static_cast<int32_t*>(plan->d_counters);
   p.c = softmax_scale * 1.4426950408889634f;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (phases & XY_PHASE_UNITS) {
-    const auto kernel = plan->narrow_team == 4 ? xy_attn_units_kernel<4, 1>
-                        : plan->narrow_team == 2 ? xy_attn_units_kernel<2, 1>
-                        : plan->row_tiles == 2 ? (short_units ? xy_attn_units_kernel<kShort, 2> : xy_attn_units_kernel<kSolo, 2>)
-                                                : (short_units ? xy_attn_units_kernel<kShort, 1> : xy_attn_units_kernel<kSolo, 1>);
+    const XyLayout& l = plan->layout;
+    const auto kernel = l.team == 4 ? xy_attn_units_kernel<4, 1>
+                        : l.team == 2 ? xy_attn_units_kernel<2, 1>
+                        : l.row_tiles == 2 ? (l.short_units ? xy_attn_units_kernel<kShort, 2> : xy_attn_units_kernel<kSolo, 2>)
+                                           : (l.short_units ? xy_attn_units_kernel<kShort, 1> : xy_attn_units_kernel<kSolo, 1>);
     // teams without wide units need no workgroup more than there are units
-    const int32_t workgroups = plan->narrow_team && p.free_workers == p.num_workers ? std::min(p.num_workers, p.num_units) : p.num_workers;
+    const int32_t workgroups = l.team && p.free_workers == p.num_workers ? std::min(p.num_workers, p.num_units) : p.num_workers;
     hipLaunchKernelGGL(kernel, dim3(workgroups), dim3(kThreads), 0, stream, p);
     if (hipGetLastError() != hipSuccess) return XY_ERR_HIP;
   }

@@ -14,6 +14,19 @@ struct XyDevUnit {
   int32_t q_len, ctx_len, token_start, kv_head;
 };
 static_assert(sizeof(XyDevUnit) == 64, "one aligned scalar load");
+// XyDevUnit::flags: kind and mask in the low bits; where wide units are on one row tile also the rows of the family's partial
+// results and the unit's first row among them
+constexpr int kSlabRowsShift = 8, kSlabFirstShift = 20;
+
+// How a launch takes the units of a plan (layout.cpp).
+struct XyLayout {
+  int32_t records = 0;                      // units as they are handed out, second halves among them
+  int32_t halved = 0;                       // units handed out as two halves
+  int32_t row_tiles = 2;                    // of a wavefront on a wide unit
+  int32_t team = 0;                         // wavefronts that share a narrow unit, 2 or 4; else 0
+  int32_t depth = 2;                        // slices a wavefront keeps in flight on a narrow unit that is not short
+  bool short_units = false;                 // narrow units are processed as short ones
+};
 
 // Per-sequence record read by the append kernel.
 struct XyDevSeq {
@@ -58,9 +71,7 @@ struct xy_attn_plan {
   int64_t workspace_floats = 0;
   int64_t merge_groups = 0;                 // workgroups of the merge pass (of the tables last copied to the GPU)
   int32_t free_workers = 0;                 // workers without units of their own (of the tables last copied to the GPU)
-  int32_t device_units = 0;                 // records of units (of the tables last copied to the GPU)
-  int32_t narrow_team = 0;                  // wavefronts that share a narrow unit, 2 or 4; else 0 (of the tables last copied to the GPU)
-  int32_t row_tiles = 2;                    // of a wavefront on a wide unit (of the tables last copied to the GPU)
+  XyLayout layout;                          // of the tables last copied to the GPU
   int32_t most_rows = 0;                    // most rows of a unit
   int64_t narrow_units = 0, narrow_rows = 0, narrow_tiles = 0, narrow_slices = 0;     // units of at most 32 rows, their rows, K/V tiles and 32-key slices
   bool has_tree = false;
@@ -81,5 +92,10 @@ struct xy_attn_plan {
   void* d_counters = nullptr;               // XY_ASSIGN_DYNAMIC: shared-list cursor and finished-workgroup counts (null without a shared list)
 };
 
+// layout.cpp; host only.  xy_plan_hand_out fills the tables of the unit kernel for the layout xy_plan_layout has just worked
+// out: the records, and behind each other the workers' offsets (W + 1; the shared list follows the last worker's) and ranks
+// (W; a worker's number among those that have no units of their own, -1 where it has some).  Returns how many have none.
+XyLayout xy_plan_layout(xy_attn_plan* plan);
+int32_t xy_plan_hand_out(xy_attn_plan* plan, const XyLayout& layout, XyDevUnit* records, int32_t* offsets);
 // Implemented in the HIP translation unit; frees the arena, the staging buffer and the event.
 void xy_plan_free_device(xy_attn_plan* plan);

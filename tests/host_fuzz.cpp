@@ -9,6 +9,7 @@
 #include <set>
 #include <vector>
 
+#include "xy_probe.h"
 #include "xy_serve.h"
 
 // the planner frees a plan's GPU memory through this hook; there is none here
@@ -79,6 +80,33 @@ void check_plan(const xy_attn_plan* plan, const xy_attn_config& cfg, const std::
   for (int64_t i = 0; i < nm; ++i) CHECK(merges[i].num_splits >= 2 && merges[i].ws_offset >= 0);
 }
 
+// the tables as they are handed out: as many rows as the plan, lists in order, a rank for every worker without units
+void check_layout(xy_attn_plan* plan, const xy_attn_config& cfg) {
+  const xy_work_unit* units = nullptr;
+  int64_t n = 0, rows = 0;
+  CHECK(xy_attn_plan_get(plan, &units, &n, nullptr, nullptr, nullptr) == XY_OK);
+  for (int64_t i = 0; i < n; ++i) rows += (int64_t)units[i].q_count * units[i].head_count;
+  xy_probe_layout l;
+  CHECK(xy_probe_plan_layout(plan, &l, nullptr, 0, nullptr) == XY_OK && l.records == n + l.halved);
+  std::vector<int64_t> records((size_t)l.records * 8 + 1);             // 64 bytes each
+  const int32_t W = cfg.num_workers;
+  std::vector<int32_t> lists((size_t)2 * W + 1);
+  CHECK(xy_probe_plan_layout(plan, &l, records.data(), l.records, lists.data()) == XY_OK);
+  for (int32_t i = 0; i < l.records; ++i) {
+    const int32_t* r = reinterpret_cast<const int32_t*>(records.data()) + 16 * i;
+    rows -= (int64_t)r[2] * r[4];
+    if (l.halved) CHECK(r[2] * r[4] <= 128);
+  }
+  CHECK(rows == 0 && lists[0] == 0 && lists[W] <= l.records);
+  std::set<int32_t> ranks;
+  int32_t idle = 0;
+  for (int32_t w = 0; w < W; ++w) {
+    CHECK(lists[w] <= lists[w + 1] && (lists[w] < lists[w + 1]) == (lists[W + 1 + w] < 0));
+    if (lists[W + 1 + w] >= 0) ++idle, ranks.insert(lists[W + 1 + w]);
+  }
+  CHECK((int32_t)ranks.size() == idle && (ranks.empty() || *ranks.rbegin() == idle - 1));
+}
+
 void fuzz_planner(int rounds) {
   xy_attn_plan* reused = nullptr;
   for (int r = 0; r < rounds; ++r) {
@@ -125,6 +153,7 @@ void fuzz_planner(int rounds) {
     if (!reused) CHECK(xy_attn_plan_create(&cfg, nullptr, 0, &reused) == XY_OK);
     CHECK(xy_attn_plan_rebuild(reused, &cfg, descs.data(), (int32_t)descs.size()) == XY_OK);
     check_plan(reused, cfg, descs);
+    check_layout(reused, cfg);
     // refused inputs leave no damage
     if (!descs.empty()) {
       std::vector<xy_seq_desc> bad = descs;

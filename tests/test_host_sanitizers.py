@@ -1,4 +1,4 @@
-"""The host-side C++ (planner, chunk scheduler, K/V block manager) under AddressSanitizer and
+"""The host-side C++ (planner, layout of its units, chunk scheduler, K/V block manager) under AddressSanitizer and
 UndefinedBehaviorSanitizer: tests/host_fuzz.cpp is built with the host compiler (no HIP, no GPU) and run."""
 import os
 import shutil
@@ -17,7 +17,7 @@ def test_planner_scheduler_and_block_manager_fuzz_under_asan_and_ubsan(tmp_path)
     exe = str(tmp_path / "host_fuzz")
     cmd = [cxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
            "-fno-omit-frame-pointer", "-static-libasan", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           os.path.join(ROOT, "tests", "host_fuzz.cpp"), os.path.join(CSRC, "plan.cpp"), os.path.join(CSRC, "serving.cpp"),
+           os.path.join(ROOT, "tests", "host_fuzz.cpp"), os.path.join(CSRC, "plan.cpp"), os.path.join(CSRC, "layout.cpp"), os.path.join(CSRC, "serving.cpp"),
            "-o", exe]
     built = subprocess.run(cmd, capture_output=True, text=True)
     assert built.returncode == 0, built.stderr[-3000:]

@@ -1562,7 +1562,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
   asm volatile("" : "+s"(args));
   const RunParams pn = load_const((const RunParams*)args);
   if constexpr (kTeams) {
-    // one unit for every team of the workers without wide units, none drawn: consecutive ones on different chiplets
+    // one unit for every team of the workers without wide units, none drawn: consecutive ones on different chiplets, by
+    // the ranks or, without wide units, by the workgroups' numbers
     if (begin < end) return;
     const int teams_begin = no_lists ? 0 : as_const(pn.worker_offsets)[pn.num_workers];
     const int rank = no_lists ? blockIdx.x : as_const(pn.worker_offsets)[pn.num_workers + 1 + worker];

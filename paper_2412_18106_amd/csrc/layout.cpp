@@ -159,6 +159,19 @@ int32_t xy_plan_hand_out(xy_attn_plan* plan, const XyLayout& l, XyDevUnit* du, i
     memcpy(offsets, lists, plan->worker_offsets.size() * sizeof(int32_t));
   }
   for (int32_t w = 0; w < W; ++w) rank[w] = offsets[w + 1] == offsets[w] ? free_workers++ : -1;
+  if (l.team && per_chip < W && free_workers < W) {
+    // Team i is the worker of rank i: the chiplets in turn, or a short launch would run on one or two of them (unit kernel, eight
+    // wide units beside 32 / 128 / 192 decodes of 2000 keys, caches cold, us: ranks in the workers' order 34.8 / 44.4 / 46.4,
+    // in turn 29.1 / 34.9 / 41.2; where a launch is bound by one unit, the same).  The shared list keeps the workers' order: units
+    // that stand next to each other there may read the same K/V.
+    int32_t at[kXcds] = {};
+    for (int32_t given = 0; given < free_workers;)
+      for (int32_t chip = 0; chip < kXcds; ++chip) {
+        const int32_t* const of_chip = rank + chip * per_chip;
+        while (at[chip] < per_chip && of_chip[at[chip]] < 0) ++at[chip];
+        if (at[chip] < per_chip) rank[chip * per_chip + at[chip]++] = given++;
+      }
+  }
   return free_workers;
 }
 

@@ -144,6 +144,22 @@ def test_layout_of_random_plans():
     assert {(2, False, 0), (1, False, 0), (1, True, 0), (1, False, 4), (1, True, 4)} <= seen
 
 
+@pytest.mark.parametrize("workers,wide,narrow", [(256, 1, 31), (256, 9, 200), (64, 20, 30), (64, 60, 4), (16, 3, 12), (12, 3, 9)])
+def test_teams_beside_wide_units_go_round_the_chiplets(workers, wide, narrow):
+    """Team i is the worker of rank i: among the first n of them no chiplet has two more than another, unless that one has no
+    worker without units left (one chiplet's L2 and path to memory would carry a short launch else)."""
+    cfg = X.xy_attn_default_config(4, 1, 64, num_workers=workers, split_kv_blocks=0)
+    layout, _, lists, ranks = check(cfg, [(32, 100 + 128 * i, P, 0, 0) for i in range(wide)] + decodes(narrow, 300))
+    assert layout.narrow_team
+    chiplets = CHIPLETS if workers % CHIPLETS == 0 else 1
+    left = [sum(ranks[w] >= 0 for w in range(workers) if w * chiplets // workers == x) for x in range(chiplets)]
+    taken = [0] * chiplets
+    for w in np.argsort(ranks)[(ranks < 0).sum():]:
+        x = w * chiplets // workers
+        assert all(taken[x] <= taken[y] or taken[y] == left[y] for y in range(chiplets)), (w, taken)
+        taken[x] += 1
+
+
 def test_probe_refuses_what_it_cannot_fill():
     import ctypes
     plan = X.xy_attn_plan_create(X.xy_attn_default_config(4, 1, 64, num_workers=2), [(64, 0, P, 0, 0)])

@@ -22,9 +22,19 @@ def gpu():
     return runner
 
 
-def run_and_check(gpu, b, what, plan_check=None, **cfg):
+def assert_layout(db, **want):
+    """The way the launches of a batch take (fields of xy_probe_layout; halved=True: any units handed out as halves)."""
+    from paper_2412_18106_amd import binding as X
+    layout = X.xy_probe_plan_layout(db.plan, db.cfg.num_workers)[0]
+    for field, value in want.items():
+        got = getattr(layout, field)
+        assert (got > 0 if value is True else got == value), (field, got, value)
+
+
+def run_and_check(gpu, b, what, plan_check=None, layout=None, **cfg):
     db = gpu.DeviceBatch(b, **cfg)
     try:
+        assert_layout(db, **(layout or {}))
         if plan_check is not None:
             from paper_2412_18106_amd import binding as X
             plan_check(*X.xy_attn_plan_get(db.plan))
@@ -56,20 +66,24 @@ def test_merge_pass_over_the_number_of_pieces_and_rows(gpu, pieces):
 
 @pytest.mark.parametrize("workers,wide,narrow", [(4, 4, 3), (4, 4, 40), (4, 5, 4), (4, 1, 3), (4, 1, 12), (4, 1, 13),
                                                  (4, 3, 50), (16, 3, 1), (16, 15, 70), (1, 1, 9)])
-def test_first_draws_from_the_shared_list(gpu, workers, wide, narrow):
+@pytest.mark.parametrize("heads,tokens,row_tiles", [(4, 32, 1), (3, 85, 2)])
+def test_first_draws_from_the_shared_list(gpu, heads, tokens, row_tiles, workers, wide, narrow):
     """Entries of the shared list are reserved for workers without wide units; the others draw four at once.  No free
     worker, one, most; fewer entries than reserved, exactly as many, one more; three launches (the last workgroup
-    puts the counters back)."""
+    puts the counters back).  Wide units of 128 rows and of 85 x 3, neither of which is ever halved; narrow ones that are too
+    short for teams where these could take them."""
     import torch
     from paper_2412_18106_amd import binding as X
-    specs = [W.SeqSpec(64, 40 + 30 * i, P) for i in range(wide)] + [W.SeqSpec(1, 100 + 37 * i, D_) for i in range(narrow)]
-    b = W.make_custom(specs, 4, 1, 77)
-    ref = A.attention_oracle(b.seqs, b.q, b.k_cache, b.v_cache, b.block_table, b.tree_masks, num_q_heads=4,
+    ctx = (100, 37) if narrow > 2 * (workers - wide) else (30, 20)
+    specs = [W.SeqSpec(tokens, 40 + 30 * i, P) for i in range(wide)] + [W.SeqSpec(1, ctx[0] + ctx[1] * i, D_) for i in range(narrow)]
+    b = W.make_custom(specs, heads, 1, 77)
+    ref = A.attention_oracle(b.seqs, b.q, b.k_cache, b.v_cache, b.block_table, b.tree_masks, num_q_heads=heads,
                              num_kv_heads=1, block_size=b.block_size, scale=b.scale)
     db = gpu.DeviceBatch(b, num_workers=workers, split_kv_blocks=0)
     try:
         units, offs, _ = X.plan_arrays(db.plan, workers)
         assert len(units) == wide + narrow and offs[workers] == wide
+        assert_layout(db, row_tiles=row_tiles, halved=0, narrow_team=0)
         first = db.run_numpy()
         err = np.abs(first.astype(np.float64) - ref)
         assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
@@ -80,27 +94,42 @@ def test_first_draws_from_the_shared_list(gpu, workers, wide, narrow):
         db.close()
 
 
+def two_halves(g):
+    """Most tokens of g heads that make a unit of at most 256 rows which goes out as halves of at most 128."""
+    return max(t for t in range(1, 256 // g + 1) if -(-t // 2) * g <= 128)
+
+
+# where every large unit finds an idle worker, it is handed out as two halves to wavefronts of one row tile; with one
+# worker none is idle and the wavefronts hold two
+WAYS = [(256, dict(row_tiles=1, halved=True)), (1, dict(row_tiles=2, halved=0))]
+
+
+@pytest.mark.parametrize("workers,layout", WAYS)
 @pytest.mark.parametrize("hq,hkv", [(1, 1), (3, 1), (5, 1), (14, 2), (24, 1)])
-def test_wide_units_row_mapping_through_lds(gpu, hq, hkv):
+def test_wide_units_row_mapping_through_lds(gpu, hq, hkv, workers, layout):
     """Q enters and O leaves a wide unit in groups of four rows (row = token x heads + head): group sizes that are no
     power of two, row counts that end inside a group of four, inside a 32-row tile and at a wavefront's first row;
-    split (partial results) and whole."""
+    split (partial results) and whole; one and two row tiles."""
     g = hq // hkv
-    tokens = [max(33, 33 // g), -(-65 // g), 256 // g, 256 // g + 3]
+    most = two_halves(g) if workers > 1 else 256 // g
+    tokens = [max(33, 33 // g), -(-65 // g), most, most + 3]
     b = W.make_custom([W.SeqSpec(t, 30 + 70 * i, P) for i, t in enumerate(tokens)], hq, hkv, 31 + hq)
-    run_and_check(gpu, b, f"{hq}/{hkv} heads, whole", split_kv_blocks=0)
+    run_and_check(gpu, b, f"{hq}/{hkv} heads, whole", layout=layout, split_kv_blocks=0, num_workers=workers, prefill_tile_tokens=most)
     b = W.make_custom([W.SeqSpec(t, 300 + 70 * i, V) for i, t in enumerate(tokens)], hq, hkv, 41 + hq)
-    run_and_check(gpu, b, f"{hq}/{hkv} heads, split", split_kv_blocks=1, verify_tile_tokens=256 // g)
+    run_and_check(gpu, b, f"{hq}/{hkv} heads, split", layout=layout, split_kv_blocks=1, num_workers=workers, verify_tile_tokens=most)
 
 
+@pytest.mark.parametrize("workers,tokens,layout", [(256, 37, dict(row_tiles=1, halved=0))] +
+                         [(workers, 70, layout) for workers, layout in WAYS])
 @pytest.mark.parametrize("dim", ["token", "head"])
-def test_wide_units_far_strides_of_q_and_out(gpu, dim):
+def test_wide_units_far_strides_of_q_and_out(gpu, dim, workers, tokens, layout):
     """Row offsets of Q and O are 32-bit while the strides stay below 2^21 elements, 64-bit from there on."""
     import torch
     from paper_2412_18106_amd import binding as X
-    b = W.make_custom([W.SeqSpec(37, 150, P), W.SeqSpec(1, 90, D_)], 2, 1, 5)
-    db = gpu.DeviceBatch(b)
+    b = W.make_custom([W.SeqSpec(tokens, 150, P), W.SeqSpec(1, 90, D_)], 2, 1, 5)
+    db = gpu.DeviceBatch(b, num_workers=workers, split_kv_blocks=0)
     try:
+        assert_layout(db, **layout)
         want = db.run_numpy()
         t = b.total_q
         for stride in ((1 << 21) - 8, 1 << 21):
@@ -140,9 +169,10 @@ def _poison(b):
     b.v_cache[blk, :, slot] = fill[::-1]
 
 
+@pytest.mark.parametrize("workers,layout", WAYS)
 @pytest.mark.parametrize("bs", [16, 32, 128])
 @pytest.mark.parametrize("hq", [4, 8])
-def test_wide_units_of_less_than_one_step_ignore_what_lies_behind_them(gpu, bs, hq):
+def test_wide_units_of_less_than_one_step_ignore_what_lies_behind_them(gpu, bs, hq, workers, layout):
     """A wide unit of fewer than 32 keys has one step, which is its first and its last: V rows behind the last key must
     not meet the zero probabilities of the step before the first (0 x NaN).  Prompts from nothing, a tree of 20 tokens,
     the last piece of a cut family with 1, 17 and 31 keys; one step and one key more."""
@@ -152,6 +182,7 @@ def test_wide_units_of_less_than_one_step_ignore_what_lies_behind_them(gpu, bs, 
     for name, specs, cfg in (("whole", whole, dict(verify_tile_tokens=256 // hq, split_kv_blocks=0)),
                              ("cut", cut, dict(verify_tile_tokens=256 // hq, split_kv_blocks=1))):
         b = W.make_custom(specs, hq, 1, 60 + hq, block_size=bs)
+        cfg["num_workers"] = workers
         db = gpu.DeviceBatch(b, **cfg)
         base = db.run_numpy()
         db.close()
@@ -161,7 +192,7 @@ def test_wide_units_of_less_than_one_step_ignore_what_lies_behind_them(gpu, bs, 
             rows = units["q_count"] * units["head_count"]
             keys = np.array([min(128 * u["kv_block_end"], b.seqs[u["seq"]][0] + b.seqs[u["seq"]][1]) - 128 * u["kv_block_begin"] for u in units])
             assert ((rows > 32) & (keys < 32)).sum() >= 3
-        run_and_check(gpu, b, f"{name}, {hq} heads, pages of {bs}", plan_check, **cfg)
+        run_and_check(gpu, b, f"{name}, {hq} heads, pages of {bs}", plan_check, layout, **cfg)
         db = gpu.DeviceBatch(b, **cfg)
         assert np.array_equal(db.run_numpy(), base), name
         db.close()
@@ -218,17 +249,19 @@ def test_merge_pass_of_more_workgroups_than_one_launch_takes(gpu):
 @pytest.mark.parametrize("hq,hkv,tokens", [(1, 1, 1), (4, 1, 1), (5, 1, 6), (8, 1, 4), (4, 2, 8), (32, 1, 1)])
 @pytest.mark.parametrize("way", ["short", "two slices", "one slice"])
 def test_ways_of_processing_narrow_units(gpu, way, hq, hkv, tokens):
-    """Units of at most 32 rows are processed in one of three ways, by the average slices (32 keys) of a unit, the number of
+    """Units of at most 32 rows that a wavefront has to itself are processed in one of three ways, by the average slices (32 keys) of a unit, the number of
     units and their tiles (128 keys) per wavefront: up to four slices (eight where units outnumber the wavefronts, two
     where they have more than 16 rows) short, else two slices in flight up to ten tiles a wavefront, else one.  Chains and trees that end inside a slice and right
-    at one, with a few long ones that move the averages; through the shared list and through the workers' own lists."""
+    at one, with a few long ones that move the averages; through the shared list and through the workers' own lists.  Few enough
+    workers that no team shares a unit."""
     tree = W.random_tree(np.random.default_rng(tokens), tokens)
     most = 70 if way == "short" and tokens * (hq // hkv) > 16 else 200
     specs = [W.SeqSpec(tokens, max(0, keys - tokens), V) for keys in (tokens, 31, 32, 33, 64, 95, 96, 97, 129, 200) if keys <= most]
     specs += [W.SeqSpec(tokens, keys - tokens, V, W.MASK_TREE, tree) for keys in (40, 64, 97, 160) if keys <= most]
     if way != "short":
         specs += [W.SeqSpec(tokens, keys - tokens, V) for keys in (1500, 1600, 1679, 1697)]
-    workers = 1 if way == "one slice" else 64
+    units = len(specs) * hkv * -(-tokens // (32 // (hq // hkv)))
+    workers = 1 if way == "one slice" else (units - 1) // 2
     b = W.make_custom(specs, hq, hkv, 17 * hq + tokens)
 
     def plan_check(units, _offs, _merges):
@@ -242,8 +275,9 @@ def test_ways_of_processing_narrow_units(gpu, way, hq, hkv, tokens):
             assert way == "short"
         else:
             assert way == ("two slices" if tiles <= 40 * workers else "one slice")
+    layout = dict(narrow_team=0, narrow_short=int(way == "short"), **({} if way == "short" else dict(narrow_depth=1 + (way == "two slices"))))
     for policy in (1, 2):
-        run_and_check(gpu, b, f"{way}, policy {policy}", plan_check, split_kv_blocks=0, num_workers=workers, assign_policy=policy)
+        run_and_check(gpu, b, f"{way}, policy {policy}", plan_check, layout, split_kv_blocks=0, num_workers=workers, assign_policy=policy)
 
 
 @pytest.mark.parametrize("scale", [None, 1.0])
@@ -258,7 +292,7 @@ def test_units_of_more_than_32_rows_on_one_and_on_two_row_tiles(gpu, hq, hkv, sc
     from paper_2412_18106_amd import binding as X
     g = hq // hkv
     rows = [33, 64, 65, 97, 128, 129, 192, 193, 255, 256]
-    tokens = sorted({max(33 // g + 1, min(256 // g, r // g)) for r in rows})
+    tokens = sorted({max(33 // g + 1, min(two_halves(g), r // g)) for r in rows})
     tree = W.random_tree(np.random.default_rng(3), 40)
     specs = [W.SeqSpec(t, 70 + 31 * i, V) for i, t in enumerate(tokens)] + [W.SeqSpec(40, 75, V, W.MASK_TREE, tree)]
     specs += [W.SeqSpec(64, c, V) for c in (0, 70, 134)]              # 64 tokens: the first 32 see no key of the last tile
@@ -277,6 +311,7 @@ def test_units_of_more_than_32_rows_on_one_and_on_two_row_tiles(gpu, hq, hkv, sc
         for workers in (256, 1):
             db = gpu.DeviceBatch(b, num_workers=workers, split_kv_blocks=split, verify_tile_tokens=256 // g)
             try:
+                assert_layout(db, **dict(WAYS)[workers])
                 outs.append(db.run_numpy())
                 views = []
                 for src in (db.k_cache, db.v_cache):
@@ -323,6 +358,7 @@ def test_teams_of_wavefronts_on_narrow_units(gpu, team, wide, hq, hkv, tokens):
             assert slices >= (3 if team == 4 else 8) * len(narrow)
         db = gpu.DeviceBatch(b, **cfg)
         try:
+            assert_layout(db, narrow_team=team, row_tiles=1, halved=0)
             first = db.run_numpy()
             assert all(np.array_equal(db.run_numpy(), first) for _ in range(2))
         finally:

@@ -32,9 +32,12 @@ def oracle(b, **kw):
                               block_size=b.block_size, scale=b.scale, **kw)
 
 
-def hip(gpu, b, **cfg):
+def hip(gpu, b, row_tiles=None, **cfg):
     db = gpu.DeviceBatch(b, **cfg)
     try:
+        if row_tiles is not None:
+            from paper_2412_18106_amd import binding as X
+            assert X.xy_probe_plan_layout(db.plan, db.cfg.num_workers)[0].row_tiles == row_tiles
         return db.run_numpy()
     finally:
         db.close()
@@ -168,40 +171,50 @@ def test_random_mixed_batches(gpu, seed):
 
 # ---- edge cases -----------------------------------------------------------------------------
 
+# a small batch leaves workers idle, so that its units of more than 128 rows are handed out as halves and the wavefronts
+# hold one row tile; with one worker they hold two
+BOTH_WAYS = pytest.mark.parametrize("way", [dict(row_tiles=1), dict(row_tiles=2, num_workers=1)],
+                                    ids=["one row tile", "two row tiles"])
+
+
+@BOTH_WAYS
 @pytest.mark.parametrize("c", [0, 1, 127, 128, 129, 255])
-def test_context_alignment_and_ragged_tiles(gpu, c):
+def test_context_alignment_and_ragged_tiles(gpu, c, way):
     specs = [W.SeqSpec(67, c, P), W.SeqSpec(1, c, D_), W.SeqSpec(3, c, V), W.SeqSpec(129, c, P)]
     b = W.make_custom(specs, 4, 1, 200 + c)
-    check(hip(gpu, b), oracle(b), f"c={c}")
+    check(hip(gpu, b, **way), oracle(b), f"c={c}")
 
 
+@BOTH_WAYS
 @pytest.mark.parametrize("scale", [0.15, 0.2, 1.0])
-def test_wide_units_on_both_sides_of_the_scale_fold(gpu, scale):
+def test_wide_units_on_both_sides_of_the_scale_fold(gpu, scale, way):
     """Wide units fold c = scale * log2(e) into Q up to c = 0.25 and keep it in fp32 above: 0.216 | 0.289, 1.44."""
     rng = np.random.default_rng(9)
     specs = [W.SeqSpec(200, 300, P), W.SeqSpec(70, 0, P), W.SeqSpec(40, 130, V, W.MASK_TREE, W.random_tree(rng, 40))]
     b = W.make_custom(specs, 8, 2, 77, scale=scale)
-    check(hip(gpu, b, verify_tile_tokens=40), oracle(b), f"scale {scale}")
+    check(hip(gpu, b, verify_tile_tokens=40, **way), oracle(b), f"scale {scale}")
 
 
-def test_wide_rows_that_meet_their_first_key_late_and_references_that_jump(gpu):
+@BOTH_WAYS
+def test_wide_rows_that_meet_their_first_key_late_and_references_that_jump(gpu, way):
     """Exact softmax prefix of the wide path: a forest verify whose later trees see nothing of the first 32
     tree positions (no reference after the first step when the context is empty), and scores that outgrow
     the running reference by far more than the lazy margin in later blocks."""
     parents = [-1] + list(range(0, 39)) + [-1] + list(range(40, 59))     # two chains: 40 and 20 tokens
     b = W.make_custom([W.SeqSpec(60, 0, V, W.MASK_TREE, parents), W.SeqSpec(60, 5, V, W.MASK_TREE, parents)], 4, 1, 31)
-    check(hip(gpu, b, verify_tile_tokens=64), oracle(b), "forest")       # 60 tokens x 4 heads: one wide unit each
+    check(hip(gpu, b, verify_tile_tokens=64, **way), oracle(b), "forest")       # 60 tokens x 4 heads: one wide unit each
     b = W.make_custom([W.SeqSpec(96, 700, P)], 4, 1, 32)
     blocks = b.block_table[0]
     k = W.bf16_bits_to_f32(b.k_cache)
     for n, pos in enumerate(range(100, 700, 100)):          # keys of growing magnitude deeper into the context
         k[blocks[pos // 128], :, pos % 128] *= 3.0 + 2.0 * n
     b.k_cache[:] = W.f32_to_bf16_bits(k)
-    check(hip(gpu, b), oracle(b), "growing keys")
+    check(hip(gpu, b, **way), oracle(b), "growing keys")
 
 
+@BOTH_WAYS
 @pytest.mark.parametrize("jump", [20.0, 45.0, 90.0, 300.0])
-def test_wide_scores_far_above_the_first_reference(gpu, jump):
+def test_wide_scores_far_above_the_first_reference(gpu, jump, way):
     """A wide unit keeps the reference of a row's first step and is checked for overflow once, at its end
     (row sums below 2^64), then repeated with exact references if need be.  Keys deep in the context are
     scaled so that some scores lie about `jump` log2 units above everything seen before: 20 and 45 stay in the
@@ -220,7 +233,7 @@ def test_wide_scores_far_above_the_first_reference(gpu, jump):
             want = jump * (1.0 + 0.5 * n) / c                         # raw q.k
             k[blocks[pos // 128], 0, pos % 128] = qrow * (want / np.dot(qrow, qrow))
     b.k_cache[:] = W.f32_to_bf16_bits(k.astype(np.float32))
-    check(hip(gpu, b), oracle(b), f"jump {jump}")
+    check(hip(gpu, b, **way), oracle(b), f"jump {jump}")
 
 
 def test_head_shapes_mha_and_wide_groups(gpu):
@@ -277,7 +290,8 @@ def test_contexts_beyond_a_hundred_thousand_tokens(gpu):
     assert total / count <= MEAN_ABS and worst <= MAX_ABS
 
 
-def test_long_tree_verify_two_mask_words_and_many_rows(gpu):
+@BOTH_WAYS
+def test_long_tree_verify_two_mask_words_and_many_rows(gpu, way):
     rng = np.random.default_rng(6)
     specs = [W.SeqSpec(40, 300, V, W.MASK_TREE, W.random_tree(rng, 40)),      # 40 x 4 = 160 rows, 2 words per row
              W.SeqSpec(31, 1000, V, W.MASK_TREE, W.random_tree(rng, 31)),
@@ -286,6 +300,7 @@ def test_long_tree_verify_two_mask_words_and_many_rows(gpu):
     b = W.make_custom(specs, 8, 2, 400)
     check(hip(gpu, b), oracle(b))
     check(hip(gpu, b, verify_tile_tokens=16, split_kv_blocks=1), oracle(b))
+    check(hip(gpu, b, verify_tile_tokens=64, **way), oracle(b))
 
 
 def test_chain_tree_equals_causal_on_gpu(gpu):
@@ -304,15 +319,16 @@ def _needle(b, seq, row, head, key_pos, value=2.0, alpha=150.0):
     b.v_cache[blk, head // g, key_pos % b.block_size] = W.f32_to_bf16_bits(np.full(b.head_dim, value, dtype=np.float32))
 
 
+@BOTH_WAYS
 @pytest.mark.parametrize("c", [0, 1, 126, 127, 128, 255, 256])
-def test_needles_at_mask_boundaries(gpu, c):
+def test_needles_at_mask_boundaries(gpu, c, way):
     """A dominant key just inside / just outside the visible range must flip / not move the row."""
     q = 70
     for row in (0, 1, 63, 64, 69):
         b = W.make_custom([W.SeqSpec(q, c, P)], 4, 2, 600 + c, scale=1.0)
-        base = hip(gpu, b)
+        base = hip(gpu, b, **way)
         _needle(b, 0, row, 3, c + row)                 # last visible key of (row, head 3)
-        hit = hip(gpu, b)
+        hit = hip(gpu, b, **way)
         assert np.abs(hit[row, 3] - 2.0).max() < 2e-2, (c, row)
         if row > 0:
             # a row's arithmetic does not depend on the keys only its neighbours see
@@ -321,11 +337,11 @@ def test_needles_at_mask_boundaries(gpu, c):
         check(hit, oracle(b), f"needle c={c} row={row}")
     # first invisible position after the last row, and a block-tail slot, when they exist in the block
     b = W.make_custom([W.SeqSpec(q, c, P)], 4, 2, 600 + c, scale=1.0)
-    base = hip(gpu, b)
+    base = hip(gpu, b, **way)
     n = c + q
     if n % 128:
         _needle(b, 0, q - 1, 3, n)
-        assert np.array_equal(hip(gpu, b), base)
+        assert np.array_equal(hip(gpu, b, **way), base)
 
 
 def test_needle_decode_split_boundary_and_spare_blocks(gpu):
@@ -351,8 +367,9 @@ def test_needle_decode_split_boundary_and_spare_blocks(gpu):
         check(hit, oracle(bb), f"pos {pos}")
 
 
+@BOTH_WAYS
 @pytest.mark.parametrize("bs", [128, 16])
-def test_nan_and_inf_bit_patterns_in_slots_nobody_may_see(gpu, bs):
+def test_nan_and_inf_bit_patterns_in_slots_nobody_may_see(gpu, bs, way):
     """A cache that was never initialised may hold any bit pattern behind a sequence's last token and in blocks no
     sequence owns: NaN and infinities there must not reach the output (a probability of zero does not cancel
     them: the kernel clears such V rows in LDS and overwrites such scores).  Every unit shape: wide prefill tiles,
@@ -363,7 +380,7 @@ def test_nan_and_inf_bit_patterns_in_slots_nobody_may_see(gpu, bs):
              W.SeqSpec(5, 90, V, W.MASK_TREE, tree5), W.SeqSpec(3, 125, V), W.SeqSpec(1, 31, D_), W.SeqSpec(1, 0, D_),
              W.SeqSpec(64, 64, P), W.SeqSpec(70, 1, P)]
     b = W.make_custom(specs, 8, 2, 1234, block_size=bs)
-    cfg = dict(split_kv_blocks=2)
+    cfg = dict(split_kv_blocks=2, **way)
     base = hip(gpu, b, **cfg)
     check(base, oracle(b), "finite garbage")
     used = set()
@@ -425,8 +442,9 @@ def test_strided_q_and_out_views_of_a_fused_qkv_buffer(gpu):
         db.close()
 
 
+@BOTH_WAYS
 @pytest.mark.parametrize("scale", [None, 1.0])
-def test_k_v_caches_whose_rows_are_not_back_to_back(gpu, scale):
+def test_k_v_caches_whose_rows_are_not_back_to_back(gpu, scale, way):
     """The cache strides are arguments: K and V as views with a token stride of 256 elements (rows padded,
     the other half filled with huge values) and a padded block stride.  The wide path then takes its
     general K/V loads instead of the ones for contiguous rows; the narrow path and the append kernel use the
@@ -438,8 +456,10 @@ def test_k_v_caches_whose_rows_are_not_back_to_back(gpu, scale):
              W.SeqSpec(64, 64, P), W.SeqSpec(1, 127, D_), W.SeqSpec(40, 1500, V)]
     kw = {} if scale is None else dict(scale=scale)
     b = W.make_custom(specs, 8, 2, 4321, **kw)
-    db = gpu.DeviceBatch(b, verify_tile_tokens=16)          # 64-row verify units: wide, K/V-split
+    workers = way.get("num_workers", 256)
+    db = gpu.DeviceBatch(b, verify_tile_tokens=16, num_workers=workers)          # 64-row verify units: wide, K/V-split
     try:
+        assert X.xy_probe_plan_layout(db.plan, workers)[0].row_tiles == way["row_tiles"]
         nb, hkv, bs, d = db.k_cache.shape
         bufs = []
         for src in (db.k_cache, db.v_cache):
@@ -639,8 +659,9 @@ def test_run_can_be_captured_in_a_hip_graph_and_replayed(gpu):
         db.close()
 
 
+@BOTH_WAYS
 @pytest.mark.parametrize("bs", [16, 32, 64])
-def test_small_pages_mixed_batch(gpu, bs):
+def test_small_pages_mixed_batch(gpu, bs, way):
     """Pages of 16 / 32 / 64 tokens (section 4.1.1): a 128-key tile is gathered from several block-table
     entries; contexts straddle page and tile boundaries, the last page is partly filled, pairs share prefixes."""
     tree = W.random_tree(np.random.default_rng(bs), 9)
@@ -648,7 +669,7 @@ def test_small_pages_mixed_batch(gpu, bs):
              W.SeqSpec(9, 500 + bs + 3, V, W.MASK_TREE, tree), W.SeqSpec(70, 0, P), W.SeqSpec(1, 2500, D_),
              W.SeqSpec(100, 3 * bs + 640, P), W.SeqSpec(100, 3 * bs + 640, P, share_prefix_with=7), W.SeqSpec(1, 0, D_)]
     b = W.make_custom(specs, 8, 2, 4000 + bs, block_size=bs)
-    check(hip(gpu, b), oracle(b), f"block_size {bs}")
+    check(hip(gpu, b, **way), oracle(b), f"block_size {bs}")
     check(hip(gpu, b, split_kv_blocks=2, prefill_tile_tokens=32), oracle(b), f"block_size {bs}, split")
 
 

@@ -1911,10 +1911,14 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
 // ---- K/V append (section 4.1.1: the cache holds historical and newly generated tokens) --------
 // One thread moves one 16-byte chunk: thread index = ((token * Hkv + kv head) * 2 + (K | V)) * 16 + chunk.
 // The sixteen threads of a row read 256 contiguous bytes and write 256 contiguous bytes.  What a small step pays for is
-// the chain of dependent loads in front of the copy, so a wavefront finds the sequence of its token among the packed
-// start positions with one load for up to 64 sequences (two up to 4096), one lane each, instead of one per halving, and
-// asks for its row before that: 24 decodes and a suffix of 200 tokens 3.4 -> 2.9 us, 7800 prompt tokens (copy rate)
-// 12.5 -> 11.2 us.  Four probes a lane (256 sequences in one round trip) and 32-bit divisions changed nothing.
+// the chain of dependent loads in front of the copy, and the code that has to be fetched for it, so a wavefront finds
+// the sequence of its token among the packed start positions with one load for up to 64 sequences (two up to 4096), one
+// lane each, instead of one per halving; the lane that holds it is uniform and read as a scalar.  One or two sequences are
+// walked with scalar loads.  us, bisection / this: 8 KV heads, one token each of 1 / 2 / 24 / 100 sequences
+// 1.40 / 1.90 / 2.87 / 3.03 -> 1.45 / 1.94 / 2.74 / 2.72, a suffix of 200 tokens beside 24 decodes 2.94 -> 2.70, prompts of 8192 x 1 /
+// 4000 x 2 / 1000 x 8 / 50 x 128 tokens 11.5 / 12.5 / 13.9 / 14.7 -> 12.0 / 12.1 / 12.2 / 10.9.  The row asked for in front of the
+// search changed small steps by nothing and made large ones slower (13.0 / 13.2 / 13.3 / 11.8); four probes a lane and 32-bit
+// divisions changed nothing.
 __global__ __launch_bounds__(256) void xy_attn_append_kernel(const XyDevSeq* __restrict__ seqs, int num_seqs,
                                                              int64_t total_tokens, int num_kv_heads,
                                                              const uint16_t* __restrict__ k_new,
@@ -1929,30 +1933,38 @@ __global__ __launch_bounds__(256) void xy_attn_append_kernel(const XyDevSeq* __r
   const int64_t row = idx >> 5;                     // token * Hkv + kv head
   const int64_t t = row / num_kv_heads;
   const int g = (int)(row - t * num_kv_heads);
-  const int64_t t0 = __shfl(t, 0);                  // the wavefront's first token (with one KV head it has two)
+  // the wavefront's first token (with one KV head it has two)
+  const int64_t t0 = (int64_t)__builtin_amdgcn_readfirstlane((int)(t >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)t);
   if (t0 >= total_tokens) return;
-  const bool live = t < total_tokens;
-  uint4 data = {0u, 0u, 0u, 0u};
-  if (live) data = *reinterpret_cast<const uint4*>((is_v ? v_new : k_new) + t * n_ts + (int64_t)g * n_hs + chunk * 8);
-  int lo = 0, left = num_seqs;                      // the last sequence whose token_start <= t0 is one of [lo, lo + left)
+  int lo = 0;                                       // the last sequence whose token_start <= t0
   XyDevSeq sq;
-  int step;
-  do {
-    step = (left + 63) >> 6;
-    XyDevSeq probe = {0, INT32_MAX};
-    if (lane < (left + step - 1) / step) probe = seqs[lo + lane * step];
-    const int hit = __popcll(__builtin_amdgcn_ballot_w64(probe.token_start <= t0)) - 1;
-    lo += hit * step;
-    left = min(step, left - hit * step);
-    sq = XyDevSeq{__shfl(probe.ctx_len, hit), __shfl(probe.token_start, hit)};
-  } while (step > 1);
-  if (!live) return;
+  if (num_seqs <= 2) {
+    sq = seqs[0];
+    while (lo + 1 < num_seqs) {
+      const XyDevSeq next = seqs[lo + 1];
+      if (next.token_start > t0) break;
+      sq = next;
+      ++lo;
+    }
+  } else {
+    int left = num_seqs, step;                      // it is one of [lo, lo + left)
+    do {
+      step = (left + 63) >> 6;
+      const XyDevSeq probe = seqs[lo + min(lane * step, left - 1)];
+      const int hit = __popcll(__builtin_amdgcn_ballot_w64(lane * step < left && probe.token_start <= t0)) - 1;
+      lo += hit * step;
+      left = min(step, left - hit * step);
+      sq = XyDevSeq{__builtin_amdgcn_readlane(probe.ctx_len, hit), __builtin_amdgcn_readlane(probe.token_start, hit)};
+    } while (step > 1);
+  }
+  if (t >= total_tokens) return;
   if (t != t0)
     while (lo + 1 < num_seqs && seqs[lo + 1].token_start <= t) sq = seqs[++lo];
   const int j = sq.ctx_len + (int)(t - sq.token_start);          // key position of this token
   const int64_t block = block_table[(int64_t)lo * max_blocks + (j >> page_shift)];
+  const uint16_t* src = (is_v ? v_new : k_new) + t * n_ts + (int64_t)g * n_hs + chunk * 8;
   uint16_t* dst = (is_v ? v_cache : k_cache) + block * kv_bs + (int64_t)g * kv_hs + (int64_t)(j & ((1 << page_shift) - 1)) * kv_ts + chunk * 8;
-  *reinterpret_cast<uint4*>(dst) = data;
+  *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
 }
 
 extern "C" int xy_attn_append_kv(xy_attn_plan* plan, const void* k_new, const void* v_new, int64_t n_ts,

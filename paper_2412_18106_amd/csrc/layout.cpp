@@ -30,7 +30,6 @@ constexpr int64_t kDeepTiles = 10;
 // reads the K/V twice and keeps two workers busy: only where there are idle workers for all second halves, with a
 // wavefront left for every narrow unit (a suffix of 150-250 tokens beside 472 narrow units 254.9 -> 266.0 us for eight layers
 // and a chunk of 512 beside 1184 157 -> 164 us where there is not).  The plan the caller sees stays as it is.
-constexpr int32_t kHalfRows = 128;
 int32_t first_half(const xy_work_unit& u) { return (u.q_count + 1) / 2; }
 // Wavefronts that share a narrow unit, for launches that have fewer such units than wavefronts: four while every unit can
 // have a worker without wide units to itself, two while half of one, else none.  Unit kernel, us, one wavefront a unit / team (decodes of 32 heads
@@ -49,42 +48,30 @@ bool is_narrow(const xy_work_unit& u) { return rows_of(u) <= 32; }
 
 }  // namespace
 
-// (leaves the halved units, worker and unit number of each, in scratch.count)
-XyLayout xy_plan_layout(xy_attn_plan* plan) {
-  const int64_t units = plan->narrow_units, slices = plan->narrow_slices, W = plan->cfg.num_workers;
+XyLayout xy_plan_layout(const xy_attn_plan* plan) {
+  const int64_t units = plan->narrow_units, slices = plan->narrow_slices, W = plan->cfg.num_workers, large = plan->large_units;
   XyLayout l;
   l.records = (int32_t)plan->units.size();
   l.row_tiles = plan->most_rows > kHalfRows ? 2 : 1;
-  const int64_t wavefronts = kWavefronts * W;
+  const int64_t wavefronts = kWavefronts * W, wide = l.records - units;
   const int64_t short_slices = plan->narrow_rows > kManyRows * units ? kShortSlicesManyRows
                                : units > wavefronts ? kShortSlicesManyUnits : kShortSlices;
   l.short_units = units > 0 && slices <= short_slices * units;
   l.depth = plan->narrow_tiles <= kDeepTiles * wavefronts ? 2 : 1;
-  int64_t halved = 0, idle = W, free = W;       // workers without units, without wide units
-  if (units < (int64_t)plan->units.size()) {
-    bool divisible = true;
-    std::vector<int32_t>& halves = plan->scratch.count;
-    halves.clear();
-    const xy_work_unit* const u = plan->units.data();
-    const int32_t* const offsets = plan->worker_offsets.data();
-    for (int64_t w = 0; w < W; ++w) {
-      if (offsets[w] == offsets[w + 1]) continue;
-      --idle;
-      int32_t wide = 0;
-      for (int32_t i = offsets[w]; i < offsets[w + 1]; ++i) {
-        const int32_t rows = rows_of(u[i]);
-        wide += rows > 32;
-        if (rows <= kHalfRows) continue;
-        if (++halved > idle) return l;
-        halves.insert(halves.end(), {(int32_t)w, i});
-        divisible &= first_half(u[i]) * u[i].head_count <= kHalfRows;
-      }
-      free -= wide > 0;
-    }
-    if (halved && (!divisible || halved > idle || units > kWavefronts * (idle - halved))) return l;
-    free -= halved;
+  const int32_t* const lists = plan->worker_offsets.data();
+  int64_t free = W;             // workers without wide units
+  if (wide > 0) {
+    int32_t busy = 0;
+    for (int64_t w = 0; w < W; ++w) busy += lists[w] != lists[w + 1];
+    const int64_t idle = W - busy;
+    if (large > 0 && (plan->half_rows > kHalfRows || large > idle || units > kWavefronts * (idle - large))) return l;
+    free = idle;
+    if (units > 0 && lists[W] > wide)           // narrow units on the workers' lists
+      for (int64_t w = 0; w < W; ++w)
+        free += lists[w] != lists[w + 1] && std::all_of(&plan->units[lists[w]], &plan->units[lists[w + 1] - 1] + 1, is_narrow);
+    free -= large;
   }
-  l.halved = (int32_t)halved;
+  l.halved = (int32_t)large;
   l.records += l.halved;
   l.row_tiles = 1;
   // (the kernels with teams hold one row tile: no unit has more than kHalfRows rows here)
@@ -96,32 +83,31 @@ XyLayout xy_plan_layout(xy_attn_plan* plan) {
 
 int32_t xy_plan_hand_out(xy_attn_plan* plan, const XyLayout& l, XyDevUnit* du, int32_t* offsets) {
   const int32_t group = plan->cfg.num_q_heads / plan->cfg.num_kv_heads;
-  const int32_t W = (int32_t)plan->worker_offsets.size() - 1, per_chip = W % kXcds == 0 ? W / kXcds : W;
+  const int32_t W = plan->cfg.num_workers, per_chip = W % kXcds == 0 ? W / kXcds : W;
   int32_t* const rank = offsets + W + 1;
+  const xy_work_unit* const units = plan->units.data();
+  const xy_seq_desc* const descs = plan->descs.data();
+  const int32_t *const starts = plan->token_start.data(), *const lists = plan->worker_offsets.data();
   std::vector<int32_t>& second_of = plan->scratch.cursor;      // worker -> the unit whose second half it gets, or -1
   if (l.halved) {
     second_of.assign(W, -1);                                    // (the planner left room for W)
     // the second half goes to an idle worker of the same chiplet if there is one: both read the same K/V
-    const std::vector<int32_t>& halves = plan->scratch.count;
-    std::vector<int32_t>& idle = plan->scratch.order;           // the next worker to look at, per chiplet
-    idle.assign(W / per_chip, 0);
+    int32_t at[kXcds] = {};                                     // the next worker to look at, per chiplet
     auto next_idle = [&](const int32_t chip) {
-      for (int32_t& at = idle[chip]; at < per_chip; ++at) {
-        const int32_t w = chip * per_chip + at;
-        if (plan->worker_offsets[w] == plan->worker_offsets[w + 1] && second_of[w] < 0) return w;
-      }
-      return -1;
+      const int32_t* const of_chip = lists + chip * per_chip;
+      int32_t& n = at[chip];
+      while (n < per_chip && of_chip[n] != of_chip[n + 1]) ++n;
+      return n < per_chip ? chip * per_chip + n++ : -1;
     };
-    for (size_t x = 0; x < halves.size(); x += 2) {
-      int32_t to = next_idle(halves[x] / per_chip);
-      for (int32_t chip = 0; to < 0; ++chip) to = next_idle(chip);       // there are as many idle workers as halves
-      second_of[to] = halves[x + 1];
-    }
+    for (int32_t w = 0; w < W; ++w)
+      for (int32_t i = lists[w]; i < lists[w + 1]; ++i) {
+        if (rows_of(units[i]) <= kHalfRows) continue;
+        int32_t to = next_idle(w / per_chip);
+        for (int32_t chip = 0; to < 0; ++chip) to = next_idle(chip);     // there are as many idle workers as halves
+        second_of[to] = i;
+      }
   }
   int32_t emitted = 0, free_workers = 0;
-  const xy_work_unit* const units = plan->units.data();
-  const xy_seq_desc* const descs = plan->descs.data();
-  const int32_t *const starts = plan->token_start.data(), *const lists = plan->worker_offsets.data();
   auto record = [=](const xy_work_unit& u, const int32_t q_begin, const int32_t q_count, const int32_t flags) {
     const xy_seq_desc& sd = descs[u.seq];
     return XyDevUnit{u.seq, u.head_begin, u.head_count, q_begin, q_count, u.kv_block_begin, u.kv_block_end, flags, u.ws_offset,

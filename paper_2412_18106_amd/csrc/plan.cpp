@@ -280,7 +280,8 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
     plan->merges.clear();
     plan->workspace_floats = 0;
     plan->has_tree = false;
-    plan->most_rows = 0;
+    plan->most_rows = plan->half_rows = 0;
+    plan->large_units = 0;
     plan->narrow_units = plan->narrow_rows = plan->narrow_tiles = plan->narrow_slices = 0;
 
     // --- size of the K/V split (see XY_SPLIT_AUTO) ---------------------------
@@ -430,6 +431,9 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
           plan->narrow_rows += (int64_t)k * head_groups * rows;
           plan->narrow_tiles += (int64_t)nb * head_groups;
           plan->narrow_slices += ceil_div(last_excl, kKvSlice) * head_groups;      // (pieces end at whole tiles)
+        } else if (rows > kHalfRows) {
+          plan->large_units += (int64_t)k * head_groups;
+          plan->half_rows = std::max(plan->half_rows, (qc + 1) / 2 * hc);
         }
         const int64_t unit_rows = std::max<int64_t>(rows, c.cost_row_floor);
         const size_t at = fam.size();
@@ -662,8 +666,6 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
     plan->worker_offsets.assign(W + 1, 0);
     for (int64_t w = 0; w < W; ++w) plan->worker_offsets[w + 1] = plan->worker_offsets[w] + count[w];
     plan->units.resize(fam.size());
-    plan->scratch.count.reserve(2 * W);        // the upload keeps lists in these
-    plan->scratch.order.reserve(W);
     std::vector<int32_t>& cursor = plan->scratch.cursor;
     cursor.assign(plan->worker_offsets.begin(), plan->worker_offsets.end() - 1);
     int32_t shared_cursor = plan->worker_offsets[W];        // the shared list follows the workers' lists

@@ -18,6 +18,8 @@ static_assert(sizeof(XyDevUnit) == 64, "one aligned scalar load");
 // results and the unit's first row among them
 constexpr int kSlabRowsShift = 8, kSlabFirstShift = 20;
 
+constexpr int32_t kHalfRows = 128;          // most rows of a wide unit that four wavefronts of one row tile hold
+
 // How a launch takes the units of a plan (layout.cpp).
 struct XyLayout {
   int32_t records = 0;                      // units as they are handed out, second halves among them
@@ -73,6 +75,8 @@ struct xy_attn_plan {
   int32_t free_workers = 0;                 // workers without units of their own (of the tables last copied to the GPU)
   XyLayout layout;                          // of the tables last copied to the GPU
   int32_t most_rows = 0;                    // most rows of a unit
+  int64_t large_units = 0;                  // units of more than kHalfRows rows
+  int32_t half_rows = 0;                    // most rows of the first half of one (half of its tokens, rounded up)
   int64_t narrow_units = 0, narrow_rows = 0, narrow_tiles = 0, narrow_slices = 0;     // units of at most 32 rows, their rows, K/V tiles and 32-key slices
   bool has_tree = false;
   XyPlanScratch scratch;
@@ -95,7 +99,7 @@ struct xy_attn_plan {
 // layout.cpp; host only.  xy_plan_hand_out fills the tables of the unit kernel for the layout xy_plan_layout has just worked
 // out: the records, and behind each other the workers' offsets (W + 1; the shared list follows the last worker's) and ranks
 // (W; a worker's number among those that have no units of their own, -1 where it has some).  Returns how many have none.
-XyLayout xy_plan_layout(xy_attn_plan* plan);
+XyLayout xy_plan_layout(const xy_attn_plan* plan);
 int32_t xy_plan_hand_out(xy_attn_plan* plan, const XyLayout& layout, XyDevUnit* records, int32_t* offsets);
 // Implemented in the HIP translation unit; frees the arena, the staging buffer and the event.
 void xy_plan_free_device(xy_attn_plan* plan);

@@ -1913,11 +1913,14 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
 // The sixteen threads of a row read 256 contiguous bytes and write 256 contiguous bytes.  What a small step pays for is
 // the chain of dependent loads in front of the copy, and the code that has to be fetched for it, so a wavefront finds
 // the sequence of its token among the packed start positions with one load for up to 64 sequences (two up to 4096), one
-// lane each, instead of one per halving; the lane that holds it is uniform and read as a scalar.  One or two sequences are
-// walked with scalar loads.  us, bisection / this: 8 KV heads, one token each of 1 / 2 / 24 / 100 sequences
-// 1.40 / 1.90 / 2.87 / 3.03 -> 1.45 / 1.94 / 2.74 / 2.72, a suffix of 200 tokens beside 24 decodes 2.94 -> 2.70, prompts of 8192 x 1 /
-// 4000 x 2 / 1000 x 8 / 50 x 128 tokens 11.5 / 12.5 / 13.9 / 14.7 -> 12.0 / 12.1 / 12.2 / 10.9.  The row asked for in front of the
-// search changed small steps by nothing and made large ones slower (13.0 / 13.2 / 13.3 / 11.8); four probes a lane and 32-bit
+// lane each, instead of one per halving; the lane that holds it is uniform and read as a scalar, and so is its neighbour for
+// a second token of the wavefront.  One or two sequences are walked with scalar loads.  us, bisection / this:
+//   one token each of 1 / 2 / 24 / 100 sequences, 8 KV heads   1.37 / 1.79 / 2.82 / 3.08 -> 1.41 / 1.75 / 2.59 / 2.78
+//   of 2 / 7 / 24 / 100 sequences, 1 KV head                   1.44 / 1.67 / 2.20 / 3.02 -> 1.43 / 1.63 / 1.97 / 2.71
+//   a suffix of 200 tokens beside 24 decodes, 8 KV heads       2.97 -> 2.70
+//   8192 x 1 / 4000 x 2 / 1000 x 8 / 50 x 128 tokens           11.7 / 12.6 / 14.0 / 14.8 -> 12.0 / 12.3 / 12.4 / 10.9
+// The neighbour by a load costs 0.2 us with one KV head.  The row asked for in front of the
+// search changed small steps by nothing and made large ones slower (13.2 / 13.6 / 13.7 / 12.0); four probes a lane and 32-bit
 // divisions changed nothing.
 __global__ __launch_bounds__(256) void xy_attn_append_kernel(const XyDevSeq* __restrict__ seqs, int num_seqs,
                                                              int64_t total_tokens, int num_kv_heads,
@@ -1933,18 +1936,19 @@ __global__ __launch_bounds__(256) void xy_attn_append_kernel(const XyDevSeq* __r
   const int64_t row = idx >> 5;                     // token * Hkv + kv head
   const int64_t t = row / num_kv_heads;
   const int g = (int)(row - t * num_kv_heads);
-  // the wavefront's first token (with one KV head it has two)
+  // the wavefront's first token (with an odd number of KV heads it may have two: a token is 32 Hkv threads)
   const int64_t t0 = (int64_t)__builtin_amdgcn_readfirstlane((int)(t >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)t);
   if (t0 >= total_tokens) return;
   int lo = 0;                                       // the last sequence whose token_start <= t0
-  XyDevSeq sq;
+  XyDevSeq sq, next = {0, INT32_MAX};               // that one, and the one behind it where the wavefront's second token may be
   if (num_seqs <= 2) {
     sq = seqs[0];
     while (lo + 1 < num_seqs) {
-      const XyDevSeq next = seqs[lo + 1];
+      next = seqs[lo + 1];
       if (next.token_start > t0) break;
       sq = next;
       ++lo;
+      next.token_start = INT32_MAX;
     }
   } else {
     int left = num_seqs, step;                      // it is one of [lo, lo + left)
@@ -1953,13 +1957,19 @@ __global__ __launch_bounds__(256) void xy_attn_append_kernel(const XyDevSeq* __r
       const XyDevSeq probe = seqs[lo + min(lane * step, left - 1)];
       const int hit = __popcll(__builtin_amdgcn_ballot_w64(lane * step < left && probe.token_start <= t0)) - 1;
       lo += hit * step;
+      if (step == 1 && (num_kv_heads & 1)) {
+        if (hit + 1 < left) next = XyDevSeq{__builtin_amdgcn_readlane(probe.ctx_len, hit + 1), __builtin_amdgcn_readlane(probe.token_start, hit + 1)};
+        else if (lo + 1 < num_seqs) next = seqs[lo + 1];
+      }
       left = min(step, left - hit * step);
       sq = XyDevSeq{__builtin_amdgcn_readlane(probe.ctx_len, hit), __builtin_amdgcn_readlane(probe.token_start, hit)};
     } while (step > 1);
   }
   if (t >= total_tokens) return;
-  if (t != t0)
-    while (lo + 1 < num_seqs && seqs[lo + 1].token_start <= t) sq = seqs[++lo];
+  if (next.token_start <= t) {                      // (no sequence is empty: the second token is in one of the two)
+    sq = next;
+    ++lo;
+  }
   const int j = sq.ctx_len + (int)(t - sq.token_start);          // key position of this token
   const int64_t block = block_table[(int64_t)lo * max_blocks + (j >> page_shift)];
   const uint16_t* src = (is_v ? v_new : k_new) + t * n_ts + (int64_t)g * n_hs + chunk * 8;

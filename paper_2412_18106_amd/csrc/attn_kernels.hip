@@ -22,10 +22,13 @@
 //    transposing LDS read (ds_read_b64_tr_b16).
 //  * rows = tokens x heads of one KV head (GQA sharing): a unit with more than
 //    32 rows gives each wavefront 64 rows and every key, the wavefronts sharing
-//    the K/V stream (every fragment read from LDS feeds two MFMAs); a unit with
+//    the K/V stream (every fragment read from LDS feeds two MFMAs), or 32 rows in
+//    launches that hand out no unit of more than 128; a unit with
 //    up to 32 rows (decode, short verify) is processed by a single wavefront
 //    streaming 32-key slices through a private LDS ring, so a CU has four such
-//    units in flight and no barrier between them.
+//    units in flight and no barrier between them; where a launch has fewer of
+//    these than wavefronts, two or four wavefronts of a workgroup share one, each
+//    with a part of its slices, and their states meet in LDS at its end.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -82,9 +85,9 @@ struct RunParams {
   float* ws;
   int64_t q_ts, q_hs, kv_bs, kv_hs, kv_ts, o_ts, o_hs;
   int32_t max_blocks, num_workers;
-  int32_t free_workers;              // workers without units of their own (plan with a shared list)
+  int32_t free_workers;              // workers without units of their own, as they are handed out
   int32_t narrow_depth;              // slices a wavefront keeps in flight (see process_solo)
-  int32_t num_units;                 // all units, the shared list of XY_ASSIGN_DYNAMIC included
+  int32_t num_units;                 // records: all units, second halves and the shared list included
   int32_t* counters;                 // plan with a shared list: its cursor and the finished-workgroup counts (kCounterStride apart); else null
   int32_t page_shift, page_mask;     // log2 of the tokens per block-table entry (page), and that size - 1
   float c;      // softmax_scale * log2(e)
@@ -729,19 +732,21 @@ __device__ __forceinline__ void scale_acc(f32x16& acc, const float alpha) {
   acc = t;
 }
 
-// A unit with more than 32 rows.  Wavefront w owns rows [64w, 64w + 64) as two 32-row tiles and sees every
+// A unit with more than 32 rows.  Wavefront w owns rows [32 NT w, 32 NT (w + 1)) as NT 32-row tiles and sees every
 // key.  K and V stream through a ring of four 64-key half blocks (32 KB each: 16 KB of K, 16 KB of V);
 // a "step" is 32 keys, a "trip" two steps = one half block.
 // Iteration t works on three steps at once (the paper's cube / vector overlap of section 4.2.1, at
 // instruction level inside one wavefront): the QK^T MFMAs of step t + 1, the softmax arithmetic of step t
-// and the PV MFMAs of step t - 1, as sixteen chunks of two MFMAs (one per row tile, sharing the chunk's
-// K or V fragment) with a few vector instructions and one LDS request behind each MFMA.
+// and the PV MFMAs of step t - 1, as sixteen chunks of NT MFMAs (one per row tile, sharing the chunk's
+// K or V fragment) with a few vector instructions behind each MFMA and the LDS request of a later chunk behind the first.
 // PRESCALE: Q carries the factor c = scale x log2(e), see the softmax notes inside.
 // NT: row tiles of a wavefront, two as described, or one, where no unit of the launch has more than 128 rows: with two
 // such a unit leaves two of the four wavefronts without rows.  One tile means half the MFMAs, exponentials and rows to
-// load and store per wavefront and the same LDS requests, so a step takes 0.38 us instead of 0.58 (124 rows, 8 units
-// alone), and what stands around the loop 7.7 us instead of 9.9; 248 of them on 1 / 4 / 16 tiles 15.2 / 24.8 / 56.3 ->
-// 12.7 / 20.4 / 45.2 us, the last at 5.8 TB/s; four trees of 31 tokens on 10-20k keys, with merge pass, 64.6 -> 60.7 us.
+// load and store per wavefront and the same LDS requests.  Eight units alone, K/V in the caches, the whole launch fitted over
+// 8 to 32 tiles, us around the loop + a step of 32 keys: 124 rows 9.3 + 0.584 on two tiles, 7.2 + 0.396 on one; 256 rows
+// 10.4 + 0.594 on two, as halves (kHalfRows in layout.cpp) 7.3 + 0.398.  248 units of 124 rows on 1 / 4 / 16 tiles
+// 15.2 / 24.8 / 56.3 -> 12.7 / 20.4 / 45.2 us: 2.1 us a tile there, the memory's rate; four trees of 31 tokens on 10-20k
+// keys, with merge pass, 64.6 -> 60.7 us.
 // K fragments asked for eight chunks ahead instead of four changed nothing.
 template <int NT>
 struct GapTables;
@@ -873,7 +878,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   // instruction moves four whole rows.  The rows (256 bytes, 16-byte chunks swizzled by the low four bits of the
   // row) wait in ring slots 2 and 3, which are requested when every wavefront has its Q.
   // With the way the results leave (below), the first reference taken without rescaling what is still zero and the
-  // last V fragments requested together, a unit spends 7.6 us around its loop instead of 10.5 (256 rows, alone).
+  // last V fragments requested together, a unit of 256 rows alone takes 2.9 us less (what is left: GapTables).
   __syncthreads();                                          // the ring is free
   const int entry0 = table_entry(0, 0), entry1 = table_entry(0, 1);
   unsigned char* const wave_buf = smem + 65536 + wave * (8192 * NT);        // 32 NT rows of 256 bytes
@@ -1297,17 +1302,17 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   return false;
 }
 
-// A unit with at most 32 rows (decode, short verify; bandwidth-bound): ONE wavefront processes the
+// A unit with at most 32 rows (decode, short verify; bandwidth-bound).  TEAM = 1: one wavefront processes the
 // whole unit on its own, streaming 32-key slices through a private ring of one or two slices (K and V slots, each
 // refilled as soon as it has been consumed).  No barrier, no cross-wavefront merge: four such
 // units are in flight per CU and hide each other's latencies.
-// Two slices (narrow_depth) where a launch has at most kDeepTiles tiles per wavefront: with every wavefront at work
+// TEAM = 2, 4: so many wavefronts share the unit, each with every TEAM-th slice from its place in the team on, and finish_team
+// puts their states together behind a barrier of the workgroup; exists: whether the team has a unit at all.
+// Two slices (narrow_depth) with teams and where a launch has at most kDeepTiles tiles per wavefront: with every wavefront at work
 // the card's bandwidth is the bound and 16 KB each are enough, but a wavefront whose neighbours have run out of work waits
 // for memory in every slice, and that is the end of every launch.  8 decodes x 32 KV heads on 2-6k tokens (7.5 tiles per
 // wavefront) 94.8 -> 92.0 us with two; 128 trees on 512-4096 tokens (14 tiles) 153.0 -> 154.7 us, 128 decodes on
 // 2-16k (54 tiles) 553.7 -> 557.2 us, so those keep one.  Launches of short units take process_short instead.
-// TEAM: wavefronts that share the unit (see finish_team), each with every TEAM-th slice from its place in the team on;
-// exists: whether the team has a unit at all.
 template <int TEAM>
 __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit& u, unsigned char* smem, const LaneOffsets& lo,
                                              const DmaOffsets& dof, const bool exists = true) {
@@ -1510,8 +1515,8 @@ __device__ __forceinline__ void process_short(const RunParams& p, const XyDevUni
 // wide units of its list together, then its four wavefronts draw the remaining (bandwidth-bound)
 // units of the same list one by one from a shared cursor, each wavefront finishing whole units
 // on its own.
-// NARROW: how its units of at most 32 rows are processed (kSolo, kShort: kShortSlices; 2 or 4: by a team of so many
-// wavefronts each, see narrow_team); a kernel for each, since the ways in one disturb each other's registers (short units
+// NARROW: how its units of at most 32 rows are processed (kSolo, kShort: kShortSlices in layout.cpp; 2 or 4: by a team of so many
+// wavefronts each, kTeamOf4Slices in layout.cpp); a kernel for each, since the ways in one disturb each other's registers (short units
 // 3 to 5 %, launches on two slices up to 2 %).
 // NT: row tiles of a wavefront on its wide units (process_wide).
 constexpr int kSolo = 0, kShort = 1;

@@ -25,11 +25,19 @@ constexpr int64_t kShortSlices = 4, kShortSlicesManyUnits = 8, kShortSlicesManyR
 // tiles, 3 % in favour of two, and at 14, 1 % against).
 constexpr int64_t kDeepTiles = 10;
 // Units of more than kHalfRows rows that go to the GPU as two, by their tokens, for a worker each: all of them or none.
-// The kernel then holds one row tile a wavefront instead of two, which takes two thirds of the time for units
-// that are alone (64 tokens x 4 heads on 1 / 4 / 16 K/V tiles, 8 units: 12.6 / 19.6 / 47.5 -> 9.1 / 13.6 / 32.9 us), but
-// reads the K/V twice and keeps two workers busy: only where there are idle workers for all second halves, with a
-// wavefront left for every narrow unit (a suffix of 150-250 tokens beside 472 narrow units 254.9 -> 266.0 us for eight layers
-// and a chunk of 512 beside 1184 157 -> 164 us where there is not).  The plan the caller sees stays as it is.
+// The kernel then holds one row tile a wavefront instead of two, which takes two thirds of the time for units that are
+// alone, but reads the K/V twice and keeps two workers busy: only where there are idle workers for all second halves, with a
+// wavefront left for every narrow unit.  Unit kernel, us, whole / halves, 64 tokens x 4 heads, caches cold:
+//   units   1 K/V tile       4              16             64
+//   8       20.4 / 13.0      25.5 / 17.0    53.1 / 36.0
+//   64      18.6 / 12.3      27.5 / 18.2    56.2 / 40.8    170 / 125
+//   112     20.2 / 14.5      26.7 / 21.6    58.9 / 52.5    177 / 149
+//   128     18.5 / 15.2      29.9 / 22.9    63.4 / 58.1    185 / 162    (every worker busy)
+// and with fewer wavefronts left than narrow units the other way round (a suffix of 150-250 tokens beside 472 narrow units
+// 254.9 -> 266.0 us for eight layers, a chunk of 512 beside 1184 157 -> 164 us).  The plan the caller sees stays as it is.
+// A half is at most kHalfRows rows, so the tokens of a unit must divide: with 3, 5, 10, 12 and some other heads a group the
+// default tile (256 / heads tokens: 85, 51, 25, 21) has a first half of 129 to 132 rows, and one such unit keeps the whole
+// launch on two row tiles, without teams.
 int32_t first_half(const xy_work_unit& u) { return (u.q_count + 1) / 2; }
 // Wavefronts that share a narrow unit, for launches that have fewer such units than wavefronts: four while every unit can
 // have a worker without wide units to itself, two while half of one, else none.  Unit kernel, us, one wavefront a unit / team (decodes of 32 heads
@@ -40,7 +48,8 @@ int32_t first_half(const xy_work_unit& u) { return (u.q_count + 1) / 2; }
 //   256     6.0 / 6.9             8.3 / 8.4    12.4 / 11.2  19.5 / 15.5  62.0 / 43.9
 //   264     7.1 / 7.4 (two)       9.1 / 9.8    12.9 / 12.4  20.1 / 19.2  62.2 / 59.0
 //   512     7.5 / 8.3             10.2 / 11.4  15.6 / 15.1  25.9 / 24.8  85.3 / 84.5
-// so a team of four takes units of three slices and more on average, a team of two those of eight.
+// so a team of four takes units of three slices and more on average, a team of two those of eight.  XY_SPLIT_AUTO cuts such
+// batches into more pieces than that; teams of two are for plans with a split size of the caller's or none.
 constexpr int64_t kTeamOf4Slices = 3, kTeamOf2Slices = 8;
 
 int32_t rows_of(const xy_work_unit& u) { return u.q_count * u.head_count; }

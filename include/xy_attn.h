@@ -145,6 +145,11 @@ enum { XY_ASSIGN_SNAKE = 0, XY_ASSIGN_LEAST_LOADED = 1, XY_ASSIGN_DYNAMIC = 2 };
  * unit goes to the least-loaded worker overall; nor are they with at most 2 num_workers such units where the largest
  * load of a worker with the groups is more than 3 % above the largest without (largest * 100 > other * 103): chiplets
  * that are level in load need not be level in units, and on a short list one unit more is most of the launch. */
+/* How units reach the wavefronts is worked out from the plan when it is copied to the GPU and changes no result beyond
+ * rounding (xy_probe_plan_layout shows it).  Where every unit of more than 128 rows finds a worker without units for one
+ * half of its tokens, and a wavefront is left for every unit of at most 32 rows, such units are handed out as two halves; both
+ * must have at most 128 rows, which the default tile of 3, 5, 10 .. 13 and some other heads a group (85 x 3 rows and so on) does not
+ * allow (up to 128 heads tiles of one token less do).  Units of at most 32 rows are shared by two or four wavefronts where there are few. */
 /* rows = tile tokens x heads per unit must be <= 256 for every kind. */
 
 /* One tiling unit (section 3.2.1) placed in the Task-Table (section 3.3.1). */

@@ -263,28 +263,31 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
     if (total > INT32_MAX) return XY_ERR_CAPACITY;
   }
 
-  auto give_up = [&](int rc) {      // what is left is an empty plan
+  auto clear = [&] {                // what is left is an empty plan of worker_offsets.size() - 1 workers
     plan->num_seqs = 0;
     plan->total_tokens = 0;
     plan->units.clear();
-    plan->merges.clear();
-    plan->workspace_floats = 0;
-    return rc;
-  };
-  try {
-    plan->device_stale = true;
-    plan->cfg = c;
-    plan->num_seqs = num_seqs;
-    plan->total_tokens = total;
-    if (descs != plan->descs.data()) plan->descs.assign(descs, descs + num_seqs);
-    plan->token_start.resize(num_seqs);
-    plan->units.clear();
+    std::fill(plan->worker_offsets.begin(), plan->worker_offsets.end(), 0);
     plan->merges.clear();
     plan->workspace_floats = 0;
     plan->has_tree = false;
     plan->most_rows = plan->half_rows = 0;
     plan->large_units = 0;
     plan->narrow_units = plan->narrow_rows = plan->narrow_tiles = plan->narrow_slices = 0;
+  };
+  auto give_up = [&](int rc) {
+    clear();
+    return rc;
+  };
+  try {
+    plan->device_stale = true;
+    clear();
+    plan->worker_offsets.assign((size_t)c.num_workers + 1, 0);      // ahead of the configuration: the lists always fit its workers
+    plan->cfg = c;
+    plan->num_seqs = num_seqs;
+    plan->total_tokens = total;
+    if (descs != plan->descs.data()) plan->descs.assign(descs, descs + num_seqs);
+    plan->token_start.resize(num_seqs);
 
     // --- size of the K/V split (see XY_SPLIT_AUTO) ---------------------------
     int32_t split_narrow = c.split_kv_blocks, split_wide = c.split_kv_blocks;
@@ -665,7 +668,6 @@ int build_plan(xy_attn_plan* plan, const xy_attn_config* cfg, const xy_seq_desc*
     }
     for (int64_t pos = 0; pos < (int64_t)order.size(); ++pos)
       if (worker_of[pos] != kShared) ++count[worker_of[pos]];
-    plan->worker_offsets.assign(W + 1, 0);
     for (int64_t w = 0; w < W; ++w) plan->worker_offsets[w + 1] = plan->worker_offsets[w] + count[w];
     plan->units.resize(fam.size());
     std::vector<int32_t>& cursor = plan->scratch.cursor;

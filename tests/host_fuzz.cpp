@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <map>
+#include <new>
 #include <set>
 #include <vector>
 
@@ -15,6 +16,14 @@
 // the planner frees a plan's GPU memory through this hook; there is none here
 struct xy_attn_plan;
 void xy_plan_free_device(xy_attn_plan*) {}
+
+// operator new of the code under test (linked with --wrap): allocations of more than this many bytes fail
+static size_t g_most_bytes = SIZE_MAX;
+extern "C" void* __real__Znwm(size_t);
+extern "C" void* __wrap__Znwm(size_t n) {
+  if (n > g_most_bytes) throw std::bad_alloc();
+  return __real__Znwm(n);
+}
 
 namespace {
 
@@ -169,6 +178,45 @@ void fuzz_planner(int rounds) {
   xy_attn_plan_destroy(nullptr);
 }
 
+// A rebuild that runs out of host memory leaves an empty plan, whatever was in it before and wherever it stopped: nothing to
+// hand out, no unit, record or list of the old plan looked at.
+void fuzz_out_of_memory(int rounds) {
+  xy_attn_config cfg;
+  CHECK(xy_attn_default_config(8, 2, 64, &cfg) == XY_OK);
+  int failed = 0;
+  for (int r = 0; r < rounds; ++r) {
+    std::vector<xy_seq_desc> before((size_t)uni(1, 30)), after((size_t)uni(200, 300));
+    for (auto* batch : {&before, &after})
+      for (xy_seq_desc& s : *batch) {
+        const bool prefill = uni(0, 1);
+        s = xy_seq_desc{prefill ? (int32_t)uni(9, 300) : 1, (int32_t)uni(0, 3000), prefill ? XY_PREFILL : XY_DECODE, 0, 0};
+      }
+    cfg.num_workers = (int32_t)uni(1, 304);
+    cfg.assign_policy = (int32_t)uni(0, 2);
+    xy_attn_plan* plan = nullptr;
+    CHECK(xy_attn_plan_create(&cfg, before.data(), (int32_t)before.size(), &plan) == XY_OK);
+    cfg.num_workers = (int32_t)uni(1, 304);
+    g_most_bytes = (size_t)uni(1500, 200000);
+    const int rc = xy_attn_plan_rebuild(plan, &cfg, after.data(), (int32_t)after.size());
+    g_most_bytes = SIZE_MAX;
+    CHECK(rc == XY_OK || rc == XY_ERR_NOMEM);
+    if (rc == XY_OK) {
+      check_plan(plan, cfg, after);
+    } else {
+      ++failed;
+      check_plan(plan, cfg, {});
+      xy_probe_layout l;
+      CHECK(xy_probe_plan_layout(plan, &l, nullptr, 0, nullptr) == XY_OK && l.records == 0 && l.halved == 0 && l.narrow_team == 0);
+    }
+    check_layout(plan, cfg);
+    CHECK(xy_attn_plan_rebuild(plan, &cfg, before.data(), (int32_t)before.size()) == XY_OK);
+    check_plan(plan, cfg, before);
+    check_layout(plan, cfg);
+    xy_attn_plan_destroy(plan);
+  }
+  CHECK(failed > rounds / 4);
+}
+
 void fuzz_scheduler(int rounds) {
   for (int r = 0; r < rounds; ++r) {
     const int32_t budget = (int32_t)uni(1, 600), reserved = (int32_t)uni(0, budget);
@@ -257,6 +305,7 @@ void fuzz_block_manager(int rounds) {
 int main(int argc, char** argv) {
   const int scale = argc > 1 ? std::atoi(argv[1]) : 1;
   fuzz_planner(150 * scale);
+  fuzz_out_of_memory(60 * scale);
   fuzz_scheduler(400 * scale);
   fuzz_block_manager(40 * scale);
   std::puts("host_fuzz: ok");

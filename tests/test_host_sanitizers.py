@@ -16,8 +16,8 @@ def test_planner_scheduler_and_block_manager_fuzz_under_asan_and_ubsan(tmp_path)
         pytest.skip("no host C++ compiler")
     exe = str(tmp_path / "host_fuzz")
     cmd = [cxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
-           "-fno-omit-frame-pointer", "-static-libasan", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           os.path.join(ROOT, "tests", "host_fuzz.cpp"), os.path.join(CSRC, "plan.cpp"), os.path.join(CSRC, "layout.cpp"), os.path.join(CSRC, "serving.cpp"),
+           "-fno-omit-frame-pointer", "-static-libasan", "-Wl,--wrap=_Znwm", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+           os.path.join(ROOT, "tests", "host_fuzz.cpp"), *(os.path.join(CSRC, s) for s in ("plan.cpp", "layout.cpp", "serving.cpp")),
            "-o", exe]
     built = subprocess.run(cmd, capture_output=True, text=True)
     assert built.returncode == 0, built.stderr[-3000:]

@@ -122,6 +122,43 @@ __device__ __forceinline__ T load_const(const T* ptr) {
   return out;
 }
 
+// The kernel arguments in registers, all of them, behind one wait.  Field by field, as the compiler loads an argument where it is
+// first used, a narrow unit starts with four round trips instead of one.
+__device__ __forceinline__ RunParams load_args() {
+  typedef __attribute__((ext_vector_type(16))) uint32_t u32x16;
+  typedef __attribute__((ext_vector_type(8))) uint32_t u32x8;
+  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+  struct Words {
+    u32x16 a, b;
+    u32x8 c;
+    u32x4 d;
+  };
+  static_assert(sizeof(RunParams) == 176, "RunParams is loaded as 16 + 16 + 8 + 4 words");
+  const XY_CONST uint32_t* at = (const XY_CONST uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(at));              // not the copy that the wide units use: what they spill would be read back lane by lane
+  u32x16 a, b;
+  u32x8 c;
+  u32x4 d;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    a[i] = at[i];
+    b[i] = at[16 + i];
+    if (i < 8) c[i] = at[32 + i];
+    if (i < 4) d[i] = at[40 + i];
+  }
+  asm volatile("" : "+s"(a), "+s"(b), "+s"(c), "+s"(d));
+  RunParams p;
+  uint32_t* to = reinterpret_cast<uint32_t*>(&p);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    to[i] = a[i];
+    to[16 + i] = b[i];
+    if (i < 8) to[32 + i] = c[i];
+    if (i < 4) to[40 + i] = d[i];
+  }
+  return p;
+}
+
 // A unit record in registers, all of it: left to itself the compiler reads it field by field where a field is first
 // used, one round trip after another.
 __device__ __forceinline__ XyDevUnit load_unit(const XyDevUnit* at) {
@@ -282,17 +319,6 @@ __device__ __forceinline__ void zero_tail_rows(unsigned slice_addr, int first_ro
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // before the hand-issued fragment reads that follow
 }
 
-// Element offset (inside the K or V cache, before the KV head is added) of key row j of a sequence:
-// page seq_table[j / page size], slot j % page size (paper section 4.1.1).  Sixteen consecutive rows
-// starting at a multiple of 16 always share a page (pages hold 16, 32, 64 or 128 tokens).  Rows past
-// the sequence's last page are never visible; they are redirected to the last page so that whatever
-// lands in LDS for them is ordinary finite cache content.
-__device__ __forceinline__ int64_t kv_row_offset(const XY_CONST int32_t* seq_table, int j, int last_page,
-                                                 const RunParams& p) {
-  const int page = min(j >> p.page_shift, last_page);
-  return (int64_t)seq_table[page] * p.kv_bs + (int64_t)(j & p.page_mask) * p.kv_ts;
-}
-
 // ---- per-lane description of the query rows a wavefront owns -------------------------
 template <int NT>
 struct Rows {
@@ -410,7 +436,7 @@ __device__ __forceinline__ void mask_step(const RunParams& p, const UnitCtx& c,
 // On return s holds the un-normalised probabilities 2^((score - m_ref) * c) <= 2^kLazyRescale.
 template <int NT>
 __device__ __forceinline__ void softmax_step(float cs, f32x16 (&s)[NT], float (&m_ref)[NT], float (&l_part)[NT],
-                                             f32x16 (&oacc)[NT][4]) {
+                                             f32x16 (&oacc)[NT][4], const bool first /* step: the accumulators are zero */) {
 #pragma unroll
   for (int rt = 0; rt < NT; ++rt) {
     float mx = fmaxf(s[rt][0], s[rt][1]);
@@ -423,10 +449,12 @@ __device__ __forceinline__ void softmax_step(float cs, f32x16 (&s)[NT], float (&
       const float m_new = bump ? fmaxf(m_ref[rt], mx) : m_ref[rt];
       const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((m_ref[rt] - m_new) * cs);
       l_part[rt] *= alpha;
+      if (!first) {
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+        for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[rt][dt][v] *= alpha;
+          for (int v = 0; v < 16; ++v) oacc[rt][dt][v] *= alpha;
+      }
       m_ref[rt] = m_new;
     }
     const float mc = (m_ref[rt] == -INFINITY) ? 0.f : m_ref[rt] * cs;
@@ -1331,7 +1359,8 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
   unsigned char* ring = smem + wave * 32768;        // one or two slices of [K 8 KB | V 8 KB]
   const int depth = p.narrow_depth;
   const unsigned ring_addr = lds_addr(ring);
-  // a 32-key slice starting at key j: two runs of sixteen rows, each inside one page; eight
+  // a 32-key slice starting at key j: two runs of sixteen rows, each inside one page (page j / page size of the sequence, slot
+  // j % page size, paper section 4.1.1; pages hold 16, 32, 64 or 128 tokens); eight
   // instructions per tensor, which is what the waits below count
   struct Slice {
     int64_t run[2];
@@ -1391,6 +1420,9 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
     } else {
       for (int e = 0; 4 * e < c.rows; ++e) load_q(q_row(e) + ((pos ^ ((4 * e + sub) & 15)) << 4), e);
     }
+    // all four here, behind Q: left to itself the compiler widens each entry as soon as it is asked for, and a unit
+    // starts with four round trips one after the other
+    asm volatile("" : "+s"(entries0.e[0]), "+s"(entries0.e[1]), "+s"(entries1.e[0]), "+s"(entries1.e[1]));
     const Slice first = locate(0, entries0), second = locate(1, entries1);
     load_slice(first, 0, true, false);          // issue order K, V
     load_slice(first, 0, false, true);
@@ -1435,7 +1467,7 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
     v_fetch<0>(vaddr, lo, vf);                // the first V fragments arrive while the softmax runs
     const int j = key_of(t);
     if (j + 32 > mask_from) mask_step<NT>(p, c, r, j + 8 * half, s);
-    softmax_step<NT>(p.c, s, st.m_ref, st.l_part, st.oacc);
+    softmax_step<NT>(p.c, s, st.m_ref, st.l_part, st.oacc, t == 0);
     pv_step<NT>(vaddr, lo, vf, s, st.oacc);   // all V reads have completed when this returns
     if (left >= depth) load_slice(next, t, false, true);
   }
@@ -1478,23 +1510,35 @@ __device__ __forceinline__ void process_short(const RunParams& p, const XyDevUni
   const int nsteps = (min(u.kv_end * kB, c.key_end) - jfirst + 31) >> 5;
   unsigned char* ring = smem + wave * 32768;        // [K slot | V slot]
   const unsigned kaddr = lds_addr(ring), vaddr = kaddr + 8192;
-  auto load_slice = [&](const int j, const bool want_k, const bool want_v) {      // eight instructions per tensor
-    const int64_t b0 = kv_row_offset(table, j, last_page, p) + head_off;
-    const int64_t b1 = kv_row_offset(table, j + 16, last_page, p) + head_off;
-    load_rows_async<4>(p.k + b0, p.v + b0, p.kv_ts, 0, ring, ring + 8192, dof, want_k, want_v);
-    load_rows_async<4>(p.k + b1, p.v + b1, p.kv_ts, 0, ring + 4096, ring + 8192 + 4096, dof, want_k, want_v);
+  // as in process_solo: two runs of sixteen rows, each inside one page (rows past the sequence's last page are never visible and
+  // redirected to that page, so that what lands in LDS for them is ordinary finite cache content)
+  struct Slice {
+    int64_t run[2];
   };
-  load_slice(jfirst, true, false);          // issue order K, V
-  load_slice(jfirst, false, true);
+  auto locate = [&](const int j) {          // both page-table entries asked for before either is waited for
+    int e0 = table[min(j >> p.page_shift, last_page)], e1 = table[min((j + 16) >> p.page_shift, last_page)];
+    asm volatile("" : "+s"(e0), "+s"(e1));
+    return Slice{{(int64_t)e0 * p.kv_bs + (int64_t)(j & p.page_mask) * p.kv_ts + head_off,
+                  (int64_t)e1 * p.kv_bs + (int64_t)((j + 16) & p.page_mask) * p.kv_ts + head_off}};
+  };
+  auto load_slice = [&](const Slice& at, const bool want_k, const bool want_v) {      // eight instructions per tensor
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+      load_rows_async<4>(p.k + at.run[g], p.v + at.run[g], p.kv_ts, 0, ring + 4096 * g, ring + 8192 + 4096 * g, dof, want_k, want_v);
+  };
+  Slice at = locate(jfirst);
+  load_slice(at, true, false);          // issue order K, V
+  load_slice(at, false, true);
 #pragma unroll 1
   for (int t = 0; t < nsteps; ++t) {
+    const int tn = t + 1;
+    if (tn < nsteps) at = locate(jfirst + 32 * tn);      // while K is waited for
     wait_vmcnt<8>();                          // K(t) has landed; only V(t) may still be in flight
     f32x16 s[NT];
     VFrags vf;
     qk_step<NT>(kaddr, lo, qf, s);            // all K reads have completed when this returns
-    const int tn = t + 1;
     if (tn < nsteps) {        // K slot is free again: refill it with the next slice
-      load_slice(jfirst + 32 * tn, true, false);
+      load_slice(at, true, false);
       wait_vmcnt<8>();        // V(t) has landed; the K refill stays in flight
     } else {
       wait_vmcnt<0>();
@@ -1504,40 +1548,126 @@ __device__ __forceinline__ void process_short(const RunParams& p, const XyDevUni
     v_fetch<0>(vaddr, lo, vf);                // the first V fragments arrive while the softmax runs
     const int j = jfirst + 32 * t;
     if (j + 32 > mask_from) mask_step<NT>(p, c, r, j + 8 * half, s);
-    softmax_step<NT>(p.c, s, st.m_ref, st.l_part, st.oacc);
+    softmax_step<NT>(p.c, s, st.m_ref, st.l_part, st.oacc, t == 0);
     pv_step<NT>(vaddr, lo, vf, s, st.oacc);   // all V reads have completed when this returns
-    if (tn < nsteps) load_slice(jfirst + 32 * tn, false, true);
+    if (tn < nsteps) load_slice(at, false, true);
   }
   finish_unit(p, u, c, r, st, col, half);
 }
 
-// Every workgroup is one worker of the Task-Table (paper section 3.3).  It first works through the
-// wide units of its list together, then its four wavefronts draw the remaining (bandwidth-bound)
-// units of the same list one by one from a shared cursor, each wavefront finishing whole units
-// on its own.
-// NARROW: how its units of at most 32 rows are processed (kSolo, kShort: kShortSlices in layout.cpp; 2 or 4: by a team of so many
+// NARROW: how the units of at most 32 rows are processed (kSolo, kShort: kShortSlices in layout.cpp; 2 or 4: by a team of so many
 // wavefronts each, kTeamOf4Slices in layout.cpp); a kernel for each, since the ways in one disturb each other's registers (short units
 // 3 to 5 %, launches on two slices up to 2 %).
-// NT: row tiles of a wavefront on its wide units (process_wide).
 constexpr int kSolo = 0, kShort = 1;
+template <int NARROW>
+__device__ __forceinline__ void process_narrow(const RunParams& p, const XyDevUnit& u, unsigned char* smem, const LaneOffsets& lo,
+                                               const DmaOffsets& dof) {
+  if constexpr (NARROW == kShort) process_short(p, u, smem, lo, dof);
+  else process_solo<1>(p, u, smem, lo, dof);
+}
+
+// consecutive workgroup ids land on different XCDs; each XCD gets a contiguous range of workers
+__device__ __forceinline__ int worker_of(int workgroup, int num_workers) {
+  return (num_workers & 7) == 0 ? (workgroup & 7) * (num_workers >> 3) + (workgroup >> 3) : workgroup;
+}
+
+// Teams: one unit for every team of the workers without wide units, none drawn; consecutive ones on different chiplets.
+// rank: of this worker among them.
+template <int TEAM>
+__device__ __forceinline__ void team_unit(const RunParams& p, int teams_begin, int rank, unsigned char* smem, const LaneOffsets& lo,
+                                          const DmaOffsets& dof) {
+  const int i = teams_begin + rank + p.free_workers * (wave_id() / TEAM);
+  const bool exists = i < p.num_units;
+  const XyDevUnit u = load_unit(p.units + (exists ? i : teams_begin));
+  process_solo<TEAM>(p, u, smem, lo, dof, exists);
+}
+
+// The narrow units of a worker's own list [begin, end): its wavefronts draw them from a cursor in LDS.
+template <int NARROW>
+__device__ __forceinline__ void own_units(const RunParams& p, int begin, int end, int& cursor, unsigned char* smem, const LaneOffsets& lo,
+                                          const DmaOffsets& dof) {
+  if (threadIdx.x == 0) cursor = begin + kThreads / 64;
+  __syncthreads();            // the cursor is initialised (and the tiles of the wide units are free)
+  int i = begin + wave_id();
+#pragma unroll 1
+  while (i < end) {
+    const XyDevUnit u = load_unit(p.units + i);
+    if (u.q_count * u.head_count <= 32) process_narrow<NARROW>(p, u, smem, lo, dof);
+    int got = 0;
+    if ((threadIdx.x & 63) == 0) got = atomicAdd(&cursor, 1);
+    i = __builtin_amdgcn_readfirstlane(got);
+  }
+}
+
+// The shared list of narrow units (dynamic assignment): every wavefront of every workgroup draws the
+// next unit of the list, largest first, until it is empty.  The last workgroup to leave puts the
+// counters back to zero for the next launch (a plan runs one launch at a time, as its workspace does).
+// First draw: a thousand wavefronts asking one counter at the same moment cost 15 us, so a worker without units
+// of its own has four entries reserved for it (numbered wavefront-major over such workers: a short list still
+// reaches every one of them).  A worker that comes here from wide units has none - an entry reserved for it
+// would wait for those to end while other CUs are idle (4 wide units and a dozen small ones: 25.8 -> 16.4 us, a chunk of 200 tokens beside 24 short decodes
+// 46.7 -> 36.3 us, a chunk of 512 beside 64 decodes 161 -> 153 us) -
+// and draws four at once, one atomic for the workgroup.  rank: of this worker among those without units of their own, or -1.
+template <int NARROW>
+__device__ __forceinline__ void shared_units(const RunParams& p, int worker, int shared_begin, int rank, int& first_draw,
+                                             unsigned char* smem, const LaneOffsets& lo, const DmaOffsets& dof) {
+  const int slots = p.free_workers * (kThreads / 64);
+  const bool any_left = shared_begin + slots < p.num_units;                        // behind the reserved entries
+  int next = wave_id() * p.free_workers + rank;
+  if (rank < 0) {
+    if (any_left && threadIdx.x == 0) first_draw = slots + atomicAdd(p.counters, kThreads / 64);
+    __syncthreads();          // the tiles of the wide units are free too
+    next = any_left ? __builtin_amdgcn_readfirstlane(first_draw) + wave_id() : p.num_units;
+  }
+#pragma unroll 1
+  while (true) {
+    const int i = shared_begin + next;
+    if (i >= p.num_units) break;
+    const XyDevUnit u = load_unit(p.units + i);
+    process_narrow<NARROW>(p, u, smem, lo, dof);
+    if (!any_left) break;
+    int got = 0;
+    if ((threadIdx.x & 63) == 0) got = slots + atomicAdd(p.counters, 1);
+    next = __builtin_amdgcn_readfirstlane(got);
+  }
+  if (!any_left) return;      // nothing was drawn: the counters are as they were
+  __syncthreads();            // all four wavefronts are done with the cursor
+  // No fence: every cursor draw above has returned its value, so it was performed at the
+  // memory side before this count is; a device-wide fence here would write back and drop
+  // this chiplet's L2 under the workgroups that are still streaming K/V through it.
+  // The count of workgroups that have left is kept in two levels (eight groups of workgroups, each
+  // on a cache line of its own, then one count of finished groups): 256 atomics on one address
+  // would take several microseconds, which a short decode step cannot hide.
+  if (threadIdx.x == 0) {
+    const int groups = p.num_workers < kDoneGroups ? p.num_workers : kDoneGroups;
+    const int g = worker % kDoneGroups;
+    const int members = (p.num_workers - g + kDoneGroups - 1) / kDoneGroups;
+    int* done = p.counters + kCounterStride * (1 + g);
+    int* top = p.counters + kCounterStride * (1 + kDoneGroups);
+    if (atomicAdd(done, 1) == members - 1) {
+      __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (atomicAdd(top, 1) == groups - 1) {
+        __hip_atomic_store(top, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p.counters, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+}
+
+// Launches with units of more than 32 rows.  Every workgroup is one worker of the Task-Table (paper section 3.3).  It first
+// works through the wide units of its list together, then its four wavefronts draw the remaining (bandwidth-bound)
+// units of the same list one by one from a shared cursor, each wavefront finishing whole units
+// on its own.
+// NT: row tiles of a wavefront on its wide units (process_wide).
 template <int NARROW, int NT>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void xy_attn_units_kernel(RunParams p) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kTileBytes];
   __shared__ int cursor, first_draw;
   __shared__ int overflow_flags[kThreads / 64];
-  // consecutive workgroup ids land on different XCDs; give each XCD a contiguous range of workers
-  int worker = blockIdx.x;
-  if ((p.num_workers & 7) == 0) worker = (blockIdx.x & 7) * (p.num_workers >> 3) + (blockIdx.x >> 3);
-  constexpr bool kTeams = NARROW > 1;
-  const bool no_lists = kTeams && p.free_workers == p.num_workers;       // teams only: nothing to look up
-  int begin = 0, end = 0;
-  if (!no_lists) {
-    begin = as_const(p.worker_offsets)[worker];
-    end = as_const(p.worker_offsets)[worker + 1];
-  }
+  const int worker = worker_of(blockIdx.x, p.num_workers);
+  const int begin = as_const(p.worker_offsets)[worker], end = as_const(p.worker_offsets)[worker + 1];
   const LaneOffsets lo = make_lane_offsets(threadIdx.x & 63);
   const DmaOffsets dof = make_dma_offsets(threadIdx.x & 63, p.kv_ts);
-  if (threadIdx.x == 0) cursor = begin;
   bool force = false;         // the unit at hand is run a second time, with exact references (see process_wide)
 #pragma unroll 1
   for (int i = begin; i < end;) {
@@ -1559,89 +1689,42 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
     force = again;              // wavefront- and workgroup-uniform
     if (!again) ++i;
   }
-  __syncthreads();            // the tiles are free; the cursor is initialised
-  // The narrow phase reads the kernel arguments afresh (through a pointer the compiler cannot see through)
+  // The narrow phase reads the kernel arguments afresh
   // instead of keeping the copies of the wide phase alive: what that phase had to spill to make room for
   // its own scalars would otherwise be reloaded lane by lane in every step of every narrow unit.
-  const XY_CONST RunParams* args = (const XY_CONST RunParams*)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(args));
-  const RunParams pn = load_const((const RunParams*)args);
-  if constexpr (kTeams) {
-    // one unit for every team of the workers without wide units, none drawn: consecutive ones on different chiplets, by
-    // the ranks or, without wide units, by the workgroups' numbers
+  const RunParams pn = load_args();
+  if constexpr (NARROW > 1) {
     if (begin < end) return;
-    const int teams_begin = no_lists ? 0 : as_const(pn.worker_offsets)[pn.num_workers];
-    const int rank = no_lists ? blockIdx.x : as_const(pn.worker_offsets)[pn.num_workers + 1 + worker];
-    const int i = teams_begin + rank + pn.free_workers * (wave_id() / NARROW);
-    const bool exists = i < pn.num_units;
-    const XyDevUnit u = load_unit(pn.units + (exists ? i : teams_begin));
-    process_solo<NARROW>(pn, u, smem, lo, dof, exists);
+    team_unit<NARROW>(pn, as_const(pn.worker_offsets)[pn.num_workers], as_const(pn.worker_offsets)[pn.num_workers + 1 + worker], smem, lo, dof);
     return;
   }
-#pragma unroll 1
-  while (true) {
-    int got = 0;
-    if ((threadIdx.x & 63) == 0) got = atomicAdd(&cursor, 1);
-    const int i = __builtin_amdgcn_readfirstlane(got);
-    if (i >= end) break;
-    const XyDevUnit u = load_unit(pn.units + i);
-    if (u.q_count * u.head_count > 32) continue;
-    if (NARROW == kShort) process_short(pn, u, smem, lo, dof);
-    else process_solo<1>(pn, u, smem, lo, dof);
+  if (!pn.counters) {
+    if (begin < end) own_units<NARROW>(pn, begin, end, cursor, smem, lo, dof);
+  } else {                    // all narrow units are on the shared list
+    shared_units<NARROW>(pn, worker, as_const(pn.worker_offsets)[pn.num_workers], as_const(pn.worker_offsets)[pn.num_workers + 1 + worker],
+                         first_draw, smem, lo, dof);
   }
-  if (pn.counters) {
-    // The shared list of narrow units (dynamic assignment): every wavefront of every workgroup draws the
-    // next unit of the list, largest first, until it is empty.  The last workgroup to leave puts the
-    // counters back to zero for the next launch (a plan runs one launch at a time, as its workspace does).
-    // First draw: a thousand wavefronts asking one counter at the same moment cost 15 us, so a worker without units
-    // of its own has four entries reserved for it (numbered wavefront-major over such workers: a short list still
-    // reaches every one of them).  A worker that comes here from wide units has none - an entry reserved for it
-    // would wait for those to end while other CUs are idle (4 wide units and a dozen small ones: 25.8 -> 16.4 us, a chunk of 200 tokens beside 24 short decodes
-    // 46.7 -> 36.3 us, a chunk of 512 beside 64 decodes 161 -> 153 us) -
-    // and draws four at once, one atomic for the workgroup.
-    const int shared_begin = as_const(pn.worker_offsets)[pn.num_workers];
-    const int rank = as_const(pn.worker_offsets)[pn.num_workers + 1 + worker];       // among the workers without units, or -1
-    const int slots = pn.free_workers * (kThreads / 64);
-    const bool any_left = shared_begin + slots < pn.num_units;                        // behind the reserved entries
-    int next = wave_id() * pn.free_workers + rank;
-    if (rank < 0) {
-      if (any_left && threadIdx.x == 0) first_draw = slots + atomicAdd(pn.counters, kThreads / 64);
-      __syncthreads();
-      next = any_left ? __builtin_amdgcn_readfirstlane(first_draw) + wave_id() : pn.num_units;
-    }
-#pragma unroll 1
-    while (true) {
-      const int i = shared_begin + next;
-      if (i >= pn.num_units) break;
-      const XyDevUnit u = load_unit(pn.units + i);
-      if (NARROW == kShort) process_short(pn, u, smem, lo, dof);
-      else process_solo<1>(pn, u, smem, lo, dof);
-      if (!any_left) break;
-      int got = 0;
-      if ((threadIdx.x & 63) == 0) got = slots + atomicAdd(pn.counters, 1);
-      next = __builtin_amdgcn_readfirstlane(got);
-    }
-    __syncthreads();            // all four wavefronts are done with the cursor
-    // No fence: every cursor draw above has returned its value, so it was performed at the
-    // memory side before this count is; a device-wide fence here would write back and drop
-    // this chiplet's L2 under the workgroups that are still streaming K/V through it.
-    // The count of workgroups that have left is kept in two levels (eight groups of workgroups, each
-    // on a cache line of its own, then one count of finished groups): 256 atomics on one address
-    // would take several microseconds, which a short decode step cannot hide.
-    if (threadIdx.x == 0) {
-      const int groups = pn.num_workers < kDoneGroups ? pn.num_workers : kDoneGroups;
-      const int g = worker % kDoneGroups;
-      const int members = (pn.num_workers - g + kDoneGroups - 1) / kDoneGroups;
-      int* done = pn.counters + kCounterStride * (1 + g);
-      int* top = pn.counters + kCounterStride * (1 + kDoneGroups);
-      if (atomicAdd(done, 1) == members - 1) {
-        __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (atomicAdd(top, 1) == groups - 1) {
-          __hip_atomic_store(top, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(pn.counters, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-      }
-    }
+}
+
+// Launches without: the workers' lists are either all there is, or empty (one shared list, or teams), and there is nothing to
+// look up then.  Short ones are bound by the chain of loads in front of a unit's first keys: arguments, record, page-table
+// entries, K, each asked for as a whole before anything waits.  With the lists, a barrier, the arguments read twice and the entries
+// one after the other, as in the kernel above until this one was split off: a decode of 1300 tokens, appended and merged, 13.4 ->
+// 11.0 us a call, 24 decodes beside a suffix of 200 tokens (the entries alone) 31.8 -> 31.0 us a layer, 8 decodes x 32 KV heads on
+// 2-6k tokens 87.8 -> 86.4, 128 trees on 512-4096 tokens 153.1 -> 152.4.
+template <int NARROW>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void xy_attn_narrow_kernel(RunParams) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kTileBytes];
+  __shared__ int cursor, first_draw;
+  const RunParams p = load_args();
+  const LaneOffsets lo = make_lane_offsets(threadIdx.x & 63);
+  const DmaOffsets dof = make_dma_offsets(threadIdx.x & 63, p.kv_ts);
+  if constexpr (NARROW > 1) {
+    team_unit<NARROW>(p, 0, blockIdx.x, smem, lo, dof);
+  } else {
+    const int worker = worker_of(blockIdx.x, p.num_workers);
+    if (p.counters) shared_units<NARROW>(p, worker, 0, worker, first_draw, smem, lo, dof);
+    else own_units<NARROW>(p, as_const(p.worker_offsets)[worker], as_const(p.worker_offsets)[worker + 1], cursor, smem, lo, dof);
   }
 }
 
@@ -1892,12 +1975,17 @@ static int run_impl(int phases, xy_attn_plan* plan, const void* q, int64_t q_ts,
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (phases & XY_PHASE_UNITS) {
     const XyLayout& l = plan->layout;
-    const auto kernel = l.team == 4 ? xy_attn_units_kernel<4, 1>
+    // without wide units either the workers' lists hold everything or none of them holds anything: narrow units have a list of
+    // their own as a whole
+    const bool narrow_only = plan->narrow_units == (int64_t)plan->units.size();
+    const auto kernel = narrow_only ? (l.team == 4 ? xy_attn_narrow_kernel<4> : l.team == 2 ? xy_attn_narrow_kernel<2>
+                                       : l.short_units ? xy_attn_narrow_kernel<kShort> : xy_attn_narrow_kernel<kSolo>)
+                        : l.team == 4 ? xy_attn_units_kernel<4, 1>
                         : l.team == 2 ? xy_attn_units_kernel<2, 1>
                         : l.row_tiles == 2 ? (l.short_units ? xy_attn_units_kernel<kShort, 2> : xy_attn_units_kernel<kSolo, 2>)
                                            : (l.short_units ? xy_attn_units_kernel<kShort, 1> : xy_attn_units_kernel<kSolo, 1>);
     // teams without wide units need no workgroup more than there are units
-    const int32_t workgroups = l.team && p.free_workers == p.num_workers ? std::min(p.num_workers, p.num_units) : p.num_workers;
+    const int32_t workgroups = l.team && narrow_only ? std::min(p.num_workers, p.num_units) : p.num_workers;
     hipLaunchKernelGGL(kernel, dim3(workgroups), dim3(kThreads), 0, stream, p);
     if (hipGetLastError() != hipSuccess) return XY_ERR_HIP;
   }

@@ -900,15 +900,29 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
 
   // ---- start of a unit -----------------------------------------------------------------------------------
   // What stands around the loop is paid once per unit and by nobody else's time (a short prompt's units spend more
-  // here than in the loop), so it is laid out for latency: the page-table entries, then Q and the first two half
-  // blocks of K and V are in flight together, and Q goes through LDS.  Read straight into fragments, a Q load touches
+  // here than in the loop), so it is laid out for latency: the page-table entries, then the first two half blocks of K and
+  // V and Q are in flight together (what bounds them is the 64 bytes a cycle that LDS-direct loads deliver to a CU, 2000
+  // cycles for 128 KB, under which the addresses of Q's rows are worked out), and Q goes through LDS.  Read straight into fragments, a Q load touches
   // 32 rows for 32 bytes each, and the address path of the CU takes about a line per cycle; through LDS an
   // instruction moves four whole rows.  The rows (256 bytes, 16-byte chunks swizzled by the low four bits of the
   // row) wait in ring slots 2 and 3, which are requested when every wavefront has its Q.
   // With the way the results leave (below), the first reference taken without rescaling what is still zero and the
   // last V fragments requested together, a unit of 256 rows alone takes 2.9 us less (what is left: GapTables).
-  __syncthreads();                                          // the ring is free
+  // K and V stand in front of Q: the compiler waits for the page-table entries together with every LDS-direct load behind
+  // them, so behind Q they were asked for when it had landed.  All three have landed at one barrier, and the scaling of Q, the first
+  // scores' MFMAs and the requests of half block 2 then share one stretch of code instead of following each other.  With
+  // the record read as a whole, us before / after: a suffix of 224 tokens beside 24 decodes, planned, appended and merged,
+  // eight layers 247.7 / 241.0; eight prompts of 60-4000 tokens 121.7 / 117.8; a chunk of 128 tokens beside three narrow sequences 10.4 / 10.2.
   const int entry0 = table_entry(0, 0), entry1 = table_entry(0, 1);
+  __syncthreads();                                          // the ring is free
+  fill_table(0, entry0, entry1);
+  auto request_now = [&](const int h) {
+    setup_request(h);
+#pragma unroll
+    for (int idx = 0; idx < 8; ++idx) issue(idx);
+  };
+  request_now(0);
+  request_now(1);
   unsigned char* const wave_buf = smem + 65536 + wave * (8192 * NT);        // 32 NT rows of 256 bytes
   const int sub = lane >> 4, pos = lane & 15;               // a load or store of four rows: row, 16-byte chunk
   auto rows_in_order = [&](const int e) { return row_index(min(row_base + 4 * e + sub, c.rows - 1), c.hc, inv_hc); };
@@ -927,14 +941,6 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
       for (int e = 0; e < 8 * NT; ++e) q_load(q0 + row_bytes<false>(rows_in_order(e), p.q_ts, p.q_hs) + chunk_of(e), e);
     }
   }
-  fill_table(0, entry0, entry1);
-  auto request_now = [&](const int h) {
-    setup_request(h);
-#pragma unroll
-    for (int idx = 0; idx < 8; ++idx) issue(idx);
-  };
-  request_now(0);
-  request_now(1);
   // the rows a lane owns, while the loads are in flight
   Rows<NT> r;
 #pragma unroll
@@ -965,7 +971,14 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
 #pragma unroll
     for (int i = 0; i < 4; ++i) l_part[rt][i] = 0.f;
   }
-  wait_vmcnt<16>();                                         // Q has landed; the two half blocks may be in flight
+  f32x16 negm[NT];          // -m_ref of the lane's row in all sixteen registers (0 while the row has no reference)
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) negm[rt][v] = 0.f;
+#pragma unroll
+  for (int rt = 0; rt < NT; ++rt) asm volatile("" : "+v"(negm[rt]));
+  wait_vmcnt<0>();                                          // this wavefront's part of half blocks 0 and 1, and Q
   if (active) {
     const unsigned qaddr = lds_addr(wave_buf) + col * 256;
 #pragma unroll
@@ -977,40 +990,25 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
       lds_wait<0>(qf[rt][4], qf[rt][5], qf[rt][6], qf[rt][7]);
     }
   }
-  __builtin_amdgcn_s_barrier();                             // slots 2 and 3 are free
-  request_now(2);                                           // K(0..3), V(0..2)
-  if (wave < 2) request_now(3);
-  if (active) {
+  __builtin_amdgcn_s_barrier();                             // half blocks 0 and 1 are there for everybody, slots 2 and 3 are free
+  auto scale_q = [&](const int ks) {
 #pragma unroll
-    for (int rt = 0; rt < NT; ++rt)
+    for (int rt = 0; rt < NT; ++rt) {
+      if (PRESCALE) {
+        uint4 w = __builtin_bit_cast(uint4, qf[rt][ks]);
+        unsigned* wp = reinterpret_cast<unsigned*>(&w);
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        if (PRESCALE) {
-          uint4 w = __builtin_bit_cast(uint4, qf[rt][ks]);
-          unsigned* wp = reinterpret_cast<unsigned*>(&w);
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            wp[i] = pack_bf16(__uint_as_float(wp[i] << 16) * cs, __uint_as_float(wp[i] & 0xffff0000u) * cs);
-          qf[rt][ks] = __builtin_bit_cast(bf16x8, w);
-        }
-        asm volatile("; Q fragment lives in the AGPR file from here on" : "+a"(qf[rt][ks]));
+        for (int i = 0; i < 4; ++i)
+          wp[i] = pack_bf16(__uint_as_float(wp[i] << 16) * cs, __uint_as_float(wp[i] & 0xffff0000u) * cs);
+        qf[rt][ks] = __builtin_bit_cast(bf16x8, w);
       }
-  }
+      asm volatile("; Q fragment lives in the AGPR file from here on" : "+a"(qf[rt][ks]));
+    }
+  };
 
   f32x16 sa[NT], sb[NT];
   bf16x8 pa[NT][2], pb[NT][2];
   bf16x8 kf[8], vf[8];
-  f32x16 negm[NT];          // -m_ref of the lane's row in all sixteen registers (0 while the row has no reference)
-#pragma unroll
-  for (int rt = 0; rt < NT; ++rt)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) negm[rt][v] = 0.f;
-#pragma unroll
-  for (int rt = 0; rt < NT; ++rt) asm volatile("" : "+v"(negm[rt]));
-  if (wave < 2) wait_vmcnt<16>();                           // half blocks 0 and 1 have landed
-  else wait_vmcnt<8>();
-  __builtin_amdgcn_s_barrier();
-
   auto request_k = [&](const unsigned kaddr, const int i) { kf[i] = lds_read_b128<0>(kaddr + lo.k[i]); };
   auto request_v = [&](const unsigned vaddr, const int i) {
     if (i < 4) v_fetch_one<0>(vaddr, lo, i, vf[i]);
@@ -1187,16 +1185,28 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   if (active) {
     // iteration 0 multiplies V of step 0 already (by zeros, see below): cleared first where that is the last step
     if (nsteps == 1) zero_tail_rows(k_slice(0) + 16384, min(u.kv_end * kB, key_end) - jfirst, lane);
-    // S^T of step 0 against reference 0, then iteration 0 (exact prefix, no previous step)
+    // S^T of step 0 against reference 0 under the scaling of Q, with the requests of half block 2 (K(0..3), V(0..2) in all)
+    // in between; then iteration 0 (exact prefix, no previous step)
 #pragma unroll
     for (int i = 0; i < 8; ++i) request_k(k_slice(0), i);
+    setup_request(2);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i == 0) lds_wait<4>(kf[0], kf[1], kf[2], kf[3]);
-      if (i == 4) lds_wait<0>(kf[4], kf[5], kf[6], kf[7]);
+    for (int i = 0; i < 9; ++i) {
+      if (i < 8) {
+        scale_q(i);
+        issue(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (i == 1) lds_wait<4>(kf[0], kf[1], kf[2], kf[3]);
+      if (i == 5) lds_wait<0>(kf[4], kf[5], kf[6], kf[7]);
+      if (i == 8) valu_to_mfma_gap();
+      if (i > 0) {
 #pragma unroll
-      for (int rt = 0; rt < NT; ++rt) mfma_qk(i, sa[rt], rt);
+        for (int rt = 0; rt < NT; ++rt) mfma_qk(i - 1, sa[rt], rt);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
+    if (wave < 2) request_now(3);
 #pragma unroll
     for (int rt = 0; rt < NT; ++rt) mfma_settle(sa[rt]);
 #pragma unroll
@@ -1208,6 +1218,9 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
     }
     // iteration 0 has no previous step: its probabilities are zero and meet V of step 0 (keys of the unit, or zeros)
     exact = iterate(true, -1, 0, k_slice(1), k_slice(0) + 16384, k_slice(2), sa, sb, pb, pa);
+  } else {
+    request_now(2);
+    if (wave < 2) request_now(3);
   }
   const int hshift = wave < 2 ? 5 : 4;
   auto hreq = [&](const int j) { return j + hshift; };
@@ -1671,7 +1684,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
   bool force = false;         // the unit at hand is run a second time, with exact references (see process_wide)
 #pragma unroll 1
   for (int i = begin; i < end;) {
-    const XyDevUnit u = load_const(p.units + i);
+    const XyDevUnit u = load_unit(p.units + i);
     if (u.q_count * u.head_count <= 32) {
       ++i;
       continue;

@@ -372,3 +372,30 @@ def test_teams_of_wavefronts_on_narrow_units(gpu, team, wide, hq, hkv, tokens):
             db.close()
         b.k_cache[:], b.v_cache[:] = saved
         run_and_check(gpu, b, f"team of {team}, split {split}", plan_check, **cfg)
+
+
+@pytest.mark.parametrize("workers, row_tiles", [(8, 2), (256, None)])
+@pytest.mark.parametrize("group", [1, 2, 4, 8, 16, 3, 12, 32])
+def test_rows_of_a_wide_unit_leave_by_steps_of_sixteen(gpu, group, workers, row_tiles):
+    """Results of whole wavefronts whose heads divide sixteen are stored by steps of sixteen rows, all others row by row: both
+    for each group size, in units that end at, one token before and one token behind a wavefront's rows, with a padded output."""
+    import torch
+    from paper_2412_18106_amd import binding as X
+    tile = max(1, 256 // group)
+    lens = [tile, tile - 1, max(33 // group + 1, tile // 2), max(33 // group + 1, tile // 2 - 1), tile // 2 + 1, max(33 // group + 1, tile // 4 + 1)]
+    b = W.make_custom([W.SeqSpec(n, 40 + n, P) for n in lens], 2 * group, 2, 7000 + group)
+    db = gpu.DeviceBatch(b, num_workers=workers, split_kv_blocks=0)
+    try:
+        if row_tiles == 2:
+            assert_layout(db, row_tiles=2)
+        out = torch.full((b.total_q, 2 * group + 1, 136), float("nan"), dtype=torch.bfloat16, device="cuda")
+        X.xy_attn_run(db.plan, db.q, db.k_cache, db.v_cache, db.block_table, db.tree_masks, out[:, :2 * group, :128], db.workspace, b.scale)
+        torch.cuda.synchronize()
+        assert torch.isnan(out[:, 2 * group]).all() and torch.isnan(out[..., 128:]).all()       # nothing beside the rows
+        got = out[:, :2 * group, :128].float().cpu().numpy()
+    finally:
+        db.close()
+    ref = A.attention_oracle(b.seqs, b.q, b.k_cache, b.v_cache, b.block_table, b.tree_masks,
+                             num_q_heads=b.num_q_heads, num_kv_heads=b.num_kv_heads, block_size=b.block_size, scale=b.scale)
+    err = np.abs(got.astype(np.float64) - ref)
+    assert not np.isnan(got).any() and err.max() <= MAX_ABS and err.mean() <= MEAN_ABS

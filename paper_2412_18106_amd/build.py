@@ -90,7 +90,7 @@ def build(verbose=False):
         if asm.returncode != 0:
             os.remove(tmp)
             raise RuntimeError("hipcc -S failed:\n" + asm.stderr)
-        problems = hazard_lint.lint(asm.stdout)
+        problems = hazard_lint.lint(asm.stdout, follow_branches=True)
         if problems:
             if os.path.exists(LIB):
                 os.remove(LIB)

@@ -723,7 +723,8 @@ __device__ __forceinline__ void valu_to_mfma_gap() { asm volatile("s_nop 4"); }
 // control flow merges it may copy them right behind the MFMA.  These statements sit directly behind the
 // last MFMA of a sequence (volatile keeps the order, the operands keep every use of the results
 // behind them) and pad the wait states a vector-ALU access of an MFMA result needs: settle covers a copy
-// the compiler may place there, ready covers a read of the values.
+// the compiler may place there, ready covers a read of the values.  No branch comes between: the copy may stand on either
+// side of it.  (The build's check of the assembly follows the branches and reports one that does.)
 __device__ __forceinline__ void mfma_settle(f32x16& a) { asm volatile("s_nop 7\n\ts_nop 4" : "+v"(a)); }
 __device__ __forceinline__ void settle_a(f32x16& a, f32x16& b, f32x16& c, f32x16& d) {
   asm volatile("s_nop 7\n\ts_nop 4" : "+a"(a), "+a"(b), "+a"(c), "+a"(d));
@@ -1209,9 +1210,9 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (wave < 2) request_now(3);
 #pragma unroll
-    for (int rt = 0; rt < NT; ++rt) mfma_settle(sa[rt]);
+    for (int rt = 0; rt < NT; ++rt) mfma_settle(sa[rt]);      // ahead of the branch
+    if (wave < 2) request_now(3);
 #pragma unroll
     for (int i = 0; i < 4; ++i) request_k(k_slice(1), i);
 #pragma unroll

@@ -19,10 +19,11 @@ on its output instead:
   forgot to name "scc" among what it clobbers; met as a loop that never ended and then read
   out of bounds);
 
-The check walks the assembly text of the device code straight down from each
-such instruction to the end of its basic block.  It is conservative in one
-direction only: everything it reports is a real hazard; a hazard that needs a
-taken branch to happen is not seen.
+Everything the check reports is a real hazard of the path it names.  Backwards (operands of an MFMA) and
+for the SCC flag it walks the assembly text straight through the basic block of the instruction.  Forwards (results
+of MFMAs and of LDS reads) it does the same by default; with ``follow_branches``, as the build calls it, it goes on
+through labels and barriers and takes both sides of every branch until the wait is over, since a copy where
+control flow merges may stand behind a taken branch.
 """
 from __future__ import annotations
 
@@ -62,9 +63,74 @@ def _operands(line):
     return parts[0], ops, parts[1]
 
 
-def lint(asm_text):
+_LABEL = re.compile(r"^([.\w$]+):")
+_CONTROL = ("s_cbranch", "s_branch", "s_endpgm", "s_setpc", "s_swappc")
+# the address of a far jump: s_getpc_b64, two additions of the distance to the label, s_setpc_b64
+_FAR = re.compile(r"\((\.L\w+)-")
+
+
+def _next_lines(lines, labels, j, t):
+    """Lines that may follow the control-flow instruction t on line j."""
+    op = t.split()[0]
+    if op == "s_endpgm":
+        return []
+    if op == "s_setpc_b64":
+        far = next((m.group(1) for k in range(j - 1, max(j - 8, -1), -1) for m in [_FAR.search(lines[k])] if m), None)
+        if far not in labels:
+            raise ValueError(f"line {j + 1}: '{t}' jumps to an address this check cannot tell")
+        return [labels[far]]
+    target = t.split()[1] if op.startswith(("s_branch", "s_cbranch")) else None
+    if target not in labels:
+        raise ValueError(f"line {j + 1}: '{t}' goes to a place this check cannot tell")
+    return [labels[target]] if op == "s_branch" else [j + 1, labels[target]]
+
+
+def _walk(lines, labels, start, limit):
+    """Yields (line, text, wait states passed) of the instructions that follow line start, until limit wait states have
+    passed on a path; a true value sent back ends the path there.  labels: None stays in the basic block."""
+    paths, least = [(start + 1, 0)], {}
+    while paths:
+        j, waited = paths.pop()
+        while j < len(lines) and waited < limit:
+            t = lines[j].strip()
+            if not t or t.startswith(";") or (labels is not None and not t.startswith("s_") and (_LABEL.match(t) or t.startswith("."))):
+                j += 1
+                continue
+            if labels is None and (t.endswith(":") or t.startswith(".")):
+                break
+            if least.get(j, limit) <= waited:
+                break                     # this line has been reached with as little waiting before
+            least[j] = waited
+            if t.startswith(_CONTROL):
+                if labels is not None:
+                    paths += [(k, waited + 1) for k in _next_lines(lines, labels, j, t)]
+                break
+            if (yield j, t, waited):
+                break
+            op = t.split()[0]
+            waited += int(t.split()[1]) + 1 if op == "s_nop" else 1
+            j += 1
+
+
+def _follow(lines, labels, start, limit, ends):
+    """Line, text and wait states of the first instruction of a path behind line start for which ends says "hit"; "safe" ends
+    a path without one."""
+    walk = _walk(lines, labels, start, limit)
+    try:
+        j, t, waited = next(walk)
+        while True:
+            verdict = ends(t)
+            if verdict == "hit":
+                return j, t, waited
+            j, t, waited = walk.send(verdict == "safe")
+    except StopIteration:
+        return None
+
+
+def lint(asm_text, follow_branches=False):
     """Returns a list of (line number, message) for the hazards found in an AMDGPU assembly listing."""
     lines = asm_text.splitlines()
+    labels = {m.group(1): i for i, line in enumerate(lines) for m in [_LABEL.match(line.strip())] if m} if follow_branches else None
     in_asm = False
     problems = []
     for i, raw in enumerate(lines):
@@ -129,43 +195,28 @@ def lint(asm_text):
                 if waited >= VALU_TO_MFMA_WAIT_STATES:
                     break
             dst = _regs(ops[0])
-            waited = 0
-            for j in range(i + 1, len(lines)):
-                t = lines[j].strip()
-                if not t or t.startswith(";"):
-                    continue
-                if t.endswith(":") or t.startswith(".") or t.startswith("s_cbranch") or t.startswith("s_branch") \
-                        or t.startswith("s_endpgm") or t.startswith("s_barrier"):
-                    break
+
+            def ends(t):
                 o2, ops2, rest2 = _operands(t)
-                if o2 == "s_nop":
-                    waited += int(ops2[0]) + 1
-                elif o2.startswith("v_mfma"):
-                    waited += 1       # the matrix pipe orders MFMAs among themselves
-                else:
-                    if _regs(rest2) & dst:
-                        problems.append((j + 1, f"'{t}' touches the result of the hand-issued MFMA at line {i + 1} "
-                                                f"after {waited} wait states (needs {MFMA_WAIT_STATES})"))
-                        break
-                    waited += 1
-                if waited >= MFMA_WAIT_STATES:
-                    break
+                if o2 == "s_barrier" and not follow_branches:
+                    return "safe"
+                # (the matrix pipe orders MFMAs among themselves)
+                return "hit" if not o2.startswith("v_mfma") and o2 != "s_nop" and _regs(rest2) & dst else None
+            found = _follow(lines, labels, i, MFMA_WAIT_STATES, ends)
+            if found:
+                j, t, waited = found
+                problems.append((j + 1, f"'{t}' touches the result of the hand-issued MFMA at line {i + 1} "
+                                        f"after {waited} wait states (needs {MFMA_WAIT_STATES})"))
         elif op.startswith("ds_read"):
             dst = _regs(ops[0])
-            for j in range(i + 1, len(lines)):
-                t = lines[j].strip()
-                if not t or t.startswith(";"):
-                    continue
-                if t.endswith(":") or t.startswith(".") or t.startswith("s_cbranch") or t.startswith("s_branch") \
-                        or t.startswith("s_endpgm"):
-                    break
+
+            def ends(t):
                 o2, ops2, rest2 = _operands(t)
                 if o2 == "s_waitcnt" and "lgkmcnt" in rest2:
-                    break
-                if o2 == "s_barrier":
-                    continue
-                if _regs(rest2) & dst:
-                    problems.append((j + 1, f"'{t}' touches the destination of the hand-issued LDS read at line {i + 1} "
-                                            "before any s_waitcnt lgkmcnt"))
-                    break
+                    return "safe"
+                return "hit" if _regs(rest2) & dst else None
+            found = _follow(lines, labels, i, 1 << 30, ends)
+            if found:
+                problems.append((found[0] + 1, f"'{found[1]}' touches the destination of the hand-issued LDS read at line {i + 1} "
+                                               "before any s_waitcnt lgkmcnt"))
     return problems

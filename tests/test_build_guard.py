@@ -1,4 +1,6 @@
 """Host-side build logic (CPU only)."""
+import pytest
+
 from paper_2412_18106_amd import build as B
 
 
@@ -62,6 +64,37 @@ def test_hazard_lint_flags_reads_of_hand_issued_results_and_passes_padded_code()
 	v_mov_b32_e32 v5, v82
 """
     assert H.lint(lds_ok) == []
+
+
+@pytest.mark.parametrize("branch, behind", [
+    ("s_cbranch_vccnz .LBB0_2", "taken"), ("s_cbranch_vccnz .LBB0_2", "not taken"), ("s_branch .LBB0_2", "taken"),
+    ("s_cbranch_scc1 .LBB0_9\n\ts_cbranch_scc0 .LBB0_2\n.LBB0_9:\n\ts_barrier", "not taken"),
+    ("s_getpc_b64 s[4:5]\n.Lpost_getpc0:\n\ts_add_u32 s4, s4, (.LBB0_2-.Lpost_getpc0)&4294967295\n"
+     "\ts_addc_u32 s5, s5, (.LBB0_2-.Lpost_getpc0)>>32\n\ts_setpc_b64 s[4:5]", "taken")])
+@pytest.mark.parametrize("issued, touched, settled", [
+    ("v_mfma_f32_32x32x16_bf16 v[18:33], v[98:101], v[146:149], v[18:33]", "v[32:33]", "s_nop 7\n\ts_nop 4"),
+    ("ds_read_b128 v[30:33], v90 offset:0", "v[32:33]", "s_waitcnt lgkmcnt(0)")])
+def test_hazard_lint_follows_branches(issued, touched, settled, branch, behind):
+    """A copy of a hand-issued result behind a branch is reported on the side it stands on, and not where the wait comes first."""
+    from paper_2412_18106_amd import hazard_lint as H
+    copy = f"v_mov_b64_e32 v[128:129], {touched}"
+    here, there = (copy, "s_nop 0") if behind == "not taken" else ("s_nop 0", copy)
+    text = f"""
+\t;;#ASMSTART
+\t{issued}
+\t;;#ASMEND
+%s
+\t{branch}
+\t{here}
+\ts_endpgm
+.LBB0_2:                                ; =>This Inner Loop Header: Depth=1
+\t{there}
+\ts_endpgm
+"""
+    found = H.lint(text % "", follow_branches=True)
+    assert len(found) == 1 and copy in found[0][1]
+    assert H.lint(text % f"\t;;#ASMSTART\n\t{settled}\n\t;;#ASMEND", follow_branches=True) == []
+    assert H.lint(text % "") == []          # by default the check ends with the basic block
 
 
 def test_hazard_lint_flags_compiler_writes_right_in_front_of_a_hand_issued_mfma():

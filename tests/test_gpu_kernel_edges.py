@@ -374,20 +374,20 @@ def test_teams_of_wavefronts_on_narrow_units(gpu, team, wide, hq, hkv, tokens):
         run_and_check(gpu, b, f"team of {team}, split {split}", plan_check, **cfg)
 
 
-@pytest.mark.parametrize("workers, row_tiles", [(8, 2), (256, None)])
+@pytest.mark.parametrize("workers, row_tiles", [(8, 2), (256, 1)])
 @pytest.mark.parametrize("group", [1, 2, 4, 8, 16, 3, 12, 32])
 def test_rows_of_a_wide_unit_leave_by_steps_of_sixteen(gpu, group, workers, row_tiles):
     """Results of whole wavefronts whose heads divide sixteen are stored by steps of sixteen rows, all others row by row: both
-    for each group size, in units that end at, one token before and one token behind a wavefront's rows, with a padded output."""
+    for each group size, on two row tiles a wavefront and on one (as halves: an even number of tokens, or those of 3 and 12 heads are
+    not divided), in units that end at, one token before and one token behind a wavefront's rows, with a padded output."""
     import torch
     from paper_2412_18106_amd import binding as X
-    tile = max(1, 256 // group)
+    tile = 256 // group if row_tiles == 2 else 256 // group // 2 * 2
     lens = [tile, tile - 1, max(33 // group + 1, tile // 2), max(33 // group + 1, tile // 2 - 1), tile // 2 + 1, max(33 // group + 1, tile // 4 + 1)]
     b = W.make_custom([W.SeqSpec(n, 40 + n, P) for n in lens], 2 * group, 2, 7000 + group)
     db = gpu.DeviceBatch(b, num_workers=workers, split_kv_blocks=0)
     try:
-        if row_tiles == 2:
-            assert_layout(db, row_tiles=2)
+        assert_layout(db, row_tiles=row_tiles)
         out = torch.full((b.total_q, 2 * group + 1, 136), float("nan"), dtype=torch.bfloat16, device="cuda")
         X.xy_attn_run(db.plan, db.q, db.k_cache, db.v_cache, db.block_table, db.tree_masks, out[:, :2 * group, :128], db.workspace, b.scale)
         torch.cuda.synchronize()

@@ -128,11 +128,6 @@ __device__ __forceinline__ RunParams load_args() {
   typedef __attribute__((ext_vector_type(16))) uint32_t u32x16;
   typedef __attribute__((ext_vector_type(8))) uint32_t u32x8;
   typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-  struct Words {
-    u32x16 a, b;
-    u32x8 c;
-    u32x4 d;
-  };
   static_assert(sizeof(RunParams) == 176, "RunParams is loaded as 16 + 16 + 8 + 4 words");
   const XY_CONST uint32_t* at = (const XY_CONST uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(at));              // not the copy that the wide units use: what they spill would be read back lane by lane
@@ -1744,10 +1739,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))
 
 // Launches without: the workers' lists are either all there is, or empty (one shared list, or teams), and there is nothing to
 // look up then.  Short ones are bound by the chain of loads in front of a unit's first keys: arguments, record, page-table
-// entries, K, each asked for as a whole before anything waits.  With the lists, a barrier, the arguments read twice and the entries
-// one after the other, as in the kernel above until this one was split off: a decode of 1300 tokens, appended and merged, 13.4 ->
-// 11.0 us a call, 24 decodes beside a suffix of 200 tokens (the entries alone) 31.8 -> 31.0 us a layer, 8 decodes x 32 KV heads on
-// 2-6k tokens 87.8 -> 86.4, 128 trees on 512-4096 tokens 153.1 -> 152.4.
+// entries, K, each asked for as a whole before anything waits (but in process_short, whose entries are waited for together
+// with its Q).  With the lists, a barrier, the arguments read twice and the entries one after the other, as in the kernel above
+// until this one was split off, us: one decode of 1000 tokens on teams (8 families in 64 pieces, this kernel alone) 7.07 -> 6.22,
+// where a call from Python is bound by the host and level; 24 decodes beside a suffix of 200 tokens (the entries alone)
+// 31.8 -> 31.0 a layer, 8 decodes x 32 KV heads on 2-6k tokens 87.8 -> 86.4, 128 trees on 512-4096 tokens 153.1 -> 152.4.
+// Teams spill no scalars.  The other two hold a body for the shared list and one for the workers' lists, of which a launch runs one,
+// and spill 43 (two of them read back in every slice of one body; else around a unit's loop) and 16.
 template <int NARROW>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void xy_attn_narrow_kernel(RunParams) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kTileBytes];

@@ -923,9 +923,6 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   const int sub = lane >> 4, pos = lane & 15;               // a load or store of four rows: row, 16-byte chunk
   auto rows_in_order = [&](const int e) { return row_index(min(row_base + 4 * e + sub, c.rows - 1), c.hc, inv_hc); };
   auto chunk_of = [&](const int e) { return (pos ^ ((4 * e + sub) & 15)) << 4; };
-  // whether sixteen rows further is so many tokens further, for all rows of the wavefront, and how many bytes that are
-  auto in_step = [&](const int hc) { return hc <= 16 && (hc & (hc - 1)) == 0 && row_base + 32 * NT <= c.rows; };
-  auto step16 = [&](const int hc, const int64_t ts) { return (32u >> (__builtin_ctz(hc) & 31)) * (unsigned)ts; };
   if (active) {
     const char* q0 = reinterpret_cast<const char*>(p.q + (int64_t)(u.token_start + u.q_begin) * p.q_ts + (int64_t)u.head_begin * p.q_hs);
     auto q_load = [&](const char* from, const int e) {
@@ -1333,14 +1330,21 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
     if (row_base + 4 * e + sub < c.rows) *reinterpret_cast<uint4*>(o0 + off + chunk_of(e)) = w;
   };
   // With heads that divide sixteen and every row there, sixteen rows further is so many tokens further, and all but the first
-  // four offsets follow by one addition instead of some sixteen instructions a store.  us before / after, append and merge
-  // included: eight prompts of 60-4000 tokens 119.0 / 118.2, eight suffixes of 1024 on 4-16k 841 / 834, a chunk of 128
-  // tokens beside three narrow sequences 10.2 / 10.1; a step whose wide units are all cut, which comes through here but for this
-  // branch, 242.8 / 244.8 for eight layers.  Other head groups keep the general way: with one of 64-bit offsets in a loop for
-  // them short prompts of 3, 5, 6 and 12 heads a group were 1 to 4 % slower.
+  // four offsets follow by one addition instead of some sixteen instructions a store.  us without / with it, append and merge
+  // included, both in turn, on two boxes: eight prompts of 60-4000 tokens 118.3 / 117.1, eight suffixes of 1024 on 4-16k 810.5 / 804.2,
+  // a chunk of 128 tokens beside three narrow sequences 10.15 / 10.01, a chunk of 1024 on 20-24k 321.8 / 320.1.  The other way
+  // round: eight layers of a suffix of 160 tokens beside 24 decodes 243.5 / 245.2, though its wide units are all cut and leave above,
+  // as those of the chunk do.  A cut unit runs the same blocks but for a few lane reads of spilled scalars, and fewer spilled ones
+  // (132 -> 114, with the strides read afresh here), a loop around the stores or hints on the branches left the loss at 0.5 to 1 %:
+  // what remains is where the code lies in a kernel of 221 KB.  Other head groups keep the general way: with one of 64-bit offsets
+  // in a loop for them short prompts of 3, 5, 6 and 12 heads a group were 1 to 4 % slower.
   const bool small_o = p.o_ts < kSmallStride && p.o_hs < kSmallStride;
   int hc = c.hc;
   asm volatile("" : "+s"(hc));      // what follows from it is worked out here, not kept from the start of the unit
+  // whether sixteen rows further is so many tokens further, for all rows of the wavefront, and how many bytes that are (as
+  // functions: written into the branch the kernel for short units on two row tiles takes 8 bytes of scratch memory)
+  auto in_step = [&](const int hc) { return hc <= 16 && (hc & (hc - 1)) == 0 && row_base + 32 * NT <= c.rows; };
+  auto step16 = [&](const int hc, const int64_t ts) { return (32u >> (__builtin_ctz(hc) & 31)) * (unsigned)ts; };
   if (small_o && in_step(hc)) {
     unsigned off[4];
     const unsigned step = step16(hc, p.o_ts);

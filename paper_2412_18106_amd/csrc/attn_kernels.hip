@@ -767,10 +767,10 @@ __device__ __forceinline__ void scale_acc(f32x16& acc, const float alpha) {
 // NT: row tiles of a wavefront, two as described, or one, where no unit of the launch has more than 128 rows: with two
 // such a unit leaves two of the four wavefronts without rows.  One tile means half the MFMAs, exponentials and rows to
 // load and store per wavefront and the same LDS requests.  Eight units alone, K/V in the caches, the whole launch fitted over
-// 8 to 32 tiles, us around the loop + a step of 32 keys: 124 rows 9.3 + 0.584 on two tiles, 7.2 + 0.396 on one; 256 rows
-// 10.4 + 0.594 on two, as halves (kHalfRows in layout.cpp) 7.3 + 0.398.  248 units of 124 rows on 1 / 4 / 16 tiles
-// 15.2 / 24.8 / 56.3 -> 12.7 / 20.4 / 45.2 us: 2.1 us a tile there, the memory's rate; four trees of 31 tokens on 10-20k
-// keys, with merge pass, 64.6 -> 60.7 us.
+// 8 to 32 tiles, us around the loop + a step of 32 keys: 124 rows 9.1 + 0.582 on two tiles, 6.9 + 0.402 on one; 256 rows
+// 9.2 + 0.592 on two, as halves (kHalfRows in layout.cpp) 6.9 + 0.400.  248 units of 124 rows on 1 / 4 / 16 tiles
+// 13.1 / 23.1 / 54.7 -> 11.1 / 19.3 / 44.4 us: 2.1 us a tile there, the memory's rate; four trees of 31 tokens on 10-20k
+// keys, with merge pass, 64.1 -> 61.3 us.
 // K fragments asked for eight chunks ahead instead of four changed nothing.
 template <int NT>
 struct GapTables;
@@ -907,7 +907,7 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
   // K and V stand in front of Q: the compiler waits for the page-table entries together with every LDS-direct load behind
   // them, so behind Q they were asked for when it had landed.  All three have landed at one barrier, and the scaling of Q, the first
   // scores' MFMAs and the requests of half block 2 then share one stretch of code instead of following each other.  With
-  // the record read as a whole, us before / after: a suffix of 224 tokens beside 24 decodes, planned, appended and merged,
+  // the record read as a whole, us before / after: a suffix of 160 tokens beside 24 decodes, planned, appended and merged,
   // eight layers 247.7 / 241.0; eight prompts of 60-4000 tokens 121.7 / 117.8; a chunk of 128 tokens beside three narrow sequences 10.4 / 10.2.
   const int entry0 = table_entry(0, 0), entry1 = table_entry(0, 1);
   __syncthreads();                                          // the ring is free
@@ -1374,8 +1374,8 @@ __device__ __forceinline__ bool process_wide(const RunParams& p, const XyDevUnit
 // Two slices (narrow_depth) with teams and where a launch has at most kDeepTiles tiles per wavefront: with every wavefront at work
 // the card's bandwidth is the bound and 16 KB each are enough, but a wavefront whose neighbours have run out of work waits
 // for memory in every slice, and that is the end of every launch.  8 decodes x 32 KV heads on 2-6k tokens (7.5 tiles per
-// wavefront) 94.8 -> 92.0 us with two; 128 trees on 512-4096 tokens (14 tiles) 153.0 -> 154.7 us, 128 decodes on
-// 2-16k (54 tiles) 553.7 -> 557.2 us, so those keep one.  Launches of short units take process_short instead.
+// wavefront), this kernel alone, 83.9 -> 82.4 us with two; 128 trees on 512-4096 tokens (14 tiles) 148.2 -> 150.7 us, so those keep one;
+// 128 decodes on 2-16k (54 tiles) are level, 552.8 / 552.1.  Launches of short units take process_short instead.
 template <int TEAM>
 __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit& u, unsigned char* smem, const LaneOffsets& lo,
                                              const DmaOffsets& dof, const bool exists = true) {
@@ -1513,7 +1513,7 @@ __device__ __forceinline__ void process_solo(const RunParams& p, const XyDevUnit
 // A unit of at most 32 rows in a launch of short ones (kShortSlices): one slice at a time, Q straight into registers and
 // no address worked out before its turn.  Such a unit is bound by the instructions of a lone wavefront and by the three
 // round trips to memory that follow each other (record, page table, K/V); what process_solo does on top pays off from the
-// fifth slice on.  512 decodes on 10-32 keys x 8 KV heads (one slice each) 22.5 -> 20.6 us.
+// fifth slice on.  512 decodes on 31 keys x 8 KV heads (one slice each) 21.8 -> 20.3 us.
 __device__ __forceinline__ void process_short(const RunParams& p, const XyDevUnit& u,
                                               unsigned char* smem, const LaneOffsets& lo, const DmaOffsets& dof) {
   constexpr int NT = 1;

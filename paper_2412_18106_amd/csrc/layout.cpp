@@ -14,27 +14,33 @@ constexpr int32_t kXcds = 8;
 constexpr int64_t kWavefronts = 4;          // per worker
 // How a launch processes its units of at most 32 rows, by what they are on average over the
 // launch; wavefronts are four per worker.  A unit on two slices costs some 200 instructions more than a short one, which
-// a lone wavefront pays for with 0.3 us, and gains where it waits for memory in every slice, with its neighbours idle.
-// Decodes of 32 heads in 8, each a unit of its own, us short / two slices: 4 slices 7.1 / 7.3 (8 units), 9.3 / 9.2 (512),
-// 24.4 / 24.7 (2048), 47.9 / 49.2 (4096); 1 and 2 slices 2 to 13 % less short; 8 slices 11.3 / 10.8, 14.5 / 13.6 up to a
-// unit for every second wavefront, 22.4 / 22.5 at one each, 89.4 / 91.6 at four: so up to four slices a unit are short,
-// up to eight where there are more units than wavefronts.  Units of 32 rows, whose Q is eight times as much: 4096 of them
-// 42.1 / 44.8 with 2 slices, 66.4 / 65.7 with 4: up to two slices above 16 rows a unit.
+// a lone wavefront pays for with 0.1 us and a busy CU with more, and gains where it waits for memory in every slice, with its
+// neighbours idle.  Unit kernel, us short / two slices, decodes of 32 heads in 8, each a unit of its own, caches cold:
+//   units   1 slice          2               3               4               5               8
+//   8       4.9 / 5.0        5.8 / 5.9       6.9 / 6.9       7.7 / 7.7       8.8 / 8.6       11.6 / 11.3
+//   512     6.1 / 6.3        7.3 / 8.2       8.7 / 9.1       10.0 / 10.2     11.7 / 11.6     15.0 / 14.7
+//   1024    7.5 / 7.9        9.8 / 10.9      12.1 / 12.6     14.6 / 14.8     17.6 / 17.7     24.7 / 24.9
+//   2048    12.5 / 13.1      16.5 / 18.8     21.6 / 22.4     25.5 / 26.1     31.4 / 31.7     46.8 / 46.3
+//   4096    20.3 / 21.8      29.0 / 32.5     38.2 / 38.9     47.9 / 49.0     59.4 / 60.4     90.5 / 90.9
+// so up to four slices a unit are short, up to eight (level there, 1 to 2 % at five) where there are more units than wavefronts.
+// Units of 32 rows, whose Q is eight times as much, 512 / 2048 / 4096 of them: 8.7 / 9.8, 22.9 / 25.4, 42.2 / 44.6 with 2 slices,
+// 10.0 / 10.7, 28.2 / 29.4, 52.7 / 53.1 with 3, 11.2 / 11.7, 32.5 / 33.7, 63.4 / 64.2 with 4.  The line of two slices above 16 rows
+// a unit was drawn when 4096 units of 4 slices took 66.4 / 65.7; with both ways as they are now it is on the safe side of where they meet.
 constexpr int64_t kShortSlices = 4, kShortSlicesManyUnits = 8, kShortSlicesManyRows = 2, kManyRows = 16;
-// Longer ones: two slices in flight up to kDeepTiles tiles a wavefront, one beyond (see process_solo; measured at 7.5
-// tiles, 3 % in favour of two, and at 14, 1 % against).
+// Longer ones: two slices in flight up to kDeepTiles tiles a wavefront, one beyond (see process_solo; two are 1 to 3 % faster at
+// 7.5 tiles and half a percent at 11.6, one is 2 % faster at 14 and 1 % at 15.5).
 constexpr int64_t kDeepTiles = 10;
 // Units of more than kHalfRows rows that go to the GPU as two, by their tokens, for a worker each: all of them or none.
 // The kernel then holds one row tile a wavefront instead of two, which takes two thirds of the time for units that are
 // alone, but reads the K/V twice and keeps two workers busy: only where there are idle workers for all second halves, with a
 // wavefront left for every narrow unit.  Unit kernel, us, whole / halves, 64 tokens x 4 heads, caches cold:
 //   units   1 K/V tile       4              16             64
-//   8       20.4 / 13.0      25.5 / 17.0    53.1 / 36.0
-//   64      18.6 / 12.3      27.5 / 18.2    56.2 / 40.8    170 / 125
-//   112     20.2 / 14.5      26.7 / 21.6    58.9 / 52.5    177 / 149
-//   128     18.5 / 15.2      29.9 / 22.9    63.4 / 58.1    185 / 162    (every worker busy)
-// and with fewer wavefronts left than narrow units the other way round (a suffix of 150-250 tokens beside 472 narrow units
-// 254.9 -> 266.0 us for eight layers, a chunk of 512 beside 1184 157 -> 164 us).  The plan the caller sees stays as it is.
+//   8       14.3 / 10.3      21.5 / 15.0    49.1 / 34.5    161 / 114
+//   64      14.7 / 11.0      22.2 / 16.4    51.0 / 37.5    166 / 119
+//   112     15.5 / 11.8      23.4 / 17.9    53.2 / 41.4    170 / 131
+//   128     15.6 / 12.1      23.9 / 18.7    53.8 / 42.6    170 / 142    (every worker busy)
+// and with fewer wavefronts left than narrow units the other way round (whole / halves: a suffix of 160 tokens beside 536
+// narrow units 244.0 / 259.7 us for eight layers, a chunk of 512 beside 1184 156.5 / 163.3).  The plan the caller sees stays as it is.
 // A half is at most kHalfRows rows, so the tokens of a unit must divide: with 3, 5, 10, 12 and some other heads a group the
 // default tile (256 / heads tokens: 85, 51, 25, 21) has a first half of 129 to 132 rows, and one such unit keeps the whole
 // launch on two row tiles, without teams.
@@ -42,12 +48,12 @@ int32_t first_half(const xy_work_unit& u) { return (u.q_count + 1) / 2; }
 // Wavefronts that share a narrow unit, for launches that have fewer such units than wavefronts: four while every unit can
 // have a worker without wide units to itself, two while half of one, else none.  Unit kernel, us, one wavefront a unit / team (decodes of 32 heads
 // in 8, caches cold):
-//   units   2 slices (64 keys)    4            8            16           63
-//   8       5.7 / 5.8             8.3 / 6.5    11.2 / 8.4   18.2 / 10.4  60.2 / 23.7
-//   224     6.8 / 6.8             8.6 / 8.1    12.2 / 10.6  19.4 / 14.1  61.4 / 39.1
-//   256     6.0 / 6.9             8.3 / 8.4    12.4 / 11.2  19.5 / 15.5  62.0 / 43.9
-//   264     7.1 / 7.4 (two)       9.1 / 9.8    12.9 / 12.4  20.1 / 19.2  62.2 / 59.0
-//   512     7.5 / 8.3             10.2 / 11.4  15.6 / 15.1  25.9 / 24.8  85.3 / 84.5
+//   units   2 slices (64 keys)   3             4             8             16            63
+//   8       6.0 / 5.7            6.6 / 6.1     7.8 / 6.4     11.3 / 8.2    18.4 / 10.0   59.8 / 23.1
+//   224     6.2 / 6.5            7.3 / 7.1     8.2 / 7.7     12.1 / 10.4   19.2 / 13.7   61.5 / 38.0
+//   256     6.4 / 6.6            7.3 / 7.3     8.5 / 8.0     12.2 / 10.9   19.4 / 14.7   61.9 / 43.0
+//   264     6.6 / 6.9 (two)      7.9 / 8.5     8.8 / 9.4     12.6 / 11.7   20.4 / 18.4   64.3 / 58.8
+//   512     7.4 / 8.0            8.8 / 9.8     10.3 / 10.9   15.7 / 15.2   26.1 / 24.6   87.1 / 83.7
 // so a team of four takes units of three slices and more on average, a team of two those of eight.  XY_SPLIT_AUTO cuts such
 // batches into more pieces than that; teams of two are for plans with a split size of the caller's or none.
 constexpr int64_t kTeamOf4Slices = 3, kTeamOf2Slices = 8;

@@ -45,8 +45,9 @@ constexpr int32_t kAutoSplitWide = 16;
 // Families of more than kNarrowRows rows (wide: a workgroup works on one unit at a time, whatever its rows, in time
 // proportional to its tiles).  A unit costs about two and a half tiles' time around its loop and a plan with cut
 // families a merge pass of another two; kWideUnitHalves and kWideMergeHalves are these in half tiles.  (With every worker
-// busy, nothing shared and the caches cold it is more: 13.5 us around the loop and 3.2 a tile for 256 rows on two row tiles, 12.1
-// and 2.45 for 128 rows on one, four to five tiles.  The rules below were measured with the constant as it is.)
+// busy, nothing shared and the caches cold it is more: launches of one unit a worker, fitted over 2 to 16 tiles, take 16.7 us and
+// 3.3 a tile for 256 rows on two row tiles, 10.4 and 2.7 for 124 rows on one, four to five tiles.  The rules below were measured with the
+// constant as it is.)
 constexpr int64_t kWideUnitHalves = 5, kWideMergeHalves = 4;
 // Few wide families (at most half as many as workers): pieces no shorter than eight tiles, or a quarter of the family
 // where that is less, at least two; a family of at most four tiles stays whole.

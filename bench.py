@@ -54,6 +54,11 @@ def sources_digest():
     return h.hexdigest()[:16]
 
 
+def unit_kernel(units):
+    """Name of the kernel that a launch of these units takes: launches without a unit of more than 32 rows have their own."""
+    return "xy_attn_units_kernel" if (units["q_count"] * units["head_count"] > 32).any() else "xy_attn_narrow_kernel"
+
+
 def time_steps(db, steps, warmup):
     import torch
     for _ in range(warmup):
@@ -268,7 +273,7 @@ def measure(index, args, overrides, extras):
     roof["frac"] = roof["achieved"] / roof["peak"]
     fresh = not overrides and TRAFFIC["sources_sha256_16"] == sources_digest()
     roof["traffic"] = TRAFFIC["bytes"].get(index) if fresh else None
-    roof["kernel"] = "xy_attn_units_kernel"
+    roof["kernel"] = unit_kernel(units)
     roof["kernel_ms"] = k_units_ms
     roof["merge_kernel_ms"] = k_merge_ms
     rec = {

@@ -274,3 +274,19 @@ def test_binding_refuses_to_import_without_the_library(tmp_path):
     res = subprocess.run([sys.executable, "-c", "import paper_2412_18106_amd.runner"], cwd=tmp_path,
                          capture_output=True, text=True, env={**os.environ, "PYTHONPATH": str(tmp_path)})
     assert res.returncode != 0 and "ImportError" in res.stderr and "no CPU fallback" in res.stderr
+
+
+@pytest.mark.parametrize("index, kernel", [(2, "xy_attn_units_kernel"), (3, "xy_attn_units_kernel"), (4, "xy_attn_narrow_kernel"),
+                                           (5, "xy_attn_units_kernel")])
+def test_bench_names_the_kernel_that_a_plan_is_launched_with(index, kernel):
+    """The roofline record of a batch without units of more than 32 rows (trees of up to 8 tokens, 4 heads a KV head) is that
+    of the kernel for such launches, as its kernel trace has it."""
+    import bench
+    from paper_2412_18106_amd import binding as X, workloads as W
+    _, hq, hkv, seqs, _, max_blocks = W.make_config_descs(index)
+    cfg = X.xy_attn_default_config(hq, hkv, max_blocks)
+    plan = X.xy_attn_plan_create(cfg, seqs)
+    try:
+        assert bench.unit_kernel(X.plan_arrays(plan, cfg.num_workers)[0]) == kernel
+    finally:
+        X.xy_attn_plan_destroy(plan)

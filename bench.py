@@ -43,7 +43,7 @@ HEADLINE = 5
 # `bench.py --config N` (one run per counter), each scaled by what the same counter reads for a plain 1 GiB device
 # copy in the same run (fetch x2.0, write x1.0).  They belong to one version of the kernel and planner sources:
 # when those differ from the version named here the line says null instead of a stale figure.
-TRAFFIC = {"sources_sha256_16": "97e5dac59ff96fee", "bytes": {2: 1279419063, 3: 339973029, 4: 1229440146, 5: 8477635451}}
+TRAFFIC = {"sources_sha256_16": "7bab6b954133874f", "bytes": {2: 1279409440, 3: 339973047, 4: 1229450533, 5: 8477729559}}
 
 
 def sources_digest():
